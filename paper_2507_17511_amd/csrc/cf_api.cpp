@@ -220,8 +220,8 @@ cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &
             partial_bytes += align_up((size_t)d.n_tokens * kLowRankRank * sizeof(float));
             v.lr_z_off = partial_bytes;
             partial_bytes += align_up((size_t)d.n_channels * kLowRankRank * sizeof(float));
-            v.lr_q_off = partial_bytes;
-            partial_bytes += align_up((size_t)d.n_channels * kLowRankRank * sizeof(float));
+            v.lr_g_off = partial_bytes;
+            partial_bytes += align_up((size_t)d.n_channels * kLowRankRank * sizeof(float));      // 8 KB per 256 channels are used
         }
         if (d.scale == CF_SCALE_RANK1) {
             L.any_rank1 = true;
@@ -272,7 +272,7 @@ cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &
         if (descs[t].scale == CF_LOWRANK) {
             L.dev[t].lr_p_off += L.off_partials;
             L.dev[t].lr_z_off += L.off_partials;
-            L.dev[t].lr_q_off += L.off_partials;
+            L.dev[t].lr_g_off += L.off_partials;
         }
     }
     return CF_OK;

@@ -73,8 +73,9 @@ struct alignas(16) TensorDev {
     uint32_t nm_block;      // N:M sparsifier: M, channels per block (8 or 16)
                             // low-rank compressor: 4 when the factors travel as 4-bit integers, else 0
     uint64_t rowpart_off;
-    // low-rank compressor: P = A Q [N][32], Z = A^T P [C][32], Q in the order k_lr_project reads it (all fp32)
-    uint64_t lr_p_off, lr_z_off, lr_q_off;
+    // low-rank compressor: P = A Q [N][32] fp32; Z = A^T P [C][32] fp32, which Q takes the place of in the order
+    // k_lr_project reads it; partial sums of Z^T Z, one [32][32] fp64 matrix per 256 channels (C > 256 only)
+    uint64_t lr_p_off, lr_z_off, lr_g_off;
 };
 
 static_assert(sizeof(TensorDev) % 4 == 0, "tables travel as 4-byte words");

@@ -123,7 +123,7 @@ __device__ __forceinline__ void lr_project_body(const BatchView &v, const Tensor
     const int64_t row_base = (int64_t)blockIdx.x * kProjTokens + wave * 64;
     if (row_base >= d.n_tokens) return;                     // uniform over the wave
     const int64_t C = d.n_channels;
-    const CF_GLOBAL f32x4 *qs = gconst<f32x4>(v.workspace + d.lr_q_off);
+    const CF_GLOBAL f32x4 *qs = gconst<f32x4>(v.workspace + d.lr_z_off);
     f32x16 acc0 = {}, acc1 = {};
     const int steps = d.n_channels / 32;
     const int chunk = lane & 7, trow = lane >> 3;           // row-major side: 8 chunks of 8 channels, 8 tokens per sweep
@@ -313,124 +313,214 @@ __global__ __launch_bounds__(256, 2) void k_lr_backproject(BatchView v, LaunchRa
 
 // ---------------------------------------------------------------- Q = orth(Z)
 
-// Gram-Schmidt over the 32 columns, left to right, every column projected twice; one workgroup of
-// 1024 lanes per tensor holds the matrix in registers (3 channel rows per lane: C <= 3072).  A column
-// left with less than 1e-4 of its length is dropped (zero): a residual of rank < 32 then gives zero
-// columns rather than amplified rounding noise.  Writes Q in the per-lane order k_lr_project reads,
-// and V = Q on the wire.
-constexpr int kOrthThreads = 1024;
-constexpr int kOrthRows = 3;
+// Gram-Schmidt over the 32 columns, left to right; a column left with less than 1e-4 of its length is dropped
+// (zero): a residual of rank < 32 then gives zero columns rather than amplified rounding noise.
+//
+// Done on the Gram matrix: with G = Z^T Z and R its (upper) Cholesky factor, Q = Z R^-1 is what Gram-Schmidt
+// gives, and the squared length a column is left with is the pivot of its elimination step.  G, R and the
+// substitution are fp64: the products of two fp32 entries are exact, and an error of eps * cond(Z)^2 stays below
+// fp32 rounding for every Z whose columns survive the 1e-4 rule (projecting the columns twice in fp32 reaches a few
+// 1e-7).  What bounds it: nothing but latency.  Projecting column by column is 96 rounds of workgroup-wide sums,
+// one after the other, on one workgroup per tensor (279 us for 57 x [3072, 32] on 57 of 256 CUs); here every
+// workgroup takes 256 channel rows, k_lr_gram sums their products on the fp64 matrix cores, and every workgroup of
+// k_lr_orth adds those partial sums up and eliminates the 32 x 32 matrix for itself: 20 + 33 us, most of them the
+// 31 dependent steps of the elimination.
+constexpr int kOrthThreads = 256;                           // one channel row per lane
+constexpr int kGramEntries = kRank * kRank;                 // of which the upper triangle is used
 
-struct OrthShared {
-    float part[kOrthThreads / 64][kRank + 1];
-    float total[kRank + 1];
-};
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef double f64x2 __attribute__((ext_vector_type(2)));
 
-// Sums `val` over the workgroup into sh.total[slot]; the caller places the barriers.
-__device__ __forceinline__ void orth_partial(OrthShared &sh, int slot, float val)
+// Sums of products of the 256 channel rows from `first` on: the three 16 x 16 tiles on or above the diagonal, one
+// partial per wave (to be added up in wave order).  v_mfma_f64_16x16x4_f64 takes column l % 16 of row l / 16 from
+// lane l on both sides, so a lane's two loads of a step (columns c and 16 + c) feed all three.  Register i of lane l
+// holds row 4 * i + l / 16, column l % 16 of a tile.
+typedef double GramParts[kOrthThreads / 64][3][256];
+__device__ __forceinline__ void gram_block(const CF_GLOBAL float *src, int first, int n_channels, GramParts &part)
 {
-    const float w = wave_tree_sum(val);
-    if (((int)threadIdx.x & 63) == 0) sh.part[(int)threadIdx.x >> 6][slot] = w;
-}
-
-__device__ __forceinline__ void orth_finish(OrthShared &sh, int n_slots)
-{
-    __syncthreads();
-    if ((int)threadIdx.x < n_slots) {
-        float s = 0.0f;
+    const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
+    const int col = lane & 15;
+    const int row0 = first + wave * 64 + (lane >> 4);
+    float lo[16], hi[16];
 #pragma unroll
-        for (int w = 0; w < kOrthThreads / 64; ++w) s += sh.part[w][threadIdx.x];
-        sh.total[threadIdx.x] = s;
+    for (int s = 0; s < 16; ++s) {
+        const int row = row0 + 4 * s;
+        const bool valid = row < n_channels;
+        lo[s] = valid ? src[(int64_t)row * kRank + col] : 0.0f;
+        hi[s] = valid ? src[(int64_t)row * kRank + 16 + col] : 0.0f;
+    }
+    f64x4 g00 = {}, g01 = {}, g11 = {};
+#pragma unroll
+    for (int s = 0; s < 16; ++s) {
+        const double a = (double)lo[s], b = (double)hi[s];
+        g00 = __builtin_amdgcn_mfma_f64_16x16x4f64(a, a, g00, 0, 0, 0);
+        g01 = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, g01, 0, 0, 0);
+        g11 = __builtin_amdgcn_mfma_f64_16x16x4f64(b, b, g11, 0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int e = (4 * i + (lane >> 4)) * 16 + col;
+        part[wave][0][e] = g00[i];
+        part[wave][1][e] = g01[i];
+        part[wave][2][e] = g11[i];
     }
     __syncthreads();
 }
 
-// Column K: project it on the finished columns 0..K-1 (twice), then normalise or drop it.  K is a
-// template parameter so that every register of the matrix is addressed statically.
-template <int K>
-__device__ __forceinline__ void orth_column(float (&a)[kOrthRows][kRank], OrthShared &sh)
+__device__ __forceinline__ double gram_sum(const GramParts &part, int tile, int e)
 {
-    float start2 = 0.0f;
-#pragma unroll
-    for (int pass = 0; pass < 2; ++pass) {
-        // <q_j, a_K> for every finished column j < K, and (first pass) the column's own length
-#pragma unroll
-        for (int j = 0; j < K; ++j) {
-            float dot = 0.0f;
-#pragma unroll
-            for (int rr = 0; rr < kOrthRows; ++rr) dot += a[rr][j] * a[rr][K];
-            orth_partial(sh, j, dot);
-        }
-        if (pass == 0) {
-            float own = 0.0f;
-#pragma unroll
-            for (int rr = 0; rr < kOrthRows; ++rr) own += a[rr][K] * a[rr][K];
-            orth_partial(sh, K, own);
-        }
-        orth_finish(sh, pass == 0 ? K + 1 : K);
-        if (pass == 0) start2 = sh.total[K];
-#pragma unroll
-        for (int j = 0; j < K; ++j) {
-            const float c = sh.total[j];
-#pragma unroll
-            for (int rr = 0; rr < kOrthRows; ++rr) a[rr][K] -= c * a[rr][j];
-        }
-    }
-    float own = 0.0f;
-#pragma unroll
-    for (int rr = 0; rr < kOrthRows; ++rr) own += a[rr][K] * a[rr][K];
-    orth_partial(sh, 0, own);
-    orth_finish(sh, 1);
-    const float left2 = sh.total[0];
-    const bool keep = start2 > 0.0f && left2 > kDrop2 * start2;
-    const float len = sqrtf(left2);
-#pragma unroll
-    for (int rr = 0; rr < kOrthRows; ++rr) a[rr][K] = keep ? a[rr][K] / len : 0.0f;
-    __syncthreads();                                        // sh.total is rewritten by the next column
+    return (part[0][tile][e] + part[1][tile][e]) + (part[2][tile][e] + part[3][tile][e]);
 }
 
-template <int K>
-__device__ __forceinline__ void orth_columns_from(float (&a)[kOrthRows][kRank], OrthShared &sh)
+// Partial G of 256 channel rows, for tensors of more than 256 channels.
+__global__ __launch_bounds__(kOrthThreads) void k_lr_gram(BatchView v, LaunchRange r, int from_q0, int min_iters)
 {
-    orth_column<K>(a, sh);
-    if constexpr (K + 1 < kRank) orth_columns_from<K + 1>(a, sh);
-}
-
-__global__ __launch_bounds__(kOrthThreads) void k_lr_orth(BatchView v, LaunchRange r, int from_q0, int min_iters)
-{
-    __shared__ OrthShared sh;
-    const int t = r.first + (int)blockIdx.x;
+    __shared__ GramParts part;
+    const int t = r.first + (int)blockIdx.y;
     const TensorDev d = v.descs[t];
     if (d.scale != LOWRANK || d.bits < min_iters) return;
+    if (d.n_channels <= kOrthThreads || (int)blockIdx.x * kOrthThreads >= d.n_channels) return;     // uniform over the workgroup
+    gram_block(from_q0 ? gconst<float>(v.ptrs[t].scales) : gconst<float>(v.workspace + d.lr_z_off), (int)blockIdx.x * kOrthThreads, d.n_channels, part);
+    CF_GLOBAL double *out = gmut<double>(v.workspace + d.lr_g_off) + (int64_t)blockIdx.x * kGramEntries;
+    const int row = (int)threadIdx.x >> 4, c = (int)threadIdx.x & 15;
+#pragma unroll
+    for (int tile = 0; tile < 3; ++tile)
+        out[(row + (tile == 2 ? 16 : 0)) * kRank + c + (tile >= 1 ? 16 : 0)] = gram_sum(part, tile, (int)threadIdx.x);
+}
+
+// 1 / p by two Newton steps on the hardware's estimate: the elimination's steps depend on each other, and a full
+// divide is most of a step.  p is a squared length, far from the ends of the fp64 range.
+__device__ __forceinline__ double reciprocal(double p)
+{
+    double x = __builtin_amdgcn_rcp(p);
+    x = __builtin_fma(__builtin_fma(-p, x, 1.0), x, x);
+    return __builtin_fma(__builtin_fma(-p, x, 1.0), x, x);
+}
+
+// Q rows of 256 channels, in the order k_lr_project reads them, and V = Q on the wire.  Q goes where Z was (a
+// workgroup has its rows in registers before it writes them, and both orders keep 32 channels in the same 4 KB).
+__global__ __launch_bounds__(kOrthThreads) void k_lr_orth(BatchView v, LaunchRange r, int from_q0, int min_iters)
+{
+    constexpr int kPitch = kRank + 2;                       // doubles; even, so that pairs of a row stay 16-byte aligned
+    __shared__ __attribute__((aligned(16))) double G[kRank][kPitch];
+    __shared__ double start2[kRank], inv_len[kRank];
+    __shared__ GramParts parts;
+    const int t = r.first + (int)blockIdx.y;
+    const TensorDev d = v.descs[t];
+    if (d.scale != LOWRANK || d.bits < min_iters) return;
+    if ((int)blockIdx.x * kOrthThreads >= d.n_channels) return;     // uniform over the workgroup
     const TensorPtrs p = v.ptrs[t];
-    const CF_GLOBAL f32x4 *src = from_q0 ? gconst<f32x4>(p.scales) : gconst<f32x4>(v.workspace + d.lr_z_off);
-    float a[kOrthRows][kRank];
+    const int tid = (int)threadIdx.x;
+    const int ch = (int)blockIdx.x * kOrthThreads + tid;
+    const bool valid = ch < d.n_channels;
+    const CF_GLOBAL f32x4 *src = (from_q0 ? gconst<f32x4>(p.scales) : gconst<f32x4>(v.workspace + d.lr_z_off)) + (int64_t)ch * (kRank / 4);
+    f32x4 raw[kRank / 4];
 #pragma unroll
-    for (int rr = 0; rr < kOrthRows; ++rr) {
-        const int ch = (int)threadIdx.x + kOrthThreads * rr;
+    for (int k = 0; k < kRank / 4; ++k) raw[k] = valid ? src[k] : (f32x4)(0.0f);
+
+    // G: this lane's entries are rows row0 + 8 * q of column col, on or above the diagonal
+    const int n_blocks = (d.n_channels + kOrthThreads - 1) / kOrthThreads;
+    const int col = tid & (kRank - 1), row0 = tid / kRank;
+    double g[4] = {0.0, 0.0, 0.0, 0.0};
+    if (n_blocks == 1) {        // uniform: the rows of this workgroup are all there are
+        gram_block(from_q0 ? gconst<float>(p.scales) : gconst<float>(v.workspace + d.lr_z_off), 0, d.n_channels, parts);
 #pragma unroll
-        for (int k = 0; k < kRank / 4; ++k) {
-            f32x4 w = {};
-            if (ch < d.n_channels) w = src[(int64_t)ch * (kRank / 4) + k];
-            a[rr][4 * k] = w.x; a[rr][4 * k + 1] = w.y; a[rr][4 * k + 2] = w.z; a[rr][4 * k + 3] = w.w;
+        for (int q = 0; q < 4; ++q) {
+            const int row = row0 + 8 * q;
+            if (row <= col) g[q] = gram_sum(parts, (row >> 4) + (col >> 4), (row & 15) * 16 + (col & 15));
+        }
+    } else {                    // the partial sums of k_lr_gram, in channel order
+        const CF_GLOBAL double *part = gconst<double>(v.workspace + d.lr_g_off);
+        constexpr int kAtOnce = 6;                          // blocks whose partial sums are in flight together
+        for (int b0 = 0; b0 < n_blocks; b0 += kAtOnce) {
+            double w[kAtOnce][4];
+#pragma unroll
+            for (int u = 0; u < kAtOnce; ++u)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    w[u][q] = (b0 + u < n_blocks && row0 + 8 * q <= col) ? part[(int64_t)(b0 + u) * kGramEntries + tid + 256 * q] : 0.0;
+#pragma unroll
+            for (int u = 0; u < kAtOnce; ++u)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) g[q] += w[u][q];
         }
     }
-    orth_columns_from<0>(a, sh);
-    CF_GLOBAL float *qs = gmut<float>(v.workspace + d.lr_q_off);
-    uint8_t *V = wire_v(d, p);
 #pragma unroll
-    for (int rr = 0; rr < kOrthRows; ++rr) {
-        const int ch = (int)threadIdx.x + kOrthThreads * rr;
-        if (ch >= d.n_channels) continue;
-        const int s = ch >> 5, c = ch & 31, hh = c >> 4, j = c & 15;
+    for (int q = 0; q < 4; ++q) {
+        G[row0 + 8 * q][col] = g[q];
+        if (row0 + 8 * q == col) start2[col] = g[q];
+    }
+    __syncthreads();
+    // elimination: after step k the rows below it hold what is left of G; a dropped column eliminates nothing
+    for (int k = 0; k + 1 < kRank; ++k) {
+        const double pivot = G[k][k], start = start2[k];
+        const bool keep = start > 0.0 && pivot > (double)kDrop2 * start;
+        const double f = keep ? G[k][col] * reciprocal(pivot) : 0.0;
 #pragma unroll
-        for (int n = 0; n < kRank; ++n) {
-            qs[((int64_t)s * 64 + hh * 32 + n) * 16 + j] = a[rr][n];
-            if (factors_int4(d)) continue;
-            if (d.dtype == BF16) gmut<uint16_t>(V)[(int64_t)ch * kRank + n] = (uint16_t)bf16_rne(a[rr][n]);
-            else gmut<float>(V)[(int64_t)ch * kRank + n] = a[rr][n];
+        for (int q = 0; q < 4; ++q) {
+            const int i = row0 + 8 * q;
+            if (i > k && i <= col) {
+                g[q] = __builtin_fma(-G[k][i], f, g[q]);
+                G[i][col] = g[q];
+            }
         }
-        if (factors_int4(d)) quantise_factor_row(a[rr], wire4_v(d, p) + (int64_t)ch * 16, wire4_v_scales(d, p) + ch);
+        __syncthreads();
+    }
+    if (tid < kRank) {
+        const double pivot = G[tid][tid], start = start2[tid];
+        inv_len[tid] = start > 0.0 && pivot > (double)kDrop2 * start ? 1.0 / __builtin_sqrt(pivot) : 0.0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        if (row0 + 8 * q < col) G[row0 + 8 * q][col] = g[q] * inv_len[row0 + 8 * q];        // R above the diagonal
+#pragma unroll
+    for (int k = 0; k < kRank / 4; ++k) asm volatile("" : "+v"(raw[k]));       // the row has arrived before any lane writes Q over it
+    __syncthreads();
+
+    // this lane's row: q_j = (z_j - sum_{i < j} q_i R_ij) / R_jj
+    double z[kRank];
+#pragma unroll
+    for (int k = 0; k < kRank / 4; ++k) {
+        z[4 * k] = (double)raw[k].x; z[4 * k + 1] = (double)raw[k].y; z[4 * k + 2] = (double)raw[k].z; z[4 * k + 3] = (double)raw[k].w;
+    }
+    float a[kRank];
+#pragma unroll
+    for (int i = 0; i < kRank; ++i) {
+        const double q = z[i] * inv_len[i];
+        a[i] = (float)q;
+        if ((i & 1) == 0) z[i + 1] = __builtin_fma(-q, G[i][i + 1], z[i + 1]);
+#pragma unroll
+        for (int j = (i / 2 + 1) * 2; j < kRank; j += 2) {
+            const f64x2 rr = *reinterpret_cast<const f64x2 *>(&G[i][j]);
+            z[j] = __builtin_fma(-q, rr.x, z[j]);
+            z[j + 1] = __builtin_fma(-q, rr.y, z[j + 1]);
+        }
+    }
+    if (!valid) return;
+    CF_GLOBAL float *qs = gmut<float>(v.workspace + d.lr_z_off);
+    uint8_t *V = wire_v(d, p);
+    const int s = ch >> 5, c = ch & 31, hh = c >> 4, j = c & 15;
+#pragma unroll
+    for (int n = 0; n < kRank; ++n) qs[((int64_t)s * 64 + hh * 32 + n) * 16 + j] = a[n];
+    if (factors_int4(d)) {
+        quantise_factor_row(a, wire4_v(d, p) + (int64_t)ch * 16, wire4_v_scales(d, p) + ch);
+        return;
+    }
+#pragma unroll
+    for (int k = 0; k < kRank / 8; ++k) {
+        F8 f;
+#pragma unroll
+        for (int n = 0; n < 8; ++n) f.v[n] = a[8 * k + n];
+        if (d.dtype == BF16) {
+            Raw8<BF16> o;
+            o.narrow(f);
+            o.store(V, (int64_t)ch * kRank + 8 * k);
+        } else {
+            Raw8<F32> o;
+            o.narrow(f);
+            o.store(V, (int64_t)ch * kRank + 8 * k);
+        }
     }
 }
 
@@ -606,8 +696,14 @@ __global__ __launch_bounds__(256) void k_lr_apply(BatchView v, LaunchRange r)
 
 hipError_t launch_lr_orth(const BatchView &v, const LaunchRange &r, bool from_q0, int min_iters, hipStream_t s)
 {
-    if (r.count == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_lr_orth, dim3(r.count), dim3(kOrthThreads), 0, s, v, r, from_q0 ? 1 : 0, min_iters);
+    if (r.count == 0 || r.lr_max_channels == 0) return hipSuccess;
+    dim3 grid((unsigned)((r.lr_max_channels + kOrthThreads - 1) / kOrthThreads), (unsigned)r.count);
+    if (r.lr_max_channels > kOrthThreads) {
+        hipLaunchKernelGGL(k_lr_gram, grid, dim3(kOrthThreads), 0, s, v, r, from_q0 ? 1 : 0, min_iters);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(k_lr_orth, grid, dim3(kOrthThreads), 0, s, v, r, from_q0 ? 1 : 0, min_iters);
     return hipGetLastError();
 }
 

@@ -407,3 +407,30 @@ def test_lowrank_full_shape():
                 say(f"lowrank full shape tensor {t} step {s}: factors within {du:.1e} (U, relative), {dv:.1e} (V, absolute)")
     finally:
         sess.close()
+
+
+@pytest.mark.parametrize("c", [32, 224, 256, 288, 512, 544, 3072])
+def test_lowrank_basis_is_orthonormal(c):
+    """V at the edges of the orthogonalisation's 256-row blocks, from a Z whose singular values span a factor of 900
+    (those of A fall by 0.9 a step, and Z = A^T A Q squares them).  V holds fp32 roundings of columns of unit length:
+    with the substitution in fp64 an inner product of two of them is off by at most 2 * 2^-24, plus what fp64 loses to
+    the conditioning (1e-16 * 900^2)."""
+    n = 200
+    say(f"lowrank basis C={c}")
+    g = torch.Generator(device=DEV)
+    g.manual_seed(c)
+    left = torch.linalg.qr(torch.randn((n, R), generator=g, device=DEV))[0] * 0.9 ** torch.arange(R, device=DEV)
+    x0 = torch.zeros((n, c), device=DEV)
+    x1 = (left @ torch.linalg.qr(torch.randn((c, R), generator=g, device=DEV))[0].T).contiguous()
+    sess = CodecSession([cf.desc(n, c, cf.CF_F32, 1, cf.CF_LOWRANK, R)], cf.options(), device=DEV)
+    try:
+        sess.warmup([x0])
+        sess.scales[0].copy_(torch.randn(c * R, generator=g, device=DEV))
+        sess.step_fused([x1])
+        cf.cf_check_device(sess.ctx, sess.stream_handle)
+        V = split_wire(as_numpy(sess.codes[0]), n, c, cf.CF_F32)[1].astype(np.float64)
+        worst = float(np.abs(V.T @ V - np.eye(R)).max())
+        say(f"   V^T V is within {worst:.1e} of the identity")
+        assert worst <= 2.0 ** -23 + 1e-9
+    finally:
+        sess.close()
