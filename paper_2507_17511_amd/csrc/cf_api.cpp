@@ -4,6 +4,7 @@
 // arxiv 2507.17511 are in include/compactfusion.h.
 #include "compactfusion.h"
 
+#include <algorithm>
 #include <cstdint>
 #include <cstring>
 #include <new>
@@ -26,6 +27,7 @@ struct Layout {
     int32_t max_group_items = 0;   // largest reduction group of the single-pass path
     bool sp_wide = false;          // single-pass items are kStripeChannelsWide channels wide (short tensors)
     bool single_pass = false;      // every channel-scale tensor has single-pass geometry
+    size_t off_lr_slices = 0, lr_slice_bytes = 0;       // slices of the low-rank back-projection, shared by the tensors of a call
     size_t total = 0;
     std::vector<TensorDev> dev;
     std::vector<uint32_t> tile_prefix, fin_prefix, ew_prefix, dec_prefix;
@@ -134,6 +136,36 @@ int pick_rb_rows(const cf_tensor_desc *descs, int32_t n, const cf_options &o)
         if (tiles >= 4096) return rb;
     }
     return 8;
+}
+
+// Runs of tokens the back-projection of a call over `count` tensors is split into (the largest low-rank tensor's
+// channels and tokens given): enough to give the device a round of workgroups, but no more than 8, since the
+// orthogonalisation adds the runs up one after the other.  Whole steps with 1 / 4 / 8 / 16 runs: 1 x [4096, 3072] 501 /
+// 415 / 404 / 409 us, 2 x [4096, 3072] 523 / 435 / 433 / 442, 2 x [500, 512] 129 / 120 / 121 / 120; with 1 / 2 / 4:
+// 30 x [4096, 2048] 1223 / 1205 / 1215 us, 57 x [4096, 3072] 3169 / 3154 / 3195 (not worth twice the memory).
+int64_t lowrank_split(int64_t max_channels, int64_t max_tokens, int64_t count)
+{
+    const int64_t blocks = (max_channels + kLowRankBackChannels - 1) / kLowRankBackChannels * count;
+    const int64_t runs = std::min<int64_t>(kLowRankSlots / blocks, (max_tokens + kLowRankRunTokens - 1) / kLowRankRunTokens);
+    return std::max<int64_t>(1, std::min<int64_t>(kLowRankMaxRuns, runs));
+}
+
+// Slices for any call on a context of these tensors: those of a call over some of them are at most as many as the
+// rule above makes for a context of as many tensors of the largest size.
+size_t lowrank_slice_bytes(const cf_tensor_desc *descs, int32_t n)
+{
+    int64_t c = 0, tok = 0, most = 0;
+    for (int32_t t = 0; t < n; ++t)
+        if (descs[t].scale == CF_LOWRANK) {
+            c = std::max<int64_t>(c, descs[t].n_channels);
+            tok = std::max<int64_t>(tok, descs[t].n_tokens);
+        }
+    if (c == 0) return 0;
+    for (int64_t count = 1; count <= n; ++count) {
+        const int64_t split = lowrank_split(c, tok, count);
+        if (split > 1) most = std::max<int64_t>(most, split * count);
+    }
+    return align_up((size_t)most * (size_t)c * kLowRankRank * sizeof(float));
 }
 
 cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &o, Layout &L)
@@ -262,6 +294,11 @@ cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &
     L.off_gave_up = off;      off = align_up(off + sizeof(uint32_t) * (size_t)items);
     L.off_error = off;        off = align_up(off + sizeof(uint32_t) * 64);      // error word, and the give-up counter 128 bytes on
     L.off_p_partials = off;   off = align_up(off + p_partial_bytes);
+    L.off_lr_slices = off;
+    L.lr_slice_bytes = lowrank_slice_bytes(descs, n);
+    // no tensors outgrow the static scratch because of the slices (and the sums are the same there and here)
+    if (off <= kStaticScratchBytes) L.lr_slice_bytes = std::min(L.lr_slice_bytes, (kStaticScratchBytes - off) / kAlign * kAlign);
+    off += L.lr_slice_bytes;
     L.total = off;
     for (int32_t t = 0; t < n; ++t) {
         if (descs[t].scale == CF_SCALE_CHANNEL || descs[t].scale == CF_SCALE_RANK1) {
@@ -343,6 +380,8 @@ struct cf_ctx {
         r.dts = descs[first].dtype;
         r.lr_max_channels = 0;
         r.lr_max_tokens = 0;
+        r.lr_split = 1;
+        r.lr_slices_off = L.off_lr_slices;
         r.p_partial_lo = ~(uint64_t)0;
         r.p_partial_hi = 0;
         for (int32_t t = first; t < first + count; ++t) {
@@ -359,6 +398,10 @@ struct cf_ctx {
                 if (descs[t].n_channels > r.lr_max_channels) r.lr_max_channels = (int32_t)descs[t].n_channels;
                 if (descs[t].n_tokens > r.lr_max_tokens) r.lr_max_tokens = descs[t].n_tokens;
             }
+        }
+        if (r.lr_max_channels > 0) {    // as many runs as the rule says and the slices hold
+            const size_t per_run = (size_t)count * (size_t)r.lr_max_channels * kLowRankRank * sizeof(float);
+            r.lr_split = (int32_t)std::max<int64_t>(1, std::min<int64_t>(lowrank_split(r.lr_max_channels, r.lr_max_tokens, count), (int64_t)(L.lr_slice_bytes / per_run)));
         }
         return r;
     }

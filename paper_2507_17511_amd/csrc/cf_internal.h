@@ -131,6 +131,8 @@ struct LaunchRange {
     int32_t naive;              // decode: recon_t = D instead of recon_{t-1} + D (CF_EF_NAIVE)
     int32_t lr_max_channels;    // low-rank tensors of the range: largest C and N (0 = none)
     int64_t lr_max_tokens;
+    int32_t lr_split;           // low-rank back-projection: runs of tokens per channel stripe (1: no slices)
+    uint64_t lr_slices_off;     // workspace offset of its slices, [count][lr_split][lr_max_channels][32] fp32
 };
 
 enum class Op { Compress, StepFused };
@@ -156,6 +158,13 @@ hipError_t launch_decode(const BatchView &v, const LaunchRange &r, hipStream_t s
 // Low-rank compressor (cf_lowrank.hip): rank 32, C a multiple of 32 and at most kLowRankMaxChannels.
 constexpr int kLowRankRank = 32;
 constexpr int kLowRankMaxChannels = 3072;
+// The back-projection's workgroups own kLowRankBackChannels channels each, and kLowRankSlots of them fit the device
+// (four per CU).  Calls that make fewer split their tokens into up to kLowRankMaxRuns runs of at least
+// kLowRankRunTokens, whose slices of Z live in the workspace.
+constexpr int kLowRankBackChannels = 128;
+constexpr int kLowRankSlots = 1024;
+constexpr int kLowRankMaxRuns = 8;
+constexpr int kLowRankRunTokens = 128;
 // min_iters: only tensors whose descriptor asks for at least that many subspace iterations take part
 hipError_t launch_lr_orth(const BatchView &v, const LaunchRange &r, bool from_q0, int min_iters, hipStream_t s);
 hipError_t launch_lr_project(const BatchView &v, const LaunchRange &r, bool wire, int min_iters, hipStream_t s);

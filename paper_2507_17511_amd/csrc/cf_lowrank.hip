@@ -16,7 +16,7 @@
 //   project      P = A Q     m = token, k = channel: a lane loads 16 consecutive channels of its token
 //                            and spends them on 16 instructions; Q is kept in that per-lane order.
 //   backproject  Z = A^T P   m = channel, k = token: a lane loads 8 consecutive channels of its token and
-//                            spends them on 8 accumulator tiles (tile j holds channels = j mod 8).
+//                            spends them on 8 channel tiles (tile j holds channels = j mod 8); 16x16x4 tiles.
 //   encode       D^T = V U^T m = channel (relabelled so that a lane ends up with 16 consecutive channels
 //                            of its token), n = token, k = rank.
 #include "cf_device.h"
@@ -33,6 +33,8 @@ constexpr int kRank = 32;
 constexpr float kDrop2 = 1e-8f;     // (1e-4)^2: a column left with less than 1e-4 of its length is dropped
 
 __device__ __forceinline__ f32x16 mfma32(float a, float b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
+
+__device__ __forceinline__ f32x4 mfma16(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
 template <int DT> __device__ __forceinline__ void load16(const void *base, int64_t elem, float (&out)[16])
 {
@@ -226,89 +228,109 @@ __global__ __launch_bounds__(kProjThreads, 2) void k_lr_project(BatchView v, Lau
 
 // ---------------------------------------------------------------- Z = A^T P
 
-// A workgroup owns a stripe of 256 channels; its 4 waves split the tokens and add their tiles up
-// through LDS in wave order.  Lane (q, h): channels 8q..8q+7 of the stripe, token 2 * pair + h.
+// Where run `run` of tensor t leaves its part of Z: Z itself when the tokens are not split.
+__device__ __forceinline__ uint8_t *lr_slice(const BatchView &v, const LaunchRange &r, const TensorDev &d, int t, int run)
+{
+    if (r.lr_split == 1) return v.workspace + d.lr_z_off;
+    return v.workspace + r.lr_slices_off + (uint64_t)((t - r.first) * r.lr_split + run) * (uint64_t)r.lr_max_channels * (kRank * sizeof(float));
+}
+
+// A workgroup owns a stripe of 128 channels and one of r.lr_split runs of tokens; its 4 waves split those and add
+// their tiles up through LDS in wave order.  With one run the sum is Z; with more it is a slice of its own, and the
+// orthogonalisation adds the slices up.
+// v_mfma_f32_16x16x4_f32 takes A[l % 16][l / 16] and B[l / 16][l % 16] from lane l: lane (q, g) holds channels
+// 8q..8q+7 of the stripe of token 4 * quad + g, straight from a 128-bit load, and spends them on 8 channel tiles
+// (tile j holds channels = j mod 8) times 2 rank tiles.  What bounds it is how much a CU has in flight: the
+// accumulators of a 128-channel tile are 64 registers, which leaves room for a ring of 8 quads (16 KB a wave) at four
+// waves per SIMD.  57 x [4096, 3072] bf16: 616 us (4.7 TB/s); with 256 channels, two waves per SIMD and 8 KB each, 717 us.
+constexpr int kBackThreads = 256;
+constexpr int kBackChannels = kLowRankBackChannels;
+
 template <int DT>
-__device__ __forceinline__ void lr_backproject_body(const BatchView &v, const TensorDev &d, const TensorPtrs &p, float *sum)
+__device__ __forceinline__ void lr_backproject_body(const BatchView &v, const LaunchRange &r, const TensorDev &d, const TensorPtrs &p, int t,
+                                                    int stripe, int run, float *sum)
 {
     const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
-    const int q = lane & 31, h = lane >> 5;
-    const int ch0 = (int)blockIdx.x * 256 + 8 * q;
-    const bool cvalid = ch0 < d.n_channels;
-    const int64_t C = d.n_channels;
-    const int64_t n_pairs = (d.n_tokens + 1) / 2;
-    const int64_t per_wave = (n_pairs + 3) / 4;
-    const int64_t lo = wave * per_wave;
-    const int64_t hi = lo + per_wave < n_pairs ? lo + per_wave : n_pairs;
-    const CF_GLOBAL float *P = gconst<float>(v.workspace + d.lr_p_off);
-    f32x16 acc[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) acc[j] = (f32x16){};
-    constexpr int U = (DT == F32) ? 2 : 4;                  // token pairs per batch (fp32 rows take twice the registers); the next batch is in flight during the MFMAs
-    Raw8<DT> xr[U], br[U];
-    float pv[U];
-    auto fetch = [&](int64_t pair0) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t row = 2 * (pair0 + u) + h;
-            const bool rvalid = pair0 + u < hi && row < d.n_tokens;
-            if (rvalid && cvalid) {
-                xr[u].load(p.x, row * C + ch0);
-                br[u].load(p.recon, row * C + ch0);
-            } else {
-                xr[u].zero();
-                br[u].zero();
-            }
-            pv[u] = rvalid ? P[row * kRank + q] : 0.0f;
-        }
+    const int q = lane & 15, g = lane >> 4;
+    const int64_t C = d.n_channels, last = d.n_tokens - 1;
+    const int64_t n_quads = (d.n_tokens + 3) / 4;
+    const int64_t per_wave = (n_quads + 4 * r.lr_split - 1) / (4 * r.lr_split);
+    const int64_t lo = (run * 4 + wave) * per_wave;         // may lie beyond the last quad: such a wave adds zeros
+    const int64_t hi = lo + per_wave < n_quads ? lo + per_wave : n_quads;
+    // Loads without branches: rows and channels outside the tensor read its last ones, P counts as zero there and the
+    // channels are not stored.
+    const int ch0 = stripe * kBackChannels + 8 * q;
+    const int ch = ch0 < d.n_channels ? ch0 : d.n_channels - 8;
+    const CF_GLOBAL float *P = gconst<float>(v.workspace + d.lr_p_off) + q;
+    constexpr int R = (DT == F32) ? 4 : 8;                  // quads in flight (fp32 rows take twice the registers)
+    Raw8<DT> xr[R], br[R];
+    float pv[R][2];
+    auto fetch = [&](int slot, int64_t quad) {
+        const int64_t row = 4 * quad + g;
+        const int64_t at = row < last ? row : last;
+        xr[slot].load(p.x, at * C + ch);
+        br[slot].load(p.recon, at * C + ch);
+        pv[slot][0] = P[at * kRank];
+        pv[slot][1] = P[at * kRank + 16];
     };
-    fetch(lo);
-    for (int64_t pair0 = lo; pair0 < hi; pair0 += U) {
-        float z[U][8], pn[U];
+    f32x4 acc[8][2];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const F8 x = xr[u].widen(), b = br[u].widen();
+    for (int j = 0; j < 8; ++j) acc[j][0] = acc[j][1] = (f32x4)(0.0f);
+    if (lo < hi) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) z[u][j] = x.v[j] - b.v[j];
-            pn[u] = pv[u];
+        for (int u = 0; u < R; ++u) fetch(u, lo + u);
+        for (int64_t quad0 = lo; quad0 < hi; quad0 += R) {
+#pragma unroll
+            for (int u = 0; u < R; ++u) {
+                const F8 x = xr[u].widen(), b = br[u].widen();
+                F8 z;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) z.v[j] = x.v[j] - b.v[j];
+                const bool valid = quad0 + u < hi && 4 * (quad0 + u) + g <= last;
+                const float p0 = valid ? pv[u][0] : 0.0f, p1 = valid ? pv[u][1] : 0.0f;
+                fetch(u, quad0 + R + u);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    acc[j][0] = mfma16(z.v[j], p0, acc[j][0]);
+                    acc[j][1] = mfma16(z.v[j], p1, acc[j][1]);
+                }
+            }
         }
-        fetch(pair0 + U);
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int j = 0; j < 8; ++j) acc[j] = mfma32(z[u][j], pn[u], acc[j]);
     }
-    // tile j, register i of lane (q, h): channel 8 * rho + j of the stripe with rho = 8 * (i / 4) + 4 * h + i % 4, column q
-    for (int w = 0; w < 4; ++w) {
+    // tile j, register i of lane (q, g): channel 8 * (4 * g + i) + j of the stripe, column q (and 16 + q)
+    for (int w = 0; w < kBackThreads / 64; ++w) {
         if (wave == w) {
 #pragma unroll
             for (int j = 0; j < 8; ++j)
 #pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const int rho = 8 * (i >> 2) + 4 * h + (i & 3);
-                    const int idx = (8 * rho + j) * kRank + q;
-                    sum[idx] = (w == 0) ? acc[j][i] : sum[idx] + acc[j][i];
-                }
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const int idx = (8 * (4 * g + i) + j) * kRank + 16 * h + q;
+                        sum[idx] = (w == 0) ? acc[j][h][i] : sum[idx] + acc[j][h][i];
+                    }
         }
         __syncthreads();
     }
-    CF_GLOBAL float *Z = gmut<float>(v.workspace + d.lr_z_off);
-    for (int k = (int)threadIdx.x; k < 256 * kRank; k += 256) {
-        const int ch = (int)blockIdx.x * 256 + k / kRank;
-        if (ch < d.n_channels) Z[(int64_t)ch * kRank + (k % kRank)] = sum[k];
+    CF_GLOBAL float *Z = gmut<float>(lr_slice(v, r, d, t, run));
+    for (int k = (int)threadIdx.x; k < kBackChannels * kRank; k += kBackThreads) {
+        const int c = stripe * kBackChannels + k / kRank;
+        if (c < d.n_channels) Z[(int64_t)c * kRank + (k % kRank)] = sum[k];
     }
 }
 
-__global__ __launch_bounds__(256, 2) void k_lr_backproject(BatchView v, LaunchRange r, int min_iters)
+__global__ __launch_bounds__(kBackThreads, 3) void k_lr_backproject(BatchView v, LaunchRange r, int min_iters)
 {
-    __shared__ float sum[256 * kRank];
+    __shared__ float sum[kBackChannels * kRank];
     const int t = r.first + (int)blockIdx.y;
     const TensorDev d = v.descs[t];
     if (d.scale != LOWRANK || d.bits < min_iters) return;
-    if ((int)blockIdx.x * 256 >= d.n_channels) return;      // uniform over the workgroup
+    const int n_stripes = (d.n_channels + kBackChannels - 1) / kBackChannels;
+    const int stripe = (int)blockIdx.x % n_stripes, run = (int)blockIdx.x / n_stripes;
+    if (run >= r.lr_split) return;                          // uniform over the workgroup: fewer stripes than the widest tensor
     const TensorPtrs p = v.ptrs[t];
-    if (d.dtype == BF16) lr_backproject_body<BF16>(v, d, p, sum);
-    else lr_backproject_body<F32>(v, d, p, sum);
+    if (d.dtype == BF16) lr_backproject_body<BF16>(v, r, d, p, t, stripe, run, sum);
+    else lr_backproject_body<F32>(v, r, d, p, t, stripe, run, sum);
 }
 
 // ---------------------------------------------------------------- Q = orth(Z)
@@ -336,8 +358,12 @@ typedef double f64x2 __attribute__((ext_vector_type(2)));
 // lane l on both sides, so a lane's two loads of a step (columns c and 16 + c) feed all three.  Register i of lane l
 // holds row 4 * i + l / 16, column l % 16 of a tile.
 typedef double GramParts[kOrthThreads / 64][3][256];
-__device__ __forceinline__ void gram_block(const CF_GLOBAL float *src, int first, int n_channels, GramParts &part)
+// The rows are Q0's, or Z's; where Z lies in slices their sum is formed here and left in Z.
+__device__ __forceinline__ void gram_block(const BatchView &v, const LaunchRange &r, const TensorDev &d, int t, bool from_q0, int first, GramParts &part)
 {
+    const int n_channels = d.n_channels;
+    const int n_slices = from_q0 ? 1 : r.lr_split;
+    const CF_GLOBAL float *src = from_q0 ? gconst<float>(v.ptrs[t].scales) : gconst<float>(lr_slice(v, r, d, t, 0));
     const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
     const int col = lane & 15;
     const int row0 = first + wave * 64 + (lane >> 4);
@@ -348,6 +374,27 @@ __device__ __forceinline__ void gram_block(const CF_GLOBAL float *src, int first
         const bool valid = row < n_channels;
         lo[s] = valid ? src[(int64_t)row * kRank + col] : 0.0f;
         hi[s] = valid ? src[(int64_t)row * kRank + 16 + col] : 0.0f;
+    }
+    if (n_slices > 1) {         // uniform over the launch
+        for (int k = 1; k < n_slices; ++k) {
+            src = gconst<float>(lr_slice(v, r, d, t, k));
+#pragma unroll
+            for (int s = 0; s < 16; ++s) {
+                const int row = row0 + 4 * s;
+                const bool valid = row < n_channels;
+                lo[s] += valid ? src[(int64_t)row * kRank + col] : 0.0f;
+                hi[s] += valid ? src[(int64_t)row * kRank + 16 + col] : 0.0f;
+            }
+        }
+        CF_GLOBAL float *Z = gmut<float>(v.workspace + d.lr_z_off);
+#pragma unroll
+        for (int s = 0; s < 16; ++s) {
+            const int row = row0 + 4 * s;
+            if (row < n_channels) {
+                Z[(int64_t)row * kRank + col] = lo[s];
+                Z[(int64_t)row * kRank + 16 + col] = hi[s];
+            }
+        }
     }
     f64x4 g00 = {}, g01 = {}, g11 = {};
 #pragma unroll
@@ -380,7 +427,7 @@ __global__ __launch_bounds__(kOrthThreads) void k_lr_gram(BatchView v, LaunchRan
     const TensorDev d = v.descs[t];
     if (d.scale != LOWRANK || d.bits < min_iters) return;
     if (d.n_channels <= kOrthThreads || (int)blockIdx.x * kOrthThreads >= d.n_channels) return;     // uniform over the workgroup
-    gram_block(from_q0 ? gconst<float>(v.ptrs[t].scales) : gconst<float>(v.workspace + d.lr_z_off), (int)blockIdx.x * kOrthThreads, d.n_channels, part);
+    gram_block(v, r, d, t, from_q0 != 0, (int)blockIdx.x * kOrthThreads, part);
     CF_GLOBAL double *out = gmut<double>(v.workspace + d.lr_g_off) + (int64_t)blockIdx.x * kGramEntries;
     const int row = (int)threadIdx.x >> 4, c = (int)threadIdx.x & 15;
 #pragma unroll
@@ -415,15 +462,13 @@ __global__ __launch_bounds__(kOrthThreads) void k_lr_orth(BatchView v, LaunchRan
     const bool valid = ch < d.n_channels;
     const CF_GLOBAL f32x4 *src = (from_q0 ? gconst<f32x4>(p.scales) : gconst<f32x4>(v.workspace + d.lr_z_off)) + (int64_t)ch * (kRank / 4);
     f32x4 raw[kRank / 4];
-#pragma unroll
-    for (int k = 0; k < kRank / 4; ++k) raw[k] = valid ? src[k] : (f32x4)(0.0f);
 
     // G: this lane's entries are rows row0 + 8 * q of column col, on or above the diagonal
     const int n_blocks = (d.n_channels + kOrthThreads - 1) / kOrthThreads;
     const int col = tid & (kRank - 1), row0 = tid / kRank;
     double g[4] = {0.0, 0.0, 0.0, 0.0};
     if (n_blocks == 1) {        // uniform: the rows of this workgroup are all there are
-        gram_block(from_q0 ? gconst<float>(p.scales) : gconst<float>(v.workspace + d.lr_z_off), 0, d.n_channels, parts);
+        gram_block(v, r, d, t, from_q0 != 0, 0, parts);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int row = row0 + 8 * q;
@@ -451,6 +496,8 @@ __global__ __launch_bounds__(kOrthThreads) void k_lr_orth(BatchView v, LaunchRan
         if (row0 + 8 * q == col) start2[col] = g[q];
     }
     __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kRank / 4; ++k) raw[k] = valid ? src[k] : (f32x4)(0.0f);    // after gram_block, which may only now have formed Z
     // elimination: after step k the rows below it hold what is left of G; a dropped column eliminates nothing
     for (int k = 0; k + 1 < kRank; ++k) {
         const double pivot = G[k][k], start = start2[k];
@@ -718,8 +765,8 @@ hipError_t launch_lr_project(const BatchView &v, const LaunchRange &r, bool wire
 hipError_t launch_lr_backproject(const BatchView &v, const LaunchRange &r, int min_iters, hipStream_t s)
 {
     if (r.count == 0 || r.lr_max_channels == 0) return hipSuccess;
-    dim3 grid((unsigned)((r.lr_max_channels + 255) / 256), (unsigned)r.count);
-    hipLaunchKernelGGL(k_lr_backproject, grid, dim3(256), 0, s, v, r, min_iters);
+    dim3 grid((unsigned)((r.lr_max_channels + kBackChannels - 1) / kBackChannels * r.lr_split), (unsigned)r.count);
+    hipLaunchKernelGGL(k_lr_backproject, grid, dim3(kBackThreads), 0, s, v, r, min_iters);
     return hipGetLastError();
 }
 
