@@ -138,8 +138,8 @@ __device__ __forceinline__ void lr_project_body(const BatchView &v, const Tensor
         for (int it = 0; it < 8; ++it) {
             const int64_t tok = row_base + trow + 8 * it;
             if (s0 < steps && tok < d.n_tokens && ch < d.n_channels) {
-                xr[it].load(p.x, tok * C + ch);
-                br[it].load(p.recon, tok * C + ch);
+                xr[it].load_stream(p.x, tok * C + ch);
+                br[it].load_stream(p.recon, tok * C + ch);
             } else {
                 xr[it].zero();
                 br[it].zero();
@@ -268,8 +268,8 @@ __device__ __forceinline__ void lr_backproject_body(const BatchView &v, const La
     auto fetch = [&](int slot, int64_t quad) {
         const int64_t row = 4 * quad + g;
         const int64_t at = row < last ? row : last;
-        xr[slot].load(p.x, at * C + ch);
-        br[slot].load(p.recon, at * C + ch);
+        xr[slot].load_stream(p.x, at * C + ch);
+        br[slot].load_stream(p.recon, at * C + ch);
         pv[slot][0] = P[at * kRank];
         pv[slot][1] = P[at * kRank + 16];
     };
