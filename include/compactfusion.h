@@ -163,11 +163,12 @@ typedef struct {
  * error-feedback mode.  Otherwise one kernel reduces and a second one, which
  * reads the operands again, writes the codes.  Results are bit-identical either
  * way.  By default a call takes the single pass where it applies, every
- * channel-scale tensor of the context has at least 256 tokens and at most 48
- * items per stripe (12288 tokens of bf16 in the default feedback mode) and the
- * call covers at least 64 items: it is about 30 % faster on MI355X at the sizes
- * of the paper's models, slower on tiny batches, and slower than two kernels
- * where 64 and more workgroups have to agree on a scale (16384 tokens and up).
+ * channel-scale tensor of the context has at least 256 tokens, the call covers at
+ * least 64 items, and either no stripe has more than 38 items (an item of such
+ * tall tensors is 512 rows of bf16 by 64 channels: 19456 tokens) or the call
+ * covers at most 4096: it is about 30 % faster on MI355X at the sizes of the
+ * paper's models, slower on tiny batches, and slower than two kernels on large
+ * ones where more workgroups have to agree on a scale.
  * CF_FLAG_SINGLE_PASS takes it whenever it applies, CF_FLAG_TWO_KERNEL never.
  *
  * Waiting in the single pass.  A workgroup normally finds the partial sums of its

@@ -26,6 +26,7 @@ struct Layout {
     size_t n_items = 0;
     int32_t max_group_items = 0;   // largest reduction group of the single-pass path
     bool sp_wide = false;          // single-pass items are kStripeChannelsWide channels wide (short tensors)
+    bool sp_slim = false;          // ... kStripeChannelsSlim channels wide (tall tensors)
     bool single_pass = false;      // every channel-scale tensor has single-pass geometry
     size_t off_lr_slices = 0, lr_slice_bytes = 0;       // slices of the low-rank back-projection, shared by the tensors of a call
     size_t total = 0;
@@ -203,7 +204,11 @@ cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &
             if (g > narrow_max_group) narrow_max_group = g;
         }
     L.sp_wide = L.single_pass && narrow_max_group > 0 && narrow_max_group <= 12;
-    const int stripe_channels = L.sp_wide ? kStripeChannelsWide : kStripeChannels;
+    // Tall tensors the other way round: all workgroups of a group wait for its slowest, and the more they are the longer.
+    // 128 -> 64 channels on batches of equal size, us: [6144, 3072] bf16 793 -> 790, [8192, 3072] 840 -> 812 (4-bit 858 ->
+    // 856), [12288, 3072] 895 -> 854, [16384, 3072] 1030 -> 902, [17776, 1920] with bf16 error 2227 -> 1976.
+    L.sp_slim = L.single_pass && narrow_max_group > 40;
+    const int stripe_channels = L.sp_wide ? kStripeChannelsWide : L.sp_slim ? kStripeChannelsSlim : kStripeChannels;
     for (int32_t t = 0; t < n; ++t) {
         const cf_tensor_desc &d = descs[t];
         TensorDev &v = L.dev[t];
@@ -263,7 +268,7 @@ cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &
         L.item_prefix[t] = (uint32_t)items;
         if (d.scale == CF_SCALE_CHANNEL && d.n_tokens < L.min_channel_scale_tokens) L.min_channel_scale_tokens = d.n_tokens;
         if (d.scale == CF_SCALE_CHANNEL && L.single_pass) {
-            v.p_rows = narrow_item_rows(d.dtype) / (L.sp_wide ? 2 : 1);
+            v.p_rows = narrow_item_rows(d.dtype) * kStripeChannels / stripe_channels;
             v.p_n_rb = (int32_t)((d.n_tokens + v.p_rows - 1) / v.p_rows);
             v.p_n_stripes = (int32_t)((d.n_channels + stripe_channels - 1) / stripe_channels);
             v.p_item_begin = (uint32_t)items;
@@ -372,6 +377,7 @@ struct cf_ctx {
         r.fin_hi = L.fin_prefix[first + count];
         r.sp_xcd_major = 0;
         r.sp_wait_polls = kWaitPolls;
+        r.sp_slim = L.sp_slim;
         r.sp_redo = 0;
         r.item_lo = L.item_prefix[first];
         r.item_hi = L.item_prefix[first + count];
@@ -714,9 +720,14 @@ cf_status run_sender(cf_ctx *ctx, int32_t first, int32_t count, const void *cons
     // unless asked for: not for tiny batches (the wait chain costs more than a second read) nor for short tensors
     // (an item is 128 or 256 rows tall: most of its lanes would idle)
     const bool forced = (ctx->opts.flags & CF_FLAG_SINGLE_PASS) != 0;
-    // nor for very tall ones (groups of more than 48 items: measured on [N, 3072] bf16 batches of equal size, single pass
-    // against two kernels: N = 8192 1.64 / 1.91 ms, 12288 1.80 / 1.88, 16384 2.04 / 1.91, 32768 2.34 / 1.92)
-    const bool worth_it = forced || (r.item_hi - r.item_lo >= 64u && ctx->L.min_channel_scale_tokens >= 256 && ctx->L.max_group_items <= 48);
+    // nor for very tall ones in large calls (groups of more than kTallGroupItems: single pass against two kernels in us,
+    // [12288, 3072] bf16, 24 items a group, 854 / 917; [16384, 3072], 32, 902 / 975; [17776, 1920], 35, 791 / 916 and with
+    // bf16 error 1976 / 2381; [20000, 3072], 40, 915 / 895; [32768, 3072], 64, 1080 / 992;
+    // calls of one tensor: [20000, 3072] 171 / 353, [32768, 3072] 267 / 370, [65536, 1024] 251 / 402, [131072, 256] 126 / 370)
+    const uint32_t items = r.item_hi - r.item_lo;
+    const bool small_call = items <= kTallCallItems;
+    const bool worth_it = forced || (items >= 64u && ctx->L.min_channel_scale_tokens >= 256 &&
+                                     (ctx->L.max_group_items <= kTallGroupItems || small_call));
     // (a group larger than what the device holds at once would have its first workgroups wait for ones that cannot
     // start before they leave: correct, they give up and the redo launch does them, but slow: such tensors take two kernels)
     const bool single_pass = ctx->L.single_pass && grid >= ctx->L.max_group_items && grid >= 1 && r.item_hi > r.item_lo && worth_it;

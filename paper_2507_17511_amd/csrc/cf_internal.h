@@ -25,10 +25,12 @@ constexpr int kMaxUploadTensors = 64;                       // pointer sets per 
 // were 50 % slower.  Short tensors do better with the wide stripe (items half
 // as tall, twice as many per group): 57 x [1024, 3072] 0.417 -> 0.382 ms; a
 // context whose tallest channel-scale tensor makes at most 12 items per group
-// with the narrow stripe (bf16: N <= 3072) takes the wide one.
+// with the narrow stripe (bf16: N <= 3072) takes the wide one, and one of more
+// than 40 (N > 10240) the slim one, whose items are twice as tall.
 constexpr int kPersistThreads = 256;
 constexpr int kStripeChannels = 128;
 constexpr int kStripeChannelsWide = 2 * kStripeChannels;    // 256
+constexpr int kStripeChannelsSlim = kStripeChannels / 2;    // 64
 // Rows a lane of the single-pass kernel keeps in registers: 128 VGPRs of raw operands, i.e. 16 rows of bf16 x and
 // recon, half as many of fp32, half as many again when the error buffer is an operand too (CF_EF_LITERAL = 1,
 // CF_EF_OFF = 2).  Measured on 114 x [4096, 3072] bf16 (two waves per SIMD): 16 rows 2.65 ms; 8 rows at three
@@ -36,6 +38,9 @@ constexpr int kStripeChannelsWide = 2 * kStripeChannels;    // 256
 constexpr int single_pass_rows_per_lane(int dtype, int ef) { return 16 / (dtype == 0 ? 2 : 1) / ((ef == 1 || ef == 2) ? 2 : 1); }
 // A workgroup polls a missing partial this many times (a microsecond or two each) before it gives its item up.
 constexpr uint32_t kWaitPolls = 4096;
+// Reduction groups of more items than this take two kernels by default, unless the call has at most kTallCallItems.
+constexpr int kTallGroupItems = 38;
+constexpr uint32_t kTallCallItems = 4096;
 constexpr int kGaveUpWord = 32;                             // 128 bytes behind the error word: how many items the call's first launch gave up
 constexpr int kRedoGrid = 512;                              // workgroups of the launch that does them
 
@@ -124,6 +129,7 @@ struct LaunchRange {
     uint32_t item_lo, item_hi;  // single-pass items
     uint32_t sp_xcd_major;      // single-pass kernel: deal the items XCD-major (a run of consecutive items per XCD)
     uint32_t sp_wait_polls;     // single-pass kernel: polls of a missing partial before the workgroup gives its item up
+    uint32_t sp_slim;           // single-pass kernel: items of kStripeChannelsSlim channels (tall tensors)
     uint32_t sp_redo;           // single-pass kernel: this is the launch over the given-up items
     uint64_t p_partial_lo, p_partial_hi;    // workspace bytes holding the single-pass partials of the range
     int32_t dts;                // storage dtype of every tensor in the range (cf_dtype), or 2 if mixed

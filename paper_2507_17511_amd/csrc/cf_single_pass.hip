@@ -10,7 +10,8 @@
 //           folded into the residual against the reconstruction), half as many
 //           of fp32, half as many again when the error buffer is an operand too
 //           (the literal and the no-feedback recursions); for contexts of short
-//           tensors half as tall and 256 channels wide (32 chunks x 8 row-lanes);
+//           tensors half as tall and 256 channels wide (32 chunks x 8 row-lanes),
+//           for contexts of tall ones twice as tall and 64 wide (8 x 32);
 //   group = the items of one such stripe of one tensor; only they have
 //           to agree on that stripe's scales, so there is no grid-wide barrier,
 //           and different groups drift apart, which keeps HBM busy while some
@@ -98,7 +99,7 @@ __device__ __forceinline__ float tree_over_published(int n, const float *mine, i
     return tree_top<LV, IS_MAX>(stack);
 }
 
-// SCH: channels per stripe (kStripeChannels or kStripeChannelsWide); the 256 lanes are SCH / 8 chunks across
+// SCH: channels per stripe (kStripeChannels, kStripeChannelsWide or kStripeChannelsSlim); the 256 lanes are SCH / 8 chunks across
 // by 2048 / SCH row-lanes down.
 template <int SCH> struct alignas(16) Shared {
     float red[kPersistThreads / (SCH / kChunk)][SCH];       // 8 KB: level 2 of the tree; afterwards the waves' patches for whole-line stores
@@ -335,17 +336,18 @@ template <int EF, int SCH> const void *pick_width(int err_dtype, bool fused)
     return fused ? persistent_fn<EF, F32, true, SCH>() : persistent_fn<EF, F32, false, SCH>();
 }
 
-template <int EF> const void *pick_ef(int err_dtype, bool fused, bool wide)
+template <int EF> const void *pick_ef(int err_dtype, bool fused, bool wide, bool slim)
 {
+    if (slim) return pick_width<EF, kStripeChannelsSlim>(err_dtype, fused);
     return wide ? pick_width<EF, kStripeChannelsWide>(err_dtype, fused) : pick_width<EF, kStripeChannels>(err_dtype, fused);
 }
 
-const void *pick(int ef, int err_dtype, bool fused, bool wide)
+const void *pick(int ef, int err_dtype, bool fused, bool wide, bool slim)
 {
-    if (ef == EF_LITERAL) return pick_ef<EF_LITERAL>(err_dtype, fused, wide);
-    if (ef == EF_OFF) return pick_ef<EF_OFF>(err_dtype, fused, wide);
-    if (ef == EF_NAIVE) return pick_ef<EF_NAIVE>(err_dtype, fused, wide);
-    return pick_ef<EF_RECON>(err_dtype, fused, wide);
+    if (ef == EF_LITERAL) return pick_ef<EF_LITERAL>(err_dtype, fused, wide, slim);
+    if (ef == EF_OFF) return pick_ef<EF_OFF>(err_dtype, fused, wide, slim);
+    if (ef == EF_NAIVE) return pick_ef<EF_NAIVE>(err_dtype, fused, wide, slim);
+    return pick_ef<EF_RECON>(err_dtype, fused, wide, slim);
 }
 
 }  // namespace
@@ -353,7 +355,7 @@ const void *pick(int ef, int err_dtype, bool fused, bool wide)
 int persistent_max_blocks_per_cu(int ef, int err_dtype, bool fused, bool wide)
 {
     int n = 0;
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, pick(ef, err_dtype, fused, wide), kPersistThreads, 0);
+    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, pick(ef, err_dtype, fused, wide, false), kPersistThreads, 0);
     if (e != hipSuccess) { (void)hipGetLastError(); return 0; }
     return n;
 }
@@ -390,7 +392,7 @@ hipError_t launch_single_pass(const BatchView &v, const LaunchRange &r, int ef, 
     if (redo) rr.sp_wait_polls = 0u;        // every partial is there; nothing to wait for
     const uint32_t n_wg = redo ? (items < (uint32_t)kRedoGrid ? items : (uint32_t)kRedoGrid) : one_shot ? items : (uint32_t)grid;
     void *args[] = {&vv, &rr};
-    return hipLaunchKernel(pick(ef, err_dtype, fused, wide), dim3(n_wg), dim3(kPersistThreads), args, 0, s);
+    return hipLaunchKernel(pick(ef, err_dtype, fused, wide, r.sp_slim != 0), dim3(n_wg), dim3(kPersistThreads), args, 0, s);
 }
 
 }  // namespace cf

@@ -137,6 +137,23 @@ def test_single_pass_stripe_width_rule_boundaries():
             run_parity(descs, cf.options(flags=cf.CF_FLAG_SINGLE_PASS), xs, mode=mode)
 
 
+@pytest.mark.parametrize("dtype", [cf.CF_BF16, cf.CF_F32])
+@pytest.mark.parametrize("ef, err_dtype", [(cf.CF_EF_RECON, cf.CF_F32), (cf.CF_EF_RECON, cf.CF_BF16), (cf.CF_EF_OFF, cf.CF_F32)])
+def test_single_pass_slim_stripes(dtype, ef, err_dtype):
+    """64-channel stripes of items twice as tall, which contexts whose tallest tensor makes more than 40 items per group
+    with 128-channel ones take: the tallest just above that line, its neighbours short ones, widths around a stripe
+    (one chunk, a chunk more or less than one or two stripes), every code width, bits against the oracle."""
+    rows = (128 if dtype == cf.CF_F32 else 256) // (2 if ef == cf.CF_EF_OFF else 1)       # of a 128-channel item
+    shapes = [(40 * rows + 1, 8, 1), (40 * rows + 1, 72, 2), (2 * rows, 120, 4), (2 * rows + 1, 136, 1), (1, 64, 2), (rows - 1, 56, 4)]
+    say(f"single pass, slim stripes dtype={dtype} ef={ef} err_dtype={err_dtype}: {shapes}")
+    descs = [cf.desc(n, c, dtype, bits, CH) for n, c, bits in shapes]
+    streams = [drift_stream((d.n_tokens, d.n_channels), d.dtype, steps=3, seed=670 + t, device=DEV) for t, d in enumerate(descs)]
+    xs = [[streams[t][s] for t in range(len(descs))] for s in range(3)]
+    for extra in (0, cf.CF_FLAG_FIXED_GRID, cf.CF_FLAG_TEST_NO_WAIT):
+        run_parity(descs, cf.options(ef=ef, err_dtype=err_dtype, flags=cf.CF_FLAG_SINGLE_PASS | extra), xs, mode="fused")
+    run_parity(descs, cf.options(ef=ef, err_dtype=err_dtype, flags=cf.CF_FLAG_SINGLE_PASS), xs, mode="split")
+
+
 def test_single_pass_long_groups_and_fixed_grid():
     """Groups of 157 items (N = 40000), as one workgroup per item and as a fixed grid of workgroups that loop
     over the items (CF_FLAG_FIXED_GRID)."""
