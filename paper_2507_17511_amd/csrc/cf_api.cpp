@@ -207,7 +207,16 @@ cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &
     // Tall tensors the other way round: all workgroups of a group wait for its slowest, and the more they are the longer.
     // 128 -> 64 channels on batches of equal size, us: [6144, 3072] bf16 793 -> 790, [8192, 3072] 840 -> 812 (4-bit 858 ->
     // 856), [12288, 3072] 895 -> 854, [16384, 3072] 1030 -> 902, [17776, 1920] with bf16 error 2227 -> 1976.
+    // Not where the last 64-channel stripe of a row would be short pieces of memory and most of what there is:
+    // 114 x [11653, 80] 360 -> 434, x [11653, 64] 272 -> 199, 60 x [17000, 96] 310 -> 298.
     L.sp_slim = L.single_pass && narrow_max_group > 40;
+    for (int32_t t = 0; t < n; ++t) {
+        const int64_t last = descs[t].n_channels % kStripeChannelsSlim;
+        const int64_t rows = narrow_item_rows(descs[t].dtype);
+        if (descs[t].scale == CF_SCALE_CHANNEL && descs[t].n_channels < kStripeChannels && last > 0 && last < kStripeChannelsSlim / 2 &&
+            (descs[t].n_tokens + rows - 1) / rows > 40)
+            L.sp_slim = false;
+    }
     const int stripe_channels = L.sp_wide ? kStripeChannelsWide : L.sp_slim ? kStripeChannelsSlim : kStripeChannels;
     for (int32_t t = 0; t < n; ++t) {
         const cf_tensor_desc &d = descs[t];
@@ -228,21 +237,27 @@ cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &
         L.tile_prefix[t] = (uint32_t)tiles;
         L.fin_prefix[t] = (uint32_t)fins;
         tiles += (uint64_t)v.n_rowblocks * (uint64_t)v.n_colblocks;
+        // Tiles across the row ends (see cf_kernels.hip) where the last 1024-channel tile of a row would be a part of one;
+        // their chunk numbers are 32-bit.  The receiver's kernel, which reads a lane's channel scales once for both rows
+        // of a tile, takes them only where whole rows would leave more than an eighth of the lanes idle.
+        const uint64_t chunks = (uint64_t)d.n_tokens * (uint64_t)v.n_chunks;
+        const bool ragged = v.n_chunks % kTileThreads != 0 && chunks < (1u << 31) - (1u << 16);
         // element-wise kernels do best with short-lived workgroups: a lane never has to wait for
         // its own stores before it can use its next loads
-        v.ew_rows = 1;
-        v.ew_n_rowblocks = (int32_t)((d.n_tokens + v.ew_rows - 1) / v.ew_rows);
+        v.ew_flat = ragged;
         v.ew_tile_begin = (uint32_t)ew_tiles;
         L.ew_prefix[t] = (uint32_t)ew_tiles;
-        ew_tiles += (uint64_t)v.ew_n_rowblocks * (uint64_t)v.n_colblocks;
+        ew_tiles += v.ew_flat ? (chunks + kTileThreads - 1) / kTileThreads : (uint64_t)d.n_tokens * (uint64_t)v.n_colblocks;
         if (ew_tiles > 0x7fffffffull) return CF_ERR_SHAPE;
         // the receiver's kernel moves 4 bytes per element, not 10: two rows per workgroup (loaded together, then
         // stored together) keep the workgroup count down; measured 1.43 -> 1.08 ms on 114 x [4096, 3072]
         v.dec_rows = o.encode_rows ? o.encode_rows : 2;
-        v.dec_n_rowblocks = (int32_t)((d.n_tokens + v.dec_rows - 1) / v.dec_rows);
+        v.dec_flat = ragged && v.n_chunks * 8 < v.n_colblocks * kTileThreads * 7;
         v.dec_tile_begin = (uint32_t)dec_tiles;
         L.dec_prefix[t] = (uint32_t)dec_tiles;
-        dec_tiles += (uint64_t)v.dec_n_rowblocks * (uint64_t)v.n_colblocks;
+        const uint64_t dec_run = (uint64_t)v.dec_rows * kTileThreads;
+        dec_tiles += v.dec_flat ? (chunks + dec_run - 1) / dec_run
+                                : (uint64_t)((d.n_tokens + v.dec_rows - 1) / v.dec_rows) * (uint64_t)v.n_colblocks;
         fins += (uint64_t)((d.n_channels + kFinalizeThreads - 1) / kFinalizeThreads);
         if (tiles > 0x7fffffffull || fins > 0x7fffffffull) return CF_ERR_SHAPE;
         if (d.scale == CF_SCALE_CHANNEL || d.scale == CF_SCALE_RANK1) {
@@ -384,6 +399,7 @@ struct cf_ctx {
         r.only_group_scale = 0;
         r.naive = opts.ef == CF_EF_NAIVE;
         r.dts = descs[first].dtype;
+        r.dec_kinds = 0;
         r.lr_max_channels = 0;
         r.lr_max_tokens = 0;
         r.lr_split = 1;
@@ -400,6 +416,7 @@ struct cf_ctx {
         if (r.p_partial_hi == 0) r.p_partial_lo = 0;
         for (int32_t t = first; t < first + count; ++t) {
             if (descs[t].dtype != descs[first].dtype) r.dts = 2;
+            if (descs[t].scale != CF_LOWRANK) r.dec_kinds |= L.dev[t].dec_flat ? 2 : 1;
             if (descs[t].scale == CF_LOWRANK) {
                 if (descs[t].n_channels > r.lr_max_channels) r.lr_max_channels = (int32_t)descs[t].n_channels;
                 if (descs[t].n_tokens > r.lr_max_tokens) r.lr_max_tokens = descs[t].n_tokens;

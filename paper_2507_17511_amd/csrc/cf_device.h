@@ -168,7 +168,7 @@ __device__ __forceinline__ void lines_exchange(float *patch, int lane, const F8 
 
 // `run` points at the first byte of the run in memory; n_valid = channel chunks of the run that exist.
 template <int RUN>
-__device__ __forceinline__ void lines_store_stream(void *run, int j, int n_valid, const f32x4 (&pieces)[2])
+__device__ __forceinline__ void lines_store_stream(void *run, int j, int64_t n_valid, const f32x4 (&pieces)[2])
 {
     CF_GLOBAL f32x4 *dst = gmut<f32x4>(run);
     if ((j >> 1) < n_valid) __builtin_nontemporal_store(pieces[0], dst + j);

@@ -65,15 +65,13 @@ struct alignas(16) TensorDev {
     int32_t p_n_stripes;    // ceil(C / stripe width of the context): reduction groups of this tensor
     uint32_t p_item_begin;  // id of this tensor's first item
     uint32_t p_pad_;
-    // element-wise kernels (warm-up, encode, decode): short tiles of ew_rows x 1024 channels
-    int32_t ew_rows;
-    int32_t ew_n_rowblocks; // ceil(N / ew_rows)
+    // element-wise kernels (warm-up, encode): tiles of one row x 1024 channels, or flat ones of 128 chunks across row ends
+    int32_t ew_flat;
     uint32_t ew_tile_begin;
-    // the receiver's kernel does less per row and likes taller tiles: dec_rows x 1024 channels
+    // the receiver's kernel does less per row and likes taller tiles: dec_rows x 1024 channels, or dec_rows x 128 chunks
     int32_t dec_rows;
-    int32_t dec_n_rowblocks;
+    int32_t dec_flat;
     uint32_t dec_tile_begin;
-    uint32_t dec_pad_;
     // rank-1 scales: per-row sums of |z| over each 1024-channel tile, rowpart[N][n_colblocks]
     uint32_t nm_block;      // N:M sparsifier: M, channels per block (8 or 16)
                             // low-rank compressor: 4 when the factors travel as 4-bit integers, else 0
@@ -135,6 +133,7 @@ struct LaunchRange {
     int32_t dts;                // storage dtype of every tensor in the range (cf_dtype), or 2 if mixed
     int32_t only_group_scale;   // tiled encode: skip tensors the single-pass kernel covers
     int32_t naive;              // decode: recon_t = D instead of recon_{t-1} + D (CF_EF_NAIVE)
+    int32_t dec_kinds;          // decode: bit 0, tensors with row tiles in the range; bit 1, with flat ones
     int32_t lr_max_channels;    // low-rank tensors of the range: largest C and N (0 = none)
     int64_t lr_max_tokens;
     int32_t lr_split;           // low-rank back-projection: runs of tokens per channel stripe (1: no slices)

@@ -8,6 +8,12 @@
 // Tiled kernels: one workgroup of 128 lanes per tile of rb_rows x 1024
 // channels; lane l owns channels [8l, 8l+8) of the tile (one 128-bit bf16
 // load per row), so a wave reads 1 KiB of contiguous row per instruction.
+// The element-wise kernels and the receiver's take runs of 128 chunks of 8
+// channels straight across the row ends instead (flat tiles) where a row is not
+// a whole number of 1024-channel tiles: x, recon, err, codes, group scales and
+// the sparsifier's masks and values all lie in chunk order, so only the scales of
+// a chunk ask for its row and column.  96 x [~4100, 1096] bf16, 2:8 sparsifier:
+// 895 -> 614 us (a row was one full tile and one with 9 of 128 lanes).
 // A batched grid covers the tiles of many tensors; a workgroup finds its
 // tensor by binary search in a prefix array of tile counts.  Each workgroup
 // copies its tensor's descriptor and pointers into registers once: nothing is
@@ -26,8 +32,45 @@ struct TileCtx {
     TensorDev d;        // by value: lives in scalar registers
     TensorPtrs p;
     int rowblock, colblock;
-    int rows;           // rows per tile of the kernel at hand
+    int rows;           // rows per tile of the kernel at hand; of a flat tile: runs of 128 chunks
+    bool flat;
+    uint32_t chunk0;    // flat: first chunk of the tile, counted from the tensor's first
 };
+
+// The chunk a lane of an element-wise tile works on (`run`: which 128 chunks of a flat tile, or which row).
+struct ChunkAt {
+    int64_t lin;        // chunk number in the tensor: elements [8 lin, 8 lin + 8)
+    int64_t row;
+    int col;            // chunk within its row
+    bool valid;
+    bool quad;          // the four chunks of this lane quad exist and their code bytes are one aligned run
+    int64_t wave_chunks;    // chunks that exist from the first lane of the wave on, contiguous in memory (may exceed 64 or be <= 0)
+};
+template <bool NEED_ROW> __device__ __forceinline__ ChunkAt chunk_at(const TileCtx &c, int run)
+{
+    ChunkAt a;
+    const int tid = (int)threadIdx.x, lane = tid & 63;
+    const uint32_t n = (uint32_t)c.d.n_chunks;
+    if (c.flat) {                                           // uniform
+        const uint32_t total = (uint32_t)c.d.n_tokens * n;  // below 2^31
+        const uint32_t lin = c.chunk0 + (uint32_t)(run * kTileThreads + tid);
+        a.lin = lin;
+        a.valid = lin < total;
+        a.quad = (lin | 3u) < total;
+        a.wave_chunks = (int64_t)total - (int64_t)(lin - (uint32_t)lane);
+        const uint32_t row = NEED_ROW ? (a.valid ? lin / n : 0u) : 0u;
+        a.row = row;
+        a.col = NEED_ROW ? (a.valid ? (int)(lin - row * n) : 0) : 0;
+    } else {
+        a.col = c.colblock * kTileThreads + tid;
+        a.row = (int64_t)c.rowblock * c.rows + run;
+        a.lin = a.row * (int64_t)n + a.col;
+        a.valid = a.col < c.d.n_chunks;
+        a.quad = (c.d.n_channels & 31) == 0;
+        a.wave_chunks = c.d.n_chunks - (a.col - lane);
+    }
+    return a;
+}
 
 // DTS: the storage dtype of every tensor in the launch when it is uniform (F32 or BF16: the other
 // dtype's code is then not even compiled in, which keeps the register count down), 2 when mixed.
@@ -36,7 +79,8 @@ template <int DTS> __device__ __forceinline__ bool is_bf16(const TensorDev &d) {
 // Which tiling of a tensor a kernel walks: the reduction's, the element-wise one (short tiles) or the receiver's.
 constexpr int TILES_REDUCE = 0, TILES_EW = 1, TILES_DECODE = 2;
 
-template <int KIND>
+// SHAPE: the tiles are known to be rows (0) or flat (1), or it depends on the tensor (2).
+template <int KIND, int SHAPE>
 __device__ __forceinline__ TileCtx locate_tile_of(const BatchView &v, const LaunchRange &r)
 {
     const uint32_t lo = KIND == TILES_EW ? r.ew_lo : KIND == TILES_DECODE ? r.dec_lo : r.tile_lo;
@@ -47,16 +91,23 @@ __device__ __forceinline__ TileCtx locate_tile_of(const BatchView &v, const Laun
     c.d = v.descs[t];
     c.p = v.ptrs[t];
     uint32_t local = tile - (KIND == TILES_EW ? c.d.ew_tile_begin : KIND == TILES_DECODE ? c.d.dec_tile_begin : c.d.tile_begin);
-    c.colblock = (int)(local % (uint32_t)c.d.n_colblocks);
-    c.rowblock = (int)(local / (uint32_t)c.d.n_colblocks);
-    c.rows = KIND == TILES_EW ? c.d.ew_rows : KIND == TILES_DECODE ? c.d.dec_rows : c.d.rb_rows;
+    c.rows = KIND == TILES_EW ? 1 : KIND == TILES_DECODE ? c.d.dec_rows : c.d.rb_rows;
+    c.flat = SHAPE != 2 ? SHAPE == 1 : KIND == TILES_EW ? c.d.ew_flat != 0 : c.d.dec_flat != 0;
+    if (c.flat) {
+        c.chunk0 = local * (uint32_t)(c.rows * kTileThreads);
+        c.rowblock = c.colblock = 0;
+    } else {
+        c.chunk0 = 0;
+        c.colblock = (int)(local % (uint32_t)c.d.n_colblocks);
+        c.rowblock = (int)(local / (uint32_t)c.d.n_colblocks);
+    }
     return c;
 }
 
 template <bool EW>
 __device__ __forceinline__ TileCtx locate_tile(const BatchView &v, const LaunchRange &r)
 {
-    return locate_tile_of<EW ? TILES_EW : TILES_REDUCE>(v, r);
+    return locate_tile_of<EW ? TILES_EW : TILES_REDUCE, EW ? 2 : 0>(v, r);
 }
 
 // ---------------------------------------------------------------- a0 warm-up
@@ -64,22 +115,18 @@ __device__ __forceinline__ TileCtx locate_tile(const BatchView &v, const LaunchR
 template <int DT, int ET>
 __device__ __forceinline__ void warmup_tile(const TileCtx &c)
 {
-    const TensorDev &d = c.d;
-    int chunk = c.colblock * kTileThreads + (int)threadIdx.x;
-    const bool cvalid = chunk < d.n_chunks;
+    const ChunkAt at = chunk_at<false>(c, 0);               // element-wise tiles are one row (or run) tall
     const int lane = (int)threadIdx.x & 63;
-    const int run_chunk0 = chunk - lane, run_valid = d.n_chunks - run_chunk0;    // the wave's 64 chunks: first, and how many exist
-    const int64_t i = c.rowblock;                   // element-wise tiles are one row tall
-    const int64_t e = i * d.n_channels + (int64_t)chunk * kChunk;
-    if (cvalid) {
+    const int64_t e = at.lin * kChunk;
+    if (at.valid) {
         Raw8<DT> x;
         x.load_stream(c.p.x, e);
         if (DT == BF16) x.store_stream(c.p.recon, e); else x.store(c.p.recon, e);
     }
     if (ET == F32) {        // zeros need no exchange: every lane fills the pieces a whole-line store gives it
         const f32x4 zero[2] = {(f32x4)(0.0f), (f32x4)(0.0f)};
-        lines_store_stream<64>(static_cast<float *>(c.p.err) + i * d.n_channels + (int64_t)run_chunk0 * kChunk, lane, run_valid, zero);
-    } else if (cvalid) {
+        lines_store_stream<64>(static_cast<float *>(c.p.err) + (at.lin - lane) * kChunk, lane, at.wave_chunks, zero);
+    } else if (at.valid) {
         Raw8<ET> zero;
         zero.zero();
         zero.store_stream(c.p.err, e);
@@ -286,25 +333,18 @@ __device__ __forceinline__ void encode_tile(const TileCtx &c, float *patch)
 {
     const TensorDev &d = c.d;
     const TensorPtrs &p = c.p;
-    int chunk = c.colblock * kTileThreads + (int)threadIdx.x;
-    const bool cvalid = chunk < d.n_chunks;
+    const ChunkAt at = chunk_at<MODE != 1>(c, 0);           // element-wise tiles are one row (or run) tall
+    const bool cvalid = at.valid;
     const int lane = (int)threadIdx.x & 63;
-    const int run_chunk0 = chunk - lane;                                // first chunk of the wave's 64
-    const int run_valid = d.n_chunks - run_chunk0;                      // chunks of the wave that exist (may exceed 64 or be <= 0)
-    const int64_t row0 = c.rowblock;            // element-wise tiles are one row tall
     const int64_t C = d.n_channels;
-    const int64_t row_bytes = C * BITS / 8;
-    const int n_groups = d.n_channels >> 7;
-    const bool wide = (d.n_channels & 31) == 0;
 
     F8 s = {}, vj = {};
-    if (MODE == 0 && cvalid) s = load_scales8(p.scales, (int64_t)chunk * kChunk);
-    if (MODE == 2 && cvalid) vj = load_scales8(p.scales, (int64_t)chunk * kChunk);
+    if (MODE == 0 && cvalid) s = load_scales8(p.scales, (int64_t)at.col * kChunk);
+    if (MODE == 2 && cvalid) vj = load_scales8(p.scales, (int64_t)at.col * kChunk);
 
     // One row per workgroup (the element-wise tiling): a lane never has to wait for its own stores
     // before it can use its next loads, and the register file holds one row's worth, not four.
-    const int64_t i = row0;
-    const int64_t e = i * C + (int64_t)chunk * kChunk;
+    const int64_t e = at.lin * kChunk;
     Raw8<DT> xr, br;
     Raw8<ET> er;
     if (cvalid) {
@@ -330,16 +370,16 @@ __device__ __forceinline__ void encode_tile(const TileCtx &c, float *patch)
         float sg = m / 7.0f;
 #pragma unroll
         for (int k = 0; k < 8; ++k) s.v[k] = sg;
-        if (cvalid && (threadIdx.x & 15) == 0) gmut<float>(p.scales)[i * n_groups + (chunk >> 4)] = sg;
+        if (cvalid && (threadIdx.x & 15) == 0) gmut<float>(p.scales)[at.lin >> 4] = sg;        // 16 chunks a group, whole groups a row
     }
     if (MODE == 2) {
-        const float ui = gconst<float>(p.scales)[C + i];
+        const float ui = gconst<float>(p.scales)[C + at.row];
 #pragma unroll
         for (int k = 0; k < 8; ++k) s.v[k] = ui * vj.v[k];
     }
     F8 dq;
     uint32_t packed = quant8<BITS>(z, s, dq);
-    if (cvalid) store_codes_wide<BITS>(p.codes + i * row_bytes, chunk, packed, wide);
+    if (cvalid) store_codes_ptr<BITS>(p.codes + at.lin * BITS, (int)threadIdx.x, packed, at.quad);
     F8 enew;
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
@@ -350,7 +390,7 @@ __device__ __forceinline__ void encode_tile(const TileCtx &c, float *patch)
     if (ET == F32) {                    // whole 128-byte lines per store, streaming
         f32x4 pieces[2];
         lines_exchange<64>(patch, lane, enew, pieces);
-        lines_store_stream<64>(static_cast<float *>(p.err) + i * C + (int64_t)run_chunk0 * kChunk, lane, run_valid, pieces);
+        lines_store_stream<64>(static_cast<float *>(p.err) + (at.lin - lane) * kChunk, lane, at.wave_chunks, pieces);
     } else if (cvalid) {
         Raw8<ET> eo;
         eo.narrow(enew);
@@ -373,16 +413,12 @@ __device__ __forceinline__ void nm_encode_tile(const TileCtx &c, float *patch)
 {
     const TensorDev &d = c.d;
     const TensorPtrs &p = c.p;
-    const int chunk = c.colblock * kTileThreads + (int)threadIdx.x;
-    const bool cvalid = chunk < d.n_chunks;         // every lane stays alive for the whole-line store of the error row
-    const int lane = (int)threadIdx.x & 63;
-    const int run_chunk0 = chunk - lane, run_valid = d.n_chunks - run_chunk0;
-    const int64_t i = c.rowblock;                   // element-wise tiles are one row tall
-    const int64_t C = d.n_channels;
-    const bool wide = (d.n_channels & 31) == 0;
+    const ChunkAt at = chunk_at<false>(c, 0);               // element-wise tiles are one row (or run) tall
+    const bool cvalid = at.valid;                           // every lane stays alive for the whole-line store of the error row
+    const int lane = (int)threadIdx.x & 63, tid = (int)threadIdx.x;
     constexpr int kValueBytes = KEEP * (DT == BF16 ? 2 : 4);
     uint8_t *values = p.codes + ((d.n_tokens * d.n_chunks + 15) / 16) * 16;
-    const int64_t e = i * C + (int64_t)chunk * kChunk;
+    const int64_t e = at.lin * kChunk;
     Raw8<DT> xr, br;
     Raw8<ET> er;
     if (cvalid) {
@@ -404,7 +440,7 @@ __device__ __forceinline__ void nm_encode_tile(const TileCtx &c, float *patch)
     uint32_t vals[KEEP];
     F8 dq;
     nm_values8<DT, KEEP>(z, mask, vals, dq);
-    if (cvalid) store_codes_wide<1>(p.codes + i * d.n_chunks, chunk, mask, wide);
+    if (cvalid) store_codes_ptr<1>(p.codes + at.lin, tid, mask, at.quad);
     if (PAIR) {
         // the even lane writes the block: its own kept values, then the odd lane's
         const int mine = __builtin_popcount(mask);
@@ -418,16 +454,16 @@ __device__ __forceinline__ void nm_encode_tile(const TileCtx &c, float *patch)
             for (int t = 0; t < KEEP; ++t) from_theirs = (q - mine == t) ? theirs[t] : from_theirs;
             block[q] = q < mine ? vals[q] : from_theirs;
         }
-        uint8_t *dst = values + (i * (d.n_chunks >> 1) + (chunk >> 1)) * kValueBytes;
-        if (DT == BF16 && KEEP == 1 && wide) {
-            // two blocks of a lane quad share one dword (whole quads are active: 32 | C)
+        uint8_t *dst = values + (at.lin >> 1) * kValueBytes;       // rows are an even number of chunks long
+        if (DT == BF16 && KEEP == 1 && at.quad) {
+            // two blocks of a lane quad share one dword (a whole quad is active)
             const uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)block[0], 0xAA, 0xF, 0xF, false);   // quad_perm [2,2,2,2]
-            if (cvalid && (chunk & 3) == 0) *gmut<uint32_t>(dst) = (block[0] & 0xFFFFu) | (next << 16);
-        } else if (cvalid && (chunk & 1) == 0) {
-            nm_store_values<DT, KEEP>(dst, chunk >> 1, block, false);
+            if (cvalid && (tid & 3) == 0) *gmut<uint32_t>(dst) = (block[0] & 0xFFFFu) | (next << 16);
+        } else if (cvalid && (tid & 1) == 0) {
+            nm_store_values<DT, KEEP>(dst, tid >> 1, block, false);
         }
     } else if (cvalid) {
-        nm_store_values<DT, KEEP>(values + (i * d.n_chunks + chunk) * kValueBytes, chunk, vals, wide);
+        nm_store_values<DT, KEEP>(values + at.lin * kValueBytes, tid, vals, at.quad);
     }
     F8 enew;
 #pragma unroll
@@ -439,7 +475,7 @@ __device__ __forceinline__ void nm_encode_tile(const TileCtx &c, float *patch)
     if (ET == F32) {                    // whole 128-byte lines per store, streaming
         f32x4 pieces[2];
         lines_exchange<64>(patch, lane, enew, pieces);
-        lines_store_stream<64>(static_cast<float *>(p.err) + i * C + (int64_t)run_chunk0 * kChunk, lane, run_valid, pieces);
+        lines_store_stream<64>(static_cast<float *>(p.err) + (at.lin - lane) * kChunk, lane, at.wave_chunks, pieces);
     } else if (cvalid) {
         Raw8<ET> eo;
         eo.narrow(enew);
@@ -567,6 +603,61 @@ __device__ __forceinline__ void decode_tile(const TileCtx &c, bool replace)
     }
 }
 
+// The same over a flat tile: c.rows runs of 128 chunks, two loaded together, then stored together.  A function of its
+// own, and a kernel of its own: with the runs' bookkeeping in the row tiles' loop the receiver of
+// 114 x [4096, 3072] took 1149 instead of 955 us, with both loops in one kernel 979.
+template <int DT, int BITS, int MODE>
+__device__ __forceinline__ void decode_flat(const TileCtx &c, bool replace)
+{
+    const TensorPtrs &p = c.p;
+    const int64_t C = c.d.n_channels;
+    constexpr int U = 2;
+    for (int u0 = 0; u0 < c.rows; u0 += U) {
+        Raw8<DT> br[U];
+        uint32_t pk[U];
+        F8 s[U];
+        int64_t lin[U];
+        bool live[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const ChunkAt at = chunk_at<MODE != 1>(c, u0 + u);
+            lin[u] = at.lin;
+            live[u] = u0 + u < c.rows && at.valid;
+            br[u].zero();
+            pk[u] = 0;
+            s[u] = {};
+            if (live[u]) {
+                if (!replace) br[u].load_stream(p.recon, at.lin * kChunk);
+                pk[u] = load_codes<BITS>(p.codes + at.lin * BITS, 0);
+                if (MODE == 1) {
+                    const float sg = gconst<float>(p.scales)[at.lin >> 4];
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) s[u].v[k] = sg;
+                } else {
+                    s[u] = load_scales8(p.scales, (int64_t)at.col * kChunk);
+                    if (MODE == 2) {
+                        const float ui = gconst<float>(p.scales)[C + at.row];
+#pragma unroll
+                        for (int k = 0; k < 8; ++k) s[u].v[k] = ui * s[u].v[k];
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (!live[u]) continue;
+            F8 dq, b = br[u].widen(), nb;
+            dequant8<BITS>(pk[u], s[u], dq);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) nb.v[k] = replace ? dq.v[k] : b.v[k] + dq.v[k];
+            Raw8<DT> out;
+            out.narrow(nb);
+            if (DT == BF16) out.store_stream(p.recon, lin[u] * kChunk);
+            else out.store(p.recon, lin[u] * kChunk);
+        }
+    }
+}
+
 template <int DT, int KEEP, bool PAIR>
 __device__ __forceinline__ void nm_decode_tile(const TileCtx &c, bool replace)
 {
@@ -622,37 +713,100 @@ __device__ __forceinline__ void nm_decode_tile(const TileCtx &c, bool replace)
     }
 }
 
-template <int DT> __device__ __forceinline__ void decode_dispatch(const TileCtx &c, bool replace)
+template <int DT, int KEEP, bool PAIR>
+__device__ __forceinline__ void nm_decode_flat(const TileCtx &c, bool replace)
+{
+    const TensorDev &d = c.d;
+    const TensorPtrs &p = c.p;
+    constexpr int kValueBytes = KEEP * (DT == BF16 ? 2 : 4);
+    const uint8_t *values = p.codes + ((d.n_tokens * d.n_chunks + 15) / 16) * 16;
+    constexpr int U = 2;                                    // rows (or runs) loaded together, then stored together
+    for (int u0 = 0; u0 < c.rows; u0 += U) {
+        Raw8<DT> br[U];
+        uint32_t mask[U];
+        uint32_t vals[U][KEEP];
+        int64_t lin[U];
+        bool live[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const ChunkAt at = chunk_at<false>(c, u0 + u);
+            lin[u] = at.lin;
+            live[u] = u0 + u < c.rows && at.valid;
+            if (live[u]) {
+                // streaming hint: the line is written back by this workgroup (measured 5 % faster than a plain load)
+                if (!replace) br[u].load_stream(p.recon, at.lin * kChunk); else br[u].zero();
+                mask[u] = load_codes<1>(p.codes + at.lin, 0);
+                nm_load_values<DT, KEEP>(values + (PAIR ? at.lin >> 1 : at.lin) * kValueBytes, vals[u]);
+            } else {
+                br[u].zero();
+                mask[u] = 0;
+#pragma unroll
+                for (int q = 0; q < KEEP; ++q) vals[u][q] = 0;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            int first = 0;
+            if (PAIR) {     // the odd lane's values come after the even lane's; every lane takes part
+                const int lower = __builtin_popcount((uint32_t)__builtin_amdgcn_update_dpp(0, (int)mask[u], 0xB1, 0xF, 0xF, false));
+                first = (threadIdx.x & 1) ? lower : 0;
+            }
+            if (!live[u]) continue;
+            F8 dq, nb;
+            nm_scatter8<DT, KEEP>(mask[u], vals[u], dq, first);
+            const F8 b = br[u].widen();
+#pragma unroll
+            for (int k = 0; k < 8; ++k) nb.v[k] = replace ? dq.v[k] : b.v[k] + dq.v[k];
+            Raw8<DT> out;
+            out.narrow(nb);
+            if (DT == BF16) out.store_stream(p.recon, lin[u] * kChunk);
+            else out.store(p.recon, lin[u] * kChunk);
+        }
+    }
+}
+
+template <bool FLAT, int DT, int BITS, int MODE> __device__ __forceinline__ void decode_any(const TileCtx &c, bool replace)
+{
+    if (FLAT) decode_flat<DT, BITS, MODE>(c, replace); else decode_tile<DT, BITS, MODE>(c, replace);
+}
+
+template <bool FLAT, int DT, int KEEP, bool PAIR> __device__ __forceinline__ void nm_decode_any(const TileCtx &c, bool replace)
+{
+    if (FLAT) nm_decode_flat<DT, KEEP, PAIR>(c, replace); else nm_decode_tile<DT, KEEP, PAIR>(c, replace);
+}
+
+template <int DT, bool FLAT> __device__ __forceinline__ void decode_dispatch(const TileCtx &c, bool replace)
 {
     const TensorDev &d = c.d;
     if (d.scale == SPARSE_NM) {
         if (d.nm_block == 16) {
-            if (d.bits == 1) nm_decode_tile<DT, 1, true>(c, replace);
-            else if (d.bits == 2) nm_decode_tile<DT, 2, true>(c, replace);
-            else nm_decode_tile<DT, 4, true>(c, replace);
+            if (d.bits == 1) nm_decode_any<FLAT, DT, 1, true>(c, replace);
+            else if (d.bits == 2) nm_decode_any<FLAT, DT, 2, true>(c, replace);
+            else nm_decode_any<FLAT, DT, 4, true>(c, replace);
         } else {
-            if (d.bits == 1) nm_decode_tile<DT, 1, false>(c, replace);
-            else if (d.bits == 2) nm_decode_tile<DT, 2, false>(c, replace);
-            else nm_decode_tile<DT, 4, false>(c, replace);
+            if (d.bits == 1) nm_decode_any<FLAT, DT, 1, false>(c, replace);
+            else if (d.bits == 2) nm_decode_any<FLAT, DT, 2, false>(c, replace);
+            else nm_decode_any<FLAT, DT, 4, false>(c, replace);
         }
         return;
     }
-    if (d.scale == SCALE_GROUP) { decode_tile<DT, 4, 1>(c, replace); return; }
+    if (d.scale == SCALE_GROUP) { decode_any<FLAT, DT, 4, 1>(c, replace); return; }
     if (d.scale == SCALE_RANK1) {
-        if (d.bits == 1) decode_tile<DT, 1, 2>(c, replace); else decode_tile<DT, 2, 2>(c, replace);
+        if (d.bits == 1) decode_any<FLAT, DT, 1, 2>(c, replace); else decode_any<FLAT, DT, 2, 2>(c, replace);
         return;
     }
-    if (d.bits == 1) decode_tile<DT, 1, 0>(c, replace);
-    else if (d.bits == 2) decode_tile<DT, 2, 0>(c, replace);
-    else decode_tile<DT, 4, 0>(c, replace);
+    if (d.bits == 1) decode_any<FLAT, DT, 1, 0>(c, replace);
+    else if (d.bits == 2) decode_any<FLAT, DT, 2, 0>(c, replace);
+    else decode_any<FLAT, DT, 4, 0>(c, replace);
 }
 
-template <int DTS>
+// FLAT: the tensors with flat tiles, else those with row tiles; kernels of their own so that neither pays for the other.
+template <int DTS, bool FLAT>
 __global__ __launch_bounds__(kTileThreads) void k_decode(BatchView v, LaunchRange r)
 {
-    TileCtx c = locate_tile_of<TILES_DECODE>(v, r);
-    if (c.d.scale == LOWRANK) return;
-    if (is_bf16<DTS>(c.d)) decode_dispatch<BF16>(c, r.naive != 0); else decode_dispatch<F32>(c, r.naive != 0);
+    TileCtx c = locate_tile_of<TILES_DECODE, FLAT ? 1 : 0>(v, r);
+    if (c.d.scale == LOWRANK || (r.dec_kinds == 3 && (c.d.dec_flat != 0) != FLAT)) return;
+    if (is_bf16<DTS>(c.d)) decode_dispatch<BF16, FLAT>(c, r.naive != 0); else decode_dispatch<F32, FLAT>(c, r.naive != 0);
 }
 
 // ---------------------------------------------------------------- table uploads and fills
@@ -822,9 +976,20 @@ hipError_t launch_decode(const BatchView &v, const LaunchRange &r, hipStream_t s
 {
     dim3 grid(r.dec_hi - r.dec_lo), block(kTileThreads);
     if (grid.x == 0) return hipSuccess;
-    if (r.dts == 0) hipLaunchKernelGGL(k_decode<0>, grid, block, kCapLdsBytes, s, v, r);
-    else if (r.dts == 1) hipLaunchKernelGGL(k_decode<1>, grid, block, kCapLdsBytes, s, v, r);
-    else hipLaunchKernelGGL(k_decode<2>, grid, block, kCapLdsBytes, s, v, r);
+    for (int flat = 0; flat < 2; ++flat) {
+        if (!(r.dec_kinds >> flat & 1)) continue;
+        if (flat) {
+            if (r.dts == 0) hipLaunchKernelGGL((k_decode<0, true>), grid, block, kCapLdsBytes, s, v, r);
+            else if (r.dts == 1) hipLaunchKernelGGL((k_decode<1, true>), grid, block, kCapLdsBytes, s, v, r);
+            else hipLaunchKernelGGL((k_decode<2, true>), grid, block, kCapLdsBytes, s, v, r);
+        } else {
+            if (r.dts == 0) hipLaunchKernelGGL((k_decode<0, false>), grid, block, kCapLdsBytes, s, v, r);
+            else if (r.dts == 1) hipLaunchKernelGGL((k_decode<1, false>), grid, block, kCapLdsBytes, s, v, r);
+            else hipLaunchKernelGGL((k_decode<2, false>), grid, block, kCapLdsBytes, s, v, r);
+        }
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
     return hipGetLastError();
 }
 

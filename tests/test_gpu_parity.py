@@ -138,13 +138,32 @@ def test_single_pass_stripe_width_rule_boundaries():
 
 
 @pytest.mark.parametrize("dtype", [cf.CF_BF16, cf.CF_F32])
+@pytest.mark.parametrize("err_dtype", [cf.CF_F32, cf.CF_BF16])
+def test_row_local_tiles_across_row_ends(dtype, err_dtype):
+    """Widths that are no whole number of 1024-channel tiles, whose element-wise tiles run on across the row ends: one
+    chunk of 8 channels, odd numbers of chunks, a chunk more or less than a tile, and token counts that leave the last
+    tile (and its last lane quad) partly empty; every row-local compressor and the channel quantisers on two kernels."""
+    shapes = [(1, 8), (3, 8), (131, 72), (127, 1016), (5, 1032), (67, 2056), (33, 24)]
+    descs = [cf.desc(n, c, dtype, (1, 2, 4)[k % 3], CH) for k, (n, c) in enumerate(shapes)]
+    descs += [cf.desc(n, c, dtype, (1, 2, 4)[(k + 1) % 3], cf.CF_SPARSE_NM, 8) for k, (n, c) in enumerate(shapes)]
+    descs += [cf.desc(n, c, dtype, (1, 2, 4)[k % 3], cf.CF_SPARSE_NM, 16) for k, (n, c) in enumerate([(1, 16), (131, 80), (127, 1008), (5, 1040), (66, 2064)])]
+    descs += [cf.desc(n, c, dtype, 4, cf.CF_SCALE_GROUP, 128) for n, c in [(1, 128), (131, 384), (33, 1152)]]
+    descs += [cf.desc(n, c, dtype, 1 + k % 2, cf.CF_SCALE_RANK1) for k, (n, c) in enumerate([(3, 8), (131, 72), (127, 1016), (5, 1032)])]
+    say(f"tiles across row ends dtype={dtype} err_dtype={err_dtype}")
+    streams = [drift_stream((d.n_tokens, d.n_channels), d.dtype, steps=3, seed=770 + t, device=DEV) for t, d in enumerate(descs)]
+    xs = [[streams[t][s] for t in range(len(descs))] for s in range(3)]
+    for mode in ("fused", "split"):
+        run_parity(descs, cf.options(err_dtype=err_dtype), xs, mode=mode)
+
+
+@pytest.mark.parametrize("dtype", [cf.CF_BF16, cf.CF_F32])
 @pytest.mark.parametrize("ef, err_dtype", [(cf.CF_EF_RECON, cf.CF_F32), (cf.CF_EF_RECON, cf.CF_BF16), (cf.CF_EF_OFF, cf.CF_F32)])
 def test_single_pass_slim_stripes(dtype, ef, err_dtype):
     """64-channel stripes of items twice as tall, which contexts whose tallest tensor makes more than 40 items per group
     with 128-channel ones take: the tallest just above that line, its neighbours short ones, widths around a stripe
-    (one chunk, a chunk more or less than one or two stripes), every code width, bits against the oracle."""
+    (a chunk more or less than one or two stripes), every code width, bits against the oracle."""
     rows = (128 if dtype == cf.CF_F32 else 256) // (2 if ef == cf.CF_EF_OFF else 1)       # of a 128-channel item
-    shapes = [(40 * rows + 1, 8, 1), (40 * rows + 1, 72, 2), (2 * rows, 120, 4), (2 * rows + 1, 136, 1), (1, 64, 2), (rows - 1, 56, 4)]
+    shapes = [(40 * rows + 1, 64, 1), (40 * rows + 1, 136, 2), (2 * rows, 120, 4), (2 * rows + 1, 136, 1), (1, 64, 2), (rows - 1, 56, 4)]
     say(f"single pass, slim stripes dtype={dtype} ef={ef} err_dtype={err_dtype}: {shapes}")
     descs = [cf.desc(n, c, dtype, bits, CH) for n, c, bits in shapes]
     streams = [drift_stream((d.n_tokens, d.n_channels), d.dtype, steps=3, seed=670 + t, device=DEV) for t, d in enumerate(descs)]
