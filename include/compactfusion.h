@@ -166,7 +166,7 @@ typedef struct {
  * channel-scale tensor of the context has at least 256 tokens, the call covers at
  * least 64 items, and either no stripe has more than 38 items (an item of such
  * tall tensors is 512 rows of bf16 by 64 channels: 19456 tokens) or the call
- * covers at most 4096: it is about 30 % faster on MI355X at the sizes of the
+ * covers at most 512: it is about 30 % faster on MI355X at the sizes of the
  * paper's models, slower on tiny batches, and slower than two kernels on large
  * ones where more workgroups have to agree on a scale.
  * CF_FLAG_SINGLE_PASS takes it whenever it applies, CF_FLAG_TWO_KERNEL never.

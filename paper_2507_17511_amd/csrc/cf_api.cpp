@@ -258,7 +258,7 @@ cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &
         const uint64_t dec_run = (uint64_t)v.dec_rows * kTileThreads;
         dec_tiles += v.dec_flat ? (chunks + dec_run - 1) / dec_run
                                 : (uint64_t)((d.n_tokens + v.dec_rows - 1) / v.dec_rows) * (uint64_t)v.n_colblocks;
-        fins += (uint64_t)((d.n_channels + kFinalizeThreads - 1) / kFinalizeThreads);
+        fins += (uint64_t)((d.n_channels + kFinalizeColumns - 1) / kFinalizeColumns);
         if (tiles > 0x7fffffffull || fins > 0x7fffffffull) return CF_ERR_SHAPE;
         if (d.scale == CF_SCALE_CHANNEL || d.scale == CF_SCALE_RANK1) {
             L.any_channel = true;
@@ -737,10 +737,10 @@ cf_status run_sender(cf_ctx *ctx, int32_t first, int32_t count, const void *cons
     // unless asked for: not for tiny batches (the wait chain costs more than a second read) nor for short tensors
     // (an item is 128 or 256 rows tall: most of its lanes would idle)
     const bool forced = (ctx->opts.flags & CF_FLAG_SINGLE_PASS) != 0;
-    // nor for very tall ones in large calls (groups of more than kTallGroupItems: single pass against two kernels in us,
-    // [12288, 3072] bf16, 24 items a group, 854 / 917; [16384, 3072], 32, 902 / 975; [17776, 1920], 35, 791 / 916 and with
-    // bf16 error 1976 / 2381; [20000, 3072], 40, 915 / 895; [32768, 3072], 64, 1080 / 992;
-    // calls of one tensor: [20000, 3072] 171 / 353, [32768, 3072] 267 / 370, [65536, 1024] 251 / 402, [131072, 256] 126 / 370)
+    // nor for very tall ones in calls of more than a round of workgroups (single pass against two kernels in us:
+    // [12288, 3072] bf16, 24 items a group, 854 / 907; [16384, 3072], 32, 902 / 965; 30 x [17776, 1920] with bf16 error, 35,
+    // 1986 / 2096; [20000, 3072], 40, 915 / 895; [32768, 3072], 64, 1080 / 992; one tensor of [32768, 3072], 3072 items,
+    // 303 / 259, of [65536, 1024], 2048 items, 249 / 177; 4 x [20000, 128], 320 items, 34 / 48)
     const uint32_t items = r.item_hi - r.item_lo;
     const bool small_call = items <= kTallCallItems;
     const bool worth_it = forced || (items >= 64u && ctx->L.min_channel_scale_tokens >= 256 &&

@@ -12,7 +12,8 @@ namespace cf {
 constexpr int kTileThreads = 128;
 constexpr int kChunk = 8;                                   // channels per lane
 constexpr int kTileChannels = kTileThreads * kChunk;        // 1024
-constexpr int kFinalizeThreads = 256;                       // columns per finalise block
+constexpr int kFinalizeThreads = 256;
+constexpr int kFinalizeColumns = 16;                        // columns per finalise block
 constexpr int kRank1Threads = 1024;                         // one block per tensor finishes the token scales u
 constexpr int kMaxRank1Colblocks = 128;                     // rank-1 scales: C <= 128 * 1024
 constexpr int kMaxUploadTensors = 64;                       // pointer sets per upload launch
@@ -38,9 +39,10 @@ constexpr int kStripeChannelsSlim = kStripeChannels / 2;    // 64
 constexpr int single_pass_rows_per_lane(int dtype, int ef) { return 16 / (dtype == 0 ? 2 : 1) / ((ef == 1 || ef == 2) ? 2 : 1); }
 // A workgroup polls a missing partial this many times (a microsecond or two each) before it gives its item up.
 constexpr uint32_t kWaitPolls = 4096;
-// Reduction groups of more items than this take two kernels by default, unless the call has at most kTallCallItems.
+// Reduction groups of more items than this take two kernels by default, unless the call has at most kTallCallItems:
+// one round of workgroups, which nothing has to wait for.
 constexpr int kTallGroupItems = 38;
-constexpr uint32_t kTallCallItems = 4096;
+constexpr uint32_t kTallCallItems = 512;
 constexpr int kGaveUpWord = 32;                             // 128 bytes behind the error word: how many items the call's first launch gave up
 constexpr int kRedoGrid = 512;                              // workgroups of the launch that does them
 

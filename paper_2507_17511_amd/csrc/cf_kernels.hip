@@ -261,27 +261,40 @@ __global__ __launch_bounds__(kTileThreads) void k_colreduce(BatchView v, LaunchR
 
 // ---------------------------------------------------------------- a3, second level: tree over tile partials
 
-// One lane per column: continues the same binary tree over the n_rowblocks
-// partials (zero padded to a power of two), then s = sum / N or max / 7.
+// Continues the same binary tree over the n_rowblocks partials of a column (zero padded to a power of two), then
+// s = sum / N or max / 7.  Latency is all it costs: a lane takes an aligned sixteenth of the padded range of its column
+// (64-byte pieces of 16 columns), the sixteen results meet in LDS.  One lane per column took 28 us for 30 x [17776,
+// 1920] and 130 of the 150 us of a call over [16384, 512], whose 8-row tiles leave 2048 partials
+// (42 us now).
 __global__ __launch_bounds__(kFinalizeThreads) void k_finalize(BatchView v, LaunchRange r)
 {
+    constexpr int kParts = kFinalizeThreads / kFinalizeColumns;
+    __shared__ float part[kParts][kFinalizeColumns];
     uint32_t blk = r.fin_lo + blockIdx.x;
     int t = find_slot(v.fin_prefix, r.first, r.first + r.count, blk);
     const TensorDev d = v.descs[t];
     if (d.scale != SCALE_CHANNEL && d.scale != SCALE_RANK1) return;
-    int col = (int)(blk - d.fin_begin) * kFinalizeThreads + (int)threadIdx.x;
-    if (col >= d.n_channels) return;
-    const CF_GLOBAL float *partial = gconst<float>(v.workspace + d.partial_off) + col;
+    const int lane_col = (int)threadIdx.x % kFinalizeColumns, mine = (int)threadIdx.x / kFinalizeColumns;
+    const int col = (int)(blk - d.fin_begin) * kFinalizeColumns + lane_col;
+    const bool cvalid = col < d.n_channels;
     const int64_t C = d.n_channels;
-    float res, s;
-    if (d.bits == 4) {
-        res = tree_over<true, 18>(d.n_rowblocks, [&](int i) { return partial[(int64_t)i * C]; });
-        s = res / 7.0f;
-    } else {
-        res = tree_over<false, 18>(d.n_rowblocks, [&](int i) { return partial[(int64_t)i * C]; });
-        s = res / (float)d.n_tokens;
-    }
-    gmut<float>(v.ptrs[t].scales)[col] = s;
+    int per = 1;                                            // leaves per lane: the padded count / kParts, at least one
+    while (per * kParts < d.n_rowblocks) per <<= 1;
+    const int first = mine * per;
+    const int n = !cvalid || first >= d.n_rowblocks ? 0 : d.n_rowblocks - first < per ? d.n_rowblocks - first : per;
+    const CF_GLOBAL float *partial = gconst<float>(v.workspace + d.partial_off) + (int64_t)first * C + (cvalid ? col : 0);
+    if (d.bits == 4) part[mine][lane_col] = tree_over<true, 18>(n, [&](int i) { return partial[(int64_t)i * C]; });
+    else part[mine][lane_col] = tree_over<false, 18>(n, [&](int i) { return partial[(int64_t)i * C]; });
+    __syncthreads();
+    if (mine != 0 || !cvalid) return;
+    float w[kParts];
+#pragma unroll
+    for (int q = 0; q < kParts; ++q) w[q] = part[q][lane_col];
+#pragma unroll
+    for (int k = 1; k < kParts; k <<= 1)
+#pragma unroll
+        for (int q = 0; q < kParts; q += 2 * k) w[q] = d.bits == 4 ? fmaxf(w[q], w[q + k]) : w[q] + w[q + k];
+    gmut<float>(v.ptrs[t].scales)[col] = d.bits == 4 ? w[0] / 7.0f : w[0] / (float)d.n_tokens;
 }
 
 // Rank-1 scales (App. D "Quantization"): u_i = (rowsum_i / C) / (sum_i rowsum_i / (N C)), written

@@ -137,6 +137,17 @@ def test_single_pass_stripe_width_rule_boundaries():
             run_parity(descs, cf.options(flags=cf.CF_FLAG_SINGLE_PASS), xs, mode=mode)
 
 
+@pytest.mark.parametrize("n", [1, 8, 9, 120, 128, 129, 136, 2048, 2049, 4104])
+def test_finalise_splits_the_tree_of_a_column(n):
+    """The second level of the two-kernel reduction, whose lanes take aligned sixteenths of a column's 8-row partials:
+    one partial, 16 and 17 of them, a batch of 16 per lane and one more, and widths around its 16 columns."""
+    say(f"finalise N={n}")
+    descs = [cf.desc(n, c, cf.CF_BF16, b, s) for c, b, s in ((8, 1, CH), (16, 2, CH), (24, 4, CH), (136, 2, cf.CF_SCALE_RANK1))]
+    streams = [drift_stream((d.n_tokens, d.n_channels), d.dtype, steps=3, seed=870 + t, device=DEV) for t, d in enumerate(descs)]
+    xs = [[streams[t][s] for t in range(len(descs))] for s in range(3)]
+    run_parity(descs, cf.options(flags=cf.CF_FLAG_TWO_KERNEL, tile_rows=8), xs, mode="fused")
+
+
 @pytest.mark.parametrize("dtype", [cf.CF_BF16, cf.CF_F32])
 @pytest.mark.parametrize("err_dtype", [cf.CF_F32, cf.CF_BF16])
 def test_row_local_tiles_across_row_ends(dtype, err_dtype):
