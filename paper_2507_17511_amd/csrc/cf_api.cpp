@@ -258,7 +258,8 @@ cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &
         const uint64_t dec_run = (uint64_t)v.dec_rows * kTileThreads;
         dec_tiles += v.dec_flat ? (chunks + dec_run - 1) / dec_run
                                 : (uint64_t)((d.n_tokens + v.dec_rows - 1) / v.dec_rows) * (uint64_t)v.n_colblocks;
-        fins += (uint64_t)((d.n_channels + kFinalizeColumns - 1) / kFinalizeColumns);
+        v.fin_columns = v.n_rowblocks > 32 ? kFinalizeColumns : kFinalizeThreads;
+        fins += (uint64_t)((d.n_channels + v.fin_columns - 1) / v.fin_columns);
         if (tiles > 0x7fffffffull || fins > 0x7fffffffull) return CF_ERR_SHAPE;
         if (d.scale == CF_SCALE_CHANNEL || d.scale == CF_SCALE_RANK1) {
             L.any_channel = true;

@@ -13,7 +13,7 @@ constexpr int kTileThreads = 128;
 constexpr int kChunk = 8;                                   // channels per lane
 constexpr int kTileChannels = kTileThreads * kChunk;        // 1024
 constexpr int kFinalizeThreads = 256;
-constexpr int kFinalizeColumns = 16;                        // columns per finalise block
+constexpr int kFinalizeColumns = 16;                        // columns per finalise block, kFinalizeThreads where they have few partials
 constexpr int kRank1Threads = 1024;                         // one block per tensor finishes the token scales u
 constexpr int kMaxRank1Colblocks = 128;                     // rank-1 scales: C <= 128 * 1024
 constexpr int kMaxUploadTensors = 64;                       // pointer sets per upload launch
@@ -66,7 +66,7 @@ struct alignas(16) TensorDev {
     int32_t p_n_rb;         // ceil(N / p_rows): items per reduction group
     int32_t p_n_stripes;    // ceil(C / stripe width of the context): reduction groups of this tensor
     uint32_t p_item_begin;  // id of this tensor's first item
-    uint32_t p_pad_;
+    int32_t fin_columns;    // columns per finalise block
     // element-wise kernels (warm-up, encode): tiles of one row x 1024 channels, or flat ones of 128 chunks across row ends
     int32_t ew_flat;
     uint32_t ew_tile_begin;

@@ -265,36 +265,36 @@ __global__ __launch_bounds__(kTileThreads) void k_colreduce(BatchView v, LaunchR
 // s = sum / N or max / 7.  Latency is all it costs: a lane takes an aligned sixteenth of the padded range of its column
 // (64-byte pieces of 16 columns), the sixteen results meet in LDS.  One lane per column took 28 us for 30 x [17776,
 // 1920] and 130 of the 150 us of a call over [16384, 512], whose 8-row tiles leave 2048 partials
-// (42 us now).
+// (42 us now).  Columns of up to 32 partials stay with one lane each: 114 x [103, 368] is 35.4 us a step that way, 38.1 split.
 __global__ __launch_bounds__(kFinalizeThreads) void k_finalize(BatchView v, LaunchRange r)
 {
-    constexpr int kParts = kFinalizeThreads / kFinalizeColumns;
-    __shared__ float part[kParts][kFinalizeColumns];
+    __shared__ float part[kFinalizeThreads];
     uint32_t blk = r.fin_lo + blockIdx.x;
     int t = find_slot(v.fin_prefix, r.first, r.first + r.count, blk);
     const TensorDev d = v.descs[t];
     if (d.scale != SCALE_CHANNEL && d.scale != SCALE_RANK1) return;
-    const int lane_col = (int)threadIdx.x % kFinalizeColumns, mine = (int)threadIdx.x / kFinalizeColumns;
-    const int col = (int)(blk - d.fin_begin) * kFinalizeColumns + lane_col;
+    const int columns = d.fin_columns, parts = kFinalizeThreads / columns;      // powers of two
+    const int lane_col = (int)threadIdx.x & (columns - 1), mine = (int)threadIdx.x / columns;
+    const int col = (int)(blk - d.fin_begin) * columns + lane_col;
     const bool cvalid = col < d.n_channels;
     const int64_t C = d.n_channels;
-    int per = 1;                                            // leaves per lane: the padded count / kParts, at least one
-    while (per * kParts < d.n_rowblocks) per <<= 1;
+    int per = 1;                                            // leaves per lane: the padded count / parts, at least one
+    while (per * parts < d.n_rowblocks) per <<= 1;
     const int first = mine * per;
     const int n = !cvalid || first >= d.n_rowblocks ? 0 : d.n_rowblocks - first < per ? d.n_rowblocks - first : per;
     const CF_GLOBAL float *partial = gconst<float>(v.workspace + d.partial_off) + (int64_t)first * C + (cvalid ? col : 0);
-    if (d.bits == 4) part[mine][lane_col] = tree_over<true, 18>(n, [&](int i) { return partial[(int64_t)i * C]; });
-    else part[mine][lane_col] = tree_over<false, 18>(n, [&](int i) { return partial[(int64_t)i * C]; });
-    __syncthreads();
-    if (mine != 0 || !cvalid) return;
-    float w[kParts];
-#pragma unroll
-    for (int q = 0; q < kParts; ++q) w[q] = part[q][lane_col];
-#pragma unroll
-    for (int k = 1; k < kParts; k <<= 1)
-#pragma unroll
-        for (int q = 0; q < kParts; q += 2 * k) w[q] = d.bits == 4 ? fmaxf(w[q], w[q + k]) : w[q] + w[q + k];
-    gmut<float>(v.ptrs[t].scales)[col] = d.bits == 4 ? w[0] / 7.0f : w[0] / (float)d.n_tokens;
+    float w = d.bits == 4 ? tree_over<true, 18>(n, [&](int i) { return partial[(int64_t)i * C]; })
+                          : tree_over<false, 18>(n, [&](int i) { return partial[(int64_t)i * C]; });
+    for (int k = 1; k < parts; k <<= 1) {                   // uniform over the workgroup
+        part[threadIdx.x] = w;
+        __syncthreads();
+        if ((mine & (2 * k - 1)) == 0) {
+            const float other = part[threadIdx.x + k * columns];
+            w = d.bits == 4 ? fmaxf(w, other) : w + other;
+        }
+        __syncthreads();
+    }
+    if (mine == 0 && cvalid) gmut<float>(v.ptrs[t].scales)[col] = d.bits == 4 ? w / 7.0f : w / (float)d.n_tokens;
 }
 
 // Rank-1 scales (App. D "Quantization"): u_i = (rowsum_i / C) / (sum_i rowsum_i / (N C)), written
