@@ -274,7 +274,7 @@ cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &
             v.lr_z_off = partial_bytes;
             partial_bytes += align_up((size_t)d.n_channels * kLowRankRank * sizeof(float));
             v.lr_g_off = partial_bytes;
-            partial_bytes += align_up((size_t)d.n_channels * kLowRankRank * sizeof(float));      // 8 KB per 256 channels are used
+            partial_bytes += align_up((size_t)d.n_channels * kLowRankRank * sizeof(float));      // 8 KB per 256 channels and the last word are used
         }
         if (d.scale == CF_SCALE_RANK1) {
             L.any_rank1 = true;

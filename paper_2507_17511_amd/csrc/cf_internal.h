@@ -79,7 +79,8 @@ struct alignas(16) TensorDev {
                             // low-rank compressor: 4 when the factors travel as 4-bit integers, else 0
     uint64_t rowpart_off;
     // low-rank compressor: P = A Q [N][32] fp32; Z = A^T P [C][32] fp32, which Q takes the place of in the order
-    // k_lr_project reads it; partial sums of Z^T Z, one [32][32] fp64 matrix per 256 channels (C > 256 only)
+    // k_lr_project reads it; partial sums of Z^T Z, one [32][32] fp64 matrix per 256 channels (C > 256 only),
+    // and a word of k_lr_orth's at the end of their area
     uint64_t lr_p_off, lr_z_off, lr_g_off;
 };
 

@@ -340,15 +340,33 @@ __global__ __launch_bounds__(kBackThreads, 3) void k_lr_backproject(BatchView v,
 //
 // Done on the Gram matrix: with G = Z^T Z and R its (upper) Cholesky factor, Q = Z R^-1 is what Gram-Schmidt
 // gives, and the squared length a column is left with is the pivot of its elimination step.  G, R and the
-// substitution are fp64: the products of two fp32 entries are exact, and an error of eps * cond(Z)^2 stays below
-// fp32 rounding for every Z whose columns survive the 1e-4 rule (projecting the columns twice in fp32 reaches a few
-// 1e-7).  What bounds it: nothing but latency.  Projecting column by column is 96 rounds of workgroup-wide sums,
-// one after the other, on one workgroup per tensor (279 us for 57 x [3072, 32] on 57 of 256 CUs); here every
-// workgroup takes 256 channel rows, k_lr_gram sums their products on the fp64 matrix cores, and every workgroup of
-// k_lr_orth adds those partial sums up and eliminates the 32 x 32 matrix for itself: 20 + 33 us, most of them the
-// 31 dependent steps of the elimination.
+// substitution are fp64: the products of two fp32 entries are exact.  What bounds it: nothing but latency.
+// Projecting column by column is 96 rounds of workgroup-wide sums, one after the other, on one workgroup per tensor
+// (279 us for 57 x [3072, 32] on 57 of 256 CUs); here every workgroup takes 256 channel rows, k_lr_gram sums their
+// products on the fp64 matrix cores, and every workgroup of k_lr_orth adds those partial sums up and eliminates the
+// 32 x 32 matrix for itself, most of it the 31 dependent steps of the elimination.
+//
+// The 1e-4 rule does not bound the conditioning of Z: columns that each lean on the one before compound, and what is
+// left of a column is then rounding noise of G.  What is left of column i is sum_j u_ij z_j with u_ii = 1 and the
+// row of L^-1 (R^T = L D^1/2) before it, so an error of eta |z_j| |z_k| in the entries of G moves its pivot by eta
+// sum_j (|u_ij| |z_j|)^2.  The elimination carries u along in the unused triangle, and a tensor is left to k_lr_orth_twice,
+// the column by column form, unless every term of a kept column's sum is at most kLeanMost pivots and a dropped column
+// stays under the 1e-4 line with kLeanNoise times its terms added.  eta comes out at 4e-16 to 1.5e-15 over cosines, bumps,
+// powers, chains and steep spectra as columns, and a sum at 9 times its largest term at most: inner products of kept
+// columns stay below 9 * kLeanMost * 1.5e-15 = 4.5e-7 (1.0e-7 is the worst seen), what projecting twice in fp32 reaches.
+// Drifts as they are met have terms up to 1e4 pivots and stay at the rounding of V.  NaN and infinities fail the
+// comparisons too.
+constexpr double kLeanMost = 33554432.0;                    // 2^25
+constexpr double kLeanNoise = 32.0 * 3.6e-15;               // 32 terms, 2^-48 each
 constexpr int kOrthThreads = 256;                           // one channel row per lane
 constexpr int kGramEntries = kRank * kRank;                 // of which the upper triangle is used
+
+// Whether k_lr_orth left the tensor to k_lr_orth_twice: the last word of the Gram matrices' area, whose partial sums
+// fill at most 32 C + 8160 of its 128 C bytes (and which k_lr_orth alone uses where C <= 256).
+__device__ __forceinline__ CF_GLOBAL uint32_t *lr_left_over(const BatchView &v, const TensorDev &d)
+{
+    return gmut<uint32_t>(v.workspace + d.lr_g_off) + (int64_t)d.n_channels * kRank - 1;
+}
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef double f64x2 __attribute__((ext_vector_type(2)));
@@ -498,15 +516,16 @@ __global__ __launch_bounds__(kOrthThreads) void k_lr_orth(BatchView v, LaunchRan
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < kRank / 4; ++k) raw[k] = valid ? src[k] : (f32x4)(0.0f);    // after gram_block, which may only now have formed Z
-    // elimination: after step k the rows below it hold what is left of G; a dropped column eliminates nothing
+    // elimination: after step k the rows below it hold what is left of G on and above the diagonal, and below it the
+    // coefficients of L^-1; a dropped column eliminates nothing
     for (int k = 0; k + 1 < kRank; ++k) {
         const double pivot = G[k][k], start = start2[k];
         const bool keep = start > 0.0 && pivot > (double)kDrop2 * start;
-        const double f = keep ? G[k][col] * reciprocal(pivot) : 0.0;
+        const double f = keep ? (col == k ? 1.0 : G[k][col]) * reciprocal(pivot) : 0.0;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int i = row0 + 8 * q;
-            if (i > k && i <= col) {
+            if (i > k && (i <= col || col <= k)) {
                 g[q] = __builtin_fma(-G[k][i], f, g[q]);
                 G[i][col] = g[q];
             }
@@ -518,6 +537,17 @@ __global__ __launch_bounds__(kOrthThreads) void k_lr_orth(BatchView v, LaunchRan
         inv_len[tid] = start > 0.0 && pivot > (double)kDrop2 * start ? 1.0 / __builtin_sqrt(pivot) : 0.0;
     }
     __syncthreads();
+    bool clear = true;          // of this lane's entries below the diagonal; the comparisons fail on NaN
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int i = row0 + 8 * q;
+        const double term = g[q] * g[q] * start2[col], inv = inv_len[i];
+        if (col < i) clear = clear && (inv > 0.0 ? term * inv * inv <= kLeanMost : G[i][i] + kLeanNoise * term <= (double)kDrop2 * start2[i]);
+        if (col == i) clear = clear && start2[i] <= 1.7e308;
+    }
+    const bool left_over = __syncthreads_or(!clear) != 0;   // the same in every workgroup of the tensor: same sums, same steps
+    if (blockIdx.x == 0 && tid == 0) *lr_left_over(v, d) = left_over ? 1u : 0u;
+    if (left_over) return;                                  // Z stays as it is
 #pragma unroll
     for (int q = 0; q < 4; ++q)
         if (row0 + 8 * q < col) G[row0 + 8 * q][col] = g[q] * inv_len[row0 + 8 * q];        // R above the diagonal
@@ -588,6 +618,125 @@ __global__ __launch_bounds__(256) void k_lr_quant_u(BatchView v, LaunchRange r)
         f[4 * k] = w.x; f[4 * k + 1] = w.y; f[4 * k + 2] = w.z; f[4 * k + 3] = w.w;
     }
     quantise_factor_row(f, wire4_u(p) + row * 16, wire4_u_scales(d, p) + row);
+}
+
+// Q = orth(Z) column by column, every column projected twice, for the tensors k_lr_orth left over (normally none: the
+// launch is empty).  One workgroup of 1024 lanes per tensor holds the matrix in registers (3 channel rows per lane: C <=
+// 3072).  Bound by its 96 rounds of workgroup-wide sums, about 280 us a tensor of 3072 channels.
+constexpr int kTwiceThreads = 1024;
+constexpr int kTwiceRows = 3;
+
+struct TwiceShared {
+    float part[kTwiceThreads / 64][kRank + 1];
+    float total[kRank + 1];
+};
+
+// Sums `val` over the workgroup into sh.total[slot]; the caller places the barriers.
+__device__ __forceinline__ void twice_partial(TwiceShared &sh, int slot, float val)
+{
+    const float w = wave_tree_sum(val);
+    if (((int)threadIdx.x & 63) == 0) sh.part[(int)threadIdx.x >> 6][slot] = w;
+}
+
+__device__ __forceinline__ void twice_finish(TwiceShared &sh, int n_slots)
+{
+    __syncthreads();
+    if ((int)threadIdx.x < n_slots) {
+        float s = 0.0f;
+#pragma unroll
+        for (int w = 0; w < kTwiceThreads / 64; ++w) s += sh.part[w][threadIdx.x];
+        sh.total[threadIdx.x] = s;
+    }
+    __syncthreads();
+}
+
+// Column K: project it on the finished columns 0..K-1 (twice), then normalise or drop it.  K is a
+// template parameter so that every register of the matrix is addressed statically.
+template <int K>
+__device__ __forceinline__ void twice_column(float (&a)[kTwiceRows][kRank], TwiceShared &sh)
+{
+    float start2 = 0.0f;
+#pragma unroll
+    for (int pass = 0; pass < 2; ++pass) {
+        // <q_j, a_K> for every finished column j < K, and (first pass) the column's own length
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            float dot = 0.0f;
+#pragma unroll
+            for (int rr = 0; rr < kTwiceRows; ++rr) dot += a[rr][j] * a[rr][K];
+            twice_partial(sh, j, dot);
+        }
+        if (pass == 0) {
+            float own = 0.0f;
+#pragma unroll
+            for (int rr = 0; rr < kTwiceRows; ++rr) own += a[rr][K] * a[rr][K];
+            twice_partial(sh, K, own);
+        }
+        twice_finish(sh, pass == 0 ? K + 1 : K);
+        if (pass == 0) start2 = sh.total[K];
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            const float c = sh.total[j];
+#pragma unroll
+            for (int rr = 0; rr < kTwiceRows; ++rr) a[rr][K] -= c * a[rr][j];
+        }
+    }
+    float own = 0.0f;
+#pragma unroll
+    for (int rr = 0; rr < kTwiceRows; ++rr) own += a[rr][K] * a[rr][K];
+    twice_partial(sh, 0, own);
+    twice_finish(sh, 1);
+    const float left2 = sh.total[0];
+    const bool keep = start2 > 0.0f && left2 > kDrop2 * start2;
+    const float len = sqrtf(left2);
+#pragma unroll
+    for (int rr = 0; rr < kTwiceRows; ++rr) a[rr][K] = keep ? a[rr][K] / len : 0.0f;
+    __syncthreads();                                        // sh.total is rewritten by the next column
+}
+
+template <int K>
+__device__ __forceinline__ void twice_columns_from(float (&a)[kTwiceRows][kRank], TwiceShared &sh)
+{
+    twice_column<K>(a, sh);
+    if constexpr (K + 1 < kRank) twice_columns_from<K + 1>(a, sh);
+}
+
+__global__ __launch_bounds__(kTwiceThreads) void k_lr_orth_twice(BatchView v, LaunchRange r, int from_q0, int min_iters)
+{
+    __shared__ TwiceShared sh;
+    const int t = r.first + (int)blockIdx.x;
+    const TensorDev d = v.descs[t];
+    if (d.scale != LOWRANK || d.bits < min_iters || *lr_left_over(v, d) == 0u) return;      // uniform over the workgroup
+    const TensorPtrs p = v.ptrs[t];
+    const CF_GLOBAL f32x4 *src = from_q0 ? gconst<f32x4>(p.scales) : gconst<f32x4>(v.workspace + d.lr_z_off);
+    float a[kTwiceRows][kRank];
+#pragma unroll
+    for (int rr = 0; rr < kTwiceRows; ++rr) {
+        const int ch = (int)threadIdx.x + kTwiceThreads * rr;
+#pragma unroll
+        for (int k = 0; k < kRank / 4; ++k) {
+            f32x4 w = {};
+            if (ch < d.n_channels) w = src[(int64_t)ch * (kRank / 4) + k];
+            a[rr][4 * k] = w.x; a[rr][4 * k + 1] = w.y; a[rr][4 * k + 2] = w.z; a[rr][4 * k + 3] = w.w;
+        }
+    }
+    twice_columns_from<0>(a, sh);
+    CF_GLOBAL float *qs = gmut<float>(v.workspace + d.lr_z_off);
+    uint8_t *V = wire_v(d, p);
+#pragma unroll
+    for (int rr = 0; rr < kTwiceRows; ++rr) {
+        const int ch = (int)threadIdx.x + kTwiceThreads * rr;
+        if (ch >= d.n_channels) continue;
+        const int s = ch >> 5, c = ch & 31, hh = c >> 4, j = c & 15;
+#pragma unroll
+        for (int n = 0; n < kRank; ++n) {
+            qs[((int64_t)s * 64 + hh * 32 + n) * 16 + j] = a[rr][n];
+            if (factors_int4(d)) continue;
+            if (d.dtype == BF16) gmut<uint16_t>(V)[(int64_t)ch * kRank + n] = (uint16_t)bf16_rne(a[rr][n]);
+            else gmut<float>(V)[(int64_t)ch * kRank + n] = a[rr][n];
+        }
+        if (factors_int4(d)) quantise_factor_row(a[rr], wire4_v(d, p) + (int64_t)ch * 16, wire4_v_scales(d, p) + ch);
+    }
 }
 
 // ---------------------------------------------------------------- D = U V^T, error and reconstruction
@@ -751,6 +900,9 @@ hipError_t launch_lr_orth(const BatchView &v, const LaunchRange &r, bool from_q0
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(k_lr_orth, grid, dim3(kOrthThreads), 0, s, v, r, from_q0 ? 1 : 0, min_iters);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_lr_orth_twice, dim3((unsigned)r.count), dim3(kTwiceThreads), 0, s, v, r, from_q0 ? 1 : 0, min_iters);
     return hipGetLastError();
 }
 

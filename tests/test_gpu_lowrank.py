@@ -434,3 +434,75 @@ def test_lowrank_basis_is_orthonormal(c):
         assert worst <= 2.0 ** -23 + 1e-9
     finally:
         sess.close()
+
+
+def leaning_starts(c):
+    """Start matrices whose columns lean on the ones before: each keeps more than 1e-4 of its length for many columns
+    (or for all), while the matrix as a whole is conditioned far worse than 1e4."""
+    x, k = np.linspace(0.0, 1.0, c)[:, None], np.arange(R)[None]
+    basis = np.linalg.qr(np.random.default_rng(c).standard_normal((c, R)))[0]
+    yield "cosines", np.cos(k * x)
+    yield "bumps", np.exp(-((x - np.linspace(0.0, 1.0, R)[None]) / 0.08) ** 2)
+    yield "powers", x ** k
+    yield "sums", basis @ (np.eye(R) - np.triu(np.ones((R, R)), 1))
+    yield "steep sums", basis @ (np.eye(R) - 100.0 * np.triu(np.ones((R, R)), 1))
+    yield "random", np.random.default_rng(c + 2).standard_normal((c, R))
+
+
+@pytest.mark.parametrize("c", [224, 512, 3072])
+@pytest.mark.parametrize("decay", [0.6, 0.8])
+def test_lowrank_columns_that_lean_on_the_ones_before(c, decay):
+    """V is orthonormal and the residual as small as the fp64 oracle leaves it, for start matrices and products Z that
+    are nearly dependent in a chain.  An inner product of two columns made orthogonal by fp32 projections carries 3
+    additions in a lane, 6 in its wave and 16 over the waves, each rounding a sum of at most 1, and the last projection
+    as many: 2 * 25 * 2^-24 = 3e-6.  Columns next to the 1e-4 line may go either way in fp32; the residual falls by the
+    spectrum's factor a column, and three columns are allowed."""
+    n = 200
+    rng = np.random.default_rng(c + 1)
+    A = ((np.linalg.qr(rng.standard_normal((n, 48)))[0] * decay ** np.arange(48)) @ np.linalg.qr(rng.standard_normal((c, 48)))[0].T)
+    A = A.astype(np.float32)
+    A64 = A.astype(np.float64)
+    sess = CodecSession([cf.desc(n, c, cf.CF_F32, 1, cf.CF_LOWRANK, R)], cf.options(), device=DEV)
+    try:
+        for name, q0 in leaning_starts(c):
+            q0 = q0.astype(np.float32)
+            sess.warmup([torch.zeros((n, c), device=DEV)])
+            sess.scales[0].copy_(torch.from_numpy(q0.reshape(-1)).to(DEV))
+            sess.step_fused([torch.from_numpy(A).to(DEV)])
+            cf.cf_check_device(sess.ctx, sess.stream_handle)
+            V = split_wire(as_numpy(sess.codes[0]), n, c, cf.CF_F32)[1].astype(np.float64)
+            kept = np.abs(V).sum(axis=0) > 0
+            off = float(np.abs(V.T @ V - np.diag(kept.astype(np.float64))).max())
+            left = float(np.linalg.norm(as_numpy(sess.err[0]).astype(np.float64)) / np.linalg.norm(A64))
+            U, Vo = lr.subspace_iteration(A64, q0.astype(np.float64), 1)
+            want = float(np.linalg.norm(A64 - U @ Vo.T) / np.linalg.norm(A64))
+            say(f"leaning columns C={c} decay={decay} {name}: {int(kept.sum())} columns, V^T V off by {off:.1e}, residual {left:.2e} (oracle {want:.2e})")
+            assert off <= 50 * 2.0 ** -24
+            assert left <= want * decay ** -3 + 1e-5
+    finally:
+        sess.close()
+
+
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+@pytest.mark.parametrize("c", [64, 512])
+def test_lowrank_non_finite_token(bad, c):
+    """One token with a value that is no number: every column of Z meets it and is dropped, so V and the other tokens'
+    factors are zero and their state stays as it was; only the token itself is lost."""
+    n, hit = 96, 17
+    say(f"lowrank with one {bad} C={c}")
+    x0 = torch.randn((n, c), generator=torch.Generator().manual_seed(c)).to(DEV)
+    x1 = x0 + 0.05
+    x1[hit, 3] = bad
+    sess = CodecSession([cf.desc(n, c, cf.CF_F32, 1, cf.CF_LOWRANK, R)], cf.options(), device=DEV)
+    try:
+        sess.warmup([x0])
+        sess.scales[0].copy_(start_matrices(c, 1, c)[0].reshape(-1))
+        sess.step_fused([x1])
+        cf.cf_check_device(sess.ctx, sess.stream_handle)
+        U, V = split_wire(as_numpy(sess.codes[0]), n, c, cf.CF_F32)
+        others = [t for t in range(n) if t != hit]
+        assert not V.any() and not U[others].any()
+        assert torch.equal(sess.recon[0][others], x0[others])
+        assert torch.equal(sess.err[0][others], (x1 - x0)[others])
+    finally:
+        sess.close()
