@@ -118,7 +118,8 @@ typedef enum { CF_F32 = 0, CF_BF16 = 1 } cf_dtype;
  * CF_EF_RECON only.  The `scales` entry of such a tensor is an INPUT of the sender:
  * the start matrix Q0 [C, 32] fp32 that the caller draws; the receiver ignores it
  * (it must still be a valid pointer).  Results agree with an fp64 evaluation to
- * fp32 rounding, not bit for bit. */
+ * fp32 rounding, not bit for bit; a tensor's own bits do not depend on the other tensors
+ * of the call or the context. */
 typedef enum { CF_SCALE_CHANNEL = 0, CF_SCALE_GROUP = 1, CF_SCALE_RANK1 = 2, CF_SPARSE_NM = 3, CF_LOWRANK = 4 } cf_scale_kind;
 
 /* How the error buffer enters (a2) and is updated (a7).

@@ -139,34 +139,35 @@ int pick_rb_rows(const cf_tensor_desc *descs, int32_t n, const cf_options &o)
     return 8;
 }
 
-// Runs of tokens the back-projection of a call over `count` tensors is split into (the largest low-rank tensor's
-// channels and tokens given): enough to give the device a round of workgroups, but no more than 8, since the
-// orthogonalisation adds the runs up one after the other.  Whole steps with 1 / 4 / 8 / 16 runs: 1 x [4096, 3072] 501 /
-// 415 / 404 / 409 us, 2 x [4096, 3072] 523 / 435 / 433 / 442, 2 x [500, 512] 129 / 120 / 121 / 120; with 1 / 2 / 4:
-// 30 x [4096, 2048] 1223 / 1205 / 1215 us, 57 x [4096, 3072] 3169 / 3154 / 3195 (not worth twice the memory).
+// Workgroups that share a channel stripe of the low-rank back-projection in a call over `count` tensors (the largest
+// low-rank tensor's channels and tokens given): more where the stripes alone would leave the device idle.
+// Whole steps with 1 / 2 / 4 sharing, us: 1 x [4096, 3072] 561 / 476 / 445, 16 x [4096, 2048] 829 / 769 / 778,
+// 30 x [4096, 2048] 1181 / 1182 / 1192; 57 x [4096, 3072] 3176 / 3129.
 int64_t lowrank_split(int64_t max_channels, int64_t max_tokens, int64_t count)
 {
-    const int64_t blocks = (max_channels + kLowRankBackChannels - 1) / kLowRankBackChannels * count;
-    const int64_t runs = std::min<int64_t>(kLowRankSlots / blocks, (max_tokens + kLowRankRunTokens - 1) / kLowRankRunTokens);
-    return std::max<int64_t>(1, std::min<int64_t>(kLowRankMaxRuns, runs));
+    const int64_t stripes = (max_channels + kLowRankBackChannels - 1) / kLowRankBackChannels * count;
+    return std::min<int64_t>(lowrank_runs(max_tokens), stripes <= 256 ? kLowRankMaxRuns : stripes <= 1536 ? 2 : 1);
 }
 
-// Slices for any call on a context of these tensors: those of a call over some of them are at most as many as the
-// rule above makes for a context of as many tensors of the largest size.
+size_t lowrank_slice_bytes_of(int64_t max_channels, int64_t split, int64_t count)
+{
+    return (size_t)((split - 1) * count) * (size_t)max_channels * kLowRankRank * sizeof(float);
+}
+
+// What the shares after the first need in any call on a context of these tensors: no more than a call over as many
+// tensors of the largest size.
 size_t lowrank_slice_bytes(const cf_tensor_desc *descs, int32_t n)
 {
-    int64_t c = 0, tok = 0, most = 0;
+    int64_t c = 0, tok = 0;
     for (int32_t t = 0; t < n; ++t)
         if (descs[t].scale == CF_LOWRANK) {
             c = std::max<int64_t>(c, descs[t].n_channels);
             tok = std::max<int64_t>(tok, descs[t].n_tokens);
         }
     if (c == 0) return 0;
-    for (int64_t count = 1; count <= n; ++count) {
-        const int64_t split = lowrank_split(c, tok, count);
-        if (split > 1) most = std::max<int64_t>(most, split * count);
-    }
-    return align_up((size_t)most * (size_t)c * kLowRankRank * sizeof(float));
+    size_t most = 0;
+    for (int64_t count = 1; count <= n; ++count) most = std::max(most, lowrank_slice_bytes_of(c, lowrank_split(c, tok, count), count));
+    return align_up(most);
 }
 
 cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &o, Layout &L)
@@ -317,7 +318,7 @@ cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &
     L.off_p_partials = off;   off = align_up(off + p_partial_bytes);
     L.off_lr_slices = off;
     L.lr_slice_bytes = lowrank_slice_bytes(descs, n);
-    // no tensors outgrow the static scratch because of the slices (and the sums are the same there and here)
+    // no tensors outgrow the static scratch because of the slices: there are fewer then, and the sums are the same
     if (off <= kStaticScratchBytes) L.lr_slice_bytes = std::min(L.lr_slice_bytes, (kStaticScratchBytes - off) / kAlign * kAlign);
     off += L.lr_slice_bytes;
     L.total = off;
@@ -423,9 +424,9 @@ struct cf_ctx {
                 if (descs[t].n_tokens > r.lr_max_tokens) r.lr_max_tokens = descs[t].n_tokens;
             }
         }
-        if (r.lr_max_channels > 0) {    // as many runs as the rule says and the slices hold
-            const size_t per_run = (size_t)count * (size_t)r.lr_max_channels * kLowRankRank * sizeof(float);
-            r.lr_split = (int32_t)std::max<int64_t>(1, std::min<int64_t>(lowrank_split(r.lr_max_channels, r.lr_max_tokens, count), (int64_t)(L.lr_slice_bytes / per_run)));
+        if (r.lr_max_channels > 0) {    // as many shares as the rule says and the workspace holds; the sums are the same either way
+            r.lr_split = (int32_t)lowrank_split(r.lr_max_channels, r.lr_max_tokens, count);
+            while (lowrank_slice_bytes_of(r.lr_max_channels, r.lr_split, count) > L.lr_slice_bytes) r.lr_split /= 2;
         }
         return r;
     }

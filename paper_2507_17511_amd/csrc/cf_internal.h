@@ -139,8 +139,8 @@ struct LaunchRange {
     int32_t dec_kinds;          // decode: bit 0, tensors with row tiles in the range; bit 1, with flat ones
     int32_t lr_max_channels;    // low-rank tensors of the range: largest C and N (0 = none)
     int64_t lr_max_tokens;
-    int32_t lr_split;           // low-rank back-projection: runs of tokens per channel stripe (1: no slices)
-    uint64_t lr_slices_off;     // workspace offset of its slices, [count][lr_split][lr_max_channels][32] fp32
+    int32_t lr_split;           // low-rank back-projection: at most so many workgroups share a channel stripe's runs of tokens (1, 2 or 4)
+    uint64_t lr_slices_off;     // workspace offset of the shares after the first, [count][lr_split - 1][lr_max_channels][32] fp32
 };
 
 enum class Op { Compress, StepFused };
@@ -166,13 +166,12 @@ hipError_t launch_decode(const BatchView &v, const LaunchRange &r, hipStream_t s
 // Low-rank compressor (cf_lowrank.hip): rank 32, C a multiple of 32 and at most kLowRankMaxChannels.
 constexpr int kLowRankRank = 32;
 constexpr int kLowRankMaxChannels = 3072;
-// The back-projection's workgroups own kLowRankBackChannels channels each, and kLowRankSlots of them fit the device
-// (four per CU).  Calls that make fewer split their tokens into up to kLowRankMaxRuns runs of at least
-// kLowRankRunTokens, whose slices of Z live in the workspace.
+// The back-projection's workgroups own kLowRankBackChannels channels each.  A tensor's tokens are summed in lowrank_runs
+// runs, a property of the tensor alone: the sum has one order in every call.  Runs cost a workgroup that takes them all a
+// drained pipeline and a sum over its waves each, so short tensors have fewer.
 constexpr int kLowRankBackChannels = 128;
-constexpr int kLowRankSlots = 1024;
-constexpr int kLowRankMaxRuns = 8;
-constexpr int kLowRankRunTokens = 128;
+constexpr int kLowRankMaxRuns = 4;
+constexpr int lowrank_runs(int64_t n_tokens) { return n_tokens <= 256 ? 1 : n_tokens <= 1024 ? 2 : kLowRankMaxRuns; }
 // min_iters: only tensors whose descriptor asks for at least that many subspace iterations take part
 hipError_t launch_lr_orth(const BatchView &v, const LaunchRange &r, bool from_q0, int min_iters, hipStream_t s);
 hipError_t launch_lr_project(const BatchView &v, const LaunchRange &r, bool wire, int min_iters, hipStream_t s);

@@ -38,7 +38,7 @@ __device__ __forceinline__ f32x4 mfma16(float a, float b, f32x4 c) { return __bu
 
 // Operands a pass reads once.  Streaming hint for bf16 only, whose lanes take their 16 bytes in one load: fp32 lanes take
 // 32 bytes in two, and the hint lets go of the line in between.  57 x [4096, 3072], plain and with the hint: bf16 project
-// 600 / 585 us, back-projection 616 / 593; fp32 project 1094 / 1263, back-projection 1348 / 1779.
+// 600 / 585 us, back-projection 616 / 593; fp32 project 1094 / 1263, back-projection 1348 / 1779 (at four waves per SIMD).
 template <int DT> __device__ __forceinline__ void load_once(Raw8<DT> &r, const void *base, int64_t elem)
 {
     if (DT == BF16) r.load_stream(base, elem); else r.load(base, elem);
@@ -236,35 +236,47 @@ __global__ __launch_bounds__(kProjThreads, 2) void k_lr_project(BatchView v, Lau
 
 // ---------------------------------------------------------------- Z = A^T P
 
-// Where run `run` of tensor t leaves its part of Z: Z itself when the tokens are not split.
-__device__ __forceinline__ uint8_t *lr_slice(const BatchView &v, const LaunchRange &r, const TensorDev &d, int t, int run)
+// Workgroups that share the runs of one stripe of a tensor.
+__device__ __forceinline__ int lr_shares(const LaunchRange &r, const TensorDev &d)
 {
-    if (r.lr_split == 1) return v.workspace + d.lr_z_off;
-    return v.workspace + r.lr_slices_off + (uint64_t)((t - r.first) * r.lr_split + run) * (uint64_t)r.lr_max_channels * (kRank * sizeof(float));
+    const int runs = lowrank_runs(d.n_tokens);
+    return r.lr_split < runs ? r.lr_split : runs;
 }
 
-// A workgroup owns a stripe of 128 channels and one of r.lr_split runs of tokens; its 4 waves split those and add
-// their tiles up through LDS in wave order.  With one run the sum is Z; with more it is a slice of its own, and the
-// orthogonalisation adds the slices up.
+// Where share `share` of tensor t leaves its part of Z: the first in Z itself.
+__device__ __forceinline__ uint8_t *lr_slice(const BatchView &v, const LaunchRange &r, const TensorDev &d, int t, int share)
+{
+    if (share == 0) return v.workspace + d.lr_z_off;
+    return v.workspace + r.lr_slices_off + (uint64_t)((t - r.first) * (r.lr_split - 1) + share - 1) * (uint64_t)r.lr_max_channels * (kRank * sizeof(float));
+}
+
+// The tokens are cut into lowrank_runs(N) = 1, 2 or 4 runs.  Z is the sum (run 0 + run 1) + (run 2 + run 3), each run the
+// sum (w0 + w1) + (w2 + w3) over its 4 waves, so the bits depend on the tensor's shape alone, whoever adds: a workgroup
+// owns a stripe of 128 channels and either takes all runs one after the other, or, in calls of few tensors, one or two
+// of them, and the orthogonalisation adds the shares.
 // v_mfma_f32_16x16x4_f32 takes A[l % 16][l / 16] and B[l / 16][l % 16] from lane l: lane (q, g) holds channels
 // 8q..8q+7 of the stripe of token 4 * quad + g, straight from a 128-bit load, and spends them on 8 channel tiles
-// (tile j holds channels = j mod 8) times 2 rank tiles.  What bounds it is how much a CU has in flight: the
-// accumulators of a 128-channel tile are 64 registers, which leaves room for a ring of 8 quads (16 KB a wave) at four
-// waves per SIMD.  57 x [4096, 3072] bf16: 616 us (4.7 TB/s); with 256 channels, two waves per SIMD and 8 KB each, 717 us.
+// (tile j holds channels = j mod 8) times 2 rank tiles.  What bounds it is how much a CU has in flight:
+// three waves per SIMD (142 registers, 64 of them accumulators), each with the loads of one quad, about 2 KB; the loop asks
+// for R quads ahead, the compiler moves their loads down to the quad before their use.  57 x [4096, 3072], us: bf16 621
+// (713 with 256 channels and two waves per SIMD; 635 at four waves with one run), fp32 1185 (1187; 1769 with the hint).
+// The sums cost a drained pipeline and two barriers a run: four turns of one wave each instead of two of two took 1 %
+// longer at 57 x [1000, 3072].
 constexpr int kBackThreads = 256;
 constexpr int kBackChannels = kLowRankBackChannels;
+constexpr int kBackEntries = kBackChannels * kRank;
+typedef float BackSums[2][kBackEntries];                    // of waves 0 + 1 and 2 + 3
 
 template <int DT>
 __device__ __forceinline__ void lr_backproject_body(const BatchView &v, const LaunchRange &r, const TensorDev &d, const TensorPtrs &p, int t,
-                                                    int stripe, int run, float *sum)
+                                                    int stripe, int share, BackSums &sums, float *total)
 {
     const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
     const int q = lane & 15, g = lane >> 4;
     const int64_t C = d.n_channels, last = d.n_tokens - 1;
     const int64_t n_quads = (d.n_tokens + 3) / 4;
-    const int64_t per_wave = (n_quads + 4 * r.lr_split - 1) / (4 * r.lr_split);
-    const int64_t lo = (run * 4 + wave) * per_wave;         // may lie beyond the last quad: such a wave adds zeros
-    const int64_t hi = lo + per_wave < n_quads ? lo + per_wave : n_quads;
+    const int n_runs = lowrank_runs(d.n_tokens), n_mine = n_runs / lr_shares(r, d), first_run = share * n_mine;
+    const int64_t per_wave = (n_quads + 4 * n_runs - 1) / (4 * n_runs);
     // Loads without branches: rows and channels outside the tensor read its last ones, P counts as zero there and the
     // channels are not stored.
     const int ch0 = stripe * kBackChannels + 8 * q;
@@ -281,64 +293,76 @@ __device__ __forceinline__ void lr_backproject_body(const BatchView &v, const La
         pv[slot][0] = P[at * kRank];
         pv[slot][1] = P[at * kRank + 16];
     };
-    f32x4 acc[8][2];
+    CF_GLOBAL float *Z = gmut<float>(lr_slice(v, r, d, t, share)) + (int64_t)stripe * kBackEntries;
+    const int n_out = (d.n_channels - stripe * kBackChannels) * kRank;      // entries of the stripe that exist
+    for (int run = first_run; run < first_run + n_mine; ++run) {            // uniform over the workgroup
+        const int64_t lo = (run * 4 + wave) * per_wave;     // may lie beyond the last quad: such a wave adds zeros
+        const int64_t hi = lo + per_wave < n_quads ? lo + per_wave : n_quads;
+        f32x4 acc[8][2];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) acc[j][0] = acc[j][1] = (f32x4)(0.0f);
-    if (lo < hi) {
+        for (int j = 0; j < 8; ++j) acc[j][0] = acc[j][1] = (f32x4)(0.0f);
+        if (lo < hi) {
 #pragma unroll
-        for (int u = 0; u < R; ++u) fetch(u, lo + u);
-        for (int64_t quad0 = lo; quad0 < hi; quad0 += R) {
+            for (int u = 0; u < R; ++u) fetch(u, lo + u);
+            for (int64_t quad0 = lo; quad0 < hi; quad0 += R) {
 #pragma unroll
-            for (int u = 0; u < R; ++u) {
-                const F8 x = xr[u].widen(), b = br[u].widen();
-                F8 z;
+                for (int u = 0; u < R; ++u) {
+                    const F8 x = xr[u].widen(), b = br[u].widen();
+                    F8 z;
 #pragma unroll
-                for (int j = 0; j < 8; ++j) z.v[j] = x.v[j] - b.v[j];
-                const bool valid = quad0 + u < hi && 4 * (quad0 + u) + g <= last;
-                const float p0 = valid ? pv[u][0] : 0.0f, p1 = valid ? pv[u][1] : 0.0f;
-                fetch(u, quad0 + R + u);
+                    for (int j = 0; j < 8; ++j) z.v[j] = x.v[j] - b.v[j];
+                    const bool valid = quad0 + u < hi && 4 * (quad0 + u) + g <= last;
+                    const float p0 = valid ? pv[u][0] : 0.0f, p1 = valid ? pv[u][1] : 0.0f;
+                    fetch(u, quad0 + R + u);
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    acc[j][0] = mfma16(z.v[j], p0, acc[j][0]);
-                    acc[j][1] = mfma16(z.v[j], p1, acc[j][1]);
+                    for (int j = 0; j < 8; ++j) {
+                        acc[j][0] = mfma16(z.v[j], p0, acc[j][0]);
+                        acc[j][1] = mfma16(z.v[j], p1, acc[j][1]);
+                    }
                 }
             }
         }
-    }
-    // tile j, register i of lane (q, g): channel 8 * (4 * g + i) + j of the stripe, column q (and 16 + q)
-    for (int w = 0; w < kBackThreads / 64; ++w) {
-        if (wave == w) {
+        // tile j, register i of lane (q, g): channel 8 * (4 * g + i) + j of the stripe, column q (and 16 + q)
+        for (int w = 0; w < 2; ++w) {
+            if ((wave & 1) == w) {
+                float *mine = sums[wave >> 1];
 #pragma unroll
-            for (int j = 0; j < 8; ++j)
+                for (int j = 0; j < 8; ++j)
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
+                    for (int i = 0; i < 4; ++i)
 #pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        const int idx = (8 * (4 * g + i) + j) * kRank + 16 * h + q;
-                        sum[idx] = (w == 0) ? acc[j][h][i] : sum[idx] + acc[j][h][i];
-                    }
+                        for (int h = 0; h < 2; ++h) {
+                            const int idx = (8 * (4 * g + i) + j) * kRank + 16 * h + q;
+                            mine[idx] = (w == 0) ? acc[j][h][i] : mine[idx] + acc[j][h][i];
+                        }
+            }
+            __syncthreads();
         }
-        __syncthreads();
-    }
-    CF_GLOBAL float *Z = gmut<float>(lr_slice(v, r, d, t, run));
-    for (int k = (int)threadIdx.x; k < kBackChannels * kRank; k += kBackThreads) {
-        const int c = stripe * kBackChannels + k / kRank;
-        if (c < d.n_channels) Z[(int64_t)c * kRank + (k % kRank)] = sum[k];
+        // a lane keeps to its own entries of `total` and of Z
+        const bool opens = run == first_run || (run & 1) == 0, closes = run + 1 == first_run + n_mine || (run & 1) == 1;
+        for (int k = (int)threadIdx.x; k < kBackEntries; k += kBackThreads) {
+            float pair = sums[0][k] + sums[1][k];
+            if (!opens) pair = total[k] + pair;
+            if (!closes) total[k] = pair;
+            else if (k < n_out) Z[k] = run < first_run + 2 ? pair : Z[k] + pair;
+        }
+        __syncthreads();                                    // before the next run's first waves write their sums
     }
 }
 
 __global__ __launch_bounds__(kBackThreads, 3) void k_lr_backproject(BatchView v, LaunchRange r, int min_iters)
 {
-    __shared__ float sum[kBackChannels * kRank];
+    __shared__ BackSums sums;
+    __shared__ float total[kBackEntries];
     const int t = r.first + (int)blockIdx.y;
     const TensorDev d = v.descs[t];
     if (d.scale != LOWRANK || d.bits < min_iters) return;
     const int n_stripes = (d.n_channels + kBackChannels - 1) / kBackChannels;
-    const int stripe = (int)blockIdx.x % n_stripes, run = (int)blockIdx.x / n_stripes;
-    if (run >= r.lr_split) return;                          // uniform over the workgroup: fewer stripes than the widest tensor
+    const int stripe = (int)blockIdx.x % n_stripes, share = (int)blockIdx.x / n_stripes;
+    if (share >= lr_shares(r, d)) return;                   // uniform over the workgroup: narrower or shorter than the largest tensor
     const TensorPtrs p = v.ptrs[t];
-    if (d.dtype == BF16) lr_backproject_body<BF16>(v, r, d, p, t, stripe, run, sum);
-    else lr_backproject_body<F32>(v, r, d, p, t, stripe, run, sum);
+    if (d.dtype == BF16) lr_backproject_body<BF16>(v, r, d, p, t, stripe, share, sums, total);
+    else lr_backproject_body<F32>(v, r, d, p, t, stripe, share, sums, total);
 }
 
 // ---------------------------------------------------------------- Q = orth(Z)
@@ -384,12 +408,12 @@ typedef double f64x2 __attribute__((ext_vector_type(2)));
 // lane l on both sides, so a lane's two loads of a step (columns c and 16 + c) feed all three.  Register i of lane l
 // holds row 4 * i + l / 16, column l % 16 of a tile.
 typedef double GramParts[kOrthThreads / 64][3][256];
-// The rows are Q0's, or Z's; where Z lies in slices their sum is formed here and left in Z.
+// The rows are Q0's, or Z's; where several workgroups shared Z the sum of the shares is formed here and left in Z.
 __device__ __forceinline__ void gram_block(const BatchView &v, const LaunchRange &r, const TensorDev &d, int t, bool from_q0, int first, GramParts &part)
 {
     const int n_channels = d.n_channels;
-    const int n_slices = from_q0 ? 1 : r.lr_split;
-    const CF_GLOBAL float *src = from_q0 ? gconst<float>(v.ptrs[t].scales) : gconst<float>(lr_slice(v, r, d, t, 0));
+    const int n_shares = from_q0 ? 1 : lr_shares(r, d);
+    const CF_GLOBAL float *src = from_q0 ? gconst<float>(v.ptrs[t].scales) : gconst<float>(v.workspace + d.lr_z_off);
     const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
     const int col = lane & 15;
     const int row0 = first + wave * 64 + (lane >> 4);
@@ -401,15 +425,23 @@ __device__ __forceinline__ void gram_block(const BatchView &v, const LaunchRange
         lo[s] = valid ? src[(int64_t)row * kRank + col] : 0.0f;
         hi[s] = valid ? src[(int64_t)row * kRank + 16 + col] : 0.0f;
     }
-    if (n_slices > 1) {         // uniform over the launch
-        for (int k = 1; k < n_slices; ++k) {
-            src = gconst<float>(lr_slice(v, r, d, t, k));
+    if (n_shares > 1) {         // uniform over the workgroup; 2 or 4
+        const CF_GLOBAL float *s1 = gconst<float>(lr_slice(v, r, d, t, 1));
+#pragma unroll
+        for (int s = 0; s < 16; ++s) {
+            const int row = row0 + 4 * s;
+            const bool valid = row < n_channels;
+            lo[s] += valid ? s1[(int64_t)row * kRank + col] : 0.0f;
+            hi[s] += valid ? s1[(int64_t)row * kRank + 16 + col] : 0.0f;
+        }
+        if (n_shares > 2) {
+            const CF_GLOBAL float *s2 = gconst<float>(lr_slice(v, r, d, t, 2)), *s3 = gconst<float>(lr_slice(v, r, d, t, 3));
 #pragma unroll
             for (int s = 0; s < 16; ++s) {
                 const int row = row0 + 4 * s;
                 const bool valid = row < n_channels;
-                lo[s] += valid ? src[(int64_t)row * kRank + col] : 0.0f;
-                hi[s] += valid ? src[(int64_t)row * kRank + 16 + col] : 0.0f;
+                lo[s] += valid ? s2[(int64_t)row * kRank + col] + s3[(int64_t)row * kRank + col] : 0.0f;
+                hi[s] += valid ? s2[(int64_t)row * kRank + 16 + col] + s3[(int64_t)row * kRank + 16 + col] : 0.0f;
             }
         }
         CF_GLOBAL float *Z = gmut<float>(v.workspace + d.lr_z_off);

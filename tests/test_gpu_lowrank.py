@@ -506,3 +506,35 @@ def test_lowrank_non_finite_token(bad, c):
         assert torch.equal(sess.err[0][others], (x1 - x0)[others])
     finally:
         sess.close()
+
+
+@pytest.mark.parametrize("n, count", [(200, 3), (600, 12), (1100, 12), (1100, 66)])
+def test_lowrank_bits_do_not_depend_on_the_call(n, count):
+    """A tensor's factors and state are the same bits alone in a context, in a call of its own in a large one, and in
+    one call with all the others: with 1, 2 and 4 runs of tokens, shared by 4, 2 or no workgroups."""
+    c = 3072
+    say(f"lowrank: one tensor alone, layer by layer and batched, {count} x [{n}, {c}]")
+    d = cf.desc(n, c, cf.CF_BF16, 2, cf.CF_LOWRANK, R)
+    xs = [stream(n, c, cf.CF_BF16, 2, 500 + t) for t in range(count)]
+    q0 = start_matrices(c, count, 550)
+    batch, layers, alone = (CodecSession([d] * k, cf.options(), device=DEV) for k in (count, count, 1))
+    try:
+        for s in (batch, layers):
+            s.warmup([x[0] for x in xs])
+            for t in range(count):
+                s.scales[t].copy_(q0[t].reshape(-1))
+        batch.step_fused([x[1] for x in xs])
+        for t in range(count):
+            layers.step_fused([xs[t][1]], first=t, count=1)
+            alone.warmup([xs[t][0]])
+            alone.scales[0].copy_(q0[t].reshape(-1))
+            alone.step_fused([xs[t][1]])
+            cf.cf_check_device(alone.ctx, alone.stream_handle)
+            for got in (layers.codes[t], alone.codes[0]):
+                assert torch.equal(got, batch.codes[t]), f"factors of tensor {t} depend on the call"
+            for name in ("recon", "err"):
+                for got in (getattr(layers, name)[t], getattr(alone, name)[0]):
+                    assert torch.equal(got, getattr(batch, name)[t]), f"{name} of tensor {t} depends on the call"
+    finally:
+        for s in (batch, layers, alone):
+            s.close()
