@@ -165,11 +165,15 @@ typedef struct {
  * reads the operands again, writes the codes.  Results are bit-identical either
  * way.  By default a call takes the single pass where it applies, every
  * channel-scale tensor of the context has at least 256 tokens, the call covers at
- * least 64 items, and either no stripe has more than 38 items (an item of such
- * tall tensors is 512 rows of bf16 by 64 channels: 19456 tokens) or the call
- * covers at most 512: it is about 30 % faster on MI355X at the sizes of the
- * paper's models, slower on tiny batches, and slower than two kernels on large
- * ones where more workgroups have to agree on a scale.
+ * least 64 items, and either no stripe has too many items or the call covers at
+ * most 512: it is about 30 % faster on MI355X at the sizes of the paper's models,
+ * slower on tiny batches, and slower than two kernels on large ones where more
+ * workgroups have to agree on a scale.  Contexts of mostly tall tensors (more than
+ * 40 of the items above: 10240 tokens of bf16), and those with one of more than
+ * 48, have items of twice the rows and half the channels and take up to 38 of them
+ * (19456 tokens; 24 in CF_EF_NAIVE, 12288 tokens); others up to 48 (12288 tokens).
+ * Where most of a context are tall tensors of fewer than 32 channels, or of 72 to
+ * 88, the limit is 40.
  * CF_FLAG_SINGLE_PASS takes it whenever it applies, CF_FLAG_TWO_KERNEL never.
  *
  * Waiting in the single pass.  A workgroup normally finds the partial sums of its

@@ -27,6 +27,7 @@ struct Layout {
     int32_t max_group_items = 0;   // largest reduction group of the single-pass path
     bool sp_wide = false;          // single-pass items are kStripeChannelsWide channels wide (short tensors)
     bool sp_slim = false;          // ... kStripeChannelsSlim channels wide (tall tensors)
+    int32_t sp_group_limit = 0;    // larger groups take two kernels by default, but for small calls
     bool single_pass = false;      // every channel-scale tensor has single-pass geometry
     size_t off_lr_slices = 0, lr_slice_bytes = 0;       // slices of the low-rank back-projection, shared by the tensors of a call
     size_t total = 0;
@@ -197,27 +198,37 @@ cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &
     // N = 2048 1.49 / 1.51 / 1.60 -> 1.52 / 1.48 / 1.55, N = 3072 1.47 / 1.52 / 1.61 -> 1.46 / 1.50 / 1.58,
     // N = 4096 1.50 / 1.55 / 1.62 -> 1.53 / 1.56 / 1.65, N = 6144 1.56 / 1.59 / 1.68 -> 1.62 / 1.66 / 1.77.
     auto narrow_item_rows = [&](int32_t dtype) { return (kPersistThreads / (kStripeChannels / kChunk)) * single_pass_rows_per_lane(dtype, o.ef); };
-    int64_t narrow_max_group = 0;
+    int64_t narrow_max_group = 0, elements = 0, tall_elements = 0, sliver_elements = 0;
     for (int32_t t = 0; t < n; ++t)
         if (descs[t].scale == CF_SCALE_CHANNEL) {
-            const int64_t rows = narrow_item_rows(descs[t].dtype);
+            const int64_t rows = narrow_item_rows(descs[t].dtype), c = descs[t].n_channels, last = c % kStripeChannelsSlim;
             const int64_t g = (descs[t].n_tokens + rows - 1) / rows;
             if (g > narrow_max_group) narrow_max_group = g;
+            elements += descs[t].n_tokens * c;
+            if (g > kTallGroupItems) tall_elements += descs[t].n_tokens * c;
+            // the last 64-channel stripe of a row is a few short pieces of memory and much of what there is
+            if (g > kTallGroupItems && c < kStripeChannels && last > 0 && last < kStripeChannelsSlim / 2) sliver_elements += descs[t].n_tokens * c;
         }
+    const bool slivers = sliver_elements > 0 && sliver_elements >= elements - sliver_elements;
     L.sp_wide = L.single_pass && narrow_max_group > 0 && narrow_max_group <= 12;
     // Tall tensors the other way round: all workgroups of a group wait for its slowest, and the more they are the longer.
     // 128 -> 64 channels on batches of equal size, us: [6144, 3072] bf16 793 -> 790, [8192, 3072] 840 -> 812 (4-bit 858 ->
-    // 856), [12288, 3072] 895 -> 854, [16384, 3072] 1030 -> 902, [17776, 1920] with bf16 error 2227 -> 1976.
-    // Not where the last 64-channel stripe of a row would be short pieces of memory and most of what there is:
-    // 114 x [11653, 80] 360 -> 434, x [11653, 64] 272 -> 199, 60 x [17000, 96] 310 -> 298.
-    L.sp_slim = L.single_pass && narrow_max_group > 40;
-    for (int32_t t = 0; t < n; ++t) {
-        const int64_t last = descs[t].n_channels % kStripeChannelsSlim;
-        const int64_t rows = narrow_item_rows(descs[t].dtype);
-        if (descs[t].scale == CF_SCALE_CHANNEL && descs[t].n_channels < kStripeChannels && last > 0 && last < kStripeChannelsSlim / 2 &&
-            (descs[t].n_tokens + rows - 1) / rows > 40)
-            L.sp_slim = false;
-    }
+    // 856), [12288, 3072] 895 -> 854, [16384, 3072] 1030 -> 902, [17776, 1920] with bf16 error 2227 -> 1976.  Tensors that
+    // are not tall lose by it, so tall ones that the 128-channel form still serves (up to kNarrowGroupLimit items) must
+    // hold half of the context: 40 x [1024, 3072] with one [12288, 3072] 332 -> 357, 40 x [4096, 3072] with one 1027 -> 1042,
+    // 20 x [4096, 3072] with seven 1080 -> 1068; beyond that two kernels are the other choice: 40 x [2048, 3072] with four
+    // [16384, 3072] 970 against 1078.  Not for slivers: 114 x [11653, 80] 360 -> 434 (x [11653, 64] 272 -> 199, 60 x
+    // [17000, 96] 310 -> 298).
+    L.sp_slim = L.single_pass && !slivers && narrow_max_group > kTallGroupItems &&
+                (narrow_max_group > kNarrowGroupLimit || tall_elements >= elements - tall_elements);
+    // Largest group of a call of any size, single pass against two kernels in us.  64-channel stripes: 20 x [12288, 3072], 24
+    // items, 854 / 907; [16384, 3072], 32, 902 / 965; 30 x [17776, 1920] with bf16 error, 35, 1986 / 2096; 16 x [9500, 3072]
+    // fp32, 38, 1985 / 2120, literal 1652 / 1798; [20000, 3072], 40, 915 / 895; [32768, 3072], 64, 1080 / 992.  Naive
+    // compression reads x only, so a second read costs little: 16 x [14000, 3072], 28, 1236 / 1219; [19000, 3072], 38, 1884 /
+    // 1654.  128-channel stripes: 4 x [10000, 3072], 40, 290 / 307; one [12288, 3072] among 40 x [4096, 3072], 48, 1027 / 1311;
+    // slivers, whose second kernel runs across the row ends: 114 x [11653, 80], 46, 351 / 312, x [10500, 72], 42, 344 / 265.
+    L.sp_group_limit = L.sp_slim ? (o.ef == CF_EF_NAIVE ? kSlimGroupLimitNaive : kSlimGroupLimit)
+                                 : slivers ? kTallGroupItems : kNarrowGroupLimit;
     const int stripe_channels = L.sp_wide ? kStripeChannelsWide : L.sp_slim ? kStripeChannelsSlim : kStripeChannels;
     for (int32_t t = 0; t < n; ++t) {
         const cf_tensor_desc &d = descs[t];
@@ -739,14 +750,14 @@ cf_status run_sender(cf_ctx *ctx, int32_t first, int32_t count, const void *cons
     // unless asked for: not for tiny batches (the wait chain costs more than a second read) nor for short tensors
     // (an item is 128 or 256 rows tall: most of its lanes would idle)
     const bool forced = (ctx->opts.flags & CF_FLAG_SINGLE_PASS) != 0;
-    // nor for very tall ones in calls of more than a round of workgroups (single pass against two kernels in us:
-    // [12288, 3072] bf16, 24 items a group, 854 / 907; [16384, 3072], 32, 902 / 965; 30 x [17776, 1920] with bf16 error, 35,
-    // 1986 / 2096; [20000, 3072], 40, 915 / 895; [32768, 3072], 64, 1080 / 992; one tensor of [32768, 3072], 3072 items,
-    // 303 / 259, of [65536, 1024], 2048 items, 249 / 177; 4 x [20000, 128], 320 items, 34 / 48)
+    // nor for very tall ones (see sp_group_limit) in calls of more than a round of workgroups (us, single pass / two kernels:
+    // one tensor of [32768, 3072], 3072 items, 303 / 259, of [65536, 1024], 2048 items, 249 / 177; 4 x [20000, 128], 320
+    // items, 34 / 48; one [65536, 128], 256 items in groups of 128, 35 / 52, [131072, 64], 256 in one group, 46 / 60, [40000,
+    // 384], 474 in groups of 79, 48 / 81, [30000, 256] fp32 39 / 59)
     const uint32_t items = r.item_hi - r.item_lo;
     const bool small_call = items <= kTallCallItems;
     const bool worth_it = forced || (items >= 64u && ctx->L.min_channel_scale_tokens >= 256 &&
-                                     (ctx->L.max_group_items <= kTallGroupItems || small_call));
+                                     (ctx->L.max_group_items <= ctx->L.sp_group_limit || small_call));
     // (a group larger than what the device holds at once would have its first workgroups wait for ones that cannot
     // start before they leave: correct, they give up and the redo launch does them, but slow: such tensors take two kernels)
     const bool single_pass = ctx->L.single_pass && grid >= ctx->L.max_group_items && grid >= 1 && r.item_hi > r.item_lo && worth_it;

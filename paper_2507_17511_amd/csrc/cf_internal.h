@@ -26,8 +26,8 @@ constexpr int kMaxUploadTensors = 64;                       // pointer sets per 
 // were 50 % slower.  Short tensors do better with the wide stripe (items half
 // as tall, twice as many per group): 57 x [1024, 3072] 0.417 -> 0.382 ms; a
 // context whose tallest channel-scale tensor makes at most 12 items per group
-// with the narrow stripe (bf16: N <= 3072) takes the wide one, and one of more
-// than 40 (N > 10240) the slim one, whose items are twice as tall.
+// with the narrow stripe (bf16: N <= 3072) takes the wide one, and one of mostly
+// tensors of more than 40 (N > 10240) the slim one, whose items are twice as tall.
 constexpr int kPersistThreads = 256;
 constexpr int kStripeChannels = 128;
 constexpr int kStripeChannelsWide = 2 * kStripeChannels;    // 256
@@ -39,9 +39,13 @@ constexpr int kStripeChannelsSlim = kStripeChannels / 2;    // 64
 constexpr int single_pass_rows_per_lane(int dtype, int ef) { return 16 / (dtype == 0 ? 2 : 1) / ((ef == 1 || ef == 2) ? 2 : 1); }
 // A workgroup polls a missing partial this many times (a microsecond or two each) before it gives its item up.
 constexpr uint32_t kWaitPolls = 4096;
-// Reduction groups of more items than this take two kernels by default, unless the call has at most kTallCallItems:
-// one round of workgroups, which nothing has to wait for.
-constexpr int kTallGroupItems = 38;
+// A tensor of more 128-channel items per group than kTallGroupItems is tall: contexts of mostly such take 64-channel
+// stripes.  Groups of more items than the limit of the stripe in use take two kernels by default, unless the call has at
+// most kTallCallItems: one round of workgroups, which nothing has to wait for.
+constexpr int kTallGroupItems = 40;
+constexpr int kNarrowGroupLimit = 48;
+constexpr int kSlimGroupLimit = 38;
+constexpr int kSlimGroupLimitNaive = 24;
 constexpr uint32_t kTallCallItems = 512;
 constexpr int kGaveUpWord = 32;                             // 128 bytes behind the error word: how many items the call's first launch gave up
 constexpr int kRedoGrid = 512;                              // workgroups of the launch that does them

@@ -11,6 +11,7 @@
 
 extern std::vector<std::string> g_launch_log;
 extern bool g_capturing;
+extern bool g_single_pass_slim;
 
 static int g_failed = 0;
 #define EXPECT(cond)                                                                    \
@@ -180,12 +181,12 @@ int main()
     cf_destroy(nullptr);
 
     // ---- which path a call takes by default: the single pass for tensors of 256 tokens and more in calls of 64
-    // items and more, two kernels for tiny ones and for tensors so tall that more than 48 workgroups share a scale
+    // items and more, two kernels for tiny ones
     {
         struct Case { int64_t n, c; const char *must, *must_not; uint32_t flags; };
         const Case cases[] = {
             {4096, 512, "k_reset_partials k_single_pass k_single_pass_redo", "k_colreduce", 0},       // 16 items per group, 64 in all
-            {16384, 64, "k_colreduce k_finalize k_encode", "k_single_pass", 0},                        // 64 items per group
+            {16384, 64, "k_colreduce k_finalize k_encode", "k_single_pass", 0},                        // 32 items of 512 rows in all: a tiny call
             {16384, 64, "k_reset_partials k_single_pass k_single_pass_redo", "k_colreduce", CF_FLAG_SINGLE_PASS},
             {4096, 256, "k_colreduce k_finalize k_encode", "k_single_pass", 0},                        // 32 items in all: a tiny call
             {128, 8192, "k_colreduce k_finalize k_encode", "k_single_pass", 0},                        // a short tensor
@@ -213,6 +214,59 @@ int main()
                 EXPECT(seq.find("ptrs_in_reset k_reset_partials") != std::string::npos && seq.find("k_upload_ptrs") == std::string::npos);
             else
                 EXPECT(seq.find("k_upload_ptrs") != std::string::npos && seq.find("ptrs_in_reset") == std::string::npos);
+            cf_destroy(ctx);
+            std::free(ws);
+        }
+    }
+
+    // ---- both sides of every line of that rule for tall tensors: items of 256 rows x 128 channels (half the rows for fp32
+    // and for a third operand), of 512 x 64 in contexts of mostly tall tensors
+    {
+        enum Path { TWO, NARROW, SLIM };
+        struct Call { int32_t ef, dtype; std::vector<std::vector<int64_t>> shapes; Path path; };     // shapes: count, tokens, channels
+        const int R = CF_EF_RECON, L = CF_EF_LITERAL, O = CF_EF_OFF, N = CF_EF_NAIVE, B = CF_BF16, F = CF_F32;
+        const std::vector<Call> calls = {
+            {R, B, {{1, 9728, 2048}}, NARROW}, {R, B, {{1, 9729, 2048}}, NARROW}, {R, B, {{4, 10000, 512}}, NARROW},     // 38, 39, 40 items
+            {R, B, {{1, 10240, 2048}}, NARROW}, {R, B, {{1, 10241, 2048}}, SLIM},                                         // 40, 41
+            {R, F, {{1, 4865, 2048}}, NARROW}, {R, F, {{1, 5120, 2048}}, NARROW}, {R, F, {{1, 5121, 2048}}, SLIM},
+            {L, B, {{1, 4865, 2048}}, NARROW}, {L, B, {{1, 5120, 2048}}, NARROW}, {L, B, {{1, 5121, 2048}}, SLIM},
+            {O, F, {{1, 2433, 2048}}, NARROW}, {O, F, {{1, 2560, 2048}}, NARROW}, {O, F, {{1, 2561, 2048}}, SLIM},
+            {R, B, {{1, 19456, 2048}}, SLIM}, {R, B, {{1, 19457, 2048}}, TWO}, {R, F, {{1, 9728, 2048}}, SLIM}, {R, F, {{1, 9729, 2048}}, TWO},
+            {N, B, {{1, 10240, 2048}}, NARROW}, {N, B, {{1, 12288, 2048}}, SLIM}, {N, B, {{1, 12289, 2048}}, TWO},
+            {R, B, {{1, 65536, 256}}, SLIM}, {R, B, {{1, 65536, 264}}, TWO},                                              // 512 items in all, 640
+            {N, B, {{1, 65536, 256}}, SLIM}, {N, B, {{1, 65536, 264}}, TWO},
+            {R, B, {{20, 10240, 80}}, NARROW}, {R, B, {{20, 10500, 80}}, TWO}, {R, B, {{20, 10500, 96}}, SLIM},            // slivers: 72 to 88 channels
+            {R, B, {{16, 4096, 3072}, {1, 10500, 80}}, NARROW}, {R, B, {{4, 12288, 3072}, {1, 10500, 80}}, SLIM},          // one of them among others
+            {R, B, {{16, 4096, 3072}, {1, 12288, 3072}}, NARROW}, {R, B, {{16, 4096, 3072}, {1, 12289, 3072}}, SLIM},      // few tall ones: 48, 49 items
+            {R, B, {{2, 4096, 3072}, {1, 12288, 3072}}, SLIM}, {R, B, {{16, 1024, 3072}, {1, 20000, 3072}}, TWO},
+        };
+        for (const Call &c : calls) {
+            std::vector<cf_tensor_desc> d;
+            for (auto &s : c.shapes) d.insert(d.end(), (size_t)s[0], desc(s[1], s[2], c.dtype, c.ef == L ? 4 : 2, CF_SCALE_CHANNEL));
+            const int n = (int)d.size();
+            std::memset(&o, 0, sizeof o);
+            o.ef = c.ef;
+            std::vector<const void *> x;
+            std::vector<void *> recon, err, codes, scales;
+            uintptr_t at = (uintptr_t)1 << 40;                      // addresses nobody looks behind
+            auto take = [&] { void *p = (void *)at; at += (uintptr_t)1 << 32; return p; };
+            for (int t = 0; t < n; ++t) { x.push_back(take()); recon.push_back(take()); err.push_back(take()); codes.push_back(take()); scales.push_back(take()); }
+            const size_t wsb = cf_workspace_bytes(d.data(), n, &o);
+            void *ws = nullptr;
+            if (posix_memalign(&ws, 256, wsb) != 0) std::abort();
+            cf_ctx *ctx = nullptr;
+            EXPECT(cf_init(&ctx, d.data(), n, &o, ws, wsb, nullptr) == CF_OK);
+            EXPECT(cf_set_warm(ctx, 0, n, 1) == CF_OK);
+            joined();
+            g_single_pass_slim = false;
+            EXPECT(cf_step_fused(ctx, 0, n, x.data(), recon.data(), err.data(), codes.data(), scales.data(), nullptr) == CF_OK);
+            const bool single = joined().find("k_single_pass ") != std::string::npos;
+            const Path took = !single ? TWO : g_single_pass_slim ? SLIM : NARROW;
+            if (took != c.path) {
+                const auto &s = c.shapes.back();
+                std::printf("ef %d dtype %d ... %d x [%d, %d]: path %d instead of %d\n", c.ef, c.dtype, (int)s[0], (int)s[1], (int)s[2], (int)took, (int)c.path);
+                ++g_failed;
+            }
             cf_destroy(ctx);
             std::free(ws);
         }
