@@ -575,7 +575,7 @@ cf_status make_ctx(cf_ctx **out, const cf_tensor_desc *descs, int32_t n_tensors,
         if (e == hipSuccess)
             for (int et = 0; et < 2; ++et)
                 for (int fu = 0; fu < 2; ++fu)
-                    ctx->persist_grid[et][fu] = persistent_max_blocks_per_cu(o.ef, et, fu != 0, L.sp_wide) * n_cu;
+                    ctx->persist_grid[et][fu] = persistent_max_blocks_per_cu(o.ef, et, fu != 0, L.sp_wide, L.sp_slim) * n_cu;
     }
     if (e != hipSuccess) {
         (void)hipGetLastError();

@@ -186,7 +186,7 @@ hipError_t launch_lr_encode(const BatchView &v, const LaunchRange &r, int err_dt
 hipError_t launch_lr_decode(const BatchView &v, const LaunchRange &r, hipStream_t s);
 
 // Single-pass kernel (channel scales, every error-feedback mode).
-int persistent_max_blocks_per_cu(int ef, int err_dtype, bool fused, bool wide);
+int persistent_max_blocks_per_cu(int ef, int err_dtype, bool fused, bool wide, bool slim);
 // wide: items of kStripeChannelsWide channels (the layout's choice, fixed at cf_init); one_shot: a workgroup per
 // item, else `grid` workgroups that loop over the items
 hipError_t launch_single_pass(const BatchView &v, const LaunchRange &r, int ef, int err_dtype, bool fused, bool wide, int grid,

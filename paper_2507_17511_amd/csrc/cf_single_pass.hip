@@ -352,10 +352,10 @@ const void *pick(int ef, int err_dtype, bool fused, bool wide, bool slim)
 
 }  // namespace
 
-int persistent_max_blocks_per_cu(int ef, int err_dtype, bool fused, bool wide)
+int persistent_max_blocks_per_cu(int ef, int err_dtype, bool fused, bool wide, bool slim)
 {
     int n = 0;
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, pick(ef, err_dtype, fused, wide, false), kPersistThreads, 0);
+    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, pick(ef, err_dtype, fused, wide, slim), kPersistThreads, 0);
     if (e != hipSuccess) { (void)hipGetLastError(); return 0; }
     return n;
 }

@@ -11,7 +11,7 @@
 
 extern std::vector<std::string> g_launch_log;
 extern bool g_capturing;
-extern bool g_single_pass_slim;
+extern bool g_single_pass_slim, g_occupancy_slim;
 
 static int g_failed = 0;
 #define EXPECT(cond)                                                                    \
@@ -261,6 +261,7 @@ int main()
             g_single_pass_slim = false;
             EXPECT(cf_step_fused(ctx, 0, n, x.data(), recon.data(), err.data(), codes.data(), scales.data(), nullptr) == CF_OK);
             const bool single = joined().find("k_single_pass ") != std::string::npos;
+            EXPECT(!single || g_occupancy_slim == g_single_pass_slim);      // the device's capacity for the kernel that runs
             const Path took = !single ? TWO : g_single_pass_slim ? SLIM : NARROW;
             if (took != c.path) {
                 const auto &s = c.shapes.back();

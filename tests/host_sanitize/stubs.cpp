@@ -11,6 +11,7 @@
 std::vector<std::string> g_launch_log;
 bool g_capturing = false;
 bool g_single_pass_slim = false;        // the stripe width of the last single pass
+bool g_occupancy_slim = false;          // and the one whose co-resident workgroups were asked for last
 static void note(const char *what) { g_launch_log.push_back(what); }
 
 extern "C" {
@@ -65,7 +66,7 @@ hipError_t launch_lr_backproject(const BatchView &, const LaunchRange &, int, hi
 hipError_t launch_lr_quant_u(const BatchView &, const LaunchRange &, hipStream_t) { note("k_lr_quant_u"); return hipSuccess; }
 hipError_t launch_lr_encode(const BatchView &, const LaunchRange &, int, bool, hipStream_t) { note("k_lr_apply"); return hipSuccess; }
 hipError_t launch_lr_decode(const BatchView &, const LaunchRange &, hipStream_t) { note("k_lr_apply"); return hipSuccess; }
-int persistent_max_blocks_per_cu(int, int, bool, bool) { return 2; }
+int persistent_max_blocks_per_cu(int, int, bool, bool, bool slim) { g_occupancy_slim = slim; return 2; }
 hipError_t launch_single_pass(const BatchView &, const LaunchRange &r, int, int, bool, bool, int, bool, bool redo, hipStream_t)
 {
     g_single_pass_slim = r.sp_slim != 0;
