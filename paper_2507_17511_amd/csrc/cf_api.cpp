@@ -179,6 +179,9 @@ cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &
         if (st != CF_OK) return st;
     }
     const int rb = pick_rb_rows(descs, n, o);
+    int64_t columns = 0;            // that k_finalize has to finish
+    for (int32_t t = 0; t < n; ++t)
+        if (descs[t].scale == CF_SCALE_CHANNEL || descs[t].scale == CF_SCALE_RANK1) columns += descs[t].n_channels;
     L.dev.resize(n);
     L.tile_prefix.assign(n + 1, 0);
     L.ew_prefix.assign(n + 1, 0);
@@ -270,7 +273,11 @@ cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &
         const uint64_t dec_run = (uint64_t)v.dec_rows * kTileThreads;
         dec_tiles += v.dec_flat ? (chunks + dec_run - 1) / dec_run
                                 : (uint64_t)((d.n_tokens + v.dec_rows - 1) / v.dec_rows) * (uint64_t)v.n_colblocks;
-        v.fin_columns = v.n_rowblocks > 32 ? kFinalizeColumns : kFinalizeThreads;
+        // a column with a lane of its own takes 2.5 us and 0.058 per partial, however many there are; sixteen lanes a column
+        // make a workgroup of 16 columns, 2.8 ns each once the device is full: k_finalize of 57 x [4096, 3072] (64 partials)
+        // 10.6 / 30.1 us, 114 x [8192, 1024] (128) 14.3 / 24.0, 16 x [4096, 3072] (128) 11.6 / 12.2, 30 x [17776, 1920] (278)
+        // 28.5 / 22.2, 8 x [4096, 3072] (256) 18.4 / 11.0, 1 x [16384, 512] (2048) 121 / 13
+        v.fin_columns = v.n_rowblocks > 32 && (int64_t)v.n_rowblocks * 320 > columns ? kFinalizeColumns : kFinalizeThreads;
         fins += (uint64_t)((d.n_channels + v.fin_columns - 1) / v.fin_columns);
         if (tiles > 0x7fffffffull || fins > 0x7fffffffull) return CF_ERR_SHAPE;
         if (d.scale == CF_SCALE_CHANNEL || d.scale == CF_SCALE_RANK1) {

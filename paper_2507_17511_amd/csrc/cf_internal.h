@@ -13,7 +13,7 @@ constexpr int kTileThreads = 128;
 constexpr int kChunk = 8;                                   // channels per lane
 constexpr int kTileChannels = kTileThreads * kChunk;        // 1024
 constexpr int kFinalizeThreads = 256;
-constexpr int kFinalizeColumns = 16;                        // columns per finalise block, kFinalizeThreads where they have few partials
+constexpr int kFinalizeColumns = 16;                        // columns per finalise block, kFinalizeThreads where columns are many or have few partials
 constexpr int kRank1Threads = 1024;                         // one block per tensor finishes the token scales u
 constexpr int kMaxRank1Colblocks = 128;                     // rank-1 scales: C <= 128 * 1024
 constexpr int kMaxUploadTensors = 64;                       // pointer sets per upload launch

@@ -265,7 +265,8 @@ __global__ __launch_bounds__(kTileThreads) void k_colreduce(BatchView v, LaunchR
 // s = sum / N or max / 7.  Latency is all it costs: a lane takes an aligned sixteenth of the padded range of its column
 // (64-byte pieces of 16 columns), the sixteen results meet in LDS.  One lane per column took 28 us for 30 x [17776,
 // 1920] and 130 of the 150 us of a call over [16384, 512], whose 8-row tiles leave 2048 partials
-// (42 us now).  Columns of up to 32 partials stay with one lane each: 114 x [103, 368] is 35.4 us a step that way, 38.1 split.
+// (42 us now).  Columns of up to 32 partials stay with one lane each (114 x [103, 368] is 35.4 us a step that way, 38.1
+// split), and so do those of contexts with columns enough to fill the device (see fin_columns).
 __global__ __launch_bounds__(kFinalizeThreads) void k_finalize(BatchView v, LaunchRange r)
 {
     __shared__ float part[kFinalizeThreads];
@@ -278,6 +279,14 @@ __global__ __launch_bounds__(kFinalizeThreads) void k_finalize(BatchView v, Laun
     const int col = (int)(blk - d.fin_begin) * columns + lane_col;
     const bool cvalid = col < d.n_channels;
     const int64_t C = d.n_channels;
+    if (parts == 1) {                                       // uniform, and so is the count: scalar branches in the tree (13.4 -> 11.6 us
+        if (!cvalid) return;                                // for 16 x [4096, 3072])
+        const CF_GLOBAL float *partial = gconst<float>(v.workspace + d.partial_off) + col;
+        const float s = d.bits == 4 ? tree_over<true, 18>(d.n_rowblocks, [&](int i) { return partial[(int64_t)i * C]; }) / 7.0f
+                                    : tree_over<false, 18>(d.n_rowblocks, [&](int i) { return partial[(int64_t)i * C]; }) / (float)d.n_tokens;
+        gmut<float>(v.ptrs[t].scales)[col] = s;
+        return;
+    }
     int per = 1;                                            // leaves per lane: the padded count / parts, at least one
     while (per * parts < d.n_rowblocks) per <<= 1;
     const int first = mine * per;

@@ -137,10 +137,11 @@ def test_single_pass_stripe_width_rule_boundaries():
             run_parity(descs, cf.options(flags=cf.CF_FLAG_SINGLE_PASS), xs, mode=mode)
 
 
-@pytest.mark.parametrize("n", [1, 8, 9, 120, 128, 129, 136, 2048, 2049, 4104])
+@pytest.mark.parametrize("n", [1, 8, 9, 120, 128, 129, 136, 255, 256, 257, 264, 512, 513, 520, 2048, 2049, 4104])
 def test_finalise_splits_the_tree_of_a_column(n):
-    """The second level of the two-kernel reduction, whose lanes take aligned sixteenths of a column's 8-row partials:
-    one partial, 16 and 17 of them, a batch of 16 per lane and one more, and widths around its 16 columns."""
+    """The second level of the two-kernel reduction over 8-row partials: a lane per column up to 32 partials (256 tokens),
+    aligned sixteenths of a column for a lane from 33 on (lanes with partly filled and empty ranges), full and one more,
+    a batch of 16 per lane and one more, and widths around its 16 columns."""
     say(f"finalise N={n}")
     descs = [cf.desc(n, c, cf.CF_BF16, b, s) for c, b, s in ((8, 1, CH), (16, 2, CH), (24, 4, CH), (136, 2, cf.CF_SCALE_RANK1))]
     streams = [drift_stream((d.n_tokens, d.n_channels), d.dtype, steps=3, seed=870 + t, device=DEV) for t, d in enumerate(descs)]
