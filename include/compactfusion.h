@@ -165,8 +165,8 @@ typedef struct {
  * reads the operands again, writes the codes.  Results are bit-identical either
  * way.  By default a call takes the single pass where it applies, every
  * channel-scale tensor of the context has at least 256 tokens, the call covers at
- * least 64 items, and either no stripe has too many items or the call covers at
- * most 512: it is about 30 % faster on MI355X at the sizes of the paper's models,
+ * least 64 items, and either no stripe has too many items or the device holds the
+ * items of the call at once (512 on MI355X): it is about 30 % faster on MI355X at the sizes of the paper's models,
  * slower on tiny batches, and slower than two kernels on large ones where more
  * workgroups have to agree on a scale.  Contexts of mostly tall tensors (more than
  * 40 of the items above: 10240 tokens of bf16), and those with one of more than

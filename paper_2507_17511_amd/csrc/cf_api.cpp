@@ -254,7 +254,10 @@ cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &
         tiles += (uint64_t)v.n_rowblocks * (uint64_t)v.n_colblocks;
         // Tiles across the row ends (see cf_kernels.hip) where the last 1024-channel tile of a row would be a part of one;
         // their chunk numbers are 32-bit.  The receiver's kernel, which reads a lane's channel scales once for both rows
-        // of a tile, takes them only where whole rows would leave more than an eighth of the lanes idle.
+        // of a tile, takes them only where whole rows would leave more than an eighth of the lanes idle.  Row tiles / flat, us,
+        // 1.5e8 bf16 elements of [2039, C]: warm-up C = 3064 218 / 194, 2600 218 / 192, 1096 277 / 197, 112 216 / 69; sparsifier's
+        // encoder 3064 278 / 255, 2600 281 / 255, 1096 384 / 257; receiver, 2-bit channel scales, 2600 117 / 110, 1784 118 / 110,
+        // 1096 176 / 111, 520 188 / 115, 112 204 / 37 (1800, just under an eighth, stays with rows at 116).
         const uint64_t chunks = (uint64_t)d.n_tokens * (uint64_t)v.n_chunks;
         const bool ragged = v.n_chunks % kTileThreads != 0 && chunks < (1u << 31) - (1u << 16);
         // element-wise kernels do best with short-lived workgroups: a lane never has to wait for
@@ -757,12 +760,12 @@ cf_status run_sender(cf_ctx *ctx, int32_t first, int32_t count, const void *cons
     // unless asked for: not for tiny batches (the wait chain costs more than a second read) nor for short tensors
     // (an item is 128 or 256 rows tall: most of its lanes would idle)
     const bool forced = (ctx->opts.flags & CF_FLAG_SINGLE_PASS) != 0;
-    // nor for very tall ones (see sp_group_limit) in calls of more than a round of workgroups (us, single pass / two kernels:
+    // nor for very tall ones (see sp_group_limit) in calls of more than a round of workgroups, 512 on the whole MI355X (us, single pass / two kernels:
     // one tensor of [32768, 3072], 3072 items, 303 / 259, of [65536, 1024], 2048 items, 249 / 177; 4 x [20000, 128], 320
     // items, 34 / 48; one [65536, 128], 256 items in groups of 128, 35 / 52, [131072, 64], 256 in one group, 46 / 60, [40000,
     // 384], 474 in groups of 79, 48 / 81, [30000, 256] fp32 39 / 59)
     const uint32_t items = r.item_hi - r.item_lo;
-    const bool small_call = items <= kTallCallItems;
+    const bool small_call = grid > 0 && items <= (uint32_t)grid;
     const bool worth_it = forced || (items >= 64u && ctx->L.min_channel_scale_tokens >= 256 &&
                                      (ctx->L.max_group_items <= ctx->L.sp_group_limit || small_call));
     // (a group larger than what the device holds at once would have its first workgroups wait for ones that cannot

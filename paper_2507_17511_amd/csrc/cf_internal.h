@@ -40,13 +40,12 @@ constexpr int single_pass_rows_per_lane(int dtype, int ef) { return 16 / (dtype 
 // A workgroup polls a missing partial this many times (a microsecond or two each) before it gives its item up.
 constexpr uint32_t kWaitPolls = 4096;
 // A tensor of more 128-channel items per group than kTallGroupItems is tall: contexts of mostly such take 64-channel
-// stripes.  Groups of more items than the limit of the stripe in use take two kernels by default, unless the call has at
-// most kTallCallItems: one round of workgroups, which nothing has to wait for.
+// stripes.  Groups of more items than the limit of the stripe in use take two kernels by default, unless the device holds
+// the whole call at once: nothing has to wait for a second round of workgroups then.
 constexpr int kTallGroupItems = 40;
 constexpr int kNarrowGroupLimit = 48;
 constexpr int kSlimGroupLimit = 38;
 constexpr int kSlimGroupLimitNaive = 24;
-constexpr uint32_t kTallCallItems = 512;
 constexpr int kGaveUpWord = 32;                             // 128 bytes behind the error word: how many items the call's first launch gave up
 constexpr int kRedoGrid = 512;                              // workgroups of the launch that does them
 
