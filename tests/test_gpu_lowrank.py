@@ -538,3 +538,35 @@ def test_lowrank_bits_do_not_depend_on_the_call(n, count):
     finally:
         for s in (batch, layers, alone):
             s.close()
+
+
+@pytest.mark.parametrize("c", [64, 3072])
+def test_lowrank_leaning_columns_on_every_wire(c):
+    """The column by column form writes its V in all three wire formats: bf16 and INT4 factors are the fp32 factors of the
+    same residual, rounded once (half a bf16 step; half a nibble step of the row's scale)."""
+    n = 96
+    say(f"lowrank leaning columns on every wire C={c}")
+    g = torch.Generator(device=DEV)
+    g.manual_seed(c)
+    x1 = (torch.randn((n, 48), generator=g, device=DEV) * 0.8 ** torch.arange(48, device=DEV) @ torch.randn((48, c), generator=g, device=DEV)).to(torch.bfloat16)
+    q0 = torch.from_numpy(dict(leaning_starts(c))["cosines"].astype(np.float32)).to(DEV)
+    V = {}
+    for wire, dtype, flags in (("f32", cf.CF_F32, 0), ("bf16", cf.CF_BF16, 0), ("int4", cf.CF_F32, cf.CF_FLAG_LOWRANK_INT4)):
+        tdt = torch.bfloat16 if dtype == cf.CF_BF16 else torch.float32
+        sess = CodecSession([cf.desc(n, c, dtype, 1, cf.CF_LOWRANK, R)], cf.options(flags=flags), device=DEV)
+        try:
+            sess.warmup([torch.zeros((n, c), dtype=tdt, device=DEV)])
+            sess.scales[0].copy_(q0.reshape(-1))
+            sess.step_fused([x1.to(tdt).contiguous()])
+            cf.cf_check_device(sess.ctx, sess.stream_handle)
+            codes = as_numpy(sess.codes[0])
+            if wire == "int4":
+                nib, sc = split_wire_int4(codes.view(np.uint8), n, c)[1]
+                V[wire], step = lr.dequantise_rows(nib, sc), sc.astype(np.float64)[:, None]
+            else:
+                V[wire] = lr.widen(split_wire(codes, n, c, dtype)[1], dtype)
+        finally:
+            sess.close()
+    assert np.count_nonzero(np.abs(V["f32"]).sum(axis=0)) >= 12
+    assert np.all(np.abs(V["bf16"] - V["f32"]) <= 2.0 ** -8 * np.abs(V["f32"]) * 1.001)
+    assert np.all(np.abs(V["int4"] - V["f32"]) <= 0.5 * step * 1.001 + 1e-30)
