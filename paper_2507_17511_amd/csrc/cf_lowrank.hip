@@ -259,7 +259,7 @@ __device__ __forceinline__ uint8_t *lr_slice(const BatchView &v, const LaunchRan
 // (tile j holds channels = j mod 8) times 2 rank tiles.  What bounds it is how much a CU has in flight:
 // three waves per SIMD (142 registers, 64 of them accumulators), each with the loads of one quad, about 2 KB; the loop asks
 // for R quads ahead, the compiler moves their loads down to the quad before their use.  57 x [4096, 3072], us: bf16 621
-// (713 with 256 channels and two waves per SIMD; 635 at four waves with one run), fp32 1185 (1187; 1769 with the hint).
+// (713 with 256 channels and two waves per SIMD; 635 at four waves with one run), fp32 1185 (1187; 1769 at four waves and with the hint).
 // The sums cost a drained pipeline and two barriers a run: four turns of one wave each instead of two of two took 1 %
 // longer at 57 x [1000, 3072].
 constexpr int kBackThreads = 256;
@@ -282,7 +282,7 @@ __device__ __forceinline__ void lr_backproject_body(const BatchView &v, const La
     const int ch0 = stripe * kBackChannels + 8 * q;
     const int ch = ch0 < d.n_channels ? ch0 : d.n_channels - 8;
     const CF_GLOBAL float *P = gconst<float>(v.workspace + d.lr_p_off) + q;
-    constexpr int R = (DT == F32) ? 4 : 8;                  // quads in flight (fp32 rows take twice the registers)
+    constexpr int R = (DT == F32) ? 4 : 8;                  // quads asked for ahead (fp32 rows take twice the registers)
     Raw8<DT> xr[R], br[R];
     float pv[R][2];
     auto fetch = [&](int slot, int64_t quad) {
