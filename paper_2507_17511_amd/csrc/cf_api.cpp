@@ -147,7 +147,7 @@ int pick_rb_rows(const cf_tensor_desc *descs, int32_t n, const cf_options &o)
 int64_t lowrank_split(int64_t max_channels, int64_t max_tokens, int64_t count)
 {
     const int64_t stripes = (max_channels + kLowRankBackChannels - 1) / kLowRankBackChannels * count;
-    return std::min<int64_t>(lowrank_runs(max_tokens), stripes <= 256 ? kLowRankMaxRuns : stripes <= 1536 ? 2 : 1);
+    return std::min<int64_t>(lowrank_runs(max_tokens, max_channels), stripes <= 256 ? kLowRankMaxRuns : stripes <= 1536 ? 2 : 1);
 }
 
 size_t lowrank_slice_bytes_of(int64_t max_channels, int64_t split, int64_t count)

@@ -171,10 +171,15 @@ constexpr int kLowRankRank = 32;
 constexpr int kLowRankMaxChannels = 3072;
 // The back-projection's workgroups own kLowRankBackChannels channels each.  A tensor's tokens are summed in lowrank_runs
 // runs, a property of the tensor alone: the sum has one order in every call.  Runs cost a workgroup that takes them all a
-// drained pipeline and a sum over its waves each, so short tensors have fewer.
+// drained pipeline and a sum over its waves each, so short tensors have fewer, wide ones above all: steps with 2 / 4
+// runs, us: 114 x [1100, 2048] T = 2 2100 / 2273, 100 x [2000, 3072] 2953 / 3002, 6 x [2000, 3072] 504 / 496; 20 x [2000, 1024]
+// 366 / 369, one [2048, 64] 103 / 92, one [2900, 1024] T = 2 368 / 328.
 constexpr int kLowRankBackChannels = 128;
 constexpr int kLowRankMaxRuns = 4;
-constexpr int lowrank_runs(int64_t n_tokens) { return n_tokens <= 256 ? 1 : n_tokens <= 1024 ? 2 : kLowRankMaxRuns; }
+constexpr int lowrank_runs(int64_t n_tokens, int64_t n_channels)
+{
+    return n_tokens <= 384 ? 1 : n_tokens <= (n_channels <= 1024 ? 1024 : 2048) ? 2 : kLowRankMaxRuns;
+}
 // min_iters: only tensors whose descriptor asks for at least that many subspace iterations take part
 hipError_t launch_lr_orth(const BatchView &v, const LaunchRange &r, bool from_q0, int min_iters, hipStream_t s);
 hipError_t launch_lr_project(const BatchView &v, const LaunchRange &r, bool wire, int min_iters, hipStream_t s);

@@ -239,7 +239,7 @@ __global__ __launch_bounds__(kProjThreads, 2) void k_lr_project(BatchView v, Lau
 // Workgroups that share the runs of one stripe of a tensor.
 __device__ __forceinline__ int lr_shares(const LaunchRange &r, const TensorDev &d)
 {
-    const int runs = lowrank_runs(d.n_tokens);
+    const int runs = lowrank_runs(d.n_tokens, d.n_channels);
     return r.lr_split < runs ? r.lr_split : runs;
 }
 
@@ -250,7 +250,7 @@ __device__ __forceinline__ uint8_t *lr_slice(const BatchView &v, const LaunchRan
     return v.workspace + r.lr_slices_off + (uint64_t)((t - r.first) * (r.lr_split - 1) + share - 1) * (uint64_t)r.lr_max_channels * (kRank * sizeof(float));
 }
 
-// The tokens are cut into lowrank_runs(N) = 1, 2 or 4 runs.  Z is the sum (run 0 + run 1) + (run 2 + run 3), each run the
+// The tokens are cut into lowrank_runs = 1, 2 or 4 runs.  Z is the sum (run 0 + run 1) + (run 2 + run 3), each run the
 // sum (w0 + w1) + (w2 + w3) over its 4 waves, so the bits depend on the tensor's shape alone, whoever adds: a workgroup
 // owns a stripe of 128 channels and either takes all runs one after the other, or, in calls of few tensors, one or two
 // of them, and the orthogonalisation adds the shares.
@@ -275,7 +275,7 @@ __device__ __forceinline__ void lr_backproject_body(const BatchView &v, const La
     const int q = lane & 15, g = lane >> 4;
     const int64_t C = d.n_channels, last = d.n_tokens - 1;
     const int64_t n_quads = (d.n_tokens + 3) / 4;
-    const int n_runs = lowrank_runs(d.n_tokens), n_mine = n_runs / lr_shares(r, d), first_run = share * n_mine;
+    const int n_runs = lowrank_runs(d.n_tokens, d.n_channels), n_mine = n_runs / lr_shares(r, d), first_run = share * n_mine;
     const int64_t per_wave = (n_quads + 4 * n_runs - 1) / (4 * n_runs);
     // Loads without branches: rows and channels outside the tensor read its last ones, P counts as zero there and the
     // channels are not stored.

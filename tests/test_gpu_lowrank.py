@@ -508,7 +508,7 @@ def test_lowrank_non_finite_token(bad, c):
         sess.close()
 
 
-@pytest.mark.parametrize("n, count", [(200, 3), (600, 12), (1100, 12), (1100, 66)])
+@pytest.mark.parametrize("n, count", [(384, 3), (385, 12), (2049, 12), (2049, 66)])
 def test_lowrank_bits_do_not_depend_on_the_call(n, count):
     """A tensor's factors and state are the same bits alone in a context, in a call of its own in a large one, and in
     one call with all the others: with 1, 2 and 4 runs of tokens, shared by 4, 2 or no workgroups."""
