@@ -142,12 +142,12 @@ int pick_rb_rows(const cf_tensor_desc *descs, int32_t n, const cf_options &o)
 
 // Workgroups that share a channel stripe of the low-rank back-projection in a call over `count` tensors (the largest
 // low-rank tensor's channels and tokens given): more where the stripes alone would leave the device idle.
-// Whole steps with 1 / 2 / 4 sharing, us: 1 x [4096, 3072] 561 / 476 / 445, 16 x [4096, 2048] 829 / 769 / 778,
-// 30 x [4096, 2048] 1181 / 1182 / 1192; 57 x [4096, 3072] 3176 / 3129.
+// Whole steps with 1 / 2 / 4 sharing, us: [4096, 3072] 1 tensor 413 / 305 / 258, 8 (96 stripes) 600 / 492 / 492, 16 930 / 842 / 863,
+// 40 1971 / 1970 / 2009, 57 (684) 2888 / 2824 / 2855; 60 x [8000, 96] 675 / 474 / 384.  Beyond, the shares' memory is not worth it.
 int64_t lowrank_split(int64_t max_channels, int64_t max_tokens, int64_t count)
 {
     const int64_t stripes = (max_channels + kLowRankBackChannels - 1) / kLowRankBackChannels * count;
-    return std::min<int64_t>(lowrank_runs(max_tokens, max_channels), stripes <= 256 ? kLowRankMaxRuns : stripes <= 1536 ? 2 : 1);
+    return std::min<int64_t>(lowrank_runs(max_tokens, max_channels), stripes <= 128 ? kLowRankMaxRuns : stripes <= 768 ? 2 : 1);
 }
 
 size_t lowrank_slice_bytes_of(int64_t max_channels, int64_t split, int64_t count)
@@ -425,6 +425,8 @@ struct cf_ctx {
         r.dec_kinds = 0;
         r.lr_max_channels = 0;
         r.lr_max_tokens = 0;
+        r.lr_wires = 0;
+        r.lr_project_blocks = 0;
         r.lr_split = 1;
         r.lr_slices_off = L.off_lr_slices;
         r.p_partial_lo = ~(uint64_t)0;
@@ -443,6 +445,9 @@ struct cf_ctx {
             if (descs[t].scale == CF_LOWRANK) {
                 if (descs[t].n_channels > r.lr_max_channels) r.lr_max_channels = (int32_t)descs[t].n_channels;
                 if (descs[t].n_tokens > r.lr_max_tokens) r.lr_max_tokens = descs[t].n_tokens;
+                r.lr_wires |= descs[t].dtype == CF_BF16 && !(opts.flags & CF_FLAG_LOWRANK_INT4) ? 1 : 2;
+                const int64_t tokens = lowrank_project_tokens(descs[t].n_channels);
+                r.lr_project_blocks = std::max<int32_t>(r.lr_project_blocks, (int32_t)((descs[t].n_tokens + tokens - 1) / tokens));
             }
         }
         if (r.lr_max_channels > 0) {    // as many shares as the rule says and the workspace holds; the sums are the same either way

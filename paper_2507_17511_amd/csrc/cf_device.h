@@ -56,6 +56,7 @@ template <> struct Raw8<BF16> {
     // Uniform base pointer plus a 32-bit per-lane byte offset: the scalar-base form of the global
     // instructions, which needs no 64-bit address arithmetic in vector registers.
     __device__ __forceinline__ void load_at(const void *ubase, uint32_t off) { w = *gconst<u32x4>(static_cast<const char *>(ubase) + off); }
+    __device__ __forceinline__ void load_stream_at(const void *ubase, uint32_t off) { w = __builtin_nontemporal_load(gconst<u32x4>(static_cast<const char *>(ubase) + off)); }
     __device__ __forceinline__ void store_at(void *ubase, uint32_t off) const { *gmut<u32x4>(static_cast<char *>(ubase) + off) = w; }
     // Makes the registers opaque to the optimiser: values derived from them earlier are not reused.
     __device__ __forceinline__ void opaque() { asm volatile("" : "+v"(w)); }

@@ -142,6 +142,8 @@ struct LaunchRange {
     int32_t dec_kinds;          // decode: bit 0, tensors with row tiles in the range; bit 1, with flat ones
     int32_t lr_max_channels;    // low-rank tensors of the range: largest C and N (0 = none)
     int64_t lr_max_tokens;
+    int32_t lr_wires;           // bit 0: factors that travel as bf16 in the range; bit 1: others
+    int32_t lr_project_blocks;  // workgroups of k_lr_project for the tensor that needs most, one block of tokens per wave
     int32_t lr_split;           // low-rank back-projection: at most so many workgroups share a channel stripe's runs of tokens (1, 2 or 4)
     uint64_t lr_slices_off;     // workspace offset of the shares after the first, [count][lr_split - 1][lr_max_channels][32] fp32
 };
@@ -174,12 +176,15 @@ constexpr int kLowRankMaxChannels = 3072;
 // drained pipeline and a sum over its waves each, so short tensors have fewer, wide ones above all: steps with 2 / 4
 // runs, us: 114 x [1100, 2048] T = 2 2100 / 2273, 100 x [2000, 3072] 2953 / 3002, 6 x [2000, 3072] 504 / 496; 20 x [2000, 1024]
 // 366 / 369, one [2048, 64] 103 / 92, one [2900, 1024] T = 2 368 / 328.
-constexpr int kLowRankBackChannels = 128;
+constexpr int kLowRankBackChannels = 256;
 constexpr int kLowRankMaxRuns = 4;
 constexpr int lowrank_runs(int64_t n_tokens, int64_t n_channels)
 {
     return n_tokens <= 384 ? 1 : n_tokens <= (n_channels <= 1024 ? 1024 : 2048) ? 2 : kLowRankMaxRuns;
 }
+// Runs of channels that P = A Q is the sum of, 64 channels or more each.
+constexpr int lowrank_project_parts(int64_t n_channels) { return n_channels > 128 ? 4 : n_channels > 64 ? 2 : 1; }
+constexpr int lowrank_project_tokens(int64_t n_channels) { return 128 / lowrank_project_parts(n_channels); }        // of a workgroup, a block of 32 per wave
 // min_iters: only tensors whose descriptor asks for at least that many subspace iterations take part
 hipError_t launch_lr_orth(const BatchView &v, const LaunchRange &r, bool from_q0, int min_iters, hipStream_t s);
 hipError_t launch_lr_project(const BatchView &v, const LaunchRange &r, bool wire, int min_iters, hipStream_t s);

@@ -4,21 +4,18 @@
 //     Q <- orth(Q0);  T x { Z <- A^T (A Q);  Q <- orth(Z) };  U <- A Q,
 // and both ends add D = U V^T to the reconstruction; e_t = A - D stays at the sender.
 //
-// This is the one dense contraction of the codec, so it runs on the matrix cores: every product is a
-// chain of v_mfma_f32_32x32x2_f32 (fp32 in, fp32 accumulate; 32 = the rank fills the N side of the
-// tile exactly).  A is never materialised: each pass re-forms it from x and recon (4 bytes per element
-// in bf16 storage, the same as reading an fp32 A would cost) and is bound by that stream.
+// This is the one dense contraction of the codec, so it runs on the matrix cores: project and backproject in bf16 pieces of
+// fp32 operands (see split2 below), apply on the bf16 factors as they travel or, for other wires, in fp32.  A is never
+// materialised: each pass re-forms it from x and recon (4 bytes per element in bf16 storage, the same as reading an fp32 A
+// would cost) and is bound by that stream.  Bytes written between the reads of a stream cost far more than they are: P, 1 % of what
+// a projection reads, took 12 % of its time, so nothing is written that the next kernel does not need.
 //
-// Operand layouts are chosen so that every lane feeds the MFMA straight from a 128-bit row-major
-// load, with no staging through LDS.  The instruction computes D[m][n] += sum_k A[m][k] B[k][n] with
-// lane l holding A[l % 32][l / 32] and B[l / 32][l % 32]: any relabelling of k that both operands share,
-// and any relabelling of m or n that the epilogue undoes, is free.
-//   project      P = A Q     m = token, k = channel: a lane loads 16 consecutive channels of its token
-//                            and spends them on 16 instructions; Q is kept in that per-lane order.
-//   backproject  Z = A^T P   m = channel, k = token: a lane loads 8 consecutive channels of its token and
-//                            spends them on 8 channel tiles (tile j holds channels = j mod 8); 16x16x4 tiles.
-//   encode       D^T = V U^T m = channel (relabelled so that a lane ends up with 16 consecutive channels
-//                            of its token), n = token, k = rank.
+// Operand layouts: an instruction computes D[m][n] += sum_k A[m][k] B[k][n]; any relabelling of k that both operands
+// share, and any relabelling of m or n that the epilogue undoes, is free.
+//   project      P = A Q     m = token, k = channel: by way of a wave's LDS patch.
+//   backproject  Z = A^T P   m = channel, k = token: a lane loads 8 consecutive channels of 4 tokens and
+//                            spends them on 8 channel tiles (tile j holds channels = j mod 8).
+//   apply        D = U V^T   m = token, n = channel, k = rank; D comes back row-major by way of a wave's LDS patch.
 #include "cf_device.h"
 #include "cf_internal.h"
 
@@ -34,15 +31,12 @@ constexpr float kDrop2 = 1e-8f;     // (1e-4)^2: a column left with less than 1e
 
 __device__ __forceinline__ f32x16 mfma32(float a, float b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
 
-__device__ __forceinline__ f32x4 mfma16(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
-
 // Operands a pass reads once.  Streaming hint for bf16 only, whose lanes take their 16 bytes in one load: fp32 lanes take
 // 32 bytes in two, and the hint lets go of the line in between.  57 x [4096, 3072], plain and with the hint: bf16 project
 // 600 / 585 us, back-projection 616 / 593; fp32 project 1094 / 1263, back-projection 1348 / 1779 (at four waves per SIMD).
-template <int DT> __device__ __forceinline__ void load_once(Raw8<DT> &r, const void *base, int64_t elem)
-{
-    if (DT == BF16) r.load_stream(base, elem); else r.load(base, elem);
-}
+// `base` uniform over the wave, `off` the lane's byte offset.
+__device__ __forceinline__ void load_once(Raw8<BF16> &r, const void *base, uint32_t off) { r.load_stream_at(base, off); }
+__device__ __forceinline__ void load_once(Raw8<F32> &r, const void *base, uint32_t off) { r.load_at(base, off); }
 
 template <int DT> __device__ __forceinline__ void load16(const void *base, int64_t elem, float (&out)[16])
 {
@@ -112,126 +106,254 @@ __device__ __forceinline__ void quantise_factor_row(const float (&f)[kRank], uin
     *gmut<float>(scale) = s;
 }
 
+// ---------------------------------------------------------------- fp32 operands on the bf16 matrix cores
+
+// An fp32 value is exactly the sum of three bf16 ones: high, its upper 16 bits, mid, those of what that leaves, and low, the
+// rest (8 significant bits each).  A product of two values is then six products of pieces; the three left out are below 2^-21
+// of it, 2^-24 on average.  The matrix cores form products of bf16 exactly and add 16 or 32 of them up in fp32 where the fp32
+// instructions round every 2 or 4, in 6/16 of their time.  Error against fp64 of products of random operands, K = 64 / 512 /
+// 3072: residuals of bf16 tensors, fp32 instructions 1.5e-7 / 3.9e-7 / 9.6e-7, as in project 3.0e-8 / 8.3e-8 / 2.0e-7, as in
+// backproject 5.8e-8 / 1.3e-7 / 3.2e-7; general fp32 operands 1.4e-7 / 4.1e-7 / 1.0e-6, 7.7e-8 / 1.5e-7 / 3.6e-7, 1.1e-7 / 2.4e-7 / 5.7e-7.
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+__device__ __forceinline__ f32x16 mfma32_bf16(u32x4 a, u32x4 b, f32x16 c)
+{
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+__device__ __forceinline__ f32x4 mfma16_bf16(u32x4 a, u32x4 b, f32x4 c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+struct Split4 {
+    u32x2 high, mid, low;       // 4 values each, in order
+};
+
+// The upper halves of two values in one word, the first value's in its lower half.
+__device__ __forceinline__ uint32_t upper_halves(float lo, float hi) { return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u); }
+__device__ __forceinline__ float upper_half(float f) { return __uint_as_float(__float_as_uint(f) & 0xffff0000u); }
+
+__device__ __forceinline__ void split2(float a, float b, uint32_t &high, uint32_t &mid, uint32_t &low)
+{
+    high = upper_halves(a, b);
+    const float ra = a - upper_half(a), rb = b - upper_half(b);
+    mid = upper_halves(ra, rb);
+    low = upper_halves(ra - upper_half(ra), rb - upper_half(rb));
+}
+
+__device__ __forceinline__ Split4 split4(const float (&v)[4])
+{
+    uint32_t w[2][3];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) split2(v[2 * k], v[2 * k + 1], w[k][0], w[k][1], w[k][2]);
+    return {{w[0][0], w[1][0]}, {w[0][1], w[1][1]}, {w[0][2], w[1][2]}};
+}
+
+__device__ __forceinline__ u32x4 join(u32x2 a, u32x2 b) { return __builtin_shufflevector(a, b, 0, 1, 2, 3); }
+
+__device__ __forceinline__ float element(const Raw8<BF16> &r, int j) { return (j & 1) ? bf16_hi(r.w[j / 2]) : bf16_lo(r.w[j / 2]); }
+__device__ __forceinline__ float element(const Raw8<F32> &r, int j) { return j < 4 ? r.a[j] : r.b[j - 4]; }
+
+struct Split8 {
+    u32x4 high, mid, low;       // 8 values each, in order
+};
+
+__device__ __forceinline__ Split8 split8(const float (&v)[8])
+{
+    uint32_t w[4][3];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) split2(v[2 * k], v[2 * k + 1], w[k][0], w[k][1], w[k][2]);
+    return {{w[0][0], w[1][0], w[2][0], w[3][0]}, {w[0][1], w[1][1], w[2][1], w[3][1]}, {w[0][2], w[1][2], w[2][2], w[3][2]}};
+}
+
+// Q as k_lr_project reads it: per 32 channels and piece 2 KB, the 8 channels of octet o and rank column n at (32 o + n) * 16
+// bytes, so that a lane of either bf16 instruction takes its 8 channels of one column in one load and a wave whole lines.  High and
+// mid take the place of Z (the same 4 KB per 32 channels), low lies in the Gram matrices' area behind their partial sums.
+__device__ __forceinline__ uint8_t *lr_q(const BatchView &v, const TensorDev &d, int step, int piece)
+{
+    if (piece < 2) return v.workspace + d.lr_z_off + (int64_t)step * 4096 + piece * 2048;
+    const int64_t behind = d.n_channels > 256 ? (int64_t)d.n_channels * 32 + 8192 : 0;
+    return v.workspace + d.lr_g_off + behind + (int64_t)step * 2048;
+}
+
 // ---------------------------------------------------------------- P = A Q  (and U on the wire)
 
-// A wave owns 64 tokens (two accumulator tiles that share the Q operand), a workgroup of two waves 128, and walks
-// the channels 64 at a time.  The MFMA wants a lane to hold one token's channels, memory wants
-// neighbouring lanes on neighbouring channels: the wave reads its [64 tokens][64 channels] of x and
-// recon row-major (8 lanes = 128 bytes of a bf16 row), leaves the residual in its own LDS patch and
-// picks it up again with lane (m, h) on token m (and m + 32), channels 16 * h ... of each 32-channel step.
-// Q is read in its per-lane order: step s (32 channels), lane l, 16 floats at ((s * 64 + l) * 16).
-constexpr int kProjThreads = 128;                           // two waves: their LDS patches stay under 64 KB at four workgroups per CU
-constexpr int kProjTokens = 128;
+// The MFMA wants a lane to hold one token's channels, memory wants neighbouring lanes on neighbouring channels: a wave
+// reads [32 tokens][64 channels] of x and recon row-major (8 lanes = 128 bytes of a bf16 row), leaves the residual in its
+// own LDS patch and picks it up again with lane (m, h) on token m, channels 8 h ... of each 16-channel step.
+//
+// The channels are cut into lowrank_project_parts = 4, 2 or 1 shares, 64-channel stages dealt in turn, and P is the sum of the
+// shares' chains.  A wave takes a share of TB blocks of 32 tokens, one block after the other within a stage, and the waves of
+// the same tokens add up in LDS; the bits do not depend on TB.
+// What rounds in a stage of 64 channels: the products of the leading pieces in the wave's accumulator, the small ones in one of
+// their own, added once: the matrix cores cut off what lies below the last bits of the sum they add to, and small products
+// of one sign would lose to that (sums of 3072 positive products: 6.1e-6 in one accumulator, 2.8e-7 in two, fp32 7.5e-7).
+constexpr int kProjThreads = 256;
 constexpr int kProjChannels = 64;
 constexpr int kProjPitch = kProjChannels + 4;               // floats per token row of the patch
+constexpr int kProjSumPitch = kRank + 4;
+// Blocks of 32 tokens a wave takes in calls of kProjMany blocks and more (of 4 waves), one after the other against the same
+// pieces of Q, which otherwise take as much of a CU's 64 bytes per clock as the operands.  Steps over [4096, 3072] bf16, one block / several, us:
+// 1 tensor 192 / 258, 4 299 / 329, 8 524 / 492, 24 1353 / 1251, 57 3041 / 2824; 28 fp32 ones 2778 / 2860, which take one.  The
+// kernel at 57: one block 636, two 566, three 535, four 605 (11 registers spilled); fp32 MFMA 587.  408 of that is the stream
+// alone, 50 or 25 the stores of P or U.
+constexpr int kProjBlocks = 3;
+constexpr int64_t kProjMany = 1024;
+typedef float ProjPatches[kProjThreads / 64][32 * kProjPitch];
 
-template <int DT>
-__device__ __forceinline__ void lr_project_body(const BatchView &v, const TensorDev &d, const TensorPtrs &p, bool wire, float *patch)
-{
-    const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
-    const int m = lane & 31, h = lane >> 5;
-    const int64_t row_base = (int64_t)blockIdx.x * kProjTokens + wave * 64;
-    if (row_base >= d.n_tokens) return;                     // uniform over the wave
-    const int64_t C = d.n_channels;
-    const CF_GLOBAL f32x4 *qs = gconst<f32x4>(v.workspace + d.lr_z_off);
-    f32x16 acc0 = {}, acc1 = {};
-    const int steps = d.n_channels / 32;
-    const int chunk = lane & 7, trow = lane >> 3;           // row-major side: 8 chunks of 8 channels, 8 tokens per sweep
-    // The loads of the next 64 channels are issued as soon as the current ones have gone to the patch,
-    // so that they are in flight while the 64 MFMAs of the current ones run.
-    Raw8<DT> xr[8], br[8];
-    auto fetch = [&](int s0) {
-        const int ch = s0 * 32 + chunk * 8;
+// What a wave reads of a stage: 8 tokens x 128 bytes an instruction.  Loads without branches: tokens and channels outside the
+// tensor read its last ones; those tokens are not stored and those channels not used.
+template <int DT> struct ProjStage {
+    Raw8<DT> x[4], b[4];
+    __device__ __forceinline__ void fetch(const TensorDev &d, const TensorPtrs &p, int64_t row_base, int stage)
+    {
+        constexpr uint32_t kBytes = DT == BF16 ? 2 : 4;
+        const int lane = (int)threadIdx.x & 63;
+        const int ch = stage * kProjChannels + (lane & 7) * 8;
+        const int64_t last = d.n_tokens - 1, base = row_base < last ? row_base : last;
+        const int room = last - base < 31 ? (int)(last - base) : 31;        // tokens after the first that exist
+        const char *px = static_cast<const char *>(p.x) + base * d.n_channels * kBytes;
+        const char *pb = static_cast<const char *>(p.recon) + base * d.n_channels * kBytes;
+        const uint32_t at = (uint32_t)(ch < d.n_channels ? ch : d.n_channels - 8) * kBytes;
 #pragma unroll
-        for (int it = 0; it < 8; ++it) {
-            const int64_t tok = row_base + trow + 8 * it;
-            if (s0 < steps && tok < d.n_tokens && ch < d.n_channels) {
-                load_once<DT>(xr[it], p.x, tok * C + ch);
-                load_once<DT>(br[it], p.recon, tok * C + ch);
-            } else {
-                xr[it].zero();
-                br[it].zero();
-            }
+        for (int it = 0; it < 4; ++it) {
+            const int tok = (lane >> 3) + 8 * it;
+            const uint32_t off = (uint32_t)(tok < room ? tok : room) * ((uint32_t)d.n_channels * kBytes) + at;
+            load_once(x[it], px, off);
+            load_once(b[it], pb, off);
         }
-    };
-    fetch(0);
-    for (int s0 = 0; s0 < steps; s0 += 2) {
+    }
+    __device__ __forceinline__ void leave(float *patch) const
+    {
+        const int lane = (int)threadIdx.x & 63;
 #pragma unroll
-        for (int it = 0; it < 8; ++it) {
-            const F8 x = xr[it].widen(), b = br[it].widen();
+        for (int it = 0; it < 4; ++it) {
+            const F8 xv = x[it].widen(), bv = b[it].widen();
             f32x4 lo, hi;
-            lo.x = x.v[0] - b.v[0]; lo.y = x.v[1] - b.v[1]; lo.z = x.v[2] - b.v[2]; lo.w = x.v[3] - b.v[3];
-            hi.x = x.v[4] - b.v[4]; hi.y = x.v[5] - b.v[5]; hi.z = x.v[6] - b.v[6]; hi.w = x.v[7] - b.v[7];
-            f32x4 *dst = reinterpret_cast<f32x4 *>(patch + (trow + 8 * it) * kProjPitch + chunk * 8);
+            lo.x = xv.v[0] - bv.v[0]; lo.y = xv.v[1] - bv.v[1]; lo.z = xv.v[2] - bv.v[2]; lo.w = xv.v[3] - bv.v[3];
+            hi.x = xv.v[4] - bv.v[4]; hi.y = xv.v[5] - bv.v[5]; hi.z = xv.v[6] - bv.v[6]; hi.w = xv.v[7] - bv.v[7];
+            f32x4 *dst = reinterpret_cast<f32x4 *>(patch + ((lane >> 3) + 8 * it) * kProjPitch + (lane & 7) * 8);
             dst[0] = lo;
             dst[1] = hi;
         }
-        // Q first, then the prefetch: loads return in issue order, so the MFMAs below wait for Q only
-        float q[2][16];
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const CF_GLOBAL f32x4 *qp = qs + ((int64_t)(s0 + u < steps ? s0 + u : s0) * 64 + lane) * 4;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const f32x4 wq = qp[k];
-                q[u][4 * k] = wq.x; q[u][4 * k + 1] = wq.y; q[u][4 * k + 2] = wq.z; q[u][4 * k + 3] = wq.w;
-            }
-        }
-        fetch(s0 + 2);
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            if (s0 + u < steps) {                           // uniform over the wave
-                float z0[16], z1[16];
-                const f32x4 *a0 = reinterpret_cast<const f32x4 *>(patch + m * kProjPitch + 32 * u + 16 * h);
-                const f32x4 *a1 = reinterpret_cast<const f32x4 *>(patch + (m + 32) * kProjPitch + 32 * u + 16 * h);
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const f32x4 w0 = a0[k], w1 = a1[k];
-                    z0[4 * k] = w0.x; z0[4 * k + 1] = w0.y; z0[4 * k + 2] = w0.z; z0[4 * k + 3] = w0.w;
-                    z1[4 * k] = w1.x; z1[4 * k + 1] = w1.y; z1[4 * k + 2] = w1.z; z1[4 * k + 3] = w1.w;
-                }
-#pragma unroll
-                for (int j = 0; j < 16; ++j) {
-                    acc0 = mfma32(z0[j], q[u][j], acc0);
-                    acc1 = mfma32(z1[j], q[u][j], acc1);
-                }
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
     }
-    // accumulator register i of lane (m, h): row 8 * (i / 4) + 4 * h + i % 4 of the tile, column m
-    CF_GLOBAL float *P = gmut<float>(v.workspace + d.lr_p_off);
-    uint8_t *U = wire_u(p);
+};
+
+// acc + small += (16 channels of the wave's 32 tokens) * Q, u: which 16 of the patch's 64; q: the lane's pieces of Q
+__device__ __forceinline__ void project16(const float *patch, int u, const u32x4 (&q)[3], f32x16 &acc, f32x16 &small)
+{
+    const int lane = (int)threadIdx.x & 63;
+    const f32x4 *src = reinterpret_cast<const f32x4 *>(patch + (lane & 31) * kProjPitch + 16 * u + 8 * (lane >> 5));
+    const f32x4 w0 = src[0], w1 = src[1];
+    const float z[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
+    const Split8 a = split8(z);
+    acc = mfma32_bf16(a.high, q[0], acc);
+    small = mfma32_bf16(a.low, q[0], small);
+    small = mfma32_bf16(a.high, q[2], small);
+    small = mfma32_bf16(a.mid, q[1], small);
+    small = mfma32_bf16(a.mid, q[0], small);
+    small = mfma32_bf16(a.high, q[1], small);
+}
+
+// 4 columns of a finished row.  Written bytes cost a stream of reads dearly, 1.7 us per MB: the last projection leaves U
+// only, but for 4-bit factors, which k_lr_quant_u makes of P.
+template <int DT> __device__ __forceinline__ void project_store(const BatchView &v, const TensorDev &d, const TensorPtrs &p, bool wire,
+                                                                int64_t row, int col, f32x4 sum)
+{
+    if (row >= d.n_tokens) return;
+    if (!wire || factors_int4(d)) {
+        __builtin_nontemporal_store(sum, gmut<f32x4>(v.workspace + d.lr_p_off) + row * (kRank / 4) + col / 4);
+    } else if (DT == BF16) {
+        u32x2 w;
+        w.x = bf16_rne(sum.x) | (bf16_rne(sum.y) << 16);
+        w.y = bf16_rne(sum.z) | (bf16_rne(sum.w) << 16);
+        *gmut<u32x2>(wire_u(p) + (row * kRank + col) * 2) = w;
+    } else {
+        *gmut<f32x4>(wire_u(p) + (row * kRank + col) * 4) = sum;
+    }
+}
+
+// Accumulator register i of lane (m, h): row 8 * (i / 4) + 4 * h + i % 4 of the tile, column m.
+__device__ __forceinline__ void project_leave_sum(float *patch, const f32x16 &acc)
+{
+    const int lane = (int)threadIdx.x & 63, m = lane & 31, h = lane >> 5;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int row = 8 * (i >> 2) + 4 * h + (i & 3);
+    for (int i = 0; i < 16; ++i) patch[(8 * (i >> 2) + 4 * h + (i & 3)) * kProjSumPitch + m] = acc[i];
+}
+
+template <int DT, int TB>
+__device__ __forceinline__ void lr_project_body(const BatchView &v, const TensorDev &d, const TensorPtrs &p, bool wire, ProjPatches &patches)
+{
+    const int lane = (int)threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int m = lane & 31, h = lane >> 5;
+    const int parts = lowrank_project_parts(d.n_channels), part = wave & (parts - 1);
+    const int64_t wg_row = (int64_t)blockIdx.x * (32 * TB * (4 / parts)), row_base = wg_row + 32 * TB * (wave / parts);
+    const int steps = d.n_channels / 32, stages = (steps + 1) / 2;
+    float *patch = patches[wave];
+    f32x16 acc[TB];
 #pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            const int64_t rr = row_base + 32 * half + row;
-            const float val = half ? acc1[i] : acc0[i];
-            if (rr < d.n_tokens) {
-                P[rr * kRank + m] = val;
-                if (wire && !factors_int4(d)) {     // 4-bit factors are quantised from P by k_lr_quant_u
-                    if (DT == BF16) gmut<uint16_t>(U)[rr * kRank + m] = (uint16_t)bf16_rne(val);
-                    else gmut<float>(U)[rr * kRank + m] = val;
+    for (int b = 0; b < TB; ++b) acc[b] = (f32x16)(0.0f);
+    ProjStage<DT> raw;
+    if (row_base < d.n_tokens && part < stages) {           // uniform over the wave
+        raw.fetch(d, p, row_base, part);
+        for (int stage = part; stage < stages; stage += parts) {
+            u32x4 q[4][3];
+#pragma unroll
+            for (int b = 0; b < TB; ++b) {
+                raw.leave(patch);
+                // Q first, then the prefetch: loads return in issue order, so the MFMAs below wait for Q only
+                if (b == 0) {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int step = 2 * stage + (u >> 1) < steps ? 2 * stage + (u >> 1) : steps - 1;
+#pragma unroll
+                        for (int k = 0; k < 3; ++k) q[u][k] = gconst<u32x4>(lr_q(v, d, step, k))[(2 * (u & 1) + h) * 32 + m];
+                    }
                 }
+                __builtin_amdgcn_sched_barrier(0);
+                if (b + 1 < TB) raw.fetch(d, p, row_base + 32 * (b + 1), stage);
+                else if (stage + parts < stages) raw.fetch(d, p, row_base, stage + parts);
+                __builtin_amdgcn_sched_barrier(0);
+                wave_lds_fence();
+                f32x16 small = {};
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (2 * stage + (u >> 1) < steps) project16(patch, u, q[u], acc[b], small);         // uniform over the wave
+                acc[b] += small;
+                __builtin_amdgcn_sched_barrier(0);
+                wave_lds_fence();
             }
         }
+    }
+    const int row = (int)threadIdx.x >> 3, col = 4 * ((int)threadIdx.x & 7);
+#pragma unroll
+    for (int b = 0; b < TB; ++b) {
+        project_leave_sum(patch, acc[b]);
+        __syncthreads();
+        for (int g = 0; g < 4 / parts; ++g) {               // uniform: the workgroup's sets of waves that share tokens
+            auto of = [&](int k) { return *reinterpret_cast<const f32x4 *>(patches[g * parts + k] + row * kProjSumPitch + col); };
+            f32x4 sum = of(0);
+            if (parts > 1) sum += of(1);
+            if (parts > 2) sum += of(2) + of(3);
+            project_store<DT>(v, d, p, wire, wg_row + 32 * (TB * g + b) + row, col, sum);
+        }
+        if (b + 1 < TB) __syncthreads();
     }
 }
 
 // min_iters: tensors that asked for fewer subspace iterations than this sit the launch out.
-__global__ __launch_bounds__(kProjThreads, 2) void k_lr_project(BatchView v, LaunchRange r, int wire, int min_iters)
+// A kernel per storage type: fp32 operands take twice the registers, and bf16 tensors would pay for them in occupancy.
+template <int DT, int TB>
+__global__ __launch_bounds__(kProjThreads, TB == 1 ? 3 : 2) void k_lr_project(BatchView v, LaunchRange r, int wire, int min_iters)
 {
-    __shared__ __attribute__((aligned(16))) float patches[kProjThreads / 64][64 * kProjPitch];
+    __shared__ __attribute__((aligned(16))) ProjPatches patches;
     const int t = r.first + (int)blockIdx.y;
     const TensorDev d = v.descs[t];
-    if (d.scale != LOWRANK || d.bits < min_iters) return;
+    if (d.scale != LOWRANK || d.dtype != DT || d.bits < min_iters) return;
+    if ((int64_t)blockIdx.x * (TB * lowrank_project_tokens(d.n_channels)) >= d.n_tokens) return;        // uniform over the workgroup
     const TensorPtrs p = v.ptrs[t];
-    float *patch = patches[(int)threadIdx.x >> 6];
-    if (d.dtype == BF16) lr_project_body<BF16>(v, d, p, wire != 0, patch);
-    else lr_project_body<F32>(v, d, p, wire != 0, patch);
+    lr_project_body<DT, TB>(v, d, p, wire != 0, patches);
 }
 
 // ---------------------------------------------------------------- Z = A^T P
@@ -251,81 +373,105 @@ __device__ __forceinline__ uint8_t *lr_slice(const BatchView &v, const LaunchRan
 }
 
 // The tokens are cut into lowrank_runs = 1, 2 or 4 runs.  Z is the sum (run 0 + run 1) + (run 2 + run 3), each run the
-// sum (w0 + w1) + (w2 + w3) over its 4 waves, so the bits depend on the tensor's shape alone, whoever adds: a workgroup
-// owns a stripe of 128 channels and either takes all runs one after the other, or, in calls of few tensors, one or two
+// sum over the waves that share its batches of 16 tokens, so the bits depend on the tensor's shape alone, whoever adds: a workgroup
+// owns a stripe of 256 channels and either takes all runs one after the other, or, in calls of few tensors, one or two
 // of them, and the orthogonalisation adds the shares.
-// v_mfma_f32_16x16x4_f32 takes A[l % 16][l / 16] and B[l / 16][l % 16] from lane l: lane (q, g) holds channels
-// 8q..8q+7 of the stripe of token 4 * quad + g, straight from a 128-bit load, and spends them on 8 channel tiles
-// (tile j holds channels = j mod 8) times 2 rank tiles.  What bounds it is how much a CU has in flight:
-// three waves per SIMD (142 registers, 64 of them accumulators), each with the loads of one quad, about 2 KB; the loop asks
-// for R quads ahead, the compiler moves their loads down to the quad before their use.  57 x [4096, 3072], us: bf16 621
-// (713 with 256 channels and two waves per SIMD; 635 at four waves with one run), fp32 1185 (1187; 1769 at four waves and with the hint).
-// The sums cost a drained pipeline and two barriers a run: four turns of one wave each instead of two of two took 1 %
-// longer at 57 x [1000, 3072].
+// v_mfma_f32_16x16x32_bf16 takes 8 entries of row l % 16 of A and of column l % 16 of B from lane l, for k = 8 (l / 16) ...:
+// lane (q, g) holds channels 8q..8q+7 of its wave's 128 of 4 tokens, straight from 128-bit loads, and makes of channel j of these
+// tokens the row of channel tile j (tile j holds channels = j mod 8): two pieces of 4 values each, against the pieces of 4 rows
+// of P.  (high, mid) (high, high) + (high, mid) (mid, mid) + (high, low) (low, high) are the six products.
+// What bounds it, 57 x [4096, 3072] bf16, 541 us (fp32 MFMA 596-620): the stream of x and recon, alone 550 in 128-channel
+// stripes and 400-430 in wider ones; two waves side by side 576 -> 541.  Neither the MFMAs nor the splitting show (without
+// either the same), nor do more batches in flight (1 / 2 / 3: 579 / 603 / 687).  The next run's first batch is asked for before
+// the waves' sums meet: 575 -> 558.
 constexpr int kBackThreads = 256;
 constexpr int kBackChannels = kLowRankBackChannels;
 constexpr int kBackEntries = kBackChannels * kRank;
-typedef float BackSums[2][kBackEntries];                    // of waves 0 + 1 and 2 + 3
+constexpr int kBackWaveChannels = kBackChannels / 2;
 
 template <int DT>
 __device__ __forceinline__ void lr_backproject_body(const BatchView &v, const LaunchRange &r, const TensorDev &d, const TensorPtrs &p, int t,
-                                                    int stripe, int share, BackSums &sums, float *total)
+                                                    int stripe, int share, float *sums, float *total)
 {
-    const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
+    const int lane = (int)threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int q = lane & 15, g = lane >> 4;
-    const int64_t C = d.n_channels, last = d.n_tokens - 1;
-    const int64_t n_quads = (d.n_tokens + 3) / 4;
+    const int64_t last = d.n_tokens - 1, n_quads = (d.n_tokens + 3) / 4;
     const int n_runs = lowrank_runs(d.n_tokens, d.n_channels), n_mine = n_runs / lr_shares(r, d), first_run = share * n_mine;
-    const int64_t per_wave = (n_quads + 4 * n_runs - 1) / (4 * n_runs);
+    const int64_t per_run = (n_quads + n_runs - 1) / n_runs;
     // Loads without branches: rows and channels outside the tensor read its last ones, P counts as zero there and the
     // channels are not stored.
-    const int ch0 = stripe * kBackChannels + 8 * q;
-    const int ch = ch0 < d.n_channels ? ch0 : d.n_channels - 8;
-    const CF_GLOBAL float *P = gconst<float>(v.workspace + d.lr_p_off) + q;
-    constexpr int R = (DT == F32) ? 4 : 8;                  // quads asked for ahead (fp32 rows take twice the registers)
-    Raw8<DT> xr[R], br[R];
-    float pv[R][2];
-    auto fetch = [&](int slot, int64_t quad) {
-        const int64_t row = 4 * quad + g;
-        const int64_t at = row < last ? row : last;
-        load_once<DT>(xr[slot], p.x, at * C + ch);
-        load_once<DT>(br[slot], p.recon, at * C + ch);
-        pv[slot][0] = P[at * kRank];
-        pv[slot][1] = P[at * kRank + 16];
+    constexpr uint32_t kBytes = DT == BF16 ? 2 : 4;
+    const uint32_t row_bytes = (uint32_t)d.n_channels * kBytes;
+    // two waves side by side and every second batch each, or, where a stripe is no wider than one, every fourth
+    const int turns = d.n_channels - stripe * kBackChannels > kBackWaveChannels ? 2 : 4;
+    const int half = turns == 2 ? wave & 1 : 0, turn = turns == 2 ? wave >> 1 : wave;
+    const int ch0 = stripe * kBackChannels + half * kBackWaveChannels + 8 * q;
+    const uint32_t ch = (uint32_t)(ch0 < d.n_channels ? ch0 : d.n_channels - 8) * kBytes;
+    struct Batch {                                          // 16 tokens: a lane has rows 4 g .. 4 g + 3
+        Raw8<DT> x[4], b[4];
+        float p[2][4];
+    } batch;
+    auto fetch = [&](Batch &w, int64_t quad0) {
+        const int64_t row0 = 4 * quad0 < last ? 4 * quad0 : last;
+        const int room = last - row0 < 15 ? (int)(last - row0) : 15;        // rows after the first that exist
+        const char *px = static_cast<const char *>(p.x) + row0 * row_bytes, *pb = static_cast<const char *>(p.recon) + row0 * row_bytes;
+        const char *P = reinterpret_cast<const char *>(v.workspace + d.lr_p_off) + row0 * (kRank * 4);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const uint32_t row = (uint32_t)(4 * g + t < room ? 4 * g + t : room);
+            load_once(w.x[t], px, row * row_bytes + ch);
+            load_once(w.b[t], pb, row * row_bytes + ch);
+            w.p[0][t] = *gconst<float>(P + (row * (kRank * 4) + 4 * q));
+            w.p[1][t] = *gconst<float>(P + (row * (kRank * 4) + 64 + 4 * q));
+        }
     };
     CF_GLOBAL float *Z = gmut<float>(lr_slice(v, r, d, t, share)) + (int64_t)stripe * kBackEntries;
     const int n_out = (d.n_channels - stripe * kBackChannels) * kRank;      // entries of the stripe that exist
     for (int run = first_run; run < first_run + n_mine; ++run) {            // uniform over the workgroup
-        const int64_t lo = (run * 4 + wave) * per_wave;     // may lie beyond the last quad: such a wave adds zeros
-        const int64_t hi = lo + per_wave < n_quads ? lo + per_wave : n_quads;
+        const int64_t lo = run * per_run + 4 * turn;        // may lie beyond the last quad: such a wave adds zeros
+        const int64_t hi = (run + 1) * per_run < n_quads ? (run + 1) * per_run : n_quads;
         f32x4 acc[8][2];
 #pragma unroll
         for (int j = 0; j < 8; ++j) acc[j][0] = acc[j][1] = (f32x4)(0.0f);
         if (lo < hi) {
+            if (run == first_run) fetch(batch, lo);
+            for (int64_t quad0 = lo; quad0 < hi; quad0 += 4 * turns) {
+                Batch &w = batch;
+                const int64_t quad = quad0 + g;
+                u32x4 pp[2][3];                             // (high, high), (mid, mid), (low, high)
 #pragma unroll
-            for (int u = 0; u < R; ++u) fetch(u, lo + u);
-            for (int64_t quad0 = lo; quad0 < hi; quad0 += R) {
+                for (int c = 0; c < 2; ++c) {
+                    float pv[4];
 #pragma unroll
-                for (int u = 0; u < R; ++u) {
-                    const F8 x = xr[u].widen(), b = br[u].widen();
-                    F8 z;
+                    for (int t = 0; t < 4; ++t) pv[t] = quad < hi && 4 * quad + t <= last ? w.p[c][t] : 0.0f;
+                    const Split4 s = split4(pv);
+                    pp[c][0] = join(s.high, s.high);
+                    pp[c][1] = join(s.mid, s.mid);
+                    pp[c][2] = join(s.low, s.high);
+                }
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) z.v[j] = x.v[j] - b.v[j];
-                    const bool valid = quad0 + u < hi && 4 * (quad0 + u) + g <= last;
-                    const float p0 = valid ? pv[u][0] : 0.0f, p1 = valid ? pv[u][1] : 0.0f;
-                    fetch(u, quad0 + R + u);
+                for (int j = 0; j < 8; ++j) {
+                    float z[4];
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        acc[j][0] = mfma16(z.v[j], p0, acc[j][0]);
-                        acc[j][1] = mfma16(z.v[j], p1, acc[j][1]);
+                    for (int t = 0; t < 4; ++t) z[t] = element(w.x[t], j) - element(w.b[t], j);
+                    const Split4 s = split4(z);
+                    const u32x4 a0 = join(s.high, s.mid), a1 = join(s.high, s.low);
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) {
+                        const f32x4 small = mfma16_bf16(a0, pp[c][1], mfma16_bf16(a1, pp[c][2], (f32x4)(0.0f)));
+                        acc[j][c] = mfma16_bf16(a0, pp[c][0], acc[j][c]) + small;
                     }
                 }
+                __builtin_amdgcn_sched_barrier(0);
+                // the next batch, or the first of the next run, so that it is in flight while the waves' sums meet
+                fetch(w, quad0 + 4 * turns < hi ? quad0 + 4 * turns : (run + 1) * per_run + 4 * turn);
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
         // tile j, register i of lane (q, g): channel 8 * (4 * g + i) + j of the stripe, column q (and 16 + q)
-        for (int w = 0; w < 2; ++w) {
-            if ((wave & 1) == w) {
-                float *mine = sums[wave >> 1];
+        for (int w = 0; w < turns; ++w) {
+            if (turn == w) {
+                float *mine = sums + half * (kBackWaveChannels * kRank);
 #pragma unroll
                 for (int j = 0; j < 8; ++j)
 #pragma unroll
@@ -341,7 +487,7 @@ __device__ __forceinline__ void lr_backproject_body(const BatchView &v, const La
         // a lane keeps to its own entries of `total` and of Z
         const bool opens = run == first_run || (run & 1) == 0, closes = run + 1 == first_run + n_mine || (run & 1) == 1;
         for (int k = (int)threadIdx.x; k < kBackEntries; k += kBackThreads) {
-            float pair = sums[0][k] + sums[1][k];
+            float pair = sums[k];
             if (!opens) pair = total[k] + pair;
             if (!closes) total[k] = pair;
             else if (k < n_out) Z[k] = run < first_run + 2 ? pair : Z[k] + pair;
@@ -350,19 +496,18 @@ __device__ __forceinline__ void lr_backproject_body(const BatchView &v, const La
     }
 }
 
-__global__ __launch_bounds__(kBackThreads, 3) void k_lr_backproject(BatchView v, LaunchRange r, int min_iters)
+template <int DT>
+__global__ __launch_bounds__(kBackThreads, 2) void k_lr_backproject(BatchView v, LaunchRange r, int min_iters)
 {
-    __shared__ BackSums sums;
-    __shared__ float total[kBackEntries];
+    __shared__ float sums[kBackEntries], total[kBackEntries];
     const int t = r.first + (int)blockIdx.y;
     const TensorDev d = v.descs[t];
-    if (d.scale != LOWRANK || d.bits < min_iters) return;
+    if (d.scale != LOWRANK || d.dtype != DT || d.bits < min_iters) return;
     const int n_stripes = (d.n_channels + kBackChannels - 1) / kBackChannels;
     const int stripe = (int)blockIdx.x % n_stripes, share = (int)blockIdx.x / n_stripes;
     if (share >= lr_shares(r, d)) return;                   // uniform over the workgroup: narrower or shorter than the largest tensor
     const TensorPtrs p = v.ptrs[t];
-    if (d.dtype == BF16) lr_backproject_body<BF16>(v, r, d, p, t, stripe, share, sums, total);
-    else lr_backproject_body<F32>(v, r, d, p, t, stripe, share, sums, total);
+    lr_backproject_body<DT>(v, r, d, p, t, stripe, share, sums, total);
 }
 
 // ---------------------------------------------------------------- Q = orth(Z)
@@ -614,12 +759,34 @@ __global__ __launch_bounds__(kOrthThreads) void k_lr_orth(BatchView v, LaunchRan
             z[j + 1] = __builtin_fma(-q, rr.y, z[j + 1]);
         }
     }
-    if (!valid) return;
-    CF_GLOBAL float *qs = gmut<float>(v.workspace + d.lr_z_off);
-    uint8_t *V = wire_v(d, p);
-    const int s = ch >> 5, c = ch & 31, hh = c >> 4, j = c & 15;
+    // Q in the order and the pieces k_lr_project reads: the wave's rows turn in its part of LDS, 32 channels at a time
+    float *turn = reinterpret_cast<float *>(parts[tid >> 6]);
+    constexpr int kTurnPitch = kRank + 1;
+    static_assert(32 * kTurnPitch * sizeof(float) <= sizeof(parts[0]), "32 rows fit a wave's part");
 #pragma unroll
-    for (int n = 0; n < kRank; ++n) qs[((int64_t)s * 64 + hh * 32 + n) * 16 + j] = a[n];
+    for (int half = 0; half < 2; ++half) {
+        const int step = (ch - (tid & 63)) / 32 + half;
+        if (32 * step >= d.n_channels) break;               // uniform over the wave
+        wave_lds_fence();
+        if (((tid >> 5) & 1) == half)
+#pragma unroll
+            for (int n = 0; n < kRank; ++n) turn[(tid & 31) * kTurnPitch + n] = a[n];
+        wave_lds_fence();
+        const int octet = (tid & 63) >> 4;
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt) {
+            const int n = 16 * rt + (tid & 15);
+            float f[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) f[i] = turn[(8 * octet + i) * kTurnPitch + n];
+            const Split8 q = split8(f);
+            gmut<u32x4>(lr_q(v, d, step, 0))[octet * 32 + n] = q.high;
+            gmut<u32x4>(lr_q(v, d, step, 1))[octet * 32 + n] = q.mid;
+            gmut<u32x4>(lr_q(v, d, step, 2))[octet * 32 + n] = q.low;
+        }
+    }
+    if (!valid) return;
+    uint8_t *V = wire_v(d, p);
     if (factors_int4(d)) {
         quantise_factor_row(a, wire4_v(d, p) + (int64_t)ch * 16, wire4_v_scales(d, p) + ch);
         return;
@@ -761,16 +928,18 @@ __global__ __launch_bounds__(kTwiceThreads) void k_lr_orth_twice(BatchView v, La
         }
     }
     twice_columns_from<0>(a, sh);
-    CF_GLOBAL float *qs = gmut<float>(v.workspace + d.lr_z_off);
     uint8_t *V = wire_v(d, p);
 #pragma unroll
     for (int rr = 0; rr < kTwiceRows; ++rr) {
         const int ch = (int)threadIdx.x + kTwiceThreads * rr;
         if (ch >= d.n_channels) continue;
-        const int s = ch >> 5, c = ch & 31, hh = c >> 4, j = c & 15;
 #pragma unroll
         for (int n = 0; n < kRank; ++n) {
-            qs[((int64_t)s * 64 + hh * 32 + n) * 16 + j] = a[rr][n];
+            const int64_t at = (((ch & 31) >> 3) * 32 + n) * 8 + (ch & 7);
+            const float high = (float)(__bf16)a[rr][n], mid = (float)(__bf16)(a[rr][n] - high);
+            gmut<__bf16>(lr_q(v, d, ch >> 5, 0))[at] = (__bf16)high;
+            gmut<__bf16>(lr_q(v, d, ch >> 5, 1))[at] = (__bf16)mid;
+            gmut<__bf16>(lr_q(v, d, ch >> 5, 2))[at] = (__bf16)(a[rr][n] - high - mid);
             if (factors_int4(d)) continue;
             if (d.dtype == BF16) gmut<uint16_t>(V)[(int64_t)ch * kRank + n] = (uint16_t)bf16_rne(a[rr][n]);
             else gmut<float>(V)[(int64_t)ch * kRank + n] = a[rr][n];
@@ -804,44 +973,80 @@ template <int DT> __device__ __forceinline__ void factor16(const uint8_t *base, 
     for (int k = 0; k < 16; ++k) out[k] = valid ? out[k] : 0.0f;
 }
 
-// A wave owns 32 tokens and kApplySpan channels, which it walks in tiles of 64 (a workgroup that
-// looped over all channels would have to drain its stores before each tile's loads count as returned).  The MFMA leaves lane (n, h) with
+// One row of a factor on the wire as the MFMAs of D take it, this lane's half of its 32 entries; times() is a 32 x 32 tile of
+// rows against rows.  BFW: bf16 factors, whose products the bf16 matrix cores form exactly and add up in fp32, two instructions
+// where the fp32 ones take sixteen.
+template <int DT, bool BFW> struct Factors {
+    float f[16];                // entries 16 h ...
+    __device__ __forceinline__ void load(const uint8_t *base, const float *scales, bool int4, int64_t row, int h, bool valid)
+    {
+        factor16<DT>(base, scales, int4, row, h, valid, f);
+    }
+    __device__ __forceinline__ f32x16 times(const Factors &other) const
+    {
+        f32x16 acc = {};
+#pragma unroll
+        for (int j = 0; j < 16; ++j) acc = mfma32(f[j], other.f[j], acc);
+        return acc;
+    }
+};
+template <> struct Factors<BF16, true> {
+    u32x4 w[2];                 // entries 8 h ... and 16 + 8 h ...
+    __device__ __forceinline__ void load(const uint8_t *base, const float *, bool, int64_t row, int h, bool valid)
+    {
+        const CF_GLOBAL u32x4 *src = gconst<u32x4>(base + (valid ? row : 0) * (kRank * 2)) + h;     // row 0 always exists
+        w[0] = valid ? src[0] : (u32x4)(0u);
+        w[1] = valid ? src[2] : (u32x4)(0u);
+    }
+    __device__ __forceinline__ f32x16 times(const Factors &other) const
+    {
+        return mfma32_bf16(w[1], other.w[1], mfma32_bf16(w[0], other.w[0], (f32x16)(0.0f)));
+    }
+};
+
+// A wave owns 32 tokens x 64 channels, the waves of a workgroup lie side by side.  The MFMA leaves lane (n, h) with
 // channel n of 16 tokens, which is the wrong way round for row-major memory, so the tile of D goes
 // through the wave's own LDS patch [32 tokens][64 channels] and comes back as 8 consecutive channels
 // of one token per lane: 8 lanes then cover 128 bytes of a bf16 row (256 of the fp32 error row).
 // SENDER: also forms A again and writes e = A - D.  UPDATE: writes recon + D.
+// What bounds it is HBM, and how well depends on how much of a row a workgroup has open and how many do: 57 x [4096, 3072],
+// waves below one another, 128 channels wide, fp32 MFMA, two workgroups per CU 1322 us; bf16 MFMA, four of them per CU 1410, two 1358;
+// waves side by side, 256 channels, three per CU 1245, two 1196 (512 channels 1254 / 1199).
 constexpr int kApplyChannels = 64;
-#ifndef CF_APPLY_SPAN
-#define CF_APPLY_SPAN 128
-#endif
-constexpr int kApplySpan = CF_APPLY_SPAN;                   // channels per workgroup
+constexpr int kApplyTokens = 32;
+// Channels per workgroup.  4-bit factors cost a wave more to widen than the products: it makes two tiles of its rows of U.
+constexpr int apply_span(bool bf16_wire) { return (bf16_wire ? 4 : 8) * kApplyChannels; }
 constexpr int kApplyPitch = kApplyChannels + 4;             // floats per token row of the patch
+constexpr unsigned kApplyCapLds = 40000;                    // dynamic LDS that nobody touches: two workgroups per CU of senders (the receiver 512 us, 573 capped)
 
-template <int DT, int ET, bool SENDER, bool UPDATE>
-__device__ __forceinline__ void lr_apply_body(const TensorDev &d, const TensorPtrs &p, float *patch, float *epatch)
+template <int DT, int ET, bool SENDER, bool UPDATE, bool BFW>
+__device__ __forceinline__ void lr_apply_body(const TensorDev &d, const TensorPtrs &p, float *patch)
 {
     const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
     const int n = lane & 31, h = lane >> 5;
-    const int n_spans = (d.n_channels + kApplySpan - 1) / kApplySpan;
+    constexpr int kSpan = apply_span(BFW);
+    const int n_spans = (d.n_channels + kSpan - 1) / kSpan;
     const int span = (int)(blockIdx.x % (unsigned)n_spans);
-    const int64_t tok_base = (int64_t)(blockIdx.x / (unsigned)n_spans) * 128 + wave * 32;
-    if (tok_base >= d.n_tokens) return;                     // uniform over the wave
+    const int64_t tok_base = (int64_t)(blockIdx.x / (unsigned)n_spans) * kApplyTokens;
+    if (tok_base >= d.n_tokens) return;                     // uniform over the workgroup
     const int64_t C = d.n_channels;
-    float u[16];
     const bool int4 = factors_int4(d);
-    factor16<DT>(int4 ? wire4_u(p) : wire_u(p), wire4_u_scales(d, p), int4, tok_base + n, h, tok_base + n < d.n_tokens, u);
+    Factors<DT, BFW> u;
+    u.load(int4 ? wire4_u(p) : wire_u(p), wire4_u_scales(d, p), int4, tok_base + n, h, tok_base + n < d.n_tokens);
     const uint8_t *V = int4 ? wire4_v(d, p) : wire_v(d, p);
     const float *Vs = wire4_v_scales(d, p);
-    const int sub_lo = span * (kApplySpan / 32);
-    const int n_sub = d.n_channels / 32 < sub_lo + kApplySpan / 32 ? d.n_channels / 32 : sub_lo + kApplySpan / 32;
     const int chunk = lane & 7, trow = lane >> 3;           // row-major side: 8 chunks of 8 channels, 8 tokens per sweep
-    for (int sub0 = sub_lo; sub0 < n_sub; sub0 += 2) {
+    const int n_sub = d.n_channels / 32;
+#pragma unroll 1
+    for (int tile = 0; tile < kSpan / (4 * kApplyChannels); ++tile) {
+        const int sub0 = span * (kSpan / 32) + 8 * tile + 2 * wave;
+        if (sub0 >= n_sub) break;                           // uniform over the wave
         const int cnt = n_sub - sub0 < 2 ? 1 : 2;
         // Issue order matters because loads return in order: first the V rows the MFMAs need, then the
         // tile's x and recon, which are only needed once D has come back through the patch.
-        float vv[2][16];
+        Factors<DT, BFW> vv[2];
 #pragma unroll
-        for (int c = 0; c < 2; ++c) factor16<DT>(V, Vs, int4, (int64_t)(sub0 + (c < cnt ? c : 0)) * 32 + n, h, true, vv[c]);
+        for (int c = 0; c < 2; ++c) vv[c].load(V, Vs, int4, (int64_t)(sub0 + (c < cnt ? c : 0)) * 32 + n, h, true);
         Raw8<DT> xr[4], br[4];
         bool live[4];
 #pragma unroll
@@ -861,21 +1066,19 @@ __device__ __forceinline__ void lr_apply_body(const TensorDev &d, const TensorPt
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
             if (c < cnt) {                                  // uniform over the wave
-                f32x16 acc = {};
-#pragma unroll
-                for (int j = 0; j < 16; ++j) acc = mfma32(u[j], vv[c][j], acc);
+                const f32x16 acc = u.times(vv[c]);
 #pragma unroll
                 for (int i = 0; i < 16; ++i) patch[(8 * (i >> 2) + 4 * h + (i & 3)) * kApplyPitch + c * 32 + n] = acc[i];
             }
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_fence();
 #pragma unroll
         for (int it = 0; it < 4; ++it) {
             const int tl = trow + 8 * it;
             const int64_t tok = tok_base + tl;
-            // every lane goes through the exchange of the error row (dead lanes carry values nobody stores)
-            const f32x4 *src = reinterpret_cast<const f32x4 *>(patch + tl * kApplyPitch + chunk * 8);
-            const f32x4 d0 = src[0], d1 = src[1];
+            float *row = patch + tl * kApplyPitch;
+            f32x4 *mine = reinterpret_cast<f32x4 *>(row + chunk * 8);
+            const f32x4 d0 = mine[0], d1 = mine[1];
             F8 D;
             D.v[0] = d0.x; D.v[1] = d0.y; D.v[2] = d0.z; D.v[3] = d0.w;
             D.v[4] = d1.x; D.v[5] = d1.y; D.v[6] = d1.z; D.v[7] = d1.w;
@@ -889,9 +1092,13 @@ __device__ __forceinline__ void lr_apply_body(const TensorDev &d, const TensorPt
                     const float z = x.v[k] - b.v[k];
                     lost.v[k] = z - D.v[k];
                 }
-                if (ET == F32) {        // the 8 lanes of a token row send its 256 bytes as two whole lines
-                    f32x4 pieces[2];
-                    lines_exchange<8>(epatch, lane, lost, pieces);
+                if (ET == F32) {        // the 8 lanes of a token row take its error back from D's place as two whole lines (dead lanes go along)
+                    Raw8<F32> eo;
+                    eo.narrow(lost);
+                    mine[0] = eo.a;
+                    mine[1] = eo.b;
+                    wave_lds_fence();
+                    const f32x4 pieces[2] = {*reinterpret_cast<const f32x4 *>(row + 4 * chunk), *reinterpret_cast<const f32x4 *>(row + 32 + 4 * chunk)};
                     if (tok < d.n_tokens)
                         lines_store_stream<8>(static_cast<float *>(p.err) + tok * C + (int64_t)sub0 * 32, chunk, cnt * 4, pieces);
                 } else if (live[it]) {
@@ -909,23 +1116,23 @@ __device__ __forceinline__ void lr_apply_body(const TensorDev &d, const TensorPt
                 if (DT == BF16) out.store_stream(p.recon, e0); else out.store(p.recon, e0);
             }
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_fence();
     }
 }
 
-template <int ET, bool SENDER, bool UPDATE>
-__global__ __launch_bounds__(256) void k_lr_apply(BatchView v, LaunchRange r)
+// KIND: tensors whose factors travel as bf16, or the others (fp32 and 4-bit factors).
+template <int ET, bool SENDER, bool UPDATE, bool BFW>
+__global__ __launch_bounds__(256, BFW ? 3 : 2) void k_lr_apply(BatchView v, LaunchRange r)
 {
     __shared__ __attribute__((aligned(16))) float patches[4][32 * kApplyPitch];
     const int t = r.first + (int)blockIdx.y;
     const TensorDev d = v.descs[t];
-    if (d.scale != LOWRANK) return;
+    if (d.scale != LOWRANK || (d.dtype == BF16 && !factors_int4(d)) != BFW) return;
     const TensorPtrs p = v.ptrs[t];
-    __shared__ __attribute__((aligned(16))) float epatches[4][512];       // the error rows' way to whole lines (2 KB per wave)
     float *patch = patches[(int)threadIdx.x >> 6];
-    float *epatch = epatches[(int)threadIdx.x >> 6];
-    if (d.dtype == BF16) lr_apply_body<BF16, ET, SENDER, UPDATE>(d, p, patch, epatch);
-    else lr_apply_body<F32, ET, SENDER, UPDATE>(d, p, patch, epatch);
+    if constexpr (BFW) lr_apply_body<BF16, ET, SENDER, UPDATE, true>(d, p, patch);
+    else if (d.dtype == BF16) lr_apply_body<BF16, ET, SENDER, UPDATE, false>(d, p, patch);
+    else lr_apply_body<F32, ET, SENDER, UPDATE, false>(d, p, patch);
 }
 
 }  // namespace
@@ -949,8 +1156,16 @@ hipError_t launch_lr_orth(const BatchView &v, const LaunchRange &r, bool from_q0
 hipError_t launch_lr_project(const BatchView &v, const LaunchRange &r, bool wire, int min_iters, hipStream_t s)
 {
     if (r.count == 0 || r.lr_max_tokens == 0) return hipSuccess;
-    dim3 grid((unsigned)((r.lr_max_tokens + kProjTokens - 1) / kProjTokens), (unsigned)r.count);
-    hipLaunchKernelGGL(k_lr_project, grid, dim3(kProjThreads), 0, s, v, r, wire ? 1 : 0, min_iters);
+    const dim3 grid((unsigned)r.lr_project_blocks, (unsigned)r.count), block(kProjThreads);
+    if (r.dts != F32) {
+        if ((int64_t)r.lr_project_blocks * r.count >= kProjMany)
+            hipLaunchKernelGGL((k_lr_project<BF16, kProjBlocks>), dim3((grid.x + kProjBlocks - 1) / kProjBlocks, grid.y), block, 0, s, v, r, wire ? 1 : 0, min_iters);
+        else
+            hipLaunchKernelGGL((k_lr_project<BF16, 1>), grid, block, 0, s, v, r, wire ? 1 : 0, min_iters);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    if (r.dts != BF16) hipLaunchKernelGGL((k_lr_project<F32, 1>), grid, block, 0, s, v, r, wire ? 1 : 0, min_iters);
     return hipGetLastError();
 }
 
@@ -958,15 +1173,19 @@ hipError_t launch_lr_backproject(const BatchView &v, const LaunchRange &r, int m
 {
     if (r.count == 0 || r.lr_max_channels == 0) return hipSuccess;
     dim3 grid((unsigned)((r.lr_max_channels + kBackChannels - 1) / kBackChannels * r.lr_split), (unsigned)r.count);
-    hipLaunchKernelGGL(k_lr_backproject, grid, dim3(kBackThreads), 0, s, v, r, min_iters);
+    if (r.dts != F32) hipLaunchKernelGGL(k_lr_backproject<BF16>, grid, dim3(kBackThreads), 0, s, v, r, min_iters);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    if (r.dts != BF16) hipLaunchKernelGGL(k_lr_backproject<F32>, grid, dim3(kBackThreads), 0, s, v, r, min_iters);
     return hipGetLastError();
 }
 
-// Blocks of 128 tokens x kApplySpan channels, for the largest low-rank tensor of the range; a tensor with
+// Blocks of kApplyTokens x apply_span channels, for the largest low-rank tensor of the range; a tensor with
 // fewer channel spans sees block indices beyond its own and returns at once (tok_base >= n_tokens).
-static unsigned apply_blocks(const LaunchRange &r)
+static dim3 apply_grid(const LaunchRange &r, bool bf16_wire)
 {
-    return (unsigned)((r.lr_max_tokens + 127) / 128) * (unsigned)((r.lr_max_channels + kApplySpan - 1) / kApplySpan);
+    const int span = apply_span(bf16_wire);
+    return dim3((unsigned)((r.lr_max_tokens + kApplyTokens - 1) / kApplyTokens) * (unsigned)((r.lr_max_channels + span - 1) / span), (unsigned)r.count);
 }
 
 hipError_t launch_lr_quant_u(const BatchView &v, const LaunchRange &r, hipStream_t s)
@@ -980,13 +1199,19 @@ hipError_t launch_lr_quant_u(const BatchView &v, const LaunchRange &r, hipStream
 hipError_t launch_lr_encode(const BatchView &v, const LaunchRange &r, int err_dtype, bool fused, hipStream_t s)
 {
     if (r.count == 0 || r.lr_max_tokens == 0) return hipSuccess;
-    dim3 grid(apply_blocks(r), (unsigned)r.count), block(256);
+    const dim3 block(256);
+    const unsigned cap = kApplyCapLds;
+#define CF_LAUNCH_APPLY(...)                                                                                              \
+    do {                                                                                                                  \
+        if (r.lr_wires & 1) hipLaunchKernelGGL((k_lr_apply<__VA_ARGS__, true>), apply_grid(r, true), block, cap, s, v, r);                 \
+        if (r.lr_wires & 2) hipLaunchKernelGGL((k_lr_apply<__VA_ARGS__, false>), apply_grid(r, false), block, 0, s, v, r); \
+    } while (0)
     if (err_dtype == BF16) {
-        if (fused) hipLaunchKernelGGL((k_lr_apply<BF16, true, true>), grid, block, 0, s, v, r);
-        else hipLaunchKernelGGL((k_lr_apply<BF16, true, false>), grid, block, 0, s, v, r);
+        if (fused) CF_LAUNCH_APPLY(BF16, true, true);
+        else CF_LAUNCH_APPLY(BF16, true, false);
     } else {
-        if (fused) hipLaunchKernelGGL((k_lr_apply<F32, true, true>), grid, block, 0, s, v, r);
-        else hipLaunchKernelGGL((k_lr_apply<F32, true, false>), grid, block, 0, s, v, r);
+        if (fused) CF_LAUNCH_APPLY(F32, true, true);
+        else CF_LAUNCH_APPLY(F32, true, false);
     }
     return hipGetLastError();
 }
@@ -994,8 +1219,10 @@ hipError_t launch_lr_encode(const BatchView &v, const LaunchRange &r, int err_dt
 hipError_t launch_lr_decode(const BatchView &v, const LaunchRange &r, hipStream_t s)
 {
     if (r.count == 0 || r.lr_max_tokens == 0) return hipSuccess;
-    dim3 grid(apply_blocks(r), (unsigned)r.count);
-    hipLaunchKernelGGL((k_lr_apply<F32, false, true>), grid, dim3(256), 0, s, v, r);
+    const dim3 block(256);
+    const unsigned cap = 0;
+    CF_LAUNCH_APPLY(F32, false, true);
+#undef CF_LAUNCH_APPLY
     return hipGetLastError();
 }
 

@@ -540,6 +540,56 @@ def test_lowrank_bits_do_not_depend_on_the_call(n, count):
             s.close()
 
 
+@pytest.mark.parametrize("dtype", [cf.CF_BF16, cf.CF_F32])
+@pytest.mark.parametrize("n, c", [(127, 96), (97, 128), (161, 160), (130, 288), (386, 416), (225, 224), (100, 544)])
+def test_lowrank_tile_edges(n, c, dtype):
+    """Token counts around the 16, 32 and 96 tokens of a batch, a block and a wave, channels around the 64 of a stage, the 128
+    and 256 of a wave and a stripe and the halves of each, against the oracle at the file's tolerances.  Those are for products
+    conditioned below 100: three times the rank in tokens and channels; [31, 32], of less than full rank, is outside them (3.7e-4)."""
+    say(f"lowrank tile edges [{n}, {c}] dtype={dtype}")
+    xs, q0 = stream(n, c, dtype, 2, 600 + n), start_matrices(c, 1, 700 + c)[0]
+    sess = CodecSession([cf.desc(n, c, dtype, 1, cf.CF_LOWRANK, R)], cf.options(), device=DEV)
+    try:
+        sess.warmup([xs[0]])
+        before = as_numpy(sess.recon[0]).copy()
+        sess.scales[0].copy_(q0.reshape(-1))
+        sess.step_fused([xs[1]])
+        cf.cf_check_device(sess.ctx, sess.stream_handle)
+        cfg = lr.LowRankConfig(n, c, dtype=lr.BF16 if dtype == cf.CF_BF16 else lr.F32, rank=R, iters=1)
+        check_step(f"edges [{n}, {c}]", cfg, sess, 0, as_numpy(xs[1]), before, as_numpy(q0))
+    finally:
+        sess.close()
+
+
+def test_lowrank_many_blocks_same_bits():
+    """Calls of at least 1024 blocks of tokens, whose waves take three of them in turn: the first and the last tensor of such a
+    call, ragged in tokens and channels, against the same tensors alone."""
+    shapes = [(97, 64), (389, 224), (1100, 96)]
+    descs = [cf.desc(*shapes[t % 3], cf.CF_BF16, 1, cf.CF_LOWRANK, R) for t in range(60)]
+    say("lowrank: 60 ragged tensors in a call of many blocks")
+    xs = [stream(*shapes[t % 3], cf.CF_BF16, 2, 800 + t) for t in range(60)]
+    q0 = [start_matrices(shapes[t % 3][1], 1, 900 + t)[0] for t in range(60)]
+    pick = [0, 1, 2, 57, 58, 59]
+    batch, alone = CodecSession(descs, cf.options(), device=DEV), CodecSession([descs[t] for t in pick], cf.options(), device=DEV)
+    try:
+        batch.warmup([x[0] for x in xs])
+        alone.warmup([xs[t][0] for t in pick])
+        for t in range(60):
+            batch.scales[t].copy_(q0[t].reshape(-1))
+        batch.step_fused([x[1] for x in xs])
+        for k, t in enumerate(pick):
+            alone.scales[k].copy_(q0[t].reshape(-1))
+            alone.step_fused([xs[t][1]], first=k, count=1)
+        cf.cf_check_device(batch.ctx, batch.stream_handle)
+        cf.cf_check_device(alone.ctx, alone.stream_handle)
+        for k, t in enumerate(pick):
+            for name in ("codes", "recon", "err"):
+                assert torch.equal(getattr(batch, name)[t], getattr(alone, name)[k]), f"{name} of tensor {t} depends on the call"
+    finally:
+        batch.close()
+        alone.close()
+
+
 @pytest.mark.parametrize("c", [64, 3072])
 def test_lowrank_leaning_columns_on_every_wire(c):
     """The column by column form writes its V in all three wire formats: bf16 and INT4 factors are the fp32 factors of the
