@@ -405,6 +405,7 @@ struct cf_ctx {
         LaunchRange r;
         r.first = first;
         r.count = count;
+        r.direct = nullptr;
         r.tile_lo = L.tile_prefix[first];
         r.tile_hi = L.tile_prefix[first + count];
         r.ew_lo = L.ew_prefix[first];
@@ -686,6 +687,26 @@ cf_status sync_ptrs(cf_ctx *ctx, int32_t first, int32_t count, const void *const
     return CF_OK;
 }
 
+// Calls over few tensors whose kernels read no table: the pointers go into the kernels' arguments.  Table and mirror stay as
+// they are, so this holds on any stream and under capture.  False, and nothing done, for calls over more tensors.
+struct DirectPtrs {
+    TensorPtrs sets[kDirectTensors];
+    bool take(LaunchRange &r, const void *const *x, const void *const *recon, const void *const *err, const void *const *codes, const void *const *scales)
+    {
+        if (r.count > kDirectTensors) return false;
+        std::memset(sets, 0, sizeof sets);
+        for (int32_t k = 0; k < r.count; ++k) {
+            if (x) sets[k].x = x[k];
+            if (recon) sets[k].recon = const_cast<void *>(recon[k]);
+            if (err) sets[k].err = const_cast<void *>(err[k]);
+            if (codes) sets[k].codes = static_cast<uint8_t *>(const_cast<void *>(codes[k]));
+            if (scales) sets[k].scales = static_cast<float *>(const_cast<void *>(scales[k]));
+        }
+        r.direct = sets;
+        return true;
+    }
+};
+
 // Alg. 3 on the low-rank tensors of the range: Q <- orth(Q0); T x { P <- A Q; Z <- A^T P; Q <- orth(Z) };
 // U <- A Q; then D = U V^T, error and reconstruction.
 cf_status run_lowrank_sender(cf_ctx *ctx, int32_t first, int32_t count, const BatchView &v, const LaunchRange &r,
@@ -778,6 +799,12 @@ cf_status run_sender(cf_ctx *ctx, int32_t first, int32_t count, const void *cons
     const bool single_pass = ctx->L.single_pass && grid >= ctx->L.max_group_items && grid >= 1 && r.item_hi > r.item_lo && worth_it;
     // the call's pointers go to the table first; the single pass's first kernel takes the last batch of them along
     DeferredPtrs defer;
+    const bool row_local_only = !ctx->range_has_channel(first, count) && ctx->range_lowrank_iters(first, count) < 0;
+    DirectPtrs direct;
+    if (row_local_only && direct.take(r, x, recon, err, codes, reinterpret_cast<const void *const *>(scales))) {
+        e = run_row_local(ctx, first, count, v, r, fused, true, s);
+        return e == hipSuccess ? CF_OK : device_fail(ctx, e);
+    }
     if ((st = sync_ptrs(ctx, first, count, x, recon, err, codes, scales, s, single_pass ? &defer : nullptr)) != CF_OK) return st;
     if (single_pass) {
         // channel-scale tensors: one pass, the operands stay in registers across the scale reduction
@@ -942,8 +969,12 @@ cf_status cf_warmup(cf_ctx *ctx, int32_t first, int32_t count, const void *const
             return CF_ERR_INVALID_ARG;
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if ((st = sync_ptrs(ctx, first, count, x0, recon, err, nullptr, nullptr, s)) != CF_OK) return st;
-    hipError_t e = launch_warmup(ctx->view(), ctx->range(first, count), ctx->opts.err_dtype, s);
+    LaunchRange r = ctx->range(first, count);
+    DirectPtrs direct;
+    if (!direct.take(r, x0, recon, err, nullptr, nullptr) &&
+        (st = sync_ptrs(ctx, first, count, x0, recon, err, nullptr, nullptr, s)) != CF_OK)
+        return st;
+    hipError_t e = launch_warmup(ctx->view(), r, ctx->opts.err_dtype, s);
     if (e != hipSuccess) return device_fail(ctx, e);
     for (int32_t t = first; t < first + count; ++t) ctx->warm[t] = 1;
     return CF_OK;
@@ -979,16 +1010,19 @@ cf_status cf_decompress(cf_ctx *ctx, int32_t first, int32_t count, const void *c
     if ((st = check_warm(ctx, first, count)) != CF_OK) return st;
     hipStream_t s = static_cast<hipStream_t>(stream);
     ProfileScope prof(ctx);
-    st = sync_ptrs(ctx, first, count, nullptr, recon, nullptr, const_cast<void *const *>(codes),
-                   const_cast<void *const *>(scales), s);
-    if (st != CF_OK) return st;
+    LaunchRange r = ctx->range(first, count);
+    DirectPtrs direct;
+    if (!direct.take(r, nullptr, recon, nullptr, codes, scales) &&
+        (st = sync_ptrs(ctx, first, count, nullptr, recon, nullptr, const_cast<void *const *>(codes),
+                        const_cast<void *const *>(scales), s)) != CF_OK)
+        return st;
     hipError_t e = hipSuccess;
     if (ctx->range_has_elementwise(first, count)) {
-        e = launch(ctx, s, "k_decode", [&] { return launch_decode(ctx->view(), ctx->range(first, count), s); });
+        e = launch(ctx, s, "k_decode", [&] { return launch_decode(ctx->view(), r, s); });
         if (e != hipSuccess) return device_fail(ctx, e);
     }
     if (ctx->range_lowrank_iters(first, count) >= 0) {
-        e = launch(ctx, s, "k_lr_apply", [&] { return launch_lr_decode(ctx->view(), ctx->range(first, count), s); });
+        e = launch(ctx, s, "k_lr_apply", [&] { return launch_lr_decode(ctx->view(), r, s); });
         if (e != hipSuccess) return device_fail(ctx, e);
     }
     return CF_OK;

@@ -10,6 +10,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "cf_internal.h"
+
 namespace cf {
 namespace dev {
 
@@ -561,6 +563,10 @@ __device__ __forceinline__ int find_slot(const uint32_t *prefix, int lo, int hi,
     }
     return lo;
 }
+
+// The device pointers of tensor t (uniform over the workgroup) of the call.
+__device__ __forceinline__ TensorPtrs call_ptrs(const BatchView &v, const LaunchRange &, int t) { return v.ptrs[t]; }
+__device__ __forceinline__ TensorPtrs call_ptrs(const BatchView &, const DirectRange &r, int t) { return r.sets[t - r.first]; }
 
 }  // namespace dev
 }  // namespace cf

@@ -17,6 +17,11 @@ constexpr int kFinalizeColumns = 16;                        // columns per final
 constexpr int kRank1Threads = 1024;                         // one block per tensor finishes the token scales u
 constexpr int kMaxRank1Colblocks = 128;                     // rank-1 scales: C <= 128 * 1024
 constexpr int kMaxUploadTensors = 64;                       // pointer sets per upload launch
+// Calls of one kernel over at most so many tensors (one layer's K and V of four peers) carry their pointers in the kernel's
+// arguments and skip the upload to the table, a launch and a gap: us a call,
+// table / arguments: 6 x [1024, 3072] 2-bit receiver 19.9 / 17.9, small calls of one kernel 12.0 / 8.4, 10.4 / 8.8, 15.4 / 13.1.
+// More sets would lengthen the arguments of the calls that gain least.
+constexpr int kDirectTensors = 8;
 // Single-pass path: one workgroup of 256 lanes keeps an item of p_rows x 128
 // channels (x and recon, raw) in registers between the scale reduction and the
 // encode; lanes are 16 chunks x 16 row-lanes, so a row segment is 256 bytes of
@@ -146,7 +151,24 @@ struct LaunchRange {
     int32_t lr_project_blocks;  // workgroups of k_lr_project for the tensor that needs most, one block of tokens per wave
     int32_t lr_split;           // low-rank back-projection: at most so many workgroups share a channel stripe's runs of tokens (1, 2 or 4)
     uint64_t lr_slices_off;     // workspace offset of the shares after the first, [count][lr_split - 1][lr_max_channels][32] fp32
+    const TensorPtrs *direct;   // host memory: the call's pointers, kDirectTensors sets at most, for kernels to take as arguments; null: they are in the table
 };
+
+// The same with the call's pointers along: what kernels of direct calls take in the range's place, in instances of their own
+// (a choice between the sets and the table within one instance cost the large kernels 3-5 %).
+struct DirectRange : LaunchRange {
+    TensorPtrs sets[kDirectTensors];
+    explicit DirectRange(const LaunchRange &r) : LaunchRange(r), sets()
+    {
+        for (int k = 0; k < r.count && k < kDirectTensors; ++k) sets[k] = r.direct[k];
+    }
+};
+
+// f(range) with the kind of range the call's kernels take
+template <class F> void with_range(const LaunchRange &r, F &&f)
+{
+    if (r.direct) f(DirectRange(r)); else f(r);
+}
 
 enum class Op { Compress, StepFused };
 

@@ -80,8 +80,8 @@ template <int DTS> __device__ __forceinline__ bool is_bf16(const TensorDev &d) {
 constexpr int TILES_REDUCE = 0, TILES_EW = 1, TILES_DECODE = 2;
 
 // SHAPE: the tiles are known to be rows (0) or flat (1), or it depends on the tensor (2).
-template <int KIND, int SHAPE>
-__device__ __forceinline__ TileCtx locate_tile_of(const BatchView &v, const LaunchRange &r)
+template <int KIND, int SHAPE, class R>
+__device__ __forceinline__ TileCtx locate_tile_of(const BatchView &v, const R &r)
 {
     const uint32_t lo = KIND == TILES_EW ? r.ew_lo : KIND == TILES_DECODE ? r.dec_lo : r.tile_lo;
     const uint32_t *prefix = KIND == TILES_EW ? v.ew_prefix : KIND == TILES_DECODE ? v.dec_prefix : v.tile_prefix;
@@ -89,7 +89,7 @@ __device__ __forceinline__ TileCtx locate_tile_of(const BatchView &v, const Laun
     int t = find_slot(prefix, r.first, r.first + r.count, tile);
     TileCtx c;
     c.d = v.descs[t];
-    c.p = v.ptrs[t];
+    c.p = call_ptrs(v, r, t);
     uint32_t local = tile - (KIND == TILES_EW ? c.d.ew_tile_begin : KIND == TILES_DECODE ? c.d.dec_tile_begin : c.d.tile_begin);
     c.rows = KIND == TILES_EW ? 1 : KIND == TILES_DECODE ? c.d.dec_rows : c.d.rb_rows;
     c.flat = SHAPE != 2 ? SHAPE == 1 : KIND == TILES_EW ? c.d.ew_flat != 0 : c.d.dec_flat != 0;
@@ -104,8 +104,8 @@ __device__ __forceinline__ TileCtx locate_tile_of(const BatchView &v, const Laun
     return c;
 }
 
-template <bool EW>
-__device__ __forceinline__ TileCtx locate_tile(const BatchView &v, const LaunchRange &r)
+template <bool EW, class R>
+__device__ __forceinline__ TileCtx locate_tile(const BatchView &v, const R &r)
 {
     return locate_tile_of<EW ? TILES_EW : TILES_REDUCE, EW ? 2 : 0>(v, r);
 }
@@ -133,8 +133,8 @@ __device__ __forceinline__ void warmup_tile(const TileCtx &c)
     }
 }
 
-template <int ET, int DTS>
-__global__ __launch_bounds__(kTileThreads) void k_warmup(BatchView v, LaunchRange r)
+template <int ET, int DTS, class R>
+__global__ __launch_bounds__(kTileThreads) void k_warmup(BatchView v, R r)
 {
     TileCtx c = locate_tile<true>(v, r);
     if (is_bf16<DTS>(c.d)) warmup_tile<BF16, ET>(c); else warmup_tile<F32, ET>(c);
@@ -537,8 +537,8 @@ __device__ __forceinline__ void encode_dispatch(const TileCtx &c, float *patch)
     else encode_tile<DT, 4, 0, EF, ET, FUSED>(c, patch);
 }
 
-template <int EF, int ET, bool FUSED, int DTS>
-__global__ __launch_bounds__(kTileThreads) void k_encode(BatchView v, LaunchRange r)
+template <int EF, int ET, bool FUSED, int DTS, class R>
+__global__ __launch_bounds__(kTileThreads) void k_encode(BatchView v, R r)
 {
     __shared__ __attribute__((aligned(16))) float patches[kTileThreads / 64][512];      // 2 KB per wave: an fp32 error row's way to whole lines
     TileCtx c = locate_tile<true>(v, r);
@@ -552,8 +552,8 @@ __global__ __launch_bounds__(kTileThreads) void k_encode(BatchView v, LaunchRang
 // The sparsifier's tensors, over the same tiles; PAIR: those with 16-channel blocks, else those with 8-channel
 // blocks.  Kernels of their own: the selection over 16-channel blocks needs half as many registers again as the
 // quantisers, and in one kernel every tensor would pay for that in occupancy.
-template <int EF, int ET, bool FUSED, bool PAIR, int DTS>
-__global__ __launch_bounds__(kTileThreads) void k_encode_nm(BatchView v, LaunchRange r)
+template <int EF, int ET, bool FUSED, bool PAIR, int DTS, class R>
+__global__ __launch_bounds__(kTileThreads) void k_encode_nm(BatchView v, R r)
 {
     __shared__ __attribute__((aligned(16))) float patches[kTileThreads / 64][512];
     TileCtx c = locate_tile<true>(v, r);
@@ -823,8 +823,8 @@ template <int DT, bool FLAT> __device__ __forceinline__ void decode_dispatch(con
 }
 
 // FLAT: the tensors with flat tiles, else those with row tiles; kernels of their own so that neither pays for the other.
-template <int DTS, bool FLAT>
-__global__ __launch_bounds__(kTileThreads) void k_decode(BatchView v, LaunchRange r)
+template <int DTS, bool FLAT, class R>
+__global__ __launch_bounds__(kTileThreads) void k_decode(BatchView v, R r)
 {
     TileCtx c = locate_tile_of<TILES_DECODE, FLAT ? 1 : 0>(v, r);
     if (c.d.scale == LOWRANK || (r.dec_kinds == 3 && (c.d.dec_flat != 0) != FLAT)) return;
@@ -935,13 +935,15 @@ constexpr unsigned kCapLdsBytes = 13312;
         }                                                                                               \
     } while (0)
 
-hipError_t launch_warmup(const BatchView &v, const LaunchRange &r, int err_dtype, hipStream_t s)
+hipError_t launch_warmup(const BatchView &v, const LaunchRange &range, int err_dtype, hipStream_t s)
 {
-    dim3 grid(r.ew_hi - r.ew_lo), block(kTileThreads);
+    dim3 grid(range.ew_hi - range.ew_lo), block(kTileThreads);
     if (grid.x == 0) return hipSuccess;
     const unsigned pad_lds = 0;
-    if (err_dtype == BF16) CF_LAUNCH_DTS(k_warmup, BF16);
-    else CF_LAUNCH_DTS(k_warmup, F32);
+    with_range(range, [&](const auto &r) {
+        if (err_dtype == BF16) CF_LAUNCH_DTS(k_warmup, BF16);
+        else CF_LAUNCH_DTS(k_warmup, F32);
+    });
     return hipGetLastError();
 }
 
@@ -969,46 +971,52 @@ hipError_t launch_finalize_rank1(const BatchView &v, const LaunchRange &r, hipSt
     return hipGetLastError();
 }
 
-hipError_t launch_encode(const BatchView &v, const LaunchRange &r, int ef, int err_dtype, bool fused, hipStream_t s)
+hipError_t launch_encode(const BatchView &v, const LaunchRange &range, int ef, int err_dtype, bool fused, hipStream_t s)
 {
-    dim3 grid(r.ew_hi - r.ew_lo), block(kTileThreads);
+    dim3 grid(range.ew_hi - range.ew_lo), block(kTileThreads);
     if (grid.x == 0) return hipSuccess;
     const unsigned pad_lds = kCapLdsBytes - (unsigned)sizeof(float) * 512 * (kTileThreads / 64);       // the kernel's own patches count
-    if (fused) CF_LAUNCH_EF_ET(k_encode, , true);
-    else CF_LAUNCH_EF_ET(k_encode, , false);
+    with_range(range, [&](const auto &r) {
+        if (fused) CF_LAUNCH_EF_ET(k_encode, , true);
+        else CF_LAUNCH_EF_ET(k_encode, , false);
+    });
     return hipGetLastError();
 }
 
-hipError_t launch_encode_nm(const BatchView &v, const LaunchRange &r, int ef, int err_dtype, bool fused, bool pair, hipStream_t s)
+hipError_t launch_encode_nm(const BatchView &v, const LaunchRange &range, int ef, int err_dtype, bool fused, bool pair, hipStream_t s)
 {
-    dim3 grid(r.ew_hi - r.ew_lo), block(kTileThreads);
+    dim3 grid(range.ew_hi - range.ew_lo), block(kTileThreads);
     if (grid.x == 0) return hipSuccess;
     const unsigned pad_lds = kCapLdsBytes - (unsigned)sizeof(float) * 512 * (kTileThreads / 64);
-    if (pair) {
-        if (fused) CF_LAUNCH_EF_ET(k_encode_nm, , true, true);
-        else CF_LAUNCH_EF_ET(k_encode_nm, , false, true);
-    } else {
-        if (fused) CF_LAUNCH_EF_ET(k_encode_nm, , true, false);
-        else CF_LAUNCH_EF_ET(k_encode_nm, , false, false);
-    }
+    with_range(range, [&](const auto &r) {
+        if (pair) {
+            if (fused) CF_LAUNCH_EF_ET(k_encode_nm, , true, true);
+            else CF_LAUNCH_EF_ET(k_encode_nm, , false, true);
+        } else {
+            if (fused) CF_LAUNCH_EF_ET(k_encode_nm, , true, false);
+            else CF_LAUNCH_EF_ET(k_encode_nm, , false, false);
+        }
+    });
     return hipGetLastError();
 }
 
-hipError_t launch_decode(const BatchView &v, const LaunchRange &r, hipStream_t s)
+hipError_t launch_decode(const BatchView &v, const LaunchRange &range, hipStream_t s)
 {
-    dim3 grid(r.dec_hi - r.dec_lo), block(kTileThreads);
+    dim3 grid(range.dec_hi - range.dec_lo), block(kTileThreads);
     if (grid.x == 0) return hipSuccess;
     for (int flat = 0; flat < 2; ++flat) {
-        if (!(r.dec_kinds >> flat & 1)) continue;
-        if (flat) {
-            if (r.dts == 0) hipLaunchKernelGGL((k_decode<0, true>), grid, block, kCapLdsBytes, s, v, r);
-            else if (r.dts == 1) hipLaunchKernelGGL((k_decode<1, true>), grid, block, kCapLdsBytes, s, v, r);
-            else hipLaunchKernelGGL((k_decode<2, true>), grid, block, kCapLdsBytes, s, v, r);
-        } else {
-            if (r.dts == 0) hipLaunchKernelGGL((k_decode<0, false>), grid, block, kCapLdsBytes, s, v, r);
-            else if (r.dts == 1) hipLaunchKernelGGL((k_decode<1, false>), grid, block, kCapLdsBytes, s, v, r);
-            else hipLaunchKernelGGL((k_decode<2, false>), grid, block, kCapLdsBytes, s, v, r);
-        }
+        if (!(range.dec_kinds >> flat & 1)) continue;
+        with_range(range, [&](const auto &r) {
+            if (flat) {
+                if (r.dts == 0) hipLaunchKernelGGL((k_decode<0, true>), grid, block, kCapLdsBytes, s, v, r);
+                else if (r.dts == 1) hipLaunchKernelGGL((k_decode<1, true>), grid, block, kCapLdsBytes, s, v, r);
+                else hipLaunchKernelGGL((k_decode<2, true>), grid, block, kCapLdsBytes, s, v, r);
+            } else {
+                if (r.dts == 0) hipLaunchKernelGGL((k_decode<0, false>), grid, block, kCapLdsBytes, s, v, r);
+                else if (r.dts == 1) hipLaunchKernelGGL((k_decode<1, false>), grid, block, kCapLdsBytes, s, v, r);
+                else hipLaunchKernelGGL((k_decode<2, false>), grid, block, kCapLdsBytes, s, v, r);
+            }
+        });
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

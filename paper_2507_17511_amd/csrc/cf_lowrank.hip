@@ -1121,14 +1121,14 @@ __device__ __forceinline__ void lr_apply_body(const TensorDev &d, const TensorPt
 }
 
 // KIND: tensors whose factors travel as bf16, or the others (fp32 and 4-bit factors).
-template <int ET, bool SENDER, bool UPDATE, bool BFW>
-__global__ __launch_bounds__(256, BFW ? 3 : 2) void k_lr_apply(BatchView v, LaunchRange r)
+template <int ET, bool SENDER, bool UPDATE, bool BFW, class R>
+__global__ __launch_bounds__(256, BFW ? 3 : 2) void k_lr_apply(BatchView v, R r)
 {
     __shared__ __attribute__((aligned(16))) float patches[4][32 * kApplyPitch];
     const int t = r.first + (int)blockIdx.y;
     const TensorDev d = v.descs[t];
     if (d.scale != LOWRANK || (d.dtype == BF16 && !factors_int4(d)) != BFW) return;
-    const TensorPtrs p = v.ptrs[t];
+    const TensorPtrs p = call_ptrs(v, r, t);
     float *patch = patches[(int)threadIdx.x >> 6];
     if constexpr (BFW) lr_apply_body<BF16, ET, SENDER, UPDATE, true>(d, p, patch);
     else if (d.dtype == BF16) lr_apply_body<BF16, ET, SENDER, UPDATE, false>(d, p, patch);
@@ -1216,12 +1216,12 @@ hipError_t launch_lr_encode(const BatchView &v, const LaunchRange &r, int err_dt
     return hipGetLastError();
 }
 
-hipError_t launch_lr_decode(const BatchView &v, const LaunchRange &r, hipStream_t s)
+hipError_t launch_lr_decode(const BatchView &v, const LaunchRange &range, hipStream_t s)
 {
-    if (r.count == 0 || r.lr_max_tokens == 0) return hipSuccess;
+    if (range.count == 0 || range.lr_max_tokens == 0) return hipSuccess;
     const dim3 block(256);
     const unsigned cap = 0;
-    CF_LAUNCH_APPLY(F32, false, true);
+    with_range(range, [&](const auto &r) { CF_LAUNCH_APPLY(F32, false, true); });
 #undef CF_LAUNCH_APPLY
     return hipGetLastError();
 }
