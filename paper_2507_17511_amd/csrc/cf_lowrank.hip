@@ -109,11 +109,15 @@ __device__ __forceinline__ void quantise_factor_row(const float (&f)[kRank], uin
 // ---------------------------------------------------------------- fp32 operands on the bf16 matrix cores
 
 // An fp32 value is exactly the sum of three bf16 ones: high, its upper 16 bits, mid, those of what that leaves, and low, the
-// rest (8 significant bits each).  A product of two values is then six products of pieces; the three left out are below 2^-21
-// of it, 2^-24 on average.  The matrix cores form products of bf16 exactly and add 16 or 32 of them up in fp32 where the fp32
-// instructions round every 2 or 4, in 6/16 of their time.  Error against fp64 of products of random operands, K = 64 / 512 /
-// 3072: residuals of bf16 tensors, fp32 instructions 1.5e-7 / 3.9e-7 / 9.6e-7, as in project 3.0e-8 / 8.3e-8 / 2.0e-7, as in
-// backproject 5.8e-8 / 1.3e-7 / 3.2e-7; general fp32 operands 1.4e-7 / 4.1e-7 / 1.0e-6, 7.7e-8 / 1.5e-7 / 3.6e-7, 1.1e-7 / 2.4e-7 / 5.7e-7.
+// rest (8 significant bits each).  A product of two values is then nine products of pieces, that of the two low ones below 2^-30 of it
+// and left out in project; backproject takes six, and the three left out are below 2^-21.  The matrix cores form products of bf16 exactly
+// and add 16 or 32 of them up where the fp32 instructions round every 2 or 4, in 8/16 or 6/16 of their time.
+// Error of U against fp64, fp32 storage, rms (largest) x 2^-24, fp32 instructions / as in project, C = 64, 512, 3072:
+//   random operands, of the sum of the terms' sizes   0.50 (4.2), 0.75 (4.7), 1.40 (12.4) / 0.18 (1.4), 0.11 (0.7), 0.09 (0.6)
+//   positive products, of the sum                      1.9 (5.3), 5.9 (15), 14.4 (45) / 0.5 (1.0), 0.6 (1.7), 0.6 (1.5)
+//   one product a sum, of the product                  0.43 (0.98), 0.42 (0.98), 0.42 (0.99) / the same (with six of nine 1.02 (5.9), 1.08 (5.0), 1.08 (5.7))
+//   one product of size 1, others of 1e-4              2.5 (14), 6.2 (31), 16 (87) / 1.3 (5.4), 1.4 (6.0), 1.7 (7.3)
+//   one product of size 1, others of 1e-8              1.3 (9.3), 2.2 (17), 2.6 (20) / 1.0 (5.5), 1.1 (5.3), 1.2 (5.6)
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 __device__ __forceinline__ f32x16 mfma32_bf16(u32x4 a, u32x4 b, f32x16 c)
@@ -186,9 +190,10 @@ __device__ __forceinline__ uint8_t *lr_q(const BatchView &v, const TensorDev &d,
 // The channels are cut into lowrank_project_parts = 4, 2 or 1 shares, 64-channel stages dealt in turn, and P is the sum of the
 // shares' chains.  A wave takes a share of TB blocks of 32 tokens, one block after the other within a stage, and the waves of
 // the same tokens add up in LDS; the bits do not depend on TB.
-// What rounds in a stage of 64 channels: the products of the leading pieces in the wave's accumulator, the small ones in one of
-// their own, added once: the matrix cores cut off what lies below the last bits of the sum they add to, and small products
-// of one sign would lose to that (sums of 3072 positive products: 6.1e-6 in one accumulator, 2.8e-7 in two, fp32 7.5e-7).
+// What rounds in a stage of 64 channels: the products of the leading pieces, exact each, in one accumulator that starts from
+// zero, the small ones in another; then one addition of the two and one to the wave's sum, as the vector units round it.
+// The matrix cores cut off what lies below the last bits of the largest product of eight and round once per instruction, so small
+// products in the sum's own accumulator would cost it a rounding each (sums of 3072 positive products: 6.1e-6).
 constexpr int kProjThreads = 256;
 constexpr int kProjChannels = 64;
 constexpr int kProjPitch = kProjChannels + 4;               // floats per token row of the patch
@@ -240,20 +245,31 @@ template <int DT> struct ProjStage {
     }
 };
 
-// acc + small += (16 channels of the wave's 32 tokens) * Q, u: which 16 of the patch's 64; q: the lane's pieces of Q
-__device__ __forceinline__ void project16(const float *patch, int u, const u32x4 (&q)[3], f32x16 &acc, f32x16 &small)
+// lead + small += (16 channels of the wave's 32 tokens) * Q, u: which 16 of the patch's 64; q: the lane's pieces of Q
+__device__ __forceinline__ void project16(const float *patch, int u, const u32x4 (&q)[3], f32x16 &lead, f32x16 &small)
 {
     const int lane = (int)threadIdx.x & 63;
     const f32x4 *src = reinterpret_cast<const f32x4 *>(patch + (lane & 31) * kProjPitch + 16 * u + 8 * (lane >> 5));
     const f32x4 w0 = src[0], w1 = src[1];
     const float z[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
     const Split8 a = split8(z);
-    acc = mfma32_bf16(a.high, q[0], acc);
+    lead = mfma32_bf16(a.high, q[0], lead);
+    small = mfma32_bf16(a.low, q[1], small);
+    small = mfma32_bf16(a.mid, q[2], small);
     small = mfma32_bf16(a.low, q[0], small);
     small = mfma32_bf16(a.high, q[2], small);
     small = mfma32_bf16(a.mid, q[1], small);
     small = mfma32_bf16(a.mid, q[0], small);
     small = mfma32_bf16(a.high, q[1], small);
+}
+
+// acc += the products of a stage's first U * 16 channels
+template <int U> __device__ __forceinline__ void project_stage(const float *patch, const u32x4 (&q)[4][3], f32x16 &acc)
+{
+    f32x16 lead = {}, small = {};
+#pragma unroll
+    for (int u = 0; u < U; ++u) project16(patch, u, q[u], lead, small);
+    acc += lead + small;
 }
 
 // 4 columns of a finished row.  Written bytes cost a stream of reads dearly, 1.7 us per MB: the last projection leaves U
@@ -316,11 +332,8 @@ __device__ __forceinline__ void lr_project_body(const BatchView &v, const Tensor
                 else if (stage + parts < stages) raw.fetch(d, p, row_base, stage + parts);
                 __builtin_amdgcn_sched_barrier(0);
                 wave_lds_fence();
-                f32x16 small = {};
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    if (2 * stage + (u >> 1) < steps) project16(patch, u, q[u], acc[b], small);         // uniform over the wave
-                acc[b] += small;
+                if (2 * stage + 1 < steps) project_stage<4>(patch, q, acc[b]);         // uniform over the wave
+                else project_stage<2>(patch, q, acc[b]);
                 __builtin_amdgcn_sched_barrier(0);
                 wave_lds_fence();
             }
@@ -345,7 +358,7 @@ __device__ __forceinline__ void lr_project_body(const BatchView &v, const Tensor
 // min_iters: tensors that asked for fewer subspace iterations than this sit the launch out.
 // A kernel per storage type: fp32 operands take twice the registers, and bf16 tensors would pay for them in occupancy.
 template <int DT, int TB>
-__global__ __launch_bounds__(kProjThreads, TB == 1 ? 3 : 2) void k_lr_project(BatchView v, LaunchRange r, int wire, int min_iters)
+__global__ __launch_bounds__(kProjThreads, TB == 1 && DT == BF16 ? 3 : 2) void k_lr_project(BatchView v, LaunchRange r, int wire, int min_iters)
 {
     __shared__ __attribute__((aligned(16))) ProjPatches patches;
     const int t = r.first + (int)blockIdx.y;

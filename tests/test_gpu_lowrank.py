@@ -620,3 +620,35 @@ def test_lowrank_leaning_columns_on_every_wire(c):
     assert np.count_nonzero(np.abs(V["f32"]).sum(axis=0)) >= 12
     assert np.all(np.abs(V["bf16"] - V["f32"]) <= 2.0 ** -8 * np.abs(V["f32"]) * 1.001)
     assert np.all(np.abs(V["int4"] - V["f32"]) <= 0.5 * step * 1.001 + 1e-30)
+
+
+def one_channel_a_token(n, c, seed):
+    """A residual with one value in every row, in [1, 2): half of them random, half 1 + 2^-7 - 2^-23, whose bits below the upper 16 are all ones."""
+    rng = np.random.default_rng(seed)
+    A = np.zeros((n, c), dtype=np.float32)
+    value = np.where(rng.random(n) < 0.5, 1.0 + rng.random(n), 1.0 + 2.0 ** -7 - 2.0 ** -23)
+    A[np.arange(n), rng.integers(0, c, n)] = value.astype(np.float32)
+    return A
+
+
+@pytest.mark.parametrize("c", [64, 96, 288, 3072])
+def test_lowrank_projection_of_one_product(c):
+    """U = A V where a row of A has one value: every entry is one product.  That of the leading pieces is exact, the others are
+    below 2^-6 of it and rounded at most seven times (7 * 2^-30), the one left out is below 2^-30; then one rounding, 2^-24."""
+    n = 1000
+    say(f"lowrank projection of one product C={c}")
+    A = one_channel_a_token(n, c, c)
+    sess = CodecSession([cf.desc(n, c, cf.CF_F32, 1, cf.CF_LOWRANK, R)], cf.options(), device=DEV)
+    try:
+        sess.warmup([torch.zeros((n, c), device=DEV)])
+        sess.scales[0].copy_(start_matrices(c, 1, c)[0].reshape(-1))
+        sess.step_fused([torch.from_numpy(A).to(DEV)])
+        cf.cf_check_device(sess.ctx, sess.stream_handle)
+        U, V = split_wire(as_numpy(sess.codes[0]), n, c, cf.CF_F32)
+        want = A.astype(np.float64) @ V.astype(np.float64)
+        assert np.count_nonzero(want) > n * R // 2
+        worst = float((np.abs(U - want) / np.maximum(np.abs(want), 1e-30)).max())
+        say(f"   off by at most {worst * 2.0 ** 24:.2f} x 2^-24")
+        assert worst <= 1.2 * 2.0 ** -24
+    finally:
+        sess.close()
