@@ -110,14 +110,20 @@ __device__ __forceinline__ void quantise_factor_row(const float (&f)[kRank], uin
 
 // An fp32 value is exactly the sum of three bf16 ones: high, its upper 16 bits, mid, those of what that leaves, and low, the
 // rest (8 significant bits each).  A product of two values is then nine products of pieces, that of the two low ones below 2^-30 of it
-// and left out in project; backproject takes six, and the three left out are below 2^-21.  The matrix cores form products of bf16 exactly
-// and add 16 or 32 of them up where the fp32 instructions round every 2 or 4, in 8/16 or 6/16 of their time.
-// Error of U against fp64, fp32 storage, rms (largest) x 2^-24, fp32 instructions / as in project, C = 64, 512, 3072:
+// and left out.  The matrix cores form products of bf16 exactly and add 16 or 32 of them up where the fp32 instructions round every 2
+// or 4, in 8/16 or 10/16 of their time.
+// Errors against fp64, fp32 storage, rms (largest) x 2^-24, fp32 instructions / pieces.  U = A V, C = 64, 512, 3072:
 //   random operands, of the sum of the terms' sizes   0.50 (4.2), 0.75 (4.7), 1.40 (12.4) / 0.18 (1.4), 0.11 (0.7), 0.09 (0.6)
 //   positive products, of the sum                      1.9 (5.3), 5.9 (15), 14.4 (45) / 0.5 (1.0), 0.6 (1.7), 0.6 (1.5)
 //   one product a sum, of the product                  0.43 (0.98), 0.42 (0.98), 0.42 (0.99) / the same (with six of nine 1.02 (5.9), 1.08 (5.0), 1.08 (5.7))
 //   one product of size 1, others of 1e-4              2.5 (14), 6.2 (31), 16 (87) / 1.3 (5.4), 1.4 (6.0), 1.7 (7.3)
 //   one product of size 1, others of 1e-8              1.3 (9.3), 2.2 (17), 2.6 (20) / 1.0 (5.5), 1.1 (5.3), 1.2 (5.6)
+// First column of V, which is that of Z to length one, C = 2048, N = 64, 4096, 20000:
+//   random operands, of the entries' rms               2.8 (11), 3.3 (23), 4.1 (40) / 1.5 (8.5), 1.6 (15), 1.8 (21)
+//   positive products, of the entry                    0.88 (3.6), 1.2 (5.3), 2.4 (9.0) / 0.77 (2.7), 0.91 (3.4), 1.4 (5.3) (six of nine in the sum's own accumulator 0.92, 1.3, 2.7)
+//   one product an entry, of the entry                 0.68 (2.4), 0.61 (1.6), 0.60 (1.5) / 0.69 (2.8), 0.61 (1.6), 0.60 (1.5) (six of nine 1.03 (5.3), 1.12 (4.7), 1.19 (5.3))
+//   one product of size 1, others of 1e-3              2.7 (13), 5.5 (20), 11 (45) / 1.5 (7.2), 2.5 (12), 4.1 (13)
+// The one kind found where fp32 was closer: [20000, 128], others of 1e-6, P of four products a row, 0.86 (2.7) / 0.95 (3.4).
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 __device__ __forceinline__ f32x16 mfma32_bf16(u32x4 a, u32x4 b, f32x16 c)
@@ -391,12 +397,14 @@ __device__ __forceinline__ uint8_t *lr_slice(const BatchView &v, const LaunchRan
 // of them, and the orthogonalisation adds the shares.
 // v_mfma_f32_16x16x32_bf16 takes 8 entries of row l % 16 of A and of column l % 16 of B from lane l, for k = 8 (l / 16) ...:
 // lane (q, g) holds channels 8q..8q+7 of its wave's 128 of 4 tokens, straight from 128-bit loads, and makes of channel j of these
-// tokens the row of channel tile j (tile j holds channels = j mod 8): two pieces of 4 values each, against the pieces of 4 rows
-// of P.  (high, mid) (high, high) + (high, mid) (mid, mid) + (high, low) (low, high) are the six products.
-// What bounds it, 57 x [4096, 3072] bf16, 541 us (fp32 MFMA 596-620): the stream of x and recon, alone 550 in 128-channel
-// stripes and 400-430 in wider ones; two waves side by side 576 -> 541.  Neither the MFMAs nor the splitting show (without
-// either the same), nor do more batches in flight (1 / 2 / 3: 579 / 603 / 687).  The next run's first batch is asked for before
-// the waves' sums meet: 575 -> 558.
+// tokens the row of channel tile j (tile j holds channels = j mod 8): two pieces of 4 values each, against two pieces of 4 rows
+// of P, or one piece and zeros: (mid, low) (low, mid) + (mid, low) (0, high) + (high, mid) (low, mid) + (high, mid) (mid, high) are the
+// small products, (high, mid) (high, 0) the leading one.  Per batch of 16 tokens each of the two starts from zero, and the vector units
+// add them up and to the sum, as in project.  Not with the form of half the length for the lone pieces: an accumulator that went
+// from v_mfma_f32_16x16x16_bf16 to v_mfma_f32_16x16x32_bf16 within two instructions came back wrong.
+// What bounds it, 57 x [4096, 3072] bf16, in a trace 608 us on average (550-698): the stream of x and recon, alone 550 in 128-channel
+// stripes and 400-430 in wider ones.  A wave has one batch in registers; the next is asked for once the residual is formed, so that it is
+// in flight while the products are: one tensor 79 -> 56 us, 28 of fp32 570 -> 536, the 57 681 -> 608 (asked for after the products).
 constexpr int kBackThreads = 256;
 constexpr int kBackChannels = kLowRankBackChannels;
 constexpr int kBackEntries = kBackChannels * kRank;
@@ -451,33 +459,40 @@ __device__ __forceinline__ void lr_backproject_body(const BatchView &v, const La
             for (int64_t quad0 = lo; quad0 < hi; quad0 += 4 * turns) {
                 Batch &w = batch;
                 const int64_t quad = quad0 + g;
-                u32x4 pp[2][3];                             // (high, high), (mid, mid), (low, high)
+                u32x4 pp[2][4];                             // (low, mid), (0, high), (mid, high), (high, 0)
 #pragma unroll
                 for (int c = 0; c < 2; ++c) {
                     float pv[4];
 #pragma unroll
                     for (int t = 0; t < 4; ++t) pv[t] = quad < hi && 4 * quad + t <= last ? w.p[c][t] : 0.0f;
                     const Split4 s = split4(pv);
-                    pp[c][0] = join(s.high, s.high);
-                    pp[c][1] = join(s.mid, s.mid);
-                    pp[c][2] = join(s.low, s.high);
+                    pp[c][0] = join(s.low, s.mid);
+                    pp[c][1] = join((u32x2)(0u), s.high);
+                    pp[c][2] = join(s.mid, s.high);
+                    pp[c][3] = join(s.high, (u32x2)(0u));
                 }
+                float z[8][4];
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) z[j][t] = element(w.x[t], j) - element(w.b[t], j);
+                __builtin_amdgcn_sched_barrier(0);
+                // the next batch, or the first of the next run: in flight while this one's products are formed and the waves' sums meet
+                fetch(w, quad0 + 4 * turns < hi ? quad0 + 4 * turns : (run + 1) * per_run + 4 * turn);
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
-                    float z[4];
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) z[t] = element(w.x[t], j) - element(w.b[t], j);
-                    const Split4 s = split4(z);
-                    const u32x4 a0 = join(s.high, s.mid), a1 = join(s.high, s.low);
+                    const Split4 s = split4(z[j]);
+                    const u32x4 a0 = join(s.high, s.mid), a1 = join(s.mid, s.low);
 #pragma unroll
                     for (int c = 0; c < 2; ++c) {
-                        const f32x4 small = mfma16_bf16(a0, pp[c][1], mfma16_bf16(a1, pp[c][2], (f32x4)(0.0f)));
-                        acc[j][c] = mfma16_bf16(a0, pp[c][0], acc[j][c]) + small;
+                        f32x4 small = mfma16_bf16(a1, pp[c][0], (f32x4)(0.0f));
+                        small = mfma16_bf16(a1, pp[c][1], small);
+                        small = mfma16_bf16(a0, pp[c][0], small);
+                        small = mfma16_bf16(a0, pp[c][2], small);
+                        acc[j][c] += mfma16_bf16(a0, pp[c][3], (f32x4)(0.0f)) + small;
                     }
                 }
-                __builtin_amdgcn_sched_barrier(0);
-                // the next batch, or the first of the next run, so that it is in flight while the waves' sums meet
-                fetch(w, quad0 + 4 * turns < hi ? quad0 + 4 * turns : (run + 1) * per_run + 4 * turn);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }

@@ -652,3 +652,31 @@ def test_lowrank_projection_of_one_product(c):
         assert worst <= 1.2 * 2.0 ** -24
     finally:
         sess.close()
+
+
+@pytest.mark.parametrize("n, c", [(203, 128), (2100, 512), (2049, 2048)])
+def test_lowrank_backprojection_of_one_product(n, c):
+    """A has one value a_c per channel, each in a token of its own, and Q0's columns are orthonormal with powers of two on
+    disjoint channels, so that P is exact and every entry of Z is one product a_c * (a_c 2^-k).  It is off by 1.2 x 2^-24 at most (see
+    the projection's test), the column's length, which divides it, by no more, and V is rounded once: 3.4 x 2^-24."""
+    say(f"lowrank back-projection of one product [{n}, {c}]")
+    value = one_channel_a_token(c, c, n).sum(axis=1)
+    A = np.zeros((n, c), dtype=np.float32)
+    A[np.random.default_rng(n).permutation(n)[:c], np.arange(c)] = value
+    q0 = np.zeros((c, R), dtype=np.float32)
+    q0[np.arange(c), np.arange(c) % R] = (R / c) ** 0.5
+    sess = CodecSession([cf.desc(n, c, cf.CF_F32, 1, cf.CF_LOWRANK, R)], cf.options(), device=DEV)
+    try:
+        sess.warmup([torch.zeros((n, c), device=DEV)])
+        sess.scales[0].copy_(torch.from_numpy(q0.reshape(-1)).to(DEV))
+        sess.step_fused([torch.from_numpy(A).to(DEV)])
+        cf.cf_check_device(sess.ctx, sess.stream_handle)
+        V = split_wire(as_numpy(sess.codes[0]), n, c, cf.CF_F32)[1].astype(np.float64)
+        Z = (A.astype(np.float64).T @ (A.astype(np.float64) @ q0.astype(np.float64)))
+        want = Z / np.linalg.norm(Z, axis=0)
+        assert np.array_equal(V != 0, want != 0)
+        worst = float((np.abs(V - want) / np.maximum(np.abs(want), 1e-30)).max())
+        say(f"   off by at most {worst * 2.0 ** 24:.2f} x 2^-24")
+        assert worst <= 3.4 * 2.0 ** -24
+    finally:
+        sess.close()
