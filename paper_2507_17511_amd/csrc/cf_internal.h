@@ -207,6 +207,27 @@ constexpr int lowrank_runs(int64_t n_tokens, int64_t n_channels)
 // Runs of channels that P = A Q is the sum of, 64 channels or more each.
 constexpr int lowrank_project_parts(int64_t n_channels) { return n_channels > 128 ? 4 : n_channels > 64 ? 2 : 1; }
 constexpr int lowrank_project_tokens(int64_t n_channels) { return 128 / lowrank_project_parts(n_channels); }        // of a workgroup, a block of 32 per wave
+// k_lr_apply: a wave owns 32 tokens and one or two tiles of 64 channels, two where widening the factors costs more than the products.  The
+// waves are counted through the rows of a tensor and on into the next 32 tokens, whatever workgroup they fall into, so that no width
+// leaves waves without tiles; of eight tiles in a row, wave k of four has tiles k and k + 4, so that the four lie side by side.
+constexpr int kLowRankApplyChannels = 64;
+constexpr int kLowRankApplyTokens = 32;
+struct ApplyTiles {
+    int first, step, end;       // tiles first, first + step ... below end; no more than the wave's one or two
+};
+constexpr int lowrank_apply_waves(int n_channels, int tiles_per_wave)       // of 32 tokens
+{
+    const int tiles = (n_channels + kLowRankApplyChannels - 1) / kLowRankApplyChannels;
+    return tiles_per_wave == 1 ? tiles : tiles / 8 * 4 + (tiles % 8 + 1) / 2;
+}
+constexpr ApplyTiles lowrank_apply_tiles(int n_channels, int tiles_per_wave, int wave)
+{
+    const int tiles = (n_channels + kLowRankApplyChannels - 1) / kLowRankApplyChannels;
+    if (tiles_per_wave == 1) return {wave, 1, wave + 1};
+    const int whole = tiles / 8 * 4, half = (tiles % 8 + 1) / 2;
+    if (wave < whole) return {wave / 4 * 8 + wave % 4, 4, wave / 4 * 8 + 8};
+    return {2 * whole + wave - whole, half, tiles};
+}
 // min_iters: only tensors whose descriptor asks for at least that many subspace iterations take part
 hipError_t launch_lr_orth(const BatchView &v, const LaunchRange &r, bool from_q0, int min_iters, hipStream_t s);
 hipError_t launch_lr_project(const BatchView &v, const LaunchRange &r, bool wire, int min_iters, hipStream_t s);

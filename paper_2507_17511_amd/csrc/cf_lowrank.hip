@@ -1032,7 +1032,7 @@ template <> struct Factors<BF16, true> {
     }
 };
 
-// A wave owns 32 tokens x 64 channels, the waves of a workgroup lie side by side.  The MFMA leaves lane (n, h) with
+// A wave owns 32 tokens x 64 channels, or two such tiles; the waves of a workgroup lie side by side.  The MFMA leaves lane (n, h) with
 // channel n of 16 tokens, which is the wrong way round for row-major memory, so the tile of D goes
 // through the wave's own LDS patch [32 tokens][64 channels] and comes back as 8 consecutive channels
 // of one token per lane: 8 lanes then cover 128 bytes of a bf16 row (256 of the fp32 error row).
@@ -1040,23 +1040,26 @@ template <> struct Factors<BF16, true> {
 // What bounds it is HBM, and how well depends on how much of a row a workgroup has open and how many do: 57 x [4096, 3072],
 // waves below one another, 128 channels wide, fp32 MFMA, two workgroups per CU 1322 us; bf16 MFMA, four of them per CU 1410, two 1358;
 // waves side by side, 256 channels, three per CU 1245, two 1196 (512 channels 1254 / 1199).
-constexpr int kApplyChannels = 64;
-constexpr int kApplyTokens = 32;
-// Channels per workgroup.  4-bit factors cost a wave more to widen than the products: it makes two tiles of its rows of U.
-constexpr int apply_span(bool bf16_wire) { return (bf16_wire ? 4 : 8) * kApplyChannels; }
+// Waves that lie side by side in workgroups of their own per 32 tokens idle where a row's tiles are no multiple of theirs.  Receivers, us,
+// waves below one another, 128 channels wide / side by side, 256 or 512 channels / counted through: 60 x [8000, 32] bf16 28 / 41 / 19, 4-bit 27 / 54 / 24,
+// [8000, 64] fp32 56 / 69 / 56, 30 x [4000, 544] fp32 137 / 193 / 133, bf16 79 / 60 / 57, 4-bit 76 / 110 / 72; 57 x [4096, 3072] bf16 731 / 504 / 504.
+constexpr int kApplyChannels = kLowRankApplyChannels;
+constexpr int kApplyTokens = kLowRankApplyTokens;
+// 4-bit factors cost a wave more to widen than the products: it makes two tiles of its rows of U.
+constexpr int apply_tiles_per_wave(bool bf16_wire) { return bf16_wire ? 1 : 2; }
 constexpr int kApplyPitch = kApplyChannels + 4;             // floats per token row of the patch
 constexpr unsigned kApplyCapLds = 40000;                    // dynamic LDS that nobody touches: two workgroups per CU of senders (the receiver 512 us, 573 capped)
 
 template <int DT, int ET, bool SENDER, bool UPDATE, bool BFW>
 __device__ __forceinline__ void lr_apply_body(const TensorDev &d, const TensorPtrs &p, float *patch)
 {
-    const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
+    const int lane = (int)threadIdx.x & 63;
     const int n = lane & 31, h = lane >> 5;
-    constexpr int kSpan = apply_span(BFW);
-    const int n_spans = (d.n_channels + kSpan - 1) / kSpan;
-    const int span = (int)(blockIdx.x % (unsigned)n_spans);
-    const int64_t tok_base = (int64_t)(blockIdx.x / (unsigned)n_spans) * kApplyTokens;
-    if (tok_base >= d.n_tokens) return;                     // uniform over the workgroup
+    const uint32_t item = blockIdx.x * 4u + (uint32_t)__builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const uint32_t row_waves = (uint32_t)lowrank_apply_waves(d.n_channels, apply_tiles_per_wave(BFW));
+    const int64_t tok_base = (int64_t)(item / row_waves) * kApplyTokens;
+    if (tok_base >= d.n_tokens) return;                     // uniform over the wave
+    const ApplyTiles tiles = lowrank_apply_tiles(d.n_channels, apply_tiles_per_wave(BFW), (int)(item % row_waves));
     const int64_t C = d.n_channels;
     const bool int4 = factors_int4(d);
     Factors<DT, BFW> u;
@@ -1066,9 +1069,8 @@ __device__ __forceinline__ void lr_apply_body(const TensorDev &d, const TensorPt
     const int chunk = lane & 7, trow = lane >> 3;           // row-major side: 8 chunks of 8 channels, 8 tokens per sweep
     const int n_sub = d.n_channels / 32;
 #pragma unroll 1
-    for (int tile = 0; tile < kSpan / (4 * kApplyChannels); ++tile) {
-        const int sub0 = span * (kSpan / 32) + 8 * tile + 2 * wave;
-        if (sub0 >= n_sub) break;                           // uniform over the wave
+    for (int tile = tiles.first; tile < tiles.end; tile += tiles.step) {
+        const int sub0 = 2 * tile;
         const int cnt = n_sub - sub0 < 2 ? 1 : 2;
         // Issue order matters because loads return in order: first the V rows the MFMAs need, then the
         // tile's x and recon, which are only needed once D has come back through the patch.
@@ -1208,12 +1210,11 @@ hipError_t launch_lr_backproject(const BatchView &v, const LaunchRange &r, int m
     return hipGetLastError();
 }
 
-// Blocks of kApplyTokens x apply_span channels, for the largest low-rank tensor of the range; a tensor with
-// fewer channel spans sees block indices beyond its own and returns at once (tok_base >= n_tokens).
+// Workgroups of four waves for the largest low-rank tensor of the range; waves beyond a smaller one's last tokens return at once.
 static dim3 apply_grid(const LaunchRange &r, bool bf16_wire)
 {
-    const int span = apply_span(bf16_wire);
-    return dim3((unsigned)((r.lr_max_tokens + kApplyTokens - 1) / kApplyTokens) * (unsigned)((r.lr_max_channels + span - 1) / span), (unsigned)r.count);
+    const int64_t waves = (r.lr_max_tokens + kApplyTokens - 1) / kApplyTokens * lowrank_apply_waves(r.lr_max_channels, apply_tiles_per_wave(bf16_wire));
+    return dim3((unsigned)((waves + 3) / 4), (unsigned)r.count);
 }
 
 hipError_t launch_lr_quant_u(const BatchView &v, const LaunchRange &r, hipStream_t s)

@@ -7,6 +7,7 @@
 #include <string>
 #include <vector>
 
+#include "cf_internal.h"
 #include "compactfusion.h"
 
 extern std::vector<std::string> g_launch_log;
@@ -272,6 +273,22 @@ int main()
             std::free(ws);
         }
     }
+
+    // ---- the low-rank apply kernel's tiles: each of a row to one wave, and at most one wave short of a tile
+    for (int channels = 32; channels <= cf::kLowRankMaxChannels; channels += 32)
+        for (int per_wave = 1; per_wave <= 2; ++per_wave) {
+            const int n_tiles = (channels + 63) / 64, waves = cf::lowrank_apply_waves(channels, per_wave);
+            std::vector<int> owners((size_t)n_tiles, 0);
+            for (int w = 0; w < waves; ++w) {
+                const cf::ApplyTiles a = cf::lowrank_apply_tiles(channels, per_wave, w);
+                int mine = 0;
+                EXPECT(a.first >= 0 && a.step >= 1 && a.end <= n_tiles);
+                for (int t = a.first; t < a.end; t += a.step, ++mine) ++owners[(size_t)t];
+                EXPECT(mine >= 1 && mine <= per_wave);
+            }
+            for (int o : owners) EXPECT(o == 1);
+            EXPECT(waves * per_wave <= n_tiles + 1);
+        }
 
     // ---- the entry point that brings no workspace
     {
