@@ -165,10 +165,7 @@ struct DirectRange : LaunchRange {
 };
 
 // f(range) with the kind of range the call's kernels take
-template <class F> void with_range(const LaunchRange &r, F &&f)
-{
-    if (r.direct) f(DirectRange(r)); else f(r);
-}
+template <class F> auto with_range(const LaunchRange &r, F &&f) { return r.direct ? f(DirectRange(r)) : f(r); }
 
 enum class Op { Compress, StepFused };
 

@@ -1150,7 +1150,7 @@ __device__ __forceinline__ void lr_apply_body(const TensorDev &d, const TensorPt
     }
 }
 
-// KIND: tensors whose factors travel as bf16, or the others (fp32 and 4-bit factors).
+// BFW: tensors whose factors travel as bf16, else the others (fp32 and 4-bit factors).
 template <int ET, bool SENDER, bool UPDATE, bool BFW, class R>
 __global__ __launch_bounds__(256, BFW ? 3 : 2) void k_lr_apply(BatchView v, R r)
 {
@@ -1225,34 +1225,30 @@ hipError_t launch_lr_quant_u(const BatchView &v, const LaunchRange &r, hipStream
     return hipGetLastError();
 }
 
+// one launch per kind of factors in the range
+template <int ET, bool SENDER, bool UPDATE, class R>
+static hipError_t launch_apply(const BatchView &v, const R &r, hipStream_t s)
+{
+    if (r.lr_wires & 1) {
+        hipLaunchKernelGGL((k_lr_apply<ET, SENDER, UPDATE, true, R>), apply_grid(r, true), dim3(256), SENDER ? kApplyCapLds : 0u, s, v, r);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    if (r.lr_wires & 2) hipLaunchKernelGGL((k_lr_apply<ET, SENDER, UPDATE, false, R>), apply_grid(r, false), dim3(256), 0, s, v, r);
+    return hipGetLastError();
+}
+
 hipError_t launch_lr_encode(const BatchView &v, const LaunchRange &r, int err_dtype, bool fused, hipStream_t s)
 {
     if (r.count == 0 || r.lr_max_tokens == 0) return hipSuccess;
-    const dim3 block(256);
-    const unsigned cap = kApplyCapLds;
-#define CF_LAUNCH_APPLY(...)                                                                                              \
-    do {                                                                                                                  \
-        if (r.lr_wires & 1) hipLaunchKernelGGL((k_lr_apply<__VA_ARGS__, true>), apply_grid(r, true), block, cap, s, v, r);                 \
-        if (r.lr_wires & 2) hipLaunchKernelGGL((k_lr_apply<__VA_ARGS__, false>), apply_grid(r, false), block, 0, s, v, r); \
-    } while (0)
-    if (err_dtype == BF16) {
-        if (fused) CF_LAUNCH_APPLY(BF16, true, true);
-        else CF_LAUNCH_APPLY(BF16, true, false);
-    } else {
-        if (fused) CF_LAUNCH_APPLY(F32, true, true);
-        else CF_LAUNCH_APPLY(F32, true, false);
-    }
-    return hipGetLastError();
+    if (err_dtype == BF16) return fused ? launch_apply<BF16, true, true>(v, r, s) : launch_apply<BF16, true, false>(v, r, s);
+    return fused ? launch_apply<F32, true, true>(v, r, s) : launch_apply<F32, true, false>(v, r, s);
 }
 
 hipError_t launch_lr_decode(const BatchView &v, const LaunchRange &range, hipStream_t s)
 {
     if (range.count == 0 || range.lr_max_tokens == 0) return hipSuccess;
-    const dim3 block(256);
-    const unsigned cap = 0;
-    with_range(range, [&](const auto &r) { CF_LAUNCH_APPLY(F32, false, true); });
-#undef CF_LAUNCH_APPLY
-    return hipGetLastError();
+    return with_range(range, [&](const auto &r) { return launch_apply<F32, false, true>(v, r, s); });
 }
 
 }  // namespace cf

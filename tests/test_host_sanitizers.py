@@ -33,3 +33,14 @@ def test_abi_host_half_under_address_and_ub_sanitizers(tmp_path):
           os.path.join(HERE, "stubs.cpp"), os.path.join(HERE, "host_driver.cpp"), "-o", exe])
     out = _run([exe], env=ENV)
     assert "all expectations hold" in out
+
+
+def test_refused_launches_are_reported(tmp_path):
+    csrc = os.path.join(ROOT, "paper_2507_17511_amd", "csrc")
+    obj, exe = str(tmp_path / "lowrank_host.o"), str(tmp_path / "launches")
+    _run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "--offload-host-only", "-x", "hip", "-std=c++17", "-O1", "-fPIC", "-w",
+          "-I", csrc, "-c", os.path.join(csrc, "cf_lowrank.hip"), "-o", obj])
+    _run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include", "-I", csrc,
+          os.path.join(HERE, "launch_driver.cpp"), obj, "-Wl,--unresolved-symbols=ignore-all", "-o", exe])      # the device code's symbol
+    out = _run([exe], env=ENV)
+    assert "every refused launch is reported" in out
