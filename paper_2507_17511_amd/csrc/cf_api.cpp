@@ -140,13 +140,14 @@ int pick_rb_rows(const cf_tensor_desc *descs, int32_t n, const cf_options &o)
     return 8;
 }
 
-// Workgroups that share a channel stripe of the low-rank back-projection in a call over `count` tensors (the largest
+int64_t lowrank_stripes(int64_t n_channels) { return (n_channels + kLowRankBackChannels - 1) / kLowRankBackChannels; }
+
+// Workgroups that share a channel stripe of the low-rank back-projection in a call of that many stripes (the largest
 // low-rank tensor's channels and tokens given): more where the stripes alone would leave the device idle.
 // Whole steps with 1 / 2 / 4 sharing, us: [4096, 3072] 1 tensor 413 / 305 / 258, 8 (96 stripes) 600 / 492 / 492, 16 930 / 842 / 863,
 // 40 1971 / 1970 / 2009, 57 (684) 2888 / 2824 / 2855; 60 x [8000, 96] 675 / 474 / 384.  Beyond, the shares' memory is not worth it.
-int64_t lowrank_split(int64_t max_channels, int64_t max_tokens, int64_t count)
+int64_t lowrank_split(int64_t max_channels, int64_t max_tokens, int64_t stripes)
 {
-    const int64_t stripes = (max_channels + kLowRankBackChannels - 1) / kLowRankBackChannels * count;
     return std::min<int64_t>(lowrank_runs(max_tokens, max_channels), stripes <= 128 ? kLowRankMaxRuns : stripes <= 768 ? 2 : 1);
 }
 
@@ -155,19 +156,20 @@ size_t lowrank_slice_bytes_of(int64_t max_channels, int64_t split, int64_t count
     return (size_t)((split - 1) * count) * (size_t)max_channels * kLowRankRank * sizeof(float);
 }
 
-// What the shares after the first need in any call on a context of these tensors: no more than a call over as many
-// tensors of the largest size.
+// What the shares after the first need in calls over any number of these tensors, were they all of the largest size; calls over
+// narrower ones that would need more share less.
 size_t lowrank_slice_bytes(const cf_tensor_desc *descs, int32_t n)
 {
-    int64_t c = 0, tok = 0;
+    int64_t c = 0, tok = 0, lowrank = 0;
     for (int32_t t = 0; t < n; ++t)
         if (descs[t].scale == CF_LOWRANK) {
             c = std::max<int64_t>(c, descs[t].n_channels);
             tok = std::max<int64_t>(tok, descs[t].n_tokens);
+            ++lowrank;
         }
-    if (c == 0) return 0;
     size_t most = 0;
-    for (int64_t count = 1; count <= n; ++count) most = std::max(most, lowrank_slice_bytes_of(c, lowrank_split(c, tok, count), count));
+    for (int64_t count = 1; count <= lowrank; ++count)
+        most = std::max(most, lowrank_slice_bytes_of(c, lowrank_split(c, tok, lowrank_stripes(c) * count), count));
     return align_up(most);
 }
 
@@ -190,6 +192,7 @@ cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &
     L.fin_prefix.assign(n + 1, 0);
     uint64_t tiles = 0, fins = 0, items = 0;
     size_t partial_bytes = 0, p_partial_bytes = 0;
+    uint32_t lr_tensors = 0;
     L.item_prefix.assign(n + 1, 0);
     L.single_pass = (o.flags & CF_FLAG_TWO_KERNEL) == 0;
     for (int32_t t = 0; t < n; ++t)
@@ -291,6 +294,7 @@ cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &
         if (d.scale == CF_LOWRANK) {
             if (o.ef != CF_EF_RECON) return CF_ERR_UNSUPPORTED;
             L.any_lowrank = true;
+            v.lr_slot = lr_tensors++;
             v.lr_p_off = partial_bytes;
             partial_bytes += align_up((size_t)d.n_tokens * kLowRankRank * sizeof(float));
             v.lr_z_off = partial_bytes;
@@ -428,7 +432,9 @@ struct cf_ctx {
         r.lr_max_tokens = 0;
         r.lr_wires = 0;
         r.lr_project_blocks = 0;
+        r.lr_project_many = 0;
         r.lr_split = 1;
+        r.lr_first_slot = 0;
         r.lr_slices_off = L.off_lr_slices;
         r.p_partial_lo = ~(uint64_t)0;
         r.p_partial_hi = 0;
@@ -440,20 +446,25 @@ struct cf_ctx {
             if (dv.p_partial_off + bytes > r.p_partial_hi) r.p_partial_hi = dv.p_partial_off + bytes;
         }
         if (r.p_partial_hi == 0) r.p_partial_lo = 0;
+        int64_t lr_tensors = 0, lr_stripes = 0, lr_bf16_blocks = 0;
         for (int32_t t = first; t < first + count; ++t) {
             if (descs[t].dtype != descs[first].dtype) r.dts = 2;
             if (descs[t].scale != CF_LOWRANK) r.dec_kinds |= L.dev[t].dec_flat ? 2 : 1;
             if (descs[t].scale == CF_LOWRANK) {
+                if (lr_tensors++ == 0) r.lr_first_slot = L.dev[t].lr_slot;
                 if (descs[t].n_channels > r.lr_max_channels) r.lr_max_channels = (int32_t)descs[t].n_channels;
                 if (descs[t].n_tokens > r.lr_max_tokens) r.lr_max_tokens = descs[t].n_tokens;
                 r.lr_wires |= descs[t].dtype == CF_BF16 && !(opts.flags & CF_FLAG_LOWRANK_INT4) ? 1 : 2;
-                const int64_t tokens = lowrank_project_tokens(descs[t].n_channels);
-                r.lr_project_blocks = std::max<int32_t>(r.lr_project_blocks, (int32_t)((descs[t].n_tokens + tokens - 1) / tokens));
+                const int64_t tokens = lowrank_project_tokens(descs[t].n_channels), blocks = (descs[t].n_tokens + tokens - 1) / tokens;
+                r.lr_project_blocks = std::max<int32_t>(r.lr_project_blocks, (int32_t)blocks);
+                if (descs[t].dtype == CF_BF16) lr_bf16_blocks += blocks;
+                lr_stripes += lowrank_stripes(descs[t].n_channels);
             }
         }
         if (r.lr_max_channels > 0) {    // as many shares as the rule says and the workspace holds; the sums are the same either way
-            r.lr_split = (int32_t)lowrank_split(r.lr_max_channels, r.lr_max_tokens, count);
-            while (lowrank_slice_bytes_of(r.lr_max_channels, r.lr_split, count) > L.lr_slice_bytes) r.lr_split /= 2;
+            r.lr_project_many = lr_bf16_blocks >= kLowRankProjectMany;
+            r.lr_split = (int32_t)lowrank_split(r.lr_max_channels, r.lr_max_tokens, lr_stripes);
+            while (lowrank_slice_bytes_of(r.lr_max_channels, r.lr_split, lr_tensors) > L.lr_slice_bytes) r.lr_split /= 2;
         }
         return r;
     }

@@ -85,6 +85,7 @@ struct alignas(16) TensorDev {
     // rank-1 scales: per-row sums of |z| over each 1024-channel tile, rowpart[N][n_colblocks]
     uint32_t nm_block;      // N:M sparsifier: M, channels per block (8 or 16)
                             // low-rank compressor: 4 when the factors travel as 4-bit integers, else 0
+    uint32_t lr_slot;       // low-rank tensors before this one in the context
     uint64_t rowpart_off;
     // low-rank compressor: P = A Q [N][32] fp32; Z = A^T P [C][32] fp32, which Q takes the place of in the order
     // k_lr_project reads it; partial sums of Z^T Z, one [32][32] fp64 matrix per 256 channels (C > 256 only),
@@ -149,8 +150,10 @@ struct LaunchRange {
     int64_t lr_max_tokens;
     int32_t lr_wires;           // bit 0: factors that travel as bf16 in the range; bit 1: others
     int32_t lr_project_blocks;  // workgroups of k_lr_project for the tensor that needs most, one block of tokens per wave
+    int32_t lr_project_many;    // whether the bf16 tensors of the range together have enough of them for several blocks a wave
     int32_t lr_split;           // low-rank back-projection: at most so many workgroups share a channel stripe's runs of tokens (1, 2 or 4)
-    uint64_t lr_slices_off;     // workspace offset of the shares after the first, [count][lr_split - 1][lr_max_channels][32] fp32
+    uint32_t lr_first_slot;     // lr_slot of the range's first low-rank tensor
+    uint64_t lr_slices_off;     // workspace offset of the shares after the first, [low-rank tensors][lr_split - 1][lr_max_channels][32] fp32
     const TensorPtrs *direct;   // host memory: the call's pointers, kDirectTensors sets at most, for kernels to take as arguments; null: they are in the table
 };
 
@@ -204,6 +207,12 @@ constexpr int lowrank_runs(int64_t n_tokens, int64_t n_channels)
 // Runs of channels that P = A Q is the sum of, 64 channels or more each.
 constexpr int lowrank_project_parts(int64_t n_channels) { return n_channels > 128 ? 4 : n_channels > 64 ? 2 : 1; }
 constexpr int lowrank_project_tokens(int64_t n_channels) { return 128 / lowrank_project_parts(n_channels); }        // of a workgroup, a block of 32 per wave
+// Blocks of 32 tokens that a wave of k_lr_project<bf16> takes in calls whose bf16 tensors have kLowRankProjectMany workgroups' blocks and
+// more, one block after the other against the same pieces of Q, which otherwise take as much of a CU's 64 bytes per clock as the operands.
+// Steps over [4096, 3072] bf16, one block / several, us: 1 tensor 192 / 258, 4 299 / 329, 8 524 / 492, 24 1353 / 1251, 57 3041 /
+// 2824; 28 fp32 ones 2778 / 2860, which take one.
+constexpr int kLowRankProjectBlocks = 3;
+constexpr int64_t kLowRankProjectMany = 1024;
 // k_lr_apply: a wave owns 32 tokens and one or two tiles of 64 channels, two where widening the factors costs more than the products.  The
 // waves are counted through the rows of a tensor and on into the next 32 tokens, whatever workgroup they fall into, so that no width
 // leaves waves without tiles; of eight tiles in a row, wave k of four has tiles k and k + 4, so that the four lie side by side.

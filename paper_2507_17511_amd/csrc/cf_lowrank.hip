@@ -204,13 +204,9 @@ constexpr int kProjThreads = 256;
 constexpr int kProjChannels = 64;
 constexpr int kProjPitch = kProjChannels + 4;               // floats per token row of the patch
 constexpr int kProjSumPitch = kRank + 4;
-// Blocks of 32 tokens a wave takes in calls of kProjMany blocks and more (of 4 waves), one after the other against the same
-// pieces of Q, which otherwise take as much of a CU's 64 bytes per clock as the operands.  Steps over [4096, 3072] bf16, one block / several, us:
-// 1 tensor 192 / 258, 4 299 / 329, 8 524 / 492, 24 1353 / 1251, 57 3041 / 2824; 28 fp32 ones 2778 / 2860, which take one.  The
-// kernel at 57: one block 636, two 566, three 535, four 605 (11 registers spilled); fp32 MFMA 587.  408 of that is the stream
-// alone, 50 or 25 the stores of P or U.
-constexpr int kProjBlocks = 3;
-constexpr int64_t kProjMany = 1024;
+// The kernel at 57 x [4096, 3072] bf16 (six products of pieces): one block of tokens a wave 636 us, two 566, three 535, four 605 (11 registers
+// spilled); fp32 MFMA 587.  408 of that is the stream alone, 50 or 25 the stores of P or U.  With eight products 543.
+constexpr int kProjBlocks = kLowRankProjectBlocks;
 typedef float ProjPatches[kProjThreads / 64][32 * kProjPitch];
 
 // What a wave reads of a stage: 8 tokens x 128 bytes an instruction.  Loads without branches: tokens and channels outside the
@@ -384,11 +380,11 @@ __device__ __forceinline__ int lr_shares(const LaunchRange &r, const TensorDev &
     return r.lr_split < runs ? r.lr_split : runs;
 }
 
-// Where share `share` of tensor t leaves its part of Z: the first in Z itself.
-__device__ __forceinline__ uint8_t *lr_slice(const BatchView &v, const LaunchRange &r, const TensorDev &d, int t, int share)
+// Where share `share` of a tensor leaves its part of Z: the first in Z itself.
+__device__ __forceinline__ uint8_t *lr_slice(const BatchView &v, const LaunchRange &r, const TensorDev &d, int share)
 {
     if (share == 0) return v.workspace + d.lr_z_off;
-    return v.workspace + r.lr_slices_off + (uint64_t)((t - r.first) * (r.lr_split - 1) + share - 1) * (uint64_t)r.lr_max_channels * (kRank * sizeof(float));
+    return v.workspace + r.lr_slices_off + ((uint64_t)(d.lr_slot - r.lr_first_slot) * (uint64_t)(r.lr_split - 1) + (uint64_t)(share - 1)) * (uint64_t)r.lr_max_channels * (kRank * sizeof(float));
 }
 
 // The tokens are cut into lowrank_runs = 1, 2 or 4 runs.  Z is the sum (run 0 + run 1) + (run 2 + run 3), each run the
@@ -446,7 +442,7 @@ __device__ __forceinline__ void lr_backproject_body(const BatchView &v, const La
             w.p[1][t] = *gconst<float>(P + (row * (kRank * 4) + 64 + 4 * q));
         }
     };
-    CF_GLOBAL float *Z = gmut<float>(lr_slice(v, r, d, t, share)) + (int64_t)stripe * kBackEntries;
+    CF_GLOBAL float *Z = gmut<float>(lr_slice(v, r, d, share)) + (int64_t)stripe * kBackEntries;
     const int n_out = (d.n_channels - stripe * kBackChannels) * kRank;      // entries of the stripe that exist
     for (int run = first_run; run < first_run + n_mine; ++run) {            // uniform over the workgroup
         const int64_t lo = run * per_run + 4 * turn;        // may lie beyond the last quad: such a wave adds zeros
@@ -599,7 +595,7 @@ __device__ __forceinline__ void gram_block(const BatchView &v, const LaunchRange
         hi[s] = valid ? src[(int64_t)row * kRank + 16 + col] : 0.0f;
     }
     if (n_shares > 1) {         // uniform over the workgroup; 2 or 4
-        const CF_GLOBAL float *s1 = gconst<float>(lr_slice(v, r, d, t, 1));
+        const CF_GLOBAL float *s1 = gconst<float>(lr_slice(v, r, d, 1));
 #pragma unroll
         for (int s = 0; s < 16; ++s) {
             const int row = row0 + 4 * s;
@@ -608,7 +604,7 @@ __device__ __forceinline__ void gram_block(const BatchView &v, const LaunchRange
             hi[s] += valid ? s1[(int64_t)row * kRank + 16 + col] : 0.0f;
         }
         if (n_shares > 2) {
-            const CF_GLOBAL float *s2 = gconst<float>(lr_slice(v, r, d, t, 2)), *s3 = gconst<float>(lr_slice(v, r, d, t, 3));
+            const CF_GLOBAL float *s2 = gconst<float>(lr_slice(v, r, d, 2)), *s3 = gconst<float>(lr_slice(v, r, d, 3));
 #pragma unroll
             for (int s = 0; s < 16; ++s) {
                 const int row = row0 + 4 * s;
@@ -1188,7 +1184,7 @@ hipError_t launch_lr_project(const BatchView &v, const LaunchRange &r, bool wire
     if (r.count == 0 || r.lr_max_tokens == 0) return hipSuccess;
     const dim3 grid((unsigned)r.lr_project_blocks, (unsigned)r.count), block(kProjThreads);
     if (r.dts != F32) {
-        if ((int64_t)r.lr_project_blocks * r.count >= kProjMany)
+        if (r.lr_project_many)
             hipLaunchKernelGGL((k_lr_project<BF16, kProjBlocks>), dim3((grid.x + kProjBlocks - 1) / kProjBlocks, grid.y), block, 0, s, v, r, wire ? 1 : 0, min_iters);
         else
             hipLaunchKernelGGL((k_lr_project<BF16, 1>), grid, block, 0, s, v, r, wire ? 1 : 0, min_iters);

@@ -13,6 +13,8 @@
 extern std::vector<std::string> g_launch_log;
 extern bool g_capturing;
 extern bool g_single_pass_slim, g_occupancy_slim;
+extern bool g_project_many;
+extern int g_split;
 
 static int g_failed = 0;
 #define EXPECT(cond)                                                                    \
@@ -267,6 +269,46 @@ int main()
             if (took != c.path) {
                 const auto &s = c.shapes.back();
                 std::printf("ef %d dtype %d ... %d x [%d, %d]: path %d instead of %d\n", c.ef, c.dtype, (int)s[0], (int)s[1], (int)s[2], (int)took, (int)c.path);
+                ++g_failed;
+            }
+            cf_destroy(ctx);
+            std::free(ws);
+        }
+    }
+
+    // ---- the low-rank kernels' rules count the low-rank tensors of a call as they are, and nothing else
+    {
+        struct Group { int count; int64_t n, c; int dtype, scale; };
+        struct Call { std::vector<Group> groups; bool many; int split; };
+        const int B = CF_BF16, F = CF_F32, L = CF_LOWRANK, Q = CF_SCALE_CHANNEL;
+        const std::vector<Call> calls = {
+            {{{4, 4096, 3072, B, L}}, false, 4}, {{{7, 4096, 1536, B, L}}, false, 4}, {{{8, 4096, 1536, B, L}}, true, 4},       // 512, 896, 1024 blocks of 128 tokens
+            {{{8, 4096, 1536, F, L}}, false, 4},
+            {{{1, 4096, 3072, B, L}, {7, 4096, 3072, B, Q}}, false, 4}, {{{100, 64, 64, B, Q}, {1, 4096, 3072, B, L}}, false, 4},
+            {{{1, 8192, 3072, B, L}, {9, 64, 96, B, L}}, false, 4}, {{{8, 64, 96, F, L}, {1, 32768, 1536, B, L}}, true, 4},     // 256 + 9, 1024 blocks
+            {{{64, 4096, 3072, B, L}}, true, 2}, {{{65, 4096, 3072, B, L}}, true, 1},                                           // 768, 780 stripes
+            {{{65, 4096, 256, F, L}, {1, 4096, 2048, B, L}}, false, 2},                                                         // 73 stripes: what the workspace holds
+        };
+        for (size_t k = 0; k < calls.size(); ++k) {
+            std::vector<cf_tensor_desc> d;
+            for (auto &g : calls[k].groups) d.insert(d.end(), (size_t)g.count, desc(g.n, g.c, g.dtype, g.scale == L ? 1 : 2, g.scale, g.scale == L ? 32 : 128));
+            const int n = (int)d.size();
+            std::memset(&o, 0, sizeof o);
+            std::vector<const void *> x;
+            std::vector<void *> recon, err, codes, scales;
+            uintptr_t at = (uintptr_t)1 << 40;
+            auto take = [&] { void *p = (void *)at; at += (uintptr_t)1 << 32; return p; };
+            for (int t = 0; t < n; ++t) { x.push_back(take()); recon.push_back(take()); err.push_back(take()); codes.push_back(take()); scales.push_back(take()); }
+            const size_t wsb = cf_workspace_bytes(d.data(), n, &o);
+            void *ws = nullptr;
+            if (posix_memalign(&ws, 256, wsb) != 0) std::abort();
+            cf_ctx *ctx = nullptr;
+            EXPECT(cf_init(&ctx, d.data(), n, &o, ws, wsb, nullptr) == CF_OK);
+            EXPECT(cf_set_warm(ctx, 0, n, 1) == CF_OK);
+            EXPECT(cf_step_fused(ctx, 0, n, x.data(), recon.data(), err.data(), codes.data(), scales.data(), nullptr) == CF_OK);
+            joined();
+            if (g_project_many != calls[k].many || g_split != calls[k].split) {
+                std::printf("low-rank call %zu: several blocks a wave %d, shares %d\n", k, (int)g_project_many, g_split);
                 ++g_failed;
             }
             cf_destroy(ctx);

@@ -12,6 +12,8 @@ std::vector<std::string> g_launch_log;
 bool g_capturing = false;
 bool g_single_pass_slim = false;        // the stripe width of the last single pass
 bool g_occupancy_slim = false;          // and the one whose co-resident workgroups were asked for last
+bool g_project_many = false;            // whether the last projection's waves take several blocks of tokens
+int g_split = 0;                        // and the workgroups that share a stripe of the last back-projection
 static void note(const char *what) { g_launch_log.push_back(what); }
 
 extern "C" {
@@ -61,8 +63,18 @@ hipError_t launch_encode(const BatchView &, const LaunchRange &, int, int, bool,
 hipError_t launch_encode_nm(const BatchView &, const LaunchRange &, int, int, bool, bool, hipStream_t) { note("k_encode_nm"); return hipSuccess; }
 hipError_t launch_decode(const BatchView &, const LaunchRange &, hipStream_t) { note("k_decode"); return hipSuccess; }
 hipError_t launch_lr_orth(const BatchView &, const LaunchRange &, bool, int, hipStream_t) { note("k_lr_orth"); return hipSuccess; }
-hipError_t launch_lr_project(const BatchView &, const LaunchRange &, bool, int, hipStream_t) { note("k_lr_project"); return hipSuccess; }
-hipError_t launch_lr_backproject(const BatchView &, const LaunchRange &, int, hipStream_t) { note("k_lr_backproject"); return hipSuccess; }
+hipError_t launch_lr_project(const BatchView &, const LaunchRange &r, bool, int, hipStream_t)
+{
+    g_project_many = r.lr_project_many != 0;
+    note("k_lr_project");
+    return hipSuccess;
+}
+hipError_t launch_lr_backproject(const BatchView &, const LaunchRange &r, int, hipStream_t)
+{
+    g_split = r.lr_split;
+    note("k_lr_backproject");
+    return hipSuccess;
+}
 hipError_t launch_lr_quant_u(const BatchView &, const LaunchRange &, hipStream_t) { note("k_lr_quant_u"); return hipSuccess; }
 hipError_t launch_lr_encode(const BatchView &, const LaunchRange &, int, bool, hipStream_t) { note("k_lr_apply"); return hipSuccess; }
 hipError_t launch_lr_decode(const BatchView &, const LaunchRange &, hipStream_t) { note("k_lr_apply"); return hipSuccess; }

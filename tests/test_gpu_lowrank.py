@@ -680,3 +680,36 @@ def test_lowrank_backprojection_of_one_product(n, c):
         assert worst <= 3.4 * 2.0 ** -24
     finally:
         sess.close()
+
+
+def test_lowrank_shares_between_other_tensors():
+    """Low-rank tensors of several runs of tokens, which workgroups share, between and behind tensors of other kinds: the bits of
+    the same tensors alone, in calls that start at the context's first tensor and behind it."""
+    say("lowrank: shared runs in a mixed context")
+    descs = [cf.desc(300, 256, cf.CF_BF16, 2, cf.CF_SCALE_CHANNEL), cf.desc(2049, 288, cf.CF_BF16, 2, cf.CF_LOWRANK, R),
+             cf.desc(130, 384, cf.CF_BF16, 4, cf.CF_SCALE_GROUP), cf.desc(900, 544, cf.CF_F32, 1, cf.CF_LOWRANK, R),
+             cf.desc(1100, 96, cf.CF_BF16, 1, cf.CF_LOWRANK, R)]
+    pick = [1, 3, 4]
+    xs = [stream(int(d.n_tokens), int(d.n_channels), int(d.dtype), 2, 1000 + t) for t, d in enumerate(descs)]
+    q0 = {t: start_matrices(int(descs[t].n_channels), 1, 1010 + t)[0] for t in pick}
+    alone = {t: CodecSession([descs[t]], cf.options(), device=DEV) for t in pick}
+    mixed = CodecSession(descs, cf.options(), device=DEV)
+    try:
+        for t in pick:
+            alone[t].warmup([xs[t][0]])
+            alone[t].scales[0].copy_(q0[t].reshape(-1))
+            alone[t].step_fused([xs[t][1]])
+        for first in (0, 1, 2):
+            mixed.warmup([x[0] for x in xs])
+            for t in pick:
+                mixed.scales[t].copy_(q0[t].reshape(-1))
+            mixed.step_fused([x[1] for x in xs[first:]], first=first, count=5 - first)
+            cf.cf_check_device(mixed.ctx, mixed.stream_handle)
+            for t in pick:
+                for name in ("codes", "recon", "err"):
+                    if t >= first:
+                        assert torch.equal(getattr(mixed, name)[t], getattr(alone[t], name)[0]), f"{name} of tensor {t} in a call from {first}"
+    finally:
+        mixed.close()
+        for s in alone.values():
+            s.close()
