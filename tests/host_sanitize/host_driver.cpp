@@ -15,6 +15,7 @@ extern bool g_capturing;
 extern bool g_single_pass_slim, g_occupancy_slim;
 extern bool g_project_many;
 extern int g_split;
+extern std::vector<cf::TensorPtrs> g_direct;
 
 static int g_failed = 0;
 #define EXPECT(cond)                                                                    \
@@ -183,6 +184,79 @@ int main()
     }
     cf_destroy(nullptr);
 
+    // ---- calls of one kernel over at most kDirectTensors tensors: their pointers go into its arguments, on any stream and while one is
+    // captured, the table stays as it is and counts as before
+    {
+        std::vector<cf_tensor_desc> d;
+        for (int t = 0; t < 12; ++t)
+            d.push_back(t % 3 == 0 ? desc(40 + t, 384, CF_BF16, 4, CF_SCALE_GROUP) : desc(40 + t, 384, CF_F32, 2, CF_SPARSE_NM, t % 3 == 1 ? 8 : 16));
+        d.push_back(desc(60, 64, CF_BF16, 1, CF_LOWRANK, 32));
+        d.push_back(desc(60, 64, CF_BF16, 1, CF_SCALE_RANK1));
+        const int n = (int)d.size(), most = cf::kDirectTensors;
+        std::memset(&o, 0, sizeof o);
+        const size_t wsb = cf_workspace_bytes(d.data(), n, &o);
+        void *ws = nullptr;
+        if (posix_memalign(&ws, 256, wsb) != 0) std::abort();
+        std::memset(ws, 0, wsb);
+        cf_ctx *ctx = nullptr;
+        EXPECT(cf_init(&ctx, d.data(), n, &o, ws, wsb, nullptr) == CF_OK);
+        EXPECT(cf_set_warm(ctx, 0, n, 1) == CF_OK);
+        uintptr_t at = (uintptr_t)1 << 40;                          // addresses nobody looks behind
+        auto take = [&](int count) { std::vector<void *> p; for (int t = 0; t < count; ++t, at += (uintptr_t)1 << 24) p.push_back((void *)at); return p; };
+        std::vector<void *> recon = take(n), err = take(n), codes = take(n), scales = take(n), xs = take(n);
+        const void *const *x = (const void *const *)xs.data();
+        joined();
+        enum What { WARMUP, STEP, COMPRESS, DECOMPRESS };
+        auto call = [&](What what, int first, int count, void *stream) {
+            switch (what) {
+            case WARMUP: return cf_warmup(ctx, first, count, x + first, recon.data() + first, err.data() + first, stream);
+            case STEP: return cf_step_fused(ctx, first, count, x + first, recon.data() + first, err.data() + first, codes.data() + first, scales.data() + first, stream);
+            case COMPRESS: return cf_compress(ctx, first, count, x + first, recon.data() + first, err.data() + first, codes.data() + first, scales.data() + first, stream);
+            default: return cf_decompress(ctx, first, count, (const void *const *)codes.data() + first, (const void *const *)scales.data() + first, recon.data() + first, stream);
+            }
+        };
+        EXPECT(call(STEP, 0, n, nullptr) == CF_OK && uploaded(joined()));
+        EXPECT(call(STEP, 0, n, nullptr) == CF_OK && !uploaded(joined()));
+        const auto table_pointers = recon;
+        recon = take(n);                                            // other buffers than the table's
+        const std::vector<uint8_t> before((uint8_t *)ws, (uint8_t *)ws + wsb);
+        for (What what : {WARMUP, STEP, COMPRESS, DECOMPRESS})
+            for (int first : {0, 2, n - 3})
+                for (int count : {1, 3, most}) {
+                    if (first + count > n || ((what == STEP || what == COMPRESS) && first + count > 12)) continue;    // those senders read the table
+                    for (int how = 0; how < 3; ++how) {             // the table's stream, another, a capture
+                        g_capturing = how == 2;
+                        EXPECT(call(what, first, count, how == 1 ? (void *)0x1000 : nullptr) == CF_OK);
+                        g_capturing = false;
+                        const std::string seq = joined();
+                        EXPECT(!seq.empty() && !uploaded(seq));
+                        EXPECT((int)g_direct.size() == count);
+                        for (int k = 0; k < (int)g_direct.size(); ++k) {
+                            const cf::TensorPtrs &p = g_direct[(size_t)k];
+                            const int t = first + k;
+                            EXPECT(p.recon == recon[t]);
+                            EXPECT(p.x == (what == DECOMPRESS ? nullptr : xs[t]) && p.err == (what == DECOMPRESS ? nullptr : err[t]));
+                            EXPECT((void *)p.codes == (what == WARMUP ? nullptr : codes[t]) && (void *)p.scales == (what == WARMUP ? nullptr : scales[t]));
+                        }
+                        EXPECT(std::memcmp(ws, before.data(), wsb) == 0);
+                    }
+                }
+        recon = table_pointers;
+        EXPECT(call(STEP, 0, n, nullptr) == CF_OK && !uploaded(joined()));         // the table still holds what it did, and is known to
+        // one tensor more, and senders of kinds that several kernels work on: by the table
+        recon = take(n);
+        for (What what : {WARMUP, STEP, COMPRESS, DECOMPRESS}) {
+            EXPECT(call(what, 1, most + 1, nullptr) == CF_OK);
+            EXPECT((uploaded(joined()) == (what == WARMUP)) && g_direct.empty());
+        }
+        for (int t : {12, 13}) {
+            EXPECT(call(STEP, t, 1, nullptr) == CF_OK && uploaded(joined()));
+            EXPECT(call(DECOMPRESS, t, 1, (void *)0x1000) == CF_OK && !uploaded(joined()) && g_direct.size() == 1);
+        }
+        cf_destroy(ctx);
+        std::free(ws);
+    }
+
     // ---- which path a call takes by default: the single pass for tensors of 256 tokens and more in calls of 64
     // items and more, two kernels for tiny ones
     {
@@ -199,7 +273,7 @@ int main()
             std::memset(&o, 0, sizeof o);
             o.flags = cs.flags;
             cf_tensor_desc d = desc(cs.n, cs.c, CF_BF16, 2, CF_SCALE_CHANNEL);
-            Buffers b(d, &o);
+            Buffers b(d, &o), other(d, &o);
             const size_t wsb = cf_workspace_bytes(&d, 1, &o);
             void *ws = nullptr;
             if (posix_memalign(&ws, 256, wsb) != 0) std::abort();
@@ -209,10 +283,15 @@ int main()
             EXPECT(cf_warmup(ctx, 0, 1, &x, &b.recon, &b.err, nullptr) == CF_OK);
             joined();
             EXPECT(cf_step_fused(ctx, 0, 1, &x, &b.recon, &b.err, &b.codes, &b.scales, nullptr) == CF_OK);
-            const std::string seq = joined();
+            std::string seq = joined();
             EXPECT(seq.find(cs.must) != std::string::npos);
             EXPECT(seq.find(cs.must_not) == std::string::npos);
-            // new pointers (codes, scales) since the warm-up: a single pass takes them along in its first kernel
+            EXPECT(uploaded(seq));                  // the first call that reads the table
+            EXPECT(cf_step_fused(ctx, 0, 1, &x, &b.recon, &b.err, &b.codes, &b.scales, nullptr) == CF_OK);
+            EXPECT(!uploaded(joined()));
+            // a new pointer: a single pass takes it along in its first kernel
+            EXPECT(cf_step_fused(ctx, 0, 1, &x, &b.recon, &b.err, &other.codes, &b.scales, nullptr) == CF_OK);
+            seq = joined();
             if (std::string(cs.must).find("k_single_pass") != std::string::npos)
                 EXPECT(seq.find("ptrs_in_reset k_reset_partials") != std::string::npos && seq.find("k_upload_ptrs") == std::string::npos);
             else

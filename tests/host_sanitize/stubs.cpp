@@ -8,12 +8,21 @@
 
 #include "cf_internal.h"
 
+using cf::LaunchRange;
+using cf::TensorPtrs;
+
 std::vector<std::string> g_launch_log;
 bool g_capturing = false;
 bool g_single_pass_slim = false;        // the stripe width of the last single pass
 bool g_occupancy_slim = false;          // and the one whose co-resident workgroups were asked for last
 bool g_project_many = false;            // whether the last projection's waves take several blocks of tokens
 int g_split = 0;                        // and the workgroups that share a stripe of the last back-projection
+std::vector<TensorPtrs> g_direct;       // the pointers that the last kernel of a direct call took as arguments; none: it read the table
+static void take_direct(const LaunchRange &r)
+{
+    g_direct.clear();
+    if (r.direct) g_direct.assign(r.direct, r.direct + r.count);
+}
 static void note(const char *what) { g_launch_log.push_back(what); }
 
 extern "C" {
@@ -55,13 +64,13 @@ hipError_t launch_fill_item_tensor(const uint32_t *item_prefix, uint32_t *item_t
         for (uint32_t i = item_prefix[t]; i < item_prefix[t + 1]; ++i) item_tensor[i] = (uint32_t)t;
     return hipSuccess;
 }
-hipError_t launch_warmup(const BatchView &, const LaunchRange &, int, hipStream_t) { note("k_warmup"); return hipSuccess; }
+hipError_t launch_warmup(const BatchView &, const LaunchRange &r, int, hipStream_t) { take_direct(r); note("k_warmup"); return hipSuccess; }
 hipError_t launch_colreduce(const BatchView &, const LaunchRange &, int, int, hipStream_t) { note("k_colreduce"); return hipSuccess; }
 hipError_t launch_finalize(const BatchView &, const LaunchRange &, hipStream_t) { note("k_finalize"); return hipSuccess; }
 hipError_t launch_finalize_rank1(const BatchView &, const LaunchRange &, hipStream_t) { note("k_finalize_rank1"); return hipSuccess; }
-hipError_t launch_encode(const BatchView &, const LaunchRange &, int, int, bool, hipStream_t) { note("k_encode"); return hipSuccess; }
-hipError_t launch_encode_nm(const BatchView &, const LaunchRange &, int, int, bool, bool, hipStream_t) { note("k_encode_nm"); return hipSuccess; }
-hipError_t launch_decode(const BatchView &, const LaunchRange &, hipStream_t) { note("k_decode"); return hipSuccess; }
+hipError_t launch_encode(const BatchView &, const LaunchRange &r, int, int, bool, hipStream_t) { take_direct(r); note("k_encode"); return hipSuccess; }
+hipError_t launch_encode_nm(const BatchView &, const LaunchRange &r, int, int, bool, bool, hipStream_t) { take_direct(r); note("k_encode_nm"); return hipSuccess; }
+hipError_t launch_decode(const BatchView &, const LaunchRange &r, hipStream_t) { take_direct(r); note("k_decode"); return hipSuccess; }
 hipError_t launch_lr_orth(const BatchView &, const LaunchRange &, bool, int, hipStream_t) { note("k_lr_orth"); return hipSuccess; }
 hipError_t launch_lr_project(const BatchView &, const LaunchRange &r, bool, int, hipStream_t)
 {
@@ -77,7 +86,7 @@ hipError_t launch_lr_backproject(const BatchView &, const LaunchRange &r, int, h
 }
 hipError_t launch_lr_quant_u(const BatchView &, const LaunchRange &, hipStream_t) { note("k_lr_quant_u"); return hipSuccess; }
 hipError_t launch_lr_encode(const BatchView &, const LaunchRange &, int, bool, hipStream_t) { note("k_lr_apply"); return hipSuccess; }
-hipError_t launch_lr_decode(const BatchView &, const LaunchRange &, hipStream_t) { note("k_lr_apply"); return hipSuccess; }
+hipError_t launch_lr_decode(const BatchView &, const LaunchRange &r, hipStream_t) { take_direct(r); note("k_lr_apply"); return hipSuccess; }
 int persistent_max_blocks_per_cu(int, int, bool, bool, bool slim) { g_occupancy_slim = slim; return 2; }
 hipError_t launch_single_pass(const BatchView &, const LaunchRange &r, int, int, bool, bool, int, bool, bool redo, hipStream_t)
 {
