@@ -8,16 +8,17 @@ import paper_2507_17511_amd as cf
 pytestmark = pytest.mark.gpu
 
 KINDS = {"channel": (cf.CF_SCALE_CHANNEL, 128, 2), "group": (cf.CF_SCALE_GROUP, 128, 4), "sparse": (cf.CF_SPARSE_NM, 8, 2),
-         "lowrank": (cf.CF_LOWRANK, 32, 1)}
+         "lowrank": (cf.CF_LOWRANK, 32, 1), "sparse16": (cf.CF_SPARSE_NM, 16, 2), "rank1": (cf.CF_SCALE_RANK1, 128, 2)}
+DTYPES = {"mixed": lambda k: cf.CF_BF16 if k % 3 else cf.CF_F32, "bf16": lambda k: cf.CF_BF16, "f32": lambda k: cf.CF_F32}
 
 
 class _Side:
     """One context of ten tensors with their buffers, all made from the same seed."""
 
-    def __init__(self, kind):
+    def __init__(self, kind, dtypes="mixed", **options):
         scale, group, bits = KINDS[kind]
-        self.descs = [cf.desc(40 + 7 * k, 384, cf.CF_BF16 if k % 3 else cf.CF_F32, bits, scale, group) for k in range(10)]
-        opts = cf.options()
+        self.descs = [cf.desc(40 + 7 * k, 384, DTYPES[dtypes](k), bits, scale, group) for k in range(10)]
+        opts = cf.options(**options)
         nbytes = cf.cf_workspace_bytes(self.descs, opts)
         self.ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
         self.stream = torch.cuda.current_stream().cuda_stream
@@ -67,3 +68,69 @@ def test_pointers_in_arguments_and_in_the_table_give_the_same_bits(kind, pieces)
         assert torch.equal(a, b)
     for side in (whole, cut):
         cf.cf_destroy(side.ctx)
+
+
+# (kind, storage types, options): the kernels have an instance for each feedback mode, error type, mix of storage types and wire
+FORMS = [(kind, dtypes, dict(ef=ef, err_dtype=err))
+         for kind in ("group", "sparse", "sparse16", "rank1", "channel")
+         for ef, err, dtypes in ((cf.CF_EF_RECON, cf.CF_BF16, "bf16"), (cf.CF_EF_LITERAL, cf.CF_F32, "mixed"), (cf.CF_EF_LITERAL, cf.CF_BF16, "f32"),
+                                 (cf.CF_EF_OFF, cf.CF_F32, "bf16"), (cf.CF_EF_OFF, cf.CF_BF16, "mixed"), (cf.CF_EF_NAIVE, cf.CF_F32, "f32"),
+                                 (cf.CF_EF_NAIVE, cf.CF_BF16, "bf16"))]
+FORMS += [(kind, dtypes, dict()) for kind in ("group", "sparse", "sparse16", "rank1", "lowrank") for dtypes in ("bf16", "f32")]
+FORMS += [("sparse16", "mixed", dict()), ("rank1", "mixed", dict())]
+FORMS += [("lowrank", dtypes, dict(err_dtype=err, flags=cf.CF_FLAG_LOWRANK_INT4)) for dtypes, err in (("mixed", cf.CF_F32), ("bf16", cf.CF_BF16), ("f32", cf.CF_F32))]
+
+
+@pytest.mark.parametrize("kind, dtypes, options", FORMS)
+def test_every_form_of_the_kernels_by_both_routes(kind, dtypes, options):
+    """Ten tensors a call read the table, calls of eight and fewer bring their pointers: two warm-ups, steps, sends and receives."""
+    whole, cut = _Side(kind, dtypes, **options), _Side(kind, dtypes, **options)
+    try:
+        for _ in range(2):
+            whole.calls([(0, 10)])
+            cut.calls([(0, 8), (8, 2)])
+            for a, b in zip(whole.outputs(), cut.outputs()):
+                assert torch.equal(a, b)
+    finally:
+        for side in (whole, cut):
+            cf.cf_destroy(side.ctx)
+
+
+@pytest.mark.parametrize("kind", ["group", "sparse", "sparse16"])
+def test_direct_calls_on_another_stream_and_from_a_graph(kind):
+    """Calls that bring their pointers, between calls by the table on the context's own stream: on a second stream, and captured with
+    other inputs and replayed, against the same calls one after the other on one stream."""
+    side, plain = _Side(kind), _Side(kind)
+    other = torch.cuda.Stream()
+    own = side.stream
+    try:
+        for s in (side, plain):
+            s.calls([(0, 10)])
+        plain.calls([(0, 8), (8, 2)])
+        side.stream = other.cuda_stream             # calls() ends with a synchronisation
+        side.calls([(0, 8), (8, 2)])
+        side.stream = own
+        for a, b in zip(side.outputs(), plain.outputs()):
+            assert torch.equal(a, b)
+        at = lambda bufs, first, count: cf.ptr_array(bufs[first:first + count])
+        fed = [x.clone() for x in side.xs[0]]
+
+        def step(s, xs, stream):
+            cf.cf_step_fused(s.ctx, 2, 8, at(xs, 2, 8), at(s.recon, 2, 8), at(s.err, 2, 8), at(s.codes, 2, 8), at(s.scales, 2, 8), stream)
+
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            step(side, fed, torch.cuda.current_stream().cuda_stream)
+        for k in range(4):
+            side.calls([(0, 10)])                   # the table's pointers, and a synchronisation
+            plain.calls([(0, 10)])
+            for x, y in zip(fed, side.xs[k % 2]):
+                x.copy_(y).mul_(1.0 + k)
+            g.replay()
+            step(plain, [y * (1.0 + k) for y in plain.xs[k % 2]], plain.stream)
+            torch.cuda.synchronize()
+            for a, b in zip(side.outputs(), plain.outputs()):
+                assert torch.equal(a, b), f"replay {k}"
+    finally:
+        for s in (side, plain):
+            cf.cf_destroy(s.ctx)
