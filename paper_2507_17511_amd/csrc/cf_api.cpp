@@ -144,8 +144,9 @@ int64_t lowrank_stripes(int64_t n_channels) { return (n_channels + kLowRankBackC
 
 // Workgroups that share a channel stripe of the low-rank back-projection in a call of that many stripes (the largest
 // low-rank tensor's channels and tokens given): more where the stripes alone would leave the device idle.
-// Whole steps with 1 / 2 / 4 sharing, us: [4096, 3072] 1 tensor 413 / 305 / 258, 8 (96 stripes) 600 / 492 / 492, 16 930 / 842 / 863,
-// 40 1971 / 1970 / 2009, 57 (684) 2888 / 2824 / 2855; 60 x [8000, 96] 675 / 474 / 384.  Beyond, the shares' memory is not worth it.
+// Whole steps with 1 / 2 / 4 sharing, us: [4096, 3072] 1 tensor 339 / 234 / 190, 8 (96 stripes) 633 / 529 / 514, 16 966 / 907 / 889,
+// 40 2053 / 2038 / 2066, 57 (684) 2910 / 2881 / 2882; 60 x [8000, 96] 456 / 353 / 311, 100 x [4096, 256] 636 / 531 / 515.  Beyond, the
+// shares' memory is not worth it.
 int64_t lowrank_split(int64_t max_channels, int64_t max_tokens, int64_t stripes)
 {
     return std::min<int64_t>(lowrank_runs(max_tokens, max_channels), stripes <= 128 ? kLowRankMaxRuns : stripes <= 768 ? 2 : 1);
@@ -300,7 +301,7 @@ cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &
             v.lr_z_off = partial_bytes;
             partial_bytes += align_up((size_t)d.n_channels * kLowRankRank * sizeof(float));
             v.lr_g_off = partial_bytes;
-            partial_bytes += align_up((size_t)d.n_channels * kLowRankRank * sizeof(float));      // 8 KB per 256 channels and the last word are used
+            partial_bytes += align_up(lowrank_g_bytes(d.n_channels));
         }
         if (d.scale == CF_SCALE_RANK1) {
             L.any_rank1 = true;
@@ -810,9 +811,9 @@ cf_status run_sender(cf_ctx *ctx, int32_t first, int32_t count, const void *cons
     const bool single_pass = ctx->L.single_pass && grid >= ctx->L.max_group_items && grid >= 1 && r.item_hi > r.item_lo && worth_it;
     // the call's pointers go to the table first; the single pass's first kernel takes the last batch of them along
     DeferredPtrs defer;
-    const bool row_local_only = !ctx->range_has_channel(first, count) && ctx->range_lowrank_iters(first, count) < 0;
     DirectPtrs direct;
-    if (row_local_only && direct.take(r, x, recon, err, codes, reinterpret_cast<const void *const *>(scales))) {
+    if (count <= kDirectTensors && !ctx->range_has_channel(first, count) && ctx->range_lowrank_iters(first, count) < 0 &&
+        direct.take(r, x, recon, err, codes, reinterpret_cast<const void *const *>(scales))) {
         e = run_row_local(ctx, first, count, v, r, fused, true, s);
         return e == hipSuccess ? CF_OK : device_fail(ctx, e);
     }

@@ -18,9 +18,9 @@ constexpr int kRank1Threads = 1024;                         // one block per ten
 constexpr int kMaxRank1Colblocks = 128;                     // rank-1 scales: C <= 128 * 1024
 constexpr int kMaxUploadTensors = 64;                       // pointer sets per upload launch
 // Calls of one kernel over at most so many tensors (one layer's K and V of four peers) carry their pointers in the kernel's
-// arguments and skip the upload to the table, a launch and a gap: us a call,
-// table / arguments: 6 x [1024, 3072] 2-bit receiver 19.9 / 17.9, small calls of one kernel 12.0 / 8.4, 10.4 / 8.8, 15.4 / 13.1.
-// More sets would lengthen the arguments of the calls that gain least.
+// arguments and skip the upload to the table, a launch and a gap, where pointers change from call to call: receivers of n x [1024, 3072], bf16, 2-bit,
+// table / arguments, us: n = 1 8.6 / 4.8, 4 13.5 / 11.3, 6 17.4 / 15.4, 8 22.1 / 19.4; with room for 16 tensors 12 29.5 / 27.3, 16 37.5 / 35.2, the
+// small calls the same.  (With room for 16 the arguments are 340 bytes longer; the lead is open.)  n x [64, 256]: 8.6 / 4.4 for any n.
 constexpr int kDirectTensors = 8;
 // Single-pass path: one workgroup of 256 lanes keeps an item of p_rows x 128
 // channels (x and recon, raw) in registers between the scale reduction and the
@@ -87,9 +87,9 @@ struct alignas(16) TensorDev {
                             // low-rank compressor: 4 when the factors travel as 4-bit integers, else 0
     uint32_t lr_slot;       // low-rank tensors before this one in the context
     uint64_t rowpart_off;
-    // low-rank compressor: P = A Q [N][32] fp32; Z = A^T P [C][32] fp32, which Q takes the place of in the order
-    // k_lr_project reads it; partial sums of Z^T Z, one [32][32] fp64 matrix per 256 channels (C > 256 only),
-    // and a word of k_lr_orth's at the end of their area
+    // low-rank compressor: P = A Q [N][32] fp32; Z = A^T P [C][32] fp32, which the high and mid pieces of Q take the place of in
+    // the order k_lr_project reads them; partial sums of Z^T Z, one [32][32] fp64 matrix per 256 channels (C > 256 only), behind them
+    // the low pieces of Q, and a word of k_lr_orth's at the end of their area
     uint64_t lr_p_off, lr_z_off, lr_g_off;
 };
 
@@ -196,23 +196,38 @@ constexpr int kLowRankMaxChannels = 3072;
 // The back-projection's workgroups own kLowRankBackChannels channels each.  A tensor's tokens are summed in lowrank_runs
 // runs, a property of the tensor alone: the sum has one order in every call.  Runs cost a workgroup that takes them all a
 // drained pipeline and a sum over its waves each, so short tensors have fewer, wide ones above all: steps with 2 / 4
-// runs, us: 114 x [1100, 2048] T = 2 2100 / 2273, 100 x [2000, 3072] 2953 / 3002, 6 x [2000, 3072] 504 / 496; 20 x [2000, 1024]
-// 366 / 369, one [2048, 64] 103 / 92, one [2900, 1024] T = 2 368 / 328.
+// runs, us: 114 x [1100, 2048] T = 2 1740 / 1818, 100 x [2000, 3072] 2595 / 2660, 6 x [2000, 3072] 262 / 261; 20 x [2000, 1024]
+// 257 / 262, one [2048, 64] 91 / 85, one [2900, 1024] T = 2 266 / 213.
 constexpr int kLowRankBackChannels = 256;
 constexpr int kLowRankMaxRuns = 4;
 constexpr int lowrank_runs(int64_t n_tokens, int64_t n_channels)
 {
     return n_tokens <= 384 ? 1 : n_tokens <= (n_channels <= 1024 ? 1024 : 2048) ? 2 : kLowRankMaxRuns;
 }
-// Runs of channels that P = A Q is the sum of, 64 channels or more each.
+// The area of the Gram matrices: partial sums, 8 KB per 256 channels (none up to 256 channels), Q's low pieces behind them, and in the last
+// word whether k_lr_orth left the tensor over.
+constexpr size_t lowrank_g_bytes(int64_t n_channels) { return (size_t)n_channels * kLowRankRank * sizeof(float); }
+constexpr size_t lowrank_q_low_off(int64_t n_channels) { return n_channels > 256 ? (size_t)n_channels * 32 + 8192 : 0; }
+constexpr bool lowrank_g_area_fits()
+{
+    for (int64_t c = 32; c <= kLowRankMaxChannels; c += 32) {
+        const size_t sums = c > 256 ? (size_t)((c + 255) / 256) * 8192 : 0;
+        if (sums > lowrank_q_low_off(c) || lowrank_q_low_off(c) + (size_t)c * kLowRankRank * 2 + sizeof(uint32_t) > lowrank_g_bytes(c)) return false;
+    }
+    return true;
+}
+static_assert(lowrank_g_area_fits(), "partial sums, low pieces and the word have places of their own");
+// Shares of the channels that P = A Q is the sum of, 64-channel stages dealt in turn: none has fewer than one stage's but where the stages
+// are no multiple of the shares (96 channels 64 / 32, 160 channels 64 / 64 / 32 and an empty one).
 constexpr int lowrank_project_parts(int64_t n_channels) { return n_channels > 128 ? 4 : n_channels > 64 ? 2 : 1; }
 constexpr int lowrank_project_tokens(int64_t n_channels) { return 128 / lowrank_project_parts(n_channels); }        // of a workgroup, a block of 32 per wave
-// Blocks of 32 tokens that a wave of k_lr_project<bf16> takes in calls whose bf16 tensors have kLowRankProjectMany workgroups' blocks and
-// more, one block after the other against the same pieces of Q, which otherwise take as much of a CU's 64 bytes per clock as the operands.
-// Steps over [4096, 3072] bf16, one block / several, us: 1 tensor 192 / 258, 4 299 / 329, 8 524 / 492, 24 1353 / 1251, 57 3041 /
-// 2824; 28 fp32 ones 2778 / 2860, which take one.
+// Blocks of 32 tokens that a wave of k_lr_project<bf16> takes in calls whose bf16 tensors have kLowRankProjectMany workgroups' blocks (seven a
+// CU) and more, one block after the other against the same pieces of Q, which otherwise take as much of a CU's 64 bytes per clock as the
+// operands.  Steps of bf16, one block / three, us: [4096, 3072] 1 tensor 190 / 242, 8 (1024 blocks) 523 / 529, 12 812 / 846, 14 (1792) 842 / 844, 16
+// 935 / 907, 24 1402 / 1361, 57 3089 / 2875; 57 x [1024, 3072] (1824) 927 / 906, 114 x [4096, 256] 571 / 567, 60 x [8000, 96] 303 / 311.
+// fp32 tensors take one: 28 of them 2778 / 2860.
 constexpr int kLowRankProjectBlocks = 3;
-constexpr int64_t kLowRankProjectMany = 1024;
+constexpr int64_t kLowRankProjectMany = 1792;
 // k_lr_apply: a wave owns 32 tokens and one or two tiles of 64 channels, two where widening the factors costs more than the products.  The
 // waves are counted through the rows of a tensor and on into the next 32 tokens, whatever workgroup they fall into, so that no width
 // leaves waves without tiles; of eight tiles in a row, wave k of four has tiles k and k + 4, so that the four lie side by side.

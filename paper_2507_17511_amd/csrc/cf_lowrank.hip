@@ -32,8 +32,8 @@ constexpr float kDrop2 = 1e-8f;     // (1e-4)^2: a column left with less than 1e
 __device__ __forceinline__ f32x16 mfma32(float a, float b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
 
 // Operands a pass reads once.  Streaming hint for bf16 only, whose lanes take their 16 bytes in one load: fp32 lanes take
-// 32 bytes in two, and the hint lets go of the line in between.  57 x [4096, 3072], plain and with the hint: bf16 project
-// 600 / 585 us, back-projection 616 / 593; fp32 project 1094 / 1263, back-projection 1348 / 1779 (at four waves per SIMD).
+// 32 bytes in two, and the hint lets go of the line in between.  Steps of [4096, 3072], plain and with the hint, us: 57 of bf16
+// 2888 / 2870, 28 of fp32 2756 / 3027.
 // `base` uniform over the wave, `off` the lane's byte offset.
 __device__ __forceinline__ void load_once(Raw8<BF16> &r, const void *base, uint32_t off) { r.load_stream_at(base, off); }
 __device__ __forceinline__ void load_once(Raw8<F32> &r, const void *base, uint32_t off) { r.load_at(base, off); }
@@ -48,21 +48,6 @@ template <int DT> __device__ __forceinline__ void load16(const void *base, int64
     for (int k = 0; k < 8; ++k) {
         out[k] = a.v[k];
         out[8 + k] = b.v[k];
-    }
-}
-
-// 16 consecutive elements of the residual x - recon of one token, or zeros.
-template <int DT> __device__ __forceinline__ void residual16(const TensorPtrs &p, int64_t elem, bool valid, float (&z)[16])
-{
-    if (valid) {
-        float x[16], b[16];
-        load16<DT>(p.x, elem, x);
-        load16<DT>(p.recon, elem, b);
-#pragma unroll
-        for (int k = 0; k < 16; ++k) z[k] = x[k] - b[k];
-    } else {
-#pragma unroll
-        for (int k = 0; k < 16; ++k) z[k] = 0.0f;
     }
 }
 
@@ -183,8 +168,7 @@ __device__ __forceinline__ Split8 split8(const float (&v)[8])
 __device__ __forceinline__ uint8_t *lr_q(const BatchView &v, const TensorDev &d, int step, int piece)
 {
     if (piece < 2) return v.workspace + d.lr_z_off + (int64_t)step * 4096 + piece * 2048;
-    const int64_t behind = d.n_channels > 256 ? (int64_t)d.n_channels * 32 + 8192 : 0;
-    return v.workspace + d.lr_g_off + behind + (int64_t)step * 2048;
+    return v.workspace + d.lr_g_off + lowrank_q_low_off(d.n_channels) + (int64_t)step * 2048;
 }
 
 // ---------------------------------------------------------------- P = A Q  (and U on the wire)
@@ -562,8 +546,8 @@ constexpr double kLeanNoise = 32.0 * 3.6e-15;               // 32 terms, 2^-48 e
 constexpr int kOrthThreads = 256;                           // one channel row per lane
 constexpr int kGramEntries = kRank * kRank;                 // of which the upper triangle is used
 
-// Whether k_lr_orth left the tensor to k_lr_orth_twice: the last word of the Gram matrices' area, whose partial sums
-// fill at most 32 C + 8160 of its 128 C bytes (and which k_lr_orth alone uses where C <= 256).
+// Whether k_lr_orth left the tensor to k_lr_orth_twice: the last word of the Gram matrices' area, of whose 128 C bytes the partial
+// sums and Q's low pieces fill at most 96 C + 8192 (64 C where C <= 256 and there are no partial sums).
 __device__ __forceinline__ CF_GLOBAL uint32_t *lr_left_over(const BatchView &v, const TensorDev &d)
 {
     return gmut<uint32_t>(v.workspace + d.lr_g_off) + (int64_t)d.n_channels * kRank - 1;

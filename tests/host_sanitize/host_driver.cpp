@@ -361,10 +361,10 @@ int main()
         struct Call { std::vector<Group> groups; bool many; int split; };
         const int B = CF_BF16, F = CF_F32, L = CF_LOWRANK, Q = CF_SCALE_CHANNEL;
         const std::vector<Call> calls = {
-            {{{4, 4096, 3072, B, L}}, false, 4}, {{{7, 4096, 1536, B, L}}, false, 4}, {{{8, 4096, 1536, B, L}}, true, 4},       // 512, 896, 1024 blocks of 128 tokens
-            {{{8, 4096, 1536, F, L}}, false, 4},
+            {{{4, 4096, 3072, B, L}}, false, 4}, {{{13, 4096, 1536, B, L}}, false, 2}, {{{14, 4096, 1536, B, L}}, true, 2},       // 512, 1664, 1792 blocks of 128 tokens
+            {{{14, 4096, 1536, F, L}}, false, 2},
             {{{1, 4096, 3072, B, L}, {7, 4096, 3072, B, Q}}, false, 4}, {{{100, 64, 64, B, Q}, {1, 4096, 3072, B, L}}, false, 4},
-            {{{1, 8192, 3072, B, L}, {9, 64, 96, B, L}}, false, 4}, {{{8, 64, 96, F, L}, {1, 32768, 1536, B, L}}, true, 4},     // 256 + 9, 1024 blocks
+            {{{1, 8192, 3072, B, L}, {9, 64, 96, B, L}}, false, 4}, {{{8, 64, 96, F, L}, {1, 65536, 1536, B, L}}, true, 4},     // 256 + 9, 2048 blocks
             {{{64, 4096, 3072, B, L}}, true, 2}, {{{65, 4096, 3072, B, L}}, true, 1},                                           // 768, 780 stripes
             {{{65, 4096, 256, F, L}, {1, 4096, 2048, B, L}}, false, 2},                                                         // 73 stripes: what the workspace holds
         };

@@ -1,7 +1,7 @@
 """GPU parity of the low-rank compressor (Alg. 3; App. D "Low-Rank Compression") against the fp64 oracle.
 
-The path is floating-point linear algebra on the matrix cores (fp32 in, fp32 accumulate), so the bar is a
-tolerance, derived here from the arithmetic:
+The path is floating-point linear algebra on the matrix cores (fp32 operands, as three bf16 pieces each in the products with A;
+fp32 sums), so the bar is a tolerance, derived here from the arithmetic:
   * factors against the oracle: an fp32 dot product over C <= 3072 channels carries a relative error of about
     sqrt(C) * 2^-24 ~ 3e-6 of the operand norms, Gram-Schmidt passes it on multiplied by the conditioning of Z
     (below 100 for the test matrices): WIRE_TOL = 2e-4 of the largest factor entry is asserted, 1e-5 is what is
@@ -562,13 +562,14 @@ def test_lowrank_tile_edges(n, c, dtype):
 
 
 def test_lowrank_many_blocks_same_bits():
-    """Calls of at least 1024 blocks of tokens, whose waves take three of them in turn: the first and the last tensor of such a
-    call, ragged in tokens and channels, against the same tensors alone."""
-    shapes = [(97, 64), (389, 224), (1100, 96)]
-    descs = [cf.desc(*shapes[t % 3], cf.CF_BF16, 1, cf.CF_LOWRANK, R) for t in range(60)]
+    """Calls of 1792 blocks of tokens and more, whose waves take three of them in turn: the first and the last tensors of such a
+    call, ragged in tokens and channels, against the same tensors alone.  These have 640 blocks, the tall one between them 1250."""
+    shapes = [(97, 64), (389, 224), (1100, 96)] * 20
+    shapes[30] = (40000, 224)
+    descs = [cf.desc(*shapes[t], cf.CF_BF16, 1, cf.CF_LOWRANK, R) for t in range(60)]
     say("lowrank: 60 ragged tensors in a call of many blocks")
-    xs = [stream(*shapes[t % 3], cf.CF_BF16, 2, 800 + t) for t in range(60)]
-    q0 = [start_matrices(shapes[t % 3][1], 1, 900 + t)[0] for t in range(60)]
+    xs = [stream(*shapes[t], cf.CF_BF16, 2, 800 + t) for t in range(60)]
+    q0 = [start_matrices(shapes[t][1], 1, 900 + t)[0] for t in range(60)]
     pick = [0, 1, 2, 57, 58, 59]
     batch, alone = CodecSession(descs, cf.options(), device=DEV), CodecSession([descs[t] for t in pick], cf.options(), device=DEV)
     try:
