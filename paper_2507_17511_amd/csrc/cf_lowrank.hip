@@ -95,7 +95,7 @@ __device__ __forceinline__ void quantise_factor_row(const float (&f)[kRank], uin
 
 // An fp32 value is exactly the sum of three bf16 ones: high, its upper 16 bits, mid, those of what that leaves, and low, the
 // rest (8 significant bits each).  A product of two values is then nine products of pieces, that of the two low ones below 2^-30 of it
-// and left out.  The matrix cores form products of bf16 exactly and add 16 or 32 of them up where the fp32 instructions round every 2
+// and left out (of values below 2^-110 the low piece is cut at 2^-133).  The matrix cores form products of bf16 exactly and add 16 or 32 of them up where the fp32 instructions round every 2
 // or 4, in 8/16 or 10/16 of their time.
 // Errors against fp64, fp32 storage, rms (largest) x 2^-24, fp32 instructions / pieces.  U = A V, C = 64, 512, 3072:
 //   random operands, of the sum of the terms' sizes   0.50 (4.2), 0.75 (4.7), 1.40 (12.4) / 0.18 (1.4), 0.11 (0.7), 0.09 (0.6)
@@ -382,7 +382,7 @@ __device__ __forceinline__ uint8_t *lr_slice(const BatchView &v, const LaunchRan
 // small products, (high, mid) (high, 0) the leading one.  Per batch of 16 tokens each of the two starts from zero, and the vector units
 // add them up and to the sum, as in project.  Not with the form of half the length for the lone pieces: an accumulator that went
 // from v_mfma_f32_16x16x16_bf16 to v_mfma_f32_16x16x32_bf16 within two instructions came back wrong.
-// What bounds it, 57 x [4096, 3072] bf16, in a trace 608 us on average (550-698): the stream of x and recon, alone 550 in 128-channel
+// What bounds it, 57 x [4096, 3072] bf16, in a trace about 600 us on average (550-700): the stream of x and recon, alone 550 in 128-channel
 // stripes and 400-430 in wider ones.  A wave has one batch in registers; the next is asked for once the residual is formed, so that it is
 // in flight while the products are: one tensor 79 -> 56 us, 28 of fp32 570 -> 536, the 57 681 -> 608 (asked for after the products).
 constexpr int kBackThreads = 256;
@@ -391,7 +391,7 @@ constexpr int kBackEntries = kBackChannels * kRank;
 constexpr int kBackWaveChannels = kBackChannels / 2;
 
 template <int DT>
-__device__ __forceinline__ void lr_backproject_body(const BatchView &v, const LaunchRange &r, const TensorDev &d, const TensorPtrs &p, int t,
+__device__ __forceinline__ void lr_backproject_body(const BatchView &v, const LaunchRange &r, const TensorDev &d, const TensorPtrs &p,
                                                     int stripe, int share, float *sums, float *total)
 {
     const int lane = (int)threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -515,7 +515,7 @@ __global__ __launch_bounds__(kBackThreads, 2) void k_lr_backproject(BatchView v,
     const int stripe = (int)blockIdx.x % n_stripes, share = (int)blockIdx.x / n_stripes;
     if (share >= lr_shares(r, d)) return;                   // uniform over the workgroup: narrower or shorter than the largest tensor
     const TensorPtrs p = v.ptrs[t];
-    lr_backproject_body<DT>(v, r, d, p, t, stripe, share, sums, total);
+    lr_backproject_body<DT>(v, r, d, p, stripe, share, sums, total);
 }
 
 // ---------------------------------------------------------------- Q = orth(Z)
