@@ -23,6 +23,9 @@
  * All calls enqueue work on it and return without synchronising; buffers must
  * stay valid until the stream has passed that work.  A context is not
  * thread-safe: use it from one host thread at a time, on one stream at a time.
+ * (The single pass carries a bit per partial sum from one call to the next: calls of
+ * one context that overlapped in time all the same may have mixed them up, and the
+ * context has to be set up anew with cf_init.)
  *
  * Layouts (all dense, row-major, C contiguous; base pointers 16-byte aligned):
  *   x, recon : [N, C] of `dtype`
@@ -67,7 +70,8 @@
  * being captured into a HIP graph, uploads the whole table again, and after a
  * captured call the next call does too: a captured call is self-contained and may
  * be replayed at any time, as long as no other use of the context is in flight.
- * Warm-ups, receivers and senders without channel, rank-1 or low-rank tensors over
+ * Warm-ups, receivers, senders without channel, rank-1 or low-rank tensors, and senders
+ * of channel tensors alone that take the single pass, over
  * at most 8 tensors take their pointers along in the kernels' arguments and
  * neither read nor change the table.
  */
@@ -182,10 +186,9 @@ typedef struct {
  * Waiting in the single pass.  A workgroup normally finds the partial sums of its
  * stripe within microseconds, because the workgroups of a stripe are launched
  * next to each other.  It does not depend on that: a workgroup that has waited
- * for a partial sum for some milliseconds gives its item up (it has written
- * nothing but its own partial sum by then), and a second launch of the same
- * kernel, which is part of every call and normally finds nothing to do, does the
- * given-up items once all partial sums are there.  So the call finishes, with the
+ * for a partial sum for some milliseconds gives its item up for the time being (it has written
+ * nothing but its own partial sum by then), computes the missing partial sums itself from their
+ * operands, and starts its item again.  So the call finishes, with the
  * same bits, whatever else runs on the device and in whatever order workgroups
  * are started; it needs no co-residency and no cooperative launch.
  * cf_given_up_items tells how many items of the last call went that way.
@@ -197,7 +200,7 @@ typedef struct {
 #define CF_FLAG_TWO_KERNEL 0x2u
 #define CF_FLAG_FIXED_GRID 0x8u
 /* TESTING ONLY: workgroups of the single pass do not wait at all: an item whose stripe's partial
- * sums are not all there at the first look is given up and done by the second launch.  Slow;
+ * sums are not all there at the first look is given up, and its workgroup computes them itself.  Slow;
  * results unchanged. */
 #define CF_FLAG_TEST_NO_WAIT 0x100u
 /* CF_LOWRANK tensors of the context send their factors as 4-bit integers (Sec. 3.4 and App. D name INT4
@@ -282,12 +285,12 @@ int32_t cf_last_hip_error(const cf_ctx *ctx);
 
 /* Synchronises `stream`; CF_ERR_DEVICE with cf_last_hip_error() != 0 if that fails (a kernel
  * enqueued before it faulted), CF_ERR_DEVICE with cf_last_hip_error() == 0 if the library's own
- * consistency check on the device tripped (the second launch of a single pass found a partial sum
- * missing, which the design rules out); the context is then unusable. */
+ * consistency check on the device tripped (a workgroup of a single pass missed a partial sum that it
+ * had stored itself, which the design rules out); the context is then unusable. */
 cf_status cf_check_device(cf_ctx *ctx, void *stream);
 
 /* Synchronises `stream` and reports in *count how many items of the LAST single pass were given
- * up by their first workgroup and done by the second launch (see "Waiting in the single pass";
+ * up at first by their workgroup (see "Waiting in the single pass";
  * 0 in ordinary operation). */
 cf_status cf_given_up_items(cf_ctx *ctx, void *stream, uint32_t *count);
 

@@ -246,7 +246,7 @@ def cf_check_device(ctx, stream=None) -> None:
 
 
 def cf_given_up_items(ctx, stream=None) -> int:
-    """Synchronises the stream; -> items of the last single pass that were given up and done by the second launch."""
+    """Synchronises the stream; -> items of the last single pass whose workgroup gave up waiting and computed missing sums itself."""
     n = ctypes.c_uint32()
     _check(lib().cf_given_up_items(ctx, _addr(stream), ctypes.byref(n)), "cf_given_up_items", ctx)
     return int(n.value)

@@ -21,7 +21,7 @@ inline size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {
     size_t off_descs = 0, off_ptrs = 0, off_tile_prefix = 0, off_fin_prefix = 0, off_partials = 0;
-    size_t off_item_prefix = 0, off_item_tensor = 0, off_gave_up = 0, off_error = 0, off_p_partials = 0;
+    size_t off_item_prefix = 0, off_item_tensor = 0, off_item_state = 0, off_error = 0, off_p_partials = 0;
     std::vector<uint32_t> item_prefix;
     size_t n_items = 0;
     int32_t max_group_items = 0;   // largest reduction group of the single-pass path
@@ -339,8 +339,8 @@ cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &
     L.off_item_prefix = off;  off = align_up(off + sizeof(uint32_t) * (size_t)(n + 1));
     L.off_item_tensor = off;  off = align_up(off + sizeof(uint32_t) * (size_t)items);
     L.n_items = (size_t)items;
-    L.off_gave_up = off;      off = align_up(off + sizeof(uint32_t) * (size_t)items);
-    L.off_error = off;        off = align_up(off + sizeof(uint32_t) * 64);      // error word, and the give-up counter 128 bytes on
+    L.off_error = off;        off = align_up(off + sizeof(uint32_t) * 64);      // error word, and the last single pass's items 128 bytes on
+    L.off_item_state = off;   off = align_up(off + (size_t)items);     // one fill with the partials behind them
     L.off_p_partials = off;   off = align_up(off + p_partial_bytes);
     L.off_lr_slices = off;
     L.lr_slice_bytes = lowrank_slice_bytes(descs, n);
@@ -399,10 +399,17 @@ struct cf_ctx {
         v.item_prefix = reinterpret_cast<const uint32_t *>(ws + L.off_item_prefix);
         v.item_tensor = reinterpret_cast<const uint32_t *>(ws + L.off_item_tensor);
         v.error_flag = reinterpret_cast<uint32_t *>(ws + L.off_error);
-        v.gave_up_items = reinterpret_cast<uint32_t *>(ws + L.off_gave_up);
+        v.item_state = ws + L.off_item_state;
         v.workspace = ws;
         v.n_tensors = (int32_t)descs.size();
         return v;
+    }
+
+    // The single pass's item states and partials as before a first call: every sign the same (see cf_single_pass.hip).
+    hipError_t fresh_partials(hipStream_t s) const
+    {
+        if (L.n_items == 0) return hipSuccess;
+        return launch_fill_words(ws + L.off_item_state, kFreshPartials, (L.off_lr_slices - L.off_item_state) / sizeof(uint32_t), s);
     }
 
     LaunchRange range(int32_t first, int32_t count) const
@@ -411,6 +418,7 @@ struct cf_ctx {
         r.first = first;
         r.count = count;
         r.direct = nullptr;
+        r.direct_descs = L.dev.data() + first;
         r.tile_lo = L.tile_prefix[first];
         r.tile_hi = L.tile_prefix[first + count];
         r.ew_lo = L.ew_prefix[first];
@@ -422,7 +430,6 @@ struct cf_ctx {
         r.sp_xcd_major = 0;
         r.sp_wait_polls = kWaitPolls;
         r.sp_slim = L.sp_slim;
-        r.sp_redo = 0;
         r.item_lo = L.item_prefix[first];
         r.item_hi = L.item_prefix[first + count];
         r.only_group_scale = 0;
@@ -437,16 +444,6 @@ struct cf_ctx {
         r.lr_split = 1;
         r.lr_first_slot = 0;
         r.lr_slices_off = L.off_lr_slices;
-        r.p_partial_lo = ~(uint64_t)0;
-        r.p_partial_hi = 0;
-        for (int32_t t = first; t < first + count; ++t) {
-            const TensorDev &dv = L.dev[t];
-            if (dv.p_rows == 0) continue;
-            const uint64_t bytes = align_up((size_t)dv.p_n_rb * (size_t)dv.n_channels * sizeof(float));
-            if (dv.p_partial_off < r.p_partial_lo) r.p_partial_lo = dv.p_partial_off;
-            if (dv.p_partial_off + bytes > r.p_partial_hi) r.p_partial_hi = dv.p_partial_off + bytes;
-        }
-        if (r.p_partial_hi == 0) r.p_partial_lo = 0;
         int64_t lr_tensors = 0, lr_stripes = 0, lr_bf16_blocks = 0;
         for (int32_t t = first; t < first + count; ++t) {
             if (descs[t].dtype != descs[first].dtype) r.dts = 2;
@@ -492,6 +489,13 @@ struct cf_ctx {
         for (int32_t t = first; t < first + count; ++t)
             if (descs[t].scale == CF_SCALE_CHANNEL || descs[t].scale == CF_SCALE_RANK1) return true;
         return false;
+    }
+
+    bool range_all_channel(int32_t first, int32_t count) const
+    {
+        for (int32_t t = first; t < first + count; ++t)
+            if (descs[t].scale != CF_SCALE_CHANNEL) return false;
+        return true;
     }
 
     int range_lowrank_iters(int32_t first, int32_t count) const       // most subspace iterations any tensor asks for; -1 = no such tensor
@@ -597,6 +601,7 @@ cf_status make_ctx(cf_ctx **out, const cf_tensor_desc *descs, int32_t n_tensors,
                                     reinterpret_cast<uint32_t *>(ctx->ws + L.off_item_tensor), n_tensors, s);
     if (e == hipSuccess) e = launch_fill_words(ctx->ws + L.off_ptrs, 0u, sizeof(TensorPtrs) * (size_t)n_tensors / 4, s);
     if (e == hipSuccess) e = launch_fill_words(ctx->ws + L.off_error, 0u, 64, s);
+    if (e == hipSuccess) e = ctx->fresh_partials(s);
     if (e == hipSuccess && L.single_pass && L.max_group_items > 0) {
         int n_cu = 0;
         e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, ctx->device);
@@ -638,18 +643,8 @@ struct ProfileScope {      // a profiled call is exactly one entry-point call
 // Brings the workspace pointer table up to date for [first, first+count).
 // Arrays that an entry point does not take are passed as nullptr and keep
 // their last value.  Nothing is launched when no pointer changed.
-// The last batch of pointer sets of a call, left for the call's next kernel to write (see sync_ptrs).
-struct DeferredPtrs {
-    PtrChunk chunk;
-    TensorPtrs *dst = nullptr;
-    int n = 0;
-    DeferredPtrs() { std::memset(&chunk, 0, sizeof chunk); }
-};
-
-// defer: the caller's next launch is a kernel that can write one batch of pointer sets itself (k_reset_partials):
-// the last batch is handed back instead of launched.
 cf_status sync_ptrs(cf_ctx *ctx, int32_t first, int32_t count, const void *const *x, void *const *recon,
-                    void *const *err, void *const *codes, void *const *scales, hipStream_t s, DeferredPtrs *defer = nullptr)
+                    void *const *err, void *const *codes, void *const *scales, hipStream_t s)
 {
     bool changed = false;
     for (int32_t k = 0; k < count; ++k) {
@@ -685,12 +680,6 @@ cf_status sync_ptrs(cf_ctx *ctx, int32_t first, int32_t count, const void *const
         PtrChunk chunk;
         std::memset(&chunk, 0, sizeof chunk);
         for (int k = 0; k < m; ++k) chunk.p[k] = ctx->ptrs[lo + k0 + k];
-        if (defer && k0 + m == n) {     // the caller's next kernel takes this one along
-            defer->chunk = chunk;
-            defer->dst = table + lo + k0;
-            defer->n = m;
-            break;
-        }
         hipError_t e = launch(ctx, s, "k_upload_ptrs", [&] { return launch_upload_ptrs(chunk, table + lo + k0, m, s); });
         if (e != hipSuccess) return device_fail(ctx, e);       // the table counts as unknown: the next call uploads all of it
     }
@@ -807,33 +796,26 @@ cf_status run_sender(cf_ctx *ctx, int32_t first, int32_t count, const void *cons
     const bool worth_it = forced || (items >= 64u && ctx->L.min_channel_scale_tokens >= 256 &&
                                      (ctx->L.max_group_items <= ctx->L.sp_group_limit || small_call));
     // (a group larger than what the device holds at once would have its first workgroups wait for ones that cannot
-    // start before they leave: correct, they give up and the redo launch does them, but slow: such tensors take two kernels)
+    // start before they leave: correct, they give up and compute the missing sums, but slow: such tensors take two kernels)
     const bool single_pass = ctx->L.single_pass && grid >= ctx->L.max_group_items && grid >= 1 && r.item_hi > r.item_lo && worth_it;
-    // the call's pointers go to the table first; the single pass's first kernel takes the last batch of them along
-    DeferredPtrs defer;
     DirectPtrs direct;
-    if (count <= kDirectTensors && !ctx->range_has_channel(first, count) && ctx->range_lowrank_iters(first, count) < 0 &&
-        direct.take(r, x, recon, err, codes, reinterpret_cast<const void *const *>(scales))) {
+    // kernels that take their pointers as arguments: the row-local ones, and the single pass
+    const bool one_pass = single_pass && ctx->range_all_channel(first, count);
+    const bool is_direct = count <= kDirectTensors && (one_pass || !ctx->range_has_channel(first, count)) && ctx->range_lowrank_iters(first, count) < 0 &&
+                           direct.take(r, x, recon, err, codes, reinterpret_cast<const void *const *>(scales));
+    if (is_direct && !one_pass) {
         e = run_row_local(ctx, first, count, v, r, fused, true, s);
         return e == hipSuccess ? CF_OK : device_fail(ctx, e);
     }
-    if ((st = sync_ptrs(ctx, first, count, x, recon, err, codes, scales, s, single_pass ? &defer : nullptr)) != CF_OK) return st;
+    if (!is_direct && (st = sync_ptrs(ctx, first, count, x, recon, err, codes, scales, s)) != CF_OK) return st;
     if (single_pass) {
         // channel-scale tensors: one pass, the operands stay in registers across the scale reduction
-        e = launch(ctx, s, "k_reset_partials", [&] { return launch_reset_partials(v, r, defer.chunk, defer.dst, defer.n, s); });
-        if (e != hipSuccess) {
-            ctx->ptrs_synced = false;       // the batch that kernel was to write never reached the table
-            return device_fail(ctx, e);
-        }
         // measured on [N, 3072] bf16 batches: up to 4 row blocks per tensor a run of consecutive items per XCD is
         // 4-20 % faster (the stripes of a code row meet in one L2), from 6 on dealing them round the XCDs is 8-15 % faster
         r.sp_xcd_major = ctx->L.max_group_items <= 4;
         r.sp_wait_polls = (ctx->opts.flags & CF_FLAG_TEST_NO_WAIT) ? 0u : kWaitPolls;
         const bool one_shot = (ctx->opts.flags & CF_FLAG_FIXED_GRID) == 0;
-        e = launch(ctx, s, "k_single_pass", [&] { return launch_single_pass(v, r, ef, et, fused, ctx->L.sp_wide, grid, one_shot, false, s); });
-        if (e != hipSuccess) return device_fail(ctx, e);
-        // the items whose workgroup gave up waiting (normally none: the launch is empty)
-        e = launch(ctx, s, "k_single_pass_redo", [&] { return launch_single_pass(v, r, ef, et, fused, ctx->L.sp_wide, grid, one_shot, true, s); });
+        e = launch(ctx, s, "k_single_pass", [&] { return launch_single_pass(v, r, ef, et, fused, ctx->L.sp_wide, grid, one_shot, s); });
         if (e != hipSuccess) return device_fail(ctx, e);
         r.only_group_scale = 1;
         if ((e = run_row_local(ctx, first, count, v, r, fused, false, s)) != hipSuccess) return device_fail(ctx, e);
@@ -942,10 +924,18 @@ cf_status cf_given_up_items(cf_ctx *ctx, void *stream, uint32_t *count)
 {
     if (!ctx || !count) return CF_ERR_INVALID_ARG;
     hipError_t e = hipStreamSynchronize(static_cast<hipStream_t>(stream));
-    uint32_t n = 0;
-    if (e == hipSuccess)
-        e = hipMemcpy(&n, ctx->ws + ctx->L.off_error + sizeof(uint32_t) * kGaveUpWord, sizeof n, hipMemcpyDeviceToHost);
+    uint32_t items[2] = {0, 0};             // of the last single pass
+    if (e == hipSuccess) e = hipMemcpy(items, ctx->ws + ctx->L.off_error + sizeof(uint32_t) * kLastItemsWord, sizeof items, hipMemcpyDeviceToHost);
     if (e != hipSuccess) return device_fail(ctx, e);
+    uint32_t n = 0;
+    for (uint32_t at = items[0]; at < items[1] && items[1] <= ctx->L.n_items;) {
+        uint8_t state[4096];
+        const uint32_t m = std::min<uint32_t>(items[1] - at, sizeof state);
+        e = hipMemcpy(state, ctx->ws + ctx->L.off_item_state + at, m, hipMemcpyDeviceToHost);
+        if (e != hipSuccess) return device_fail(ctx, e);
+        for (uint32_t k = 0; k < m; ++k) n += state[k] & 1u;
+        at += m;
+    }
     *count = n;
     return CF_OK;
 }
@@ -1074,6 +1064,9 @@ cf_status cf_step_fused_static(const cf_tensor_desc *descs, int32_t n_tensors, c
         st = make_ctx(&ctx, descs, n_tensors, o, ws, kStaticScratchBytes, s);
         if (st != CF_OK) return st;
         for (auto &w : ctx->warm) w = 1;        // the caller vouches for recon and err
+    } else if (ctx->fresh_partials(s) != hipSuccess) {      // calls that overlapped against the rules spoil nothing but themselves
+        (void)hipGetLastError();
+        return CF_ERR_DEVICE;
     }
     return run_sender(ctx, 0, n_tensors, x, recon, err, codes, scales, stream, true);
 }

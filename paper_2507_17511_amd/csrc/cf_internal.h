@@ -51,8 +51,11 @@ constexpr int kTallGroupItems = 40;
 constexpr int kNarrowGroupLimit = 48;
 constexpr int kSlimGroupLimit = 38;
 constexpr int kSlimGroupLimitNaive = 24;
-constexpr int kGaveUpWord = 32;                             // 128 bytes behind the error word: how many items the call's first launch gave up
-constexpr int kRedoGrid = 512;                              // workgroups of the launch that does them
+constexpr int kLastItemsWord = 32;                          // 128 bytes behind the error word: the first item of the last single pass, and the one past its last
+
+// The single pass's partials carry the sign of their call in this bit; item states and partials are filled with the other word before a first call.
+constexpr uint32_t kPartialSign = 0x80000000u;
+constexpr uint32_t kFreshPartials = 0x80808080u;
 
 // Static description of one tensor; built at cf_init, lives in the workspace.
 struct alignas(16) TensorDev {
@@ -124,8 +127,8 @@ struct BatchView {
     const uint32_t *fin_prefix;     // [n_tensors + 1]
     const uint32_t *item_prefix;    // [n_tensors + 1] items of the single-pass path
     const uint32_t *item_tensor;    // [n_items] tensor of every item: one load where a search over the prefix would be seven
-    uint32_t *error_flag;           // set if the redo launch finds a partial missing (cannot happen); kGaveUpWord words on: the give-up counter
-    uint32_t *gave_up_items;        // [n_items] the items the first launch of a call gave up
+    uint32_t *error_flag;           // set if a partial is missing that a workgroup has stored itself (cannot happen); kLastItemsWord words on: the last call's items
+    uint8_t *item_state;            // [n_items] single-pass path: the sign (bit 7) of the item's partial in its last call, and in bit 0 whether it gave up waiting in it
     uint8_t *workspace;
     int32_t n_tensors;
 };
@@ -138,10 +141,8 @@ struct LaunchRange {
     uint32_t fin_lo, fin_hi;    // finalise blocks
     uint32_t item_lo, item_hi;  // single-pass items
     uint32_t sp_xcd_major;      // single-pass kernel: deal the items XCD-major (a run of consecutive items per XCD)
-    uint32_t sp_wait_polls;     // single-pass kernel: polls of a missing partial before the workgroup gives its item up
+    uint32_t sp_wait_polls;     // single-pass kernel: polls of a missing partial before the workgroup computes it itself
     uint32_t sp_slim;           // single-pass kernel: items of kStripeChannelsSlim channels (tall tensors)
-    uint32_t sp_redo;           // single-pass kernel: this is the launch over the given-up items
-    uint64_t p_partial_lo, p_partial_hi;    // workspace bytes holding the single-pass partials of the range
     int32_t dts;                // storage dtype of every tensor in the range (cf_dtype), or 2 if mixed
     int32_t only_group_scale;   // tiled encode: skip tensors the single-pass kernel covers
     int32_t naive;              // decode: recon_t = D instead of recon_{t-1} + D (CF_EF_NAIVE)
@@ -155,17 +156,32 @@ struct LaunchRange {
     uint32_t lr_first_slot;     // lr_slot of the range's first low-rank tensor
     uint64_t lr_slices_off;     // workspace offset of the shares after the first, [low-rank tensors][lr_split - 1][lr_max_channels][32] fp32
     const TensorPtrs *direct;   // host memory: the call's pointers, kDirectTensors sets at most, for kernels to take as arguments; null: they are in the table
+    const TensorDev *direct_descs;      // host memory: the descriptors of the call's tensors
 };
 
 // The same with the call's pointers along: what kernels of direct calls take in the range's place, in instances of their own
 // (a choice between the sets and the table within one instance cost the large kernels 3-5 %).
+// The sets begin 256 bytes into the arguments, behind the BatchView: 16 bytes earlier, receivers of 6 x [1024, 3072] took 17.87 instead of 17.55 us.
 struct DirectRange : LaunchRange {
+    uint64_t unused[3] = {};
     TensorPtrs sets[kDirectTensors];
     explicit DirectRange(const LaunchRange &r) : LaunchRange(r), sets()
     {
         for (int k = 0; k < r.count && k < kDirectTensors; ++k) sets[k] = r.direct[k];
     }
 };
+
+// The arguments of k_single_pass: direct calls bring their tensors' descriptors and pointers along.
+struct SinglePassArgs {
+    BatchView v;
+    LaunchRange r;
+    struct {
+        TensorPtrs sets[kDirectTensors];
+        TensorDev descs[kDirectTensors];
+    } direct;
+};
+
+static_assert(sizeof(BatchView) + sizeof(DirectRange) == 256 + sizeof(TensorPtrs) * kDirectTensors, "where the sets begin");
 
 // f(range) with the kind of range the call's kernels take
 template <class F> auto with_range(const LaunchRange &r, F &&f) { return r.direct ? f(DirectRange(r)) : f(r); }
@@ -263,8 +279,6 @@ int persistent_max_blocks_per_cu(int ef, int err_dtype, bool fused, bool wide, b
 // wide: items of kStripeChannelsWide channels (the layout's choice, fixed at cf_init); one_shot: a workgroup per
 // item, else `grid` workgroups that loop over the items
 hipError_t launch_single_pass(const BatchView &v, const LaunchRange &r, int ef, int err_dtype, bool fused, bool wide, int grid,
-                             bool one_shot, bool redo, hipStream_t s);
-// also writes `n` pointer sets of the call to the table (dst), which saves the call a launch of k_upload_ptrs; n may be 0
-hipError_t launch_reset_partials(const BatchView &v, const LaunchRange &r, const PtrChunk &chunk, TensorPtrs *dst, int n, hipStream_t s);
+                             bool one_shot, hipStream_t s);
 
 }  // namespace cf

@@ -22,25 +22,29 @@
 // appear and finishes the tree itself -> scales -> codes, error and
 // reconstruction straight from the registers.
 //
-// A partial is its own ready flag: the buffer is filled with a pattern no
-// partial can take before the kernel starts, and a reader fetches a slot again
-// until it has changed.  One store and one load per hop; no counter.
+// A partial is its own ready flag: it is no less than zero, and its sign bit, which it does not need, tells in which of two
+// alternating calls it was stored.  Every item keeps a byte in the workspace with the sign of its last call and turns it over
+// when it is done (a word each, whose lines come from memory one for four workgroups of an XCD, cost 114 x [4096, 3072] 15 us); the items of a group always run in the same calls, so they agree on it, the slots need no clearing between
+// calls, and a captured call can be replayed.  One store and one load per hop; no counter, no launch before the kernel.
 //
 // Forward progress does not depend on how the hardware schedules workgroups.
 // Items are numbered group-major and dealt to the workgroups in index order
 // (or, for short tensors, XCD-major: see the kernel), so the items of a group
 // start at about the same time and a waiter normally sees the partials within
 // microseconds.  But no workgroup waits for ever: one that has polled a slot
-// `sp_wait_polls` times in vain GIVES ITS ITEM UP.  Up to that point it has
-// written nothing but its own partial (codes, error and reconstruction are all
-// written after the wait), so it only appends the item to a list in the
-// workspace and goes on (or exits, which frees its slot for the workgroups the
-// others are waiting for).  Every workgroup publishes its partial before it
-// waits, so when the kernel has ended every partial of the call is there, and a
-// second, normally empty launch of the same kernel walks the list and does the
-// given-up items without any waiting.  The pass therefore always ends, on a
-// device shared with other kernels and with a dispatcher that does not go by
+// `sp_wait_polls` times in vain GIVES ITS ITEM UP for the time being and does the missing
+// items' sums itself, one after the other: it loads such an item's operands, publishes its partial, and then starts
+// its own item again, whose operands it has dropped.  Up to that point it has
+// written nothing but partials (codes, error and reconstruction are all
+// written after the wait).  The missing item may start meanwhile, and writes over its operands (error and reconstruction are
+// updated in place) once all partials of its group are there, its own among them: so the helper stores with a
+// compare-and-swap against the partial of the call before.  If that finds one, the item had written nothing yet and the helper
+// read what it should; if not, the item's own partial stands.  Both compute the same bits.  A workgroup helps each item of its
+// group once at most, so it always ends, on a device shared with other kernels and with a dispatcher that does not go by
 // index too, and the outputs are the same bits either way.
+#include <cstddef>
+#include <cstring>
+
 #include "cf_device.h"
 #include "cf_internal.h"
 
@@ -49,21 +53,29 @@ namespace {
 
 using namespace dev;
 
-__device__ __forceinline__ void publish(float *p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ float fetch(const float *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void publish(uint32_t *p, uint32_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ uint32_t fetch(const uint32_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
-// A partial that has not been published yet reads as this pattern: a negative NaN with every
-// mantissa bit set, which neither a sum of magnitudes nor a maximum of magnitudes can produce.
-constexpr uint32_t kUnpublished = 0xFFFFFFFFu;
+// What is the same for the whole workgroup and nobody writes while it is looked at, by way of the scalar cache.
+template <class T> __device__ __forceinline__ T scalar_load(uint64_t at)
+{
+    T out;
+    const __attribute__((address_space(4))) uint32_t *const from = (const __attribute__((address_space(4))) uint32_t *)at;
+    uint32_t words[sizeof(T) / 4];
+#pragma unroll
+    for (unsigned k = 0; k < sizeof(T) / 4; ++k) words[k] = from[k];
+    __builtin_memcpy(&out, words, sizeof(T));
+    return out;
+}
 
 constexpr int kPollBatch = 8;       // leaves fetched (and re-fetched) together
 
-// tree_over whose leaves are other workgroups' partials: a leaf that still reads as kUnpublished is
-// fetched again until its owner has stored it, at most max_polls times (then ok = false and the
+// tree_over whose leaves are other workgroups' partials: a leaf that does not have the call's sign yet is
+// fetched again until its owner has stored it, at most max_polls times (then `missing` is its number and the
 // result is meaningless).  The data word is its own ready flag, so a group needs no counter and no
 // second round trip.
 template <bool IS_MAX, int LV>
-__device__ __forceinline__ float tree_over_published(int n, const float *mine, int64_t stride, uint32_t max_polls, bool &ok)
+__device__ __forceinline__ float tree_over_published(int n, const uint32_t *mine, int64_t stride, uint32_t sign, uint32_t max_polls, int &missing)
 {
     constexpr int NB = kPollBatch;
     float stack[LV];
@@ -73,22 +85,29 @@ __device__ __forceinline__ float tree_over_published(int n, const float *mine, i
     int bpad = 1;
     while (bpad < nbatch) bpad <<= 1;
     for (int b = 0; b < bpad; ++b) {
-        float vals[NB];
+        uint32_t words[NB];         // nothing is done with them before all are asked for
 #pragma unroll
-        for (int u = 0; u < NB; ++u) vals[u] = (b * NB + u < n) ? fetch(mine + (int64_t)(b * NB + u) * stride) : 0.0f;
+        for (int u = 0; u < NB; ++u) words[u] = (b * NB + u < n) ? fetch(mine + (int64_t)(b * NB + u) * stride) : sign;
         uint32_t polls = 0;
         for (;;) {
             uint32_t pending = 0;
 #pragma unroll
-            for (int u = 0; u < NB; ++u) pending |= (__float_as_uint(vals[u]) == kUnpublished ? 1u : 0u) << u;
+            for (int u = 0; u < NB; ++u) pending |= ((words[u] ^ sign) >> 31) << u;
             if (pending == 0) break;
-            if (polls >= max_polls) { ok = false; break; }
+            if (polls >= max_polls) {
+                const int q = b * NB + __builtin_ctz(pending);
+                missing = q < missing ? q : missing;
+                break;
+            }
             __builtin_amdgcn_s_sleep(1);
 #pragma unroll
             for (int u = 0; u < NB; ++u)
-                if ((pending >> u) & 1u) vals[u] = fetch(mine + (int64_t)(b * NB + u) * stride);
+                if ((pending >> u) & 1u) words[u] = fetch(mine + (int64_t)(b * NB + u) * stride);
             ++polls;
         }
+        float vals[NB];
+#pragma unroll
+        for (int u = 0; u < NB; ++u) vals[u] = __uint_as_float(words[u] ^ sign);
         // balanced tree over the batch: neighbours, then neighbours of neighbours, ...
 #pragma unroll
         for (int w = 1; w < NB; w <<= 1)
@@ -104,12 +123,17 @@ __device__ __forceinline__ float tree_over_published(int n, const float *mine, i
 template <int SCH> struct alignas(16) Shared {
     float red[kPersistThreads / (SCH / kChunk)][SCH];       // 8 KB: level 2 of the tree; afterwards the waves' patches for whole-line stores
     float scale[SCH];
-    uint32_t ok;
+    int missing;                // the first item whose partial did not come in time, or kNoneMissing
+    uint32_t sign;              // of the call's partials: kept here for the end, where a load would wait for the stores before it
 };
+constexpr int kNoneMissing = 0x7fffffff;
+constexpr uint32_t kMaxHelps = 4096u;
 
+// help: do no more than store the partial of item rb, which is another workgroup's.  max_polls: of a missing partial.
+// Returns kNoneMissing when the item is done, else the item whose partial was missing; nothing but a partial has been written then.
 template <int DT, int BITS, int EF, int ET, bool FUSED, int SCH>
-__device__ __forceinline__ bool persist_item(const BatchView &v, const LaunchRange &r, const TensorDev &d, const TensorPtrs &p, int stripe,
-                                             int rb, Shared<SCH> &sh)
+__device__ __forceinline__ int persist_item(const BatchView &v, const TensorDev &d, const TensorPtrs &p, int stripe,
+                                            int rb, uint32_t sign, uint32_t max_polls, bool help, Shared<SCH> &sh)
 {
     constexpr int kStripeChannels = SCH, kStripeChunks = SCH / kChunk, kRowLanes = kPersistThreads / kStripeChunks;
     constexpr int RPT = single_pass_rows_per_lane(DT, EF);      // rows per lane
@@ -175,13 +199,17 @@ __device__ __forceinline__ bool persist_item(const BatchView &v, const LaunchRan
         dst[0] = lo;
         dst[1] = hi;
     }
-    if (tid == 0) sh.ok = 1u;
+    if (tid == 0) {
+        sh.missing = kNoneMissing;
+        sh.sign = sign;
+    }
     __syncthreads();
 
     // ---- level 2: tree over the row-lanes (consecutive RPT-row blocks); one lane per channel
     const bool owner = tid < kStripeChannels;
     const int64_t col = owner ? (int64_t)stripe * kStripeChannels + tid : C;
-    float *partial = reinterpret_cast<float *>(v.workspace + d.p_partial_off);
+    uint32_t *partial = reinterpret_cast<uint32_t *>(v.workspace + d.p_partial_off);
+    float res = 0.0f;
     if (owner) {
         float lanes[kRowLanes];
 #pragma unroll
@@ -190,22 +218,36 @@ __device__ __forceinline__ bool persist_item(const BatchView &v, const LaunchRan
         for (int w = 1; w < kRowLanes; w <<= 1)
 #pragma unroll
             for (int q = 0; q < kRowLanes; q += 2 * w) lanes[q] = comb<IS_MAX>(lanes[q], lanes[q + w]);
-        if (col < C) publish(partial + (int64_t)rb * C + col, lanes[0]);
+        res = lanes[0];
+        if (col < C && d.p_n_rb > 1) {
+            uint32_t *const slot = partial + (int64_t)rb * C + col;
+            const uint32_t word = (__float_as_uint(res) & ~kPartialSign) | sign;
+            if (!help) {
+                publish(slot, word);
+            } else {        // unless its owner, or another helper, has been faster
+                uint32_t old = fetch(slot);
+                if ((old & kPartialSign) != sign)
+                    (void)__hip_atomic_compare_exchange_strong(slot, &old, word, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
     }
+    if (help) return kNoneMissing;
     // The partials are agent-scope atomic stores (written through to where the other XCDs read them)
     // and every partial is its own ready flag: nothing to drain, no arrival to count.
 
-    // ---- level 3: the same tree continued over the group's item partials as they appear, then the scale
+    // ---- level 3: the same tree continued over the group's item partials as they appear, then the scale.  An item that is
+    // alone in its group has nothing to exchange.
     if (col < C) {
-        bool ok = true;
-        const float res = tree_over_published<IS_MAX, 10>(d.p_n_rb, partial + col, C, r.sp_wait_polls, ok);
+        int missing = kNoneMissing;
+        if (d.p_n_rb > 1) res = tree_over_published<IS_MAX, 10>(d.p_n_rb, partial + col, C, sign, max_polls, missing);
         const float s = IS_MAX ? res / 7.0f : res / (float)d.n_tokens;
         sh.scale[tid] = s;
-        if (!ok) sh.ok = 0u;                        // a partial did not come in time
-        if (ok && rb == 0) gmut<float>(p.scales)[col] = s;
+        if (missing != kNoneMissing) atomicMin(&sh.missing, missing);       // a partial did not come in time
+        else if (rb == 0) gmut<float>(p.scales)[col] = s;
     }
     __syncthreads();
-    if (!sh.ok) return false;                       // uniform: nothing of this item has been written but its partial
+    const int missing_item = __builtin_amdgcn_readfirstlane(sh.missing);
+    if (missing_item != kNoneMissing) return missing_item;
 
     // ---- a4-a8 from the registers.  z is formed again from the raw operands: keeping the first
     // phase's fp32 residuals alive across the wait would double the register footprint.
@@ -267,65 +309,83 @@ __device__ __forceinline__ bool persist_item(const BatchView &v, const LaunchRan
             if (DT == BF16) out.store_stream(p.recon, e); else out.store(p.recon, e);
         }
     }
-    return true;
+    return kNoneMissing;
 }
 
 template <int EF, int ET, bool FUSED, int SCH>
-__global__ __launch_bounds__(kPersistThreads, 2) void k_single_pass(BatchView v, LaunchRange r)
+__global__ __launch_bounds__(kPersistThreads, 2) void k_single_pass(SinglePassArgs args)
 {
+    const BatchView &v = args.v;
+    const LaunchRange &r = args.r;
     __shared__ Shared<SCH> sh;
     // Workgroups are handed to the 8 XCDs in turn (blockIdx.x % 8).  Taking item b in workgroup b runs the
     // consecutive items of a reduction group on different XCDs at the same time, and a tensor whose row
     // blocks number a multiple of 8 keeps each of them on one XCD, whose L2 then sees all stripes of a code row.  Short tensors
     // (few items per group) do better XCD-major, a run of consecutive items per XCD; the host chooses.
-    // The second launch of a call (r.sp_redo): the items the first one gave up, from the list it left.
-    uint32_t *const gave_up = v.error_flag + kGaveUpWord;
-    const uint32_t n_todo = r.sp_redo ? *gconst<uint32_t>(gave_up) : r.item_hi - r.item_lo;
+    const uint32_t n_items = r.item_hi - r.item_lo;
     uint32_t vb = blockIdx.x;
-    if (r.sp_xcd_major && !r.sp_redo) {
+    if (r.sp_xcd_major) {
         const uint32_t q = gridDim.x >> 3, rem = gridDim.x & 7u, xcd = blockIdx.x & 7u;
         vb = xcd * q + (xcd < rem ? xcd : rem) + (blockIdx.x >> 3);
     }
-    for (uint32_t k = vb; k < n_todo; k += gridDim.x) {
-        const uint32_t item = r.sp_redo ? v.gave_up_items[k] : r.item_lo + k;
-        const int t = (int)v.item_tensor[item];
-        const TensorDev d = v.descs[t];                             // by value: scalar registers, never re-read
-        const TensorPtrs p = v.ptrs[t];
+    uint32_t gave_up = 0u;          // how often, at this item
+    int at = -1;                    // the item of the group that this workgroup helps; -1: it does its own
+    for (uint32_t k = vb; k < n_items;) {
+        uint32_t item = __builtin_amdgcn_readfirstlane(r.item_lo + k);
+        asm volatile("" : "+s"(item));      // a second turn, which hardly ever comes, finds everything anew: kept for it, it would cost registers
+        uint64_t descs = (uint64_t)v.descs, sets = (uint64_t)v.ptrs;
+        uint32_t t;
+        if (r.direct) {             // both are among the arguments
+            t = 0;
+#pragma unroll
+            for (int q = 1; q < kDirectTensors; ++q) t += item >= args.direct.descs[q].p_item_begin ? 1u : 0u;
+            descs = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(SinglePassArgs, direct.descs);
+            sets = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(SinglePassArgs, direct.sets);
+        } else {
+            t = scalar_load<uint32_t>((uint64_t)(v.item_tensor + item));
+        }
+        TensorDev d = scalar_load<TensorDev>(descs + t * sizeof(TensorDev));      // by value: scalar registers, never re-read
+        TensorPtrs p = scalar_load<TensorPtrs>(sets + t * sizeof(TensorPtrs));
+        uint32_t state = scalar_load<uint32_t>((uint64_t)v.item_state + (item & ~3u));       // four items' bytes
+        asm volatile("" : "+s"(d.n_tokens), "+s"(d.n_channels), "+s"(d.n_chunks), "+s"(d.dtype), "+s"(d.bits), "+s"(d.p_partial_off), "+s"(d.p_rows),
+                          "+s"(d.p_n_rb), "+s"(d.p_item_begin), "+s"(p.x), "+s"(p.recon), "+s"(p.err), "+s"(p.codes), "+s"(p.scales), "+s"(state));  // one wait for all of them
         const uint32_t local = item - d.p_item_begin;               // group-major: stripe, then row block
         const int stripe = (int)(local / (uint32_t)d.p_n_rb);
-        const int rb = (int)(local % (uint32_t)d.p_n_rb);
-        bool done;
+        const int rb = at >= 0 ? at : (int)(local % (uint32_t)d.p_n_rb);
+        const uint32_t sign = ~(state << (24u - 8u * (item & 3u))) & kPartialSign;     // nobody else writes the byte, and this workgroup at the very end
+        const uint32_t polls = gave_up ? 0u : r.sp_wait_polls;
+        int missing;
         if (d.dtype == BF16) {
-            if (d.bits == 1) done = persist_item<BF16, 1, EF, ET, FUSED, SCH>(v, r, d, p, stripe, rb, sh);
-            else if (d.bits == 2) done = persist_item<BF16, 2, EF, ET, FUSED, SCH>(v, r, d, p, stripe, rb, sh);
-            else done = persist_item<BF16, 4, EF, ET, FUSED, SCH>(v, r, d, p, stripe, rb, sh);
+            if (d.bits == 1) missing = persist_item<BF16, 1, EF, ET, FUSED, SCH>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
+            else if (d.bits == 2) missing = persist_item<BF16, 2, EF, ET, FUSED, SCH>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
+            else missing = persist_item<BF16, 4, EF, ET, FUSED, SCH>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
         } else {
-            if (d.bits == 1) done = persist_item<F32, 1, EF, ET, FUSED, SCH>(v, r, d, p, stripe, rb, sh);
-            else if (d.bits == 2) done = persist_item<F32, 2, EF, ET, FUSED, SCH>(v, r, d, p, stripe, rb, sh);
-            else done = persist_item<F32, 4, EF, ET, FUSED, SCH>(v, r, d, p, stripe, rb, sh);
+            if (d.bits == 1) missing = persist_item<F32, 1, EF, ET, FUSED, SCH>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
+            else if (d.bits == 2) missing = persist_item<F32, 2, EF, ET, FUSED, SCH>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
+            else missing = persist_item<F32, 4, EF, ET, FUSED, SCH>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
         }
-        if (!done && threadIdx.x == 0) {
-            if (r.sp_redo) {        // cannot happen: every partial was published before the first launch ended
-                __hip_atomic_store(v.error_flag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            } else {
-                const uint32_t slot = __hip_atomic_fetch_add(gave_up, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                *gmut<uint32_t>(v.gave_up_items + slot) = item;
+        missing = __builtin_amdgcn_readfirstlane(missing);      // it is the same for all, which the compiler does not see
+        __syncthreads();            // the shared arrays are used again
+        if (at >= 0) {              // helped; now its own item again
+            at = -1;
+            continue;
+        }
+        if (missing != kNoneMissing) {
+            at = missing;
+            if (++gave_up <= kMaxHelps) continue;       // always: each turn brings a partial that was missing, and no group has that many
+            if (threadIdx.x == 0) __hip_atomic_store(v.error_flag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if (threadIdx.x == 0) {
+            *gmut<uint8_t>(v.item_state + r.item_lo + k) = (uint8_t)(sh.sign >> 24 | (gave_up ? 1u : 0u));
+            if (k == 0) {               // which items the call had, for cf_given_up_items
+                *gmut<uint32_t>(v.error_flag + kLastItemsWord) = r.item_lo;
+                *gmut<uint32_t>(v.error_flag + kLastItemsWord + 1) = r.item_hi;
             }
         }
-        __syncthreads();            // a looping workgroup reuses the shared arrays for its next item
+        at = -1;
+        gave_up = 0u;
+        k += gridDim.x;
     }
-}
-
-// Every partial starts a call as "unpublished" (a fill kernel, so the call can be captured in a graph).  The
-// first kernel of a single pass also takes the call's last batch of device pointers to the table (see
-// k_upload_ptrs): one launch fewer per call.
-__global__ void k_reset_partials(u32x4 *words, uint64_t n_vec, uint32_t *gave_up, PtrChunk chunk, TensorPtrs *dst, int n)
-{
-    if (blockIdx.x == 0 && threadIdx.x == 0) *gmut<uint32_t>(gave_up) = 0u;        // the list of given-up items is empty
-    if (blockIdx.x == 0 && (int)threadIdx.x < n) dst[threadIdx.x] = chunk.p[threadIdx.x];
-    const u32x4 fill = (u32x4)(kUnpublished);
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_vec; i += (uint64_t)gridDim.x * blockDim.x)
-        *gmut<u32x4>(words + i) = fill;
 }
 
 template <int EF, int ET, bool FUSED, int SCH> const void *persistent_fn() { return reinterpret_cast<const void *>(&k_single_pass<EF, ET, FUSED, SCH>); }
@@ -360,38 +420,33 @@ int persistent_max_blocks_per_cu(int ef, int err_dtype, bool fused, bool wide, b
     return n;
 }
 
-hipError_t launch_reset_partials(const BatchView &v, const LaunchRange &r, const PtrChunk &chunk, TensorPtrs *dst, int n, hipStream_t s)
-{
-    static_assert(kMaxUploadTensors <= 256, "one block of k_reset_partials writes the pointer sets");
-    const bool none = r.p_partial_hi <= r.p_partial_lo;
-    if (none && n == 0) return hipSuccess;
-    const uint64_t n_vec = none ? 0 : (r.p_partial_hi - r.p_partial_lo) / 16;      // offsets are multiples of 256
-    const uint64_t want = n_vec == 0 ? 1 : (n_vec + 255) / 256;
-    hipLaunchKernelGGL(k_reset_partials, dim3((unsigned)(want < 2048 ? want : 2048)), dim3(256), 0, s,
-                       reinterpret_cast<u32x4 *>(v.workspace + r.p_partial_lo), n_vec, v.error_flag + kGaveUpWord, chunk, dst, n);
-    return hipGetLastError();
-}
-
 // one_shot: one workgroup per item instead of a smaller grid whose workgroups loop over the items.
 // A workgroup that loops has to drain its stores before its next loads count as returned (the loads and
 // stores of a wave share one in-order counter); one that exits leaves the draining to the memory system
 // while the next workgroup already loads: measured faster by 15 % (114 x [4096, 3072] bf16: 2.65 against 3.04 ms).  Neither form needs co-residency to
 // finish (see the top of the file); the looping grid is for callers who share the device with other work
-// and want the codec to hold a fixed number of workgroup slots.  redo: the second launch of a call, over
-// the items the first one gave up (kRedoGrid workgroups; all of them leave at once when the list is empty).
+// and want the codec to hold a fixed number of workgroup slots.
 hipError_t launch_single_pass(const BatchView &v, const LaunchRange &r, int ef, int err_dtype, bool fused, bool wide, int grid,
-                             bool one_shot, bool redo, hipStream_t s)
+                             bool one_shot, hipStream_t s)
 {
     if (r.item_hi == r.item_lo) return hipSuccess;
     uint32_t items = r.item_hi - r.item_lo;
     if ((uint32_t)grid > items) grid = (int)items;
     if (grid < 1) grid = 1;
-    BatchView vv = v;
-    LaunchRange rr = r;
-    rr.sp_redo = redo ? 1u : 0u;
-    if (redo) rr.sp_wait_polls = 0u;        // every partial is there; nothing to wait for
-    const uint32_t n_wg = redo ? (items < (uint32_t)kRedoGrid ? items : (uint32_t)kRedoGrid) : one_shot ? items : (uint32_t)grid;
-    void *args[] = {&vv, &rr};
+    const uint32_t n_wg = one_shot ? items : (uint32_t)grid;
+    SinglePassArgs a;
+    a.v = v;
+    a.r = r;
+    std::memset(static_cast<void *>(&a.direct), 0, sizeof a.direct);
+    for (int k = 0; r.direct && k < kDirectTensors; ++k) {
+        if (k < r.count) {
+            a.direct.sets[k] = r.direct[k];
+            a.direct.descs[k] = r.direct_descs[k];
+        } else {
+            a.direct.descs[k].p_item_begin = ~0u;       // behind every item
+        }
+    }
+    void *args[] = {&a};
     return hipLaunchKernel(pick(ef, err_dtype, fused, wide, r.sp_slim != 0), dim3(n_wg), dim3(kPersistThreads), args, 0, s);
 }
 

@@ -88,17 +88,11 @@ hipError_t launch_lr_quant_u(const BatchView &, const LaunchRange &, hipStream_t
 hipError_t launch_lr_encode(const BatchView &, const LaunchRange &, int, bool, hipStream_t) { note("k_lr_apply"); return hipSuccess; }
 hipError_t launch_lr_decode(const BatchView &, const LaunchRange &r, hipStream_t) { take_direct(r); note("k_lr_apply"); return hipSuccess; }
 int persistent_max_blocks_per_cu(int, int, bool, bool, bool slim) { g_occupancy_slim = slim; return 2; }
-hipError_t launch_single_pass(const BatchView &, const LaunchRange &r, int, int, bool, bool, int, bool, bool redo, hipStream_t)
+hipError_t launch_single_pass(const BatchView &, const LaunchRange &r, int, int, bool, bool, int, bool, hipStream_t)
 {
+    take_direct(r);
     g_single_pass_slim = r.sp_slim != 0;
-    note(redo ? "k_single_pass_redo" : "k_single_pass");
-    return hipSuccess;
-}
-hipError_t launch_reset_partials(const BatchView &, const LaunchRange &, const PtrChunk &chunk, TensorPtrs *dst, int n, hipStream_t)
-{
-    if (n > 0) note("ptrs_in_reset");       // the call's last batch of pointer sets rides along
-    note("k_reset_partials");
-    if (n > 0) std::memcpy(dst, chunk.p, sizeof(TensorPtrs) * (size_t)n);
+    note("k_single_pass");
     return hipSuccess;
 }
 hipError_t static_scratch(void **ptr)

@@ -1,0 +1,74 @@
+"""Calls of one context after one another: the single pass carries a bit per partial sum from one call to the next, so
+which tensors a call covers, by which route their pointers come, and whether its workgroups wait must not matter."""
+import pytest
+import torch
+
+import paper_2507_17511_amd as cf
+from helpers import drift_stream
+from paper_2507_17511_amd.session import CodecSession
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def say(msg):
+    print(msg, flush=True)
+
+
+@pytest.mark.parametrize("flags", [0, cf.CF_FLAG_FIXED_GRID, cf.CF_FLAG_TEST_NO_WAIT])
+@pytest.mark.parametrize("ef", [cf.CF_EF_RECON, cf.CF_EF_OFF])
+def test_calls_over_changing_ranges(ef, flags):
+    """Ten tensors, groups of one item to six: whole batches by the table of pointers, parts with their pointers as
+    arguments (at most eight tensors), one tensor alone, odd and even numbers of calls for each tensor; every output
+    bit for bit what the two-kernel path gives in the same sequence."""
+    shapes = [(1500, 1096), (700, 520), (1, 8), (257, 256), (256, 264), (129, 72), (1030, 512), (300, 3072), (64, 64), (511, 1032)]
+    descs = [cf.desc(n, c, cf.CF_F32 if t % 4 == 1 else cf.CF_BF16, (1, 2, 4)[t % 3], cf.CF_SCALE_CHANNEL) for t, (n, c) in enumerate(shapes)]
+    streams = [drift_stream((d.n_tokens, d.n_channels), d.dtype, steps=4, seed=910 + t, device=DEV) for t, d in enumerate(descs)]
+    one = CodecSession(descs, cf.options(ef=ef, flags=cf.CF_FLAG_SINGLE_PASS | flags), device=DEV)
+    two = CodecSession(descs, cf.options(ef=ef, flags=cf.CF_FLAG_TWO_KERNEL), device=DEV)
+    try:
+        for sess in (one, two):
+            sess.warmup([s[0] for s in streams])
+        for k, (first, count) in enumerate([(0, 10), (0, 3), (1, 9), (7, 1), (7, 1), (0, 8), (2, 8), (0, 10), (9, 1), (0, 10)]):
+            x = [s[1 + k % 3] for s in streams]
+            for sess in (one, two):
+                sess.step_fused(x[first:first + count], first, count)
+            cf.cf_check_device(one.ctx, one.stream_handle)
+            say(f"ef={ef} flags={flags} call {k}: tensors {first}..{first + count - 1}, {cf.cf_given_up_items(one.ctx, one.stream_handle)} items given up")
+            for t in range(len(descs)):
+                for name in ("codes", "scales", "recon", "err"):
+                    a, b = getattr(one, name)[t], getattr(two, name)[t]
+                    assert torch.equal(a.view(torch.uint8).reshape(-1), b.view(torch.uint8).reshape(-1)), f"call {k}: {name}[{t}]"
+    finally:
+        one.close()
+        two.close()
+
+
+def test_small_call_replays_from_a_graph():
+    """A captured call that carries its pointers: replays and eager calls in turn, against an eager context."""
+    descs = [cf.desc(1024, 512, cf.CF_BF16, 2, cf.CF_SCALE_CHANNEL), cf.desc(900, 384, cf.CF_BF16, 1, cf.CF_SCALE_CHANNEL)]
+    streams = [drift_stream((d.n_tokens, d.n_channels), d.dtype, steps=8, seed=950 + t, device=DEV) for t, d in enumerate(descs)]
+    graphed, eager = (CodecSession(descs, cf.options(flags=cf.CF_FLAG_SINGLE_PASS), device=DEV) for _ in range(2))
+    try:
+        x = [s[0].clone() for s in streams]
+        for sess in (graphed, eager):
+            sess.warmup(x)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            graphed.step_fused(x)
+        for k in range(1, 8):
+            for t in range(len(descs)):
+                x[t].copy_(streams[t][k])
+            if k in (3, 4):
+                graphed.step_fused(x)
+            else:
+                g.replay()
+            eager.step_fused([s[k] for s in streams])
+            torch.cuda.synchronize()
+            for t in range(len(descs)):
+                for name in ("codes", "scales", "recon", "err"):
+                    assert torch.equal(getattr(graphed, name)[t], getattr(eager, name)[t]), f"step {k}: {name}[{t}]"
+    finally:
+        graphed.close()
+        eager.close()
