@@ -170,11 +170,12 @@ typedef struct {
  * CF_SCALE_CHANNEL tensor of a context without CF_SCALE_RANK1 tensors, in every
  * error-feedback mode.  Otherwise one kernel reduces and a second one, which
  * reads the operands again, writes the codes.  Results are bit-identical either
- * way.  By default a call takes the single pass where it applies, every
- * channel-scale tensor of the context has at least 256 tokens, the call covers at
- * least 64 items, and either no stripe has too many items or the device holds the
- * items of the call at once (512 on MI355X): it is about 30 % faster on MI355X at the sizes of the paper's models,
- * slower on tiny batches, and slower than two kernels on large ones where more
+ * way.  By default a call takes the single pass where it applies and the device holds the
+ * items of the call at once (512 on MI355X); larger calls where no stripe has too many
+ * items and the tensors fill a third of theirs: it is about 30 % faster on MI355X at the
+ * sizes of the paper's models, and twice as fast on tiny calls of at most 8 tensors, which are
+ * one launch of smaller items; it is slower than two kernels on large calls over
+ * tensors that leave most of an item empty, and on those where more
  * workgroups have to agree on a scale.  Contexts of mostly tall tensors (more than
  * 40 of the items above: 10240 tokens of bf16), and those with one of more than
  * 48, have items of twice the rows and half the channels and take up to 38 of them

@@ -29,13 +29,19 @@ struct Layout {
     bool sp_slim = false;          // ... kStripeChannelsSlim channels wide (tall tensors)
     int32_t sp_group_limit = 0;    // larger groups take two kernels by default, but for small calls
     bool single_pass = false;      // every channel-scale tensor has single-pass geometry
+    // Short items: calls whose items leave the device half empty take ones a quarter as tall, kernels of their own with a
+    // quarter of the code, which the first workgroup of a CU has to wait for.  Those tensors have a second geometry, with partials and item
+    // states of its own.  Sent layer by layer, us, items as tall as in large calls / half / a quarter: 2 x [1024, 3072] bf16 (192 items) 18.1 / 16.2 / 14.6,
+    // [2048, 3072] (192) 20.5 / 16.7 / 16.6, [512, 512] (8) 17.1 / 11.3 / 9.6; 2 x [2048, 3072] (384) 28.3 / 25.5 / 31.0, [4096, 3072] (384)
+    // 28.6 / 26.9 / 31.9: the line is what the device holds at once.
+    std::vector<TensorDev> short_dev;           // p_rows = 0: none
+    size_t off_short_state = 0, n_short_items = 0;
     size_t off_lr_slices = 0, lr_slice_bytes = 0;       // slices of the low-rank back-projection, shared by the tensors of a call
     size_t total = 0;
     std::vector<TensorDev> dev;
     std::vector<uint32_t> tile_prefix, fin_prefix, ew_prefix, dec_prefix;
     size_t off_ew_prefix = 0, off_dec_prefix = 0;
     bool any_channel = false, any_rank1 = false, any_lowrank = false;
-    int64_t min_channel_scale_tokens = INT64_MAX;
 };
 
 cf_status check_opts(const cf_options *o, cf_options &out)
@@ -309,7 +315,6 @@ cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &
             partial_bytes += align_up((size_t)d.n_tokens * (size_t)v.n_colblocks * sizeof(float));
         }
         L.item_prefix[t] = (uint32_t)items;
-        if (d.scale == CF_SCALE_CHANNEL && d.n_tokens < L.min_channel_scale_tokens) L.min_channel_scale_tokens = d.n_tokens;
         if (d.scale == CF_SCALE_CHANNEL && L.single_pass) {
             v.p_rows = narrow_item_rows(d.dtype) * kStripeChannels / stripe_channels;
             v.p_n_rb = (int32_t)((d.n_tokens + v.p_rows - 1) / v.p_rows);
@@ -341,9 +346,37 @@ cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &
     L.n_items = (size_t)items;
     L.off_error = off;        off = align_up(off + sizeof(uint32_t) * 64);      // error word, and the last single pass's items 128 bytes on
     L.off_item_state = off;   off = align_up(off + (size_t)items);     // one fill with the partials behind them
-    L.off_p_partials = off;   off = align_up(off + p_partial_bytes);
-    L.off_lr_slices = off;
     L.lr_slice_bytes = lowrank_slice_bytes(descs, n);
+    size_t short_bytes = 0, short_items = 0;
+    L.short_dev = L.dev;
+    for (TensorDev &v : L.short_dev) {
+        const int64_t rows = kPersistThreads / (kShortStripeChannels / kChunk) * single_pass_rows_per_lane(v.dtype, o.ef) / kShortFraction;
+        const int64_t rb = (v.n_tokens + rows - 1) / rows, stripes = (v.n_channels + kShortStripeChannels - 1) / kShortStripeChannels;
+        const bool fits = v.p_rows > 0 && o.ef == CF_EF_RECON && rb <= kShortGroupLimit && rb * stripes <= kShortItems;
+        v.p_rows = fits ? (int32_t)rows : 0;
+        if (!fits) continue;
+        v.p_n_rb = (int32_t)rb;
+        v.p_n_stripes = (int32_t)stripes;
+        v.p_item_begin = (uint32_t)short_items;
+        v.p_partial_off = short_bytes;                      // relative; rebased below
+        short_bytes += align_up((size_t)rb * (size_t)v.n_channels * sizeof(float));
+        short_items += (size_t)(rb * stripes);
+    }
+    {   // nor do tensors outgrow the static scratch because of them
+        const size_t without = align_up(off + p_partial_bytes), with = align_up(align_up(off + short_items) + p_partial_bytes) + short_bytes;
+        if (without <= kStaticScratchBytes && with + L.lr_slice_bytes > kStaticScratchBytes) {
+            short_items = 0;
+            for (TensorDev &v : L.short_dev) v.p_rows = 0;
+        }
+    }
+    L.n_short_items = short_items;
+    L.off_short_state = off;  off = align_up(off + short_items);
+    L.off_p_partials = off;   off = align_up(off + p_partial_bytes);
+    if (short_items > 0) {
+        for (TensorDev &v : L.short_dev) v.p_partial_off += off;
+        off += short_bytes;
+    }
+    L.off_lr_slices = off;
     // no tensors outgrow the static scratch because of the slices: there are fewer then, and the sums are the same
     if (off <= kStaticScratchBytes) L.lr_slice_bytes = std::min(L.lr_slice_bytes, (kStaticScratchBytes - off) / kAlign * kAlign);
     off += L.lr_slice_bytes;
@@ -430,6 +463,7 @@ struct cf_ctx {
         r.sp_xcd_major = 0;
         r.sp_wait_polls = kWaitPolls;
         r.sp_slim = L.sp_slim;
+        r.sp_short = 0;
         r.item_lo = L.item_prefix[first];
         r.item_hi = L.item_prefix[first + count];
         r.only_group_scale = 0;
@@ -465,6 +499,23 @@ struct cf_ctx {
             while (lowrank_slice_bytes_of(r.lr_max_channels, r.lr_split, lr_tensors) > L.lr_slice_bytes) r.lr_split /= 2;
         }
         return r;
+    }
+
+    // Whether short items serve the call: `r` and `v` are theirs then.
+    bool take_short(int32_t first, int32_t count, LaunchRange &r, BatchView &v) const
+    {
+        uint32_t items = 0;
+        for (int32_t t = first; t < first + count; ++t) {
+            if (L.n_short_items == 0 || L.short_dev[t].p_rows == 0) return false;
+            items += (uint32_t)(L.short_dev[t].p_n_rb * L.short_dev[t].p_n_stripes);
+        }
+        if (items > (uint32_t)kShortItems) return false;
+        r.sp_short = 1;
+        r.item_lo = L.short_dev[first].p_item_begin;
+        r.item_hi = r.item_lo + items;
+        r.direct_descs = L.short_dev.data() + first;
+        v.item_state = ws + L.off_short_state;
+        return true;
     }
 
     // anything for k_encode (with_channel: channel-scale tensors too; not when the single-pass kernel took them)
@@ -784,17 +835,25 @@ cf_status run_sender(cf_ctx *ctx, int32_t first, int32_t count, const void *cons
     const int ef = ctx->opts.ef, et = ctx->opts.err_dtype;
     hipError_t e;
     const int grid = ctx->persist_grid[et == CF_BF16 ? 1 : 0][fused ? 1 : 0];
-    // unless asked for: not for tiny batches (the wait chain costs more than a second read) nor for short tensors
-    // (an item is 128 or 256 rows tall: most of its lanes would idle)
     const bool forced = (ctx->opts.flags & CF_FLAG_SINGLE_PASS) != 0;
-    // nor for very tall ones (see sp_group_limit) in calls of more than a round of workgroups, 512 on the whole MI355X (us, single pass / two kernels:
+    // unless asked for, not for very tall tensors (see sp_group_limit) in calls of more than a round of workgroups, 512 on the whole MI355X (us, single pass / two kernels:
     // one tensor of [32768, 3072], 3072 items, 303 / 259, of [65536, 1024], 2048 items, 249 / 177; 4 x [20000, 128], 320
     // items, 34 / 48; one [65536, 128], 256 items in groups of 128, 35 / 52, [131072, 64], 256 in one group, 46 / 60, [40000,
     // 384], 474 in groups of 79, 48 / 81, [30000, 256] fp32 39 / 59)
     const uint32_t items = r.item_hi - r.item_lo;
     const bool small_call = grid > 0 && items <= (uint32_t)grid;
-    const bool worth_it = forced || (items >= 64u && ctx->L.min_channel_scale_tokens >= 256 &&
-                                     (ctx->L.max_group_items <= ctx->L.sp_group_limit || small_call));
+    // nor, in calls of more than a round, for tensors so short that their items are mostly empty.  Single pass / two kernels, us, wide items of
+    // 128 rows of bf16: 114 x [16, 3072] 48.9 / 33.6, 57 x [40, 3072] 32.3 / 31.6, x [77, 3072] 37.2 / 46.6, 114 x [100, 3072] 85 / 101; 64 rows of
+    // fp32: 114 x [16, 3072] 34.7 / 41.3, 57 x [77, 3072] 69.5 / 68.4.  Calls of a round, whatever their shape: 114 x [8, 1024] bf16 (456 items) 20.8 / 25.2, 30 x
+    // [128, 512] (60) 20.2 / 20.2, 9 x [64, 256] (9) 18.3 / 19.5; with their pointers along 8 x [64, 256] 9.6 / 19.3, [1, 8] 9.9 / 19.2, [4096, 256] 14.1 / 17.0,
+    // [16384, 64] 20.0 / 23.1 (what Python adds to a call, some 9 us, hides what the kernel takes below that).
+    int64_t filled = 0, room = 0;
+    for (int32_t t = first; t < first + count; ++t)
+        if (ctx->L.dev[t].p_rows > 0) {
+            filled += ctx->L.dev[t].n_tokens;
+            room += (int64_t)ctx->L.dev[t].p_n_rb * ctx->L.dev[t].p_rows;
+        }
+    const bool worth_it = forced || small_call || (ctx->L.max_group_items <= ctx->L.sp_group_limit && 3 * filled >= room);
     // (a group larger than what the device holds at once would have its first workgroups wait for ones that cannot
     // start before they leave: correct, they give up and compute the missing sums, but slow: such tensors take two kernels)
     const bool single_pass = ctx->L.single_pass && grid >= ctx->L.max_group_items && grid >= 1 && r.item_hi > r.item_lo && worth_it;
@@ -807,12 +866,13 @@ cf_status run_sender(cf_ctx *ctx, int32_t first, int32_t count, const void *cons
         e = run_row_local(ctx, first, count, v, r, fused, true, s);
         return e == hipSuccess ? CF_OK : device_fail(ctx, e);
     }
+    if (is_direct && !(ctx->opts.flags & CF_FLAG_FIXED_GRID)) ctx->take_short(first, count, r, v);
     if (!is_direct && (st = sync_ptrs(ctx, first, count, x, recon, err, codes, scales, s)) != CF_OK) return st;
     if (single_pass) {
         // channel-scale tensors: one pass, the operands stay in registers across the scale reduction
         // measured on [N, 3072] bf16 batches: up to 4 row blocks per tensor a run of consecutive items per XCD is
         // 4-20 % faster (the stripes of a code row meet in one L2), from 6 on dealing them round the XCDs is 8-15 % faster
-        r.sp_xcd_major = ctx->L.max_group_items <= 4;
+        r.sp_xcd_major = !r.sp_short && ctx->L.max_group_items <= 4;
         r.sp_wait_polls = (ctx->opts.flags & CF_FLAG_TEST_NO_WAIT) ? 0u : kWaitPolls;
         const bool one_shot = (ctx->opts.flags & CF_FLAG_FIXED_GRID) == 0;
         e = launch(ctx, s, "k_single_pass", [&] { return launch_single_pass(v, r, ef, et, fused, ctx->L.sp_wide, grid, one_shot, s); });
@@ -924,14 +984,15 @@ cf_status cf_given_up_items(cf_ctx *ctx, void *stream, uint32_t *count)
 {
     if (!ctx || !count) return CF_ERR_INVALID_ARG;
     hipError_t e = hipStreamSynchronize(static_cast<hipStream_t>(stream));
-    uint32_t items[2] = {0, 0};             // of the last single pass
+    uint32_t items[3] = {0, 0, 0};          // of the last single pass, and whether they were short ones
     if (e == hipSuccess) e = hipMemcpy(items, ctx->ws + ctx->L.off_error + sizeof(uint32_t) * kLastItemsWord, sizeof items, hipMemcpyDeviceToHost);
     if (e != hipSuccess) return device_fail(ctx, e);
     uint32_t n = 0;
-    for (uint32_t at = items[0]; at < items[1] && items[1] <= ctx->L.n_items;) {
+    const size_t off_state = items[2] ? ctx->L.off_short_state : ctx->L.off_item_state;
+    for (uint32_t at = items[0]; at < items[1] && items[1] <= (items[2] ? ctx->L.n_short_items : ctx->L.n_items);) {
         uint8_t state[4096];
         const uint32_t m = std::min<uint32_t>(items[1] - at, sizeof state);
-        e = hipMemcpy(state, ctx->ws + ctx->L.off_item_state + at, m, hipMemcpyDeviceToHost);
+        e = hipMemcpy(state, ctx->ws + off_state + at, m, hipMemcpyDeviceToHost);
         if (e != hipSuccess) return device_fail(ctx, e);
         for (uint32_t k = 0; k < m; ++k) n += state[k] & 1u;
         at += m;

@@ -41,6 +41,12 @@ constexpr int kStripeChannelsSlim = kStripeChannels / 2;    // 64
 // recon, half as many of fp32, half as many again when the error buffer is an operand too (CF_EF_LITERAL = 1,
 // CF_EF_OFF = 2).  Measured on 114 x [4096, 3072] bf16 (two waves per SIMD): 16 rows 2.65 ms; 8 rows at three
 // waves per SIMD 2.97 ms, at four (spills) 4.8 ms.  dtype: cf_dtype (CF_F32 = 0).
+// Short items, of calls that leave most of the device idle otherwise, have a quarter of them and are 64 channels wide (128 channels, 32 rows to
+// 64 of bf16 and groups of twice the items: [4096, 512] 14.9 us against 12.3, 2 x [1024, 3072] 15.3 / 14.7, 8 x [512, 1024] 11.8 / 12.3); see Layout::short_dev.
+constexpr int kShortFraction = 4;
+constexpr int kShortStripeChannels = 64;
+constexpr int kShortItems = 1024;                           // the most of a call: four workgroups a CU of the MI355X
+constexpr int kShortGroupLimit = 64;                        // the most of a group
 constexpr int single_pass_rows_per_lane(int dtype, int ef) { return 16 / (dtype == 0 ? 2 : 1) / ((ef == 1 || ef == 2) ? 2 : 1); }
 // A workgroup polls a missing partial this many times (a microsecond or two each) before it gives its item up.
 constexpr uint32_t kWaitPolls = 4096;
@@ -143,6 +149,7 @@ struct LaunchRange {
     uint32_t sp_xcd_major;      // single-pass kernel: deal the items XCD-major (a run of consecutive items per XCD)
     uint32_t sp_wait_polls;     // single-pass kernel: polls of a missing partial before the workgroup computes it itself
     uint32_t sp_slim;           // single-pass kernel: items of kStripeChannelsSlim channels (tall tensors)
+    uint32_t sp_short;          // single-pass kernel: short items; item_lo, item_hi, direct_descs and the view's item_state are theirs
     int32_t dts;                // storage dtype of every tensor in the range (cf_dtype), or 2 if mixed
     int32_t only_group_scale;   // tiled encode: skip tensors the single-pass kernel covers
     int32_t naive;              // decode: recon_t = D instead of recon_{t-1} + D (CF_EF_NAIVE)
@@ -163,7 +170,7 @@ struct LaunchRange {
 // (a choice between the sets and the table within one instance cost the large kernels 3-5 %).
 // The sets begin 256 bytes into the arguments, behind the BatchView: 16 bytes earlier, receivers of 6 x [1024, 3072] took 17.87 instead of 17.55 us.
 struct DirectRange : LaunchRange {
-    uint64_t unused[3] = {};
+    char unused[256 - sizeof(BatchView) - sizeof(LaunchRange)] = {};
     TensorPtrs sets[kDirectTensors];
     explicit DirectRange(const LaunchRange &r) : LaunchRange(r), sets()
     {

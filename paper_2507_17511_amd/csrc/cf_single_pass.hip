@@ -131,12 +131,12 @@ constexpr uint32_t kMaxHelps = 4096u;
 
 // help: do no more than store the partial of item rb, which is another workgroup's.  max_polls: of a missing partial.
 // Returns kNoneMissing when the item is done, else the item whose partial was missing; nothing but a partial has been written then.
-template <int DT, int BITS, int EF, int ET, bool FUSED, int SCH>
+template <int DT, int BITS, int EF, int ET, bool FUSED, int SCH, bool SHORT>
 __device__ __forceinline__ int persist_item(const BatchView &v, const TensorDev &d, const TensorPtrs &p, int stripe,
                                             int rb, uint32_t sign, uint32_t max_polls, bool help, Shared<SCH> &sh)
 {
     constexpr int kStripeChannels = SCH, kStripeChunks = SCH / kChunk, kRowLanes = kPersistThreads / kStripeChunks;
-    constexpr int RPT = single_pass_rows_per_lane(DT, EF);      // rows per lane
+    constexpr int RPT = single_pass_rows_per_lane(DT, EF) / (SHORT ? kShortFraction : 1);       // rows per lane
     constexpr bool IS_MAX = BITS == 4;
     constexpr bool HAS_B = EF != EF_NAIVE;                      // recon is an operand
     constexpr bool HAS_E = EF == EF_LITERAL || EF == EF_OFF;    // the error buffer is an operand
@@ -312,8 +312,8 @@ __device__ __forceinline__ int persist_item(const BatchView &v, const TensorDev 
     return kNoneMissing;
 }
 
-template <int EF, int ET, bool FUSED, int SCH>
-__global__ __launch_bounds__(kPersistThreads, 2) void k_single_pass(SinglePassArgs args)
+template <int EF, int ET, bool FUSED, int SCH, bool SHORT>
+__global__ __launch_bounds__(kPersistThreads, SHORT ? 4 : 2) void k_single_pass(SinglePassArgs args)
 {
     const BatchView &v = args.v;
     const LaunchRange &r = args.r;
@@ -356,13 +356,13 @@ __global__ __launch_bounds__(kPersistThreads, 2) void k_single_pass(SinglePassAr
         const uint32_t polls = gave_up ? 0u : r.sp_wait_polls;
         int missing;
         if (d.dtype == BF16) {
-            if (d.bits == 1) missing = persist_item<BF16, 1, EF, ET, FUSED, SCH>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
-            else if (d.bits == 2) missing = persist_item<BF16, 2, EF, ET, FUSED, SCH>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
-            else missing = persist_item<BF16, 4, EF, ET, FUSED, SCH>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
+            if (d.bits == 1) missing = persist_item<BF16, 1, EF, ET, FUSED, SCH, SHORT>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
+            else if (d.bits == 2) missing = persist_item<BF16, 2, EF, ET, FUSED, SCH, SHORT>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
+            else missing = persist_item<BF16, 4, EF, ET, FUSED, SCH, SHORT>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
         } else {
-            if (d.bits == 1) missing = persist_item<F32, 1, EF, ET, FUSED, SCH>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
-            else if (d.bits == 2) missing = persist_item<F32, 2, EF, ET, FUSED, SCH>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
-            else missing = persist_item<F32, 4, EF, ET, FUSED, SCH>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
+            if (d.bits == 1) missing = persist_item<F32, 1, EF, ET, FUSED, SCH, SHORT>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
+            else if (d.bits == 2) missing = persist_item<F32, 2, EF, ET, FUSED, SCH, SHORT>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
+            else missing = persist_item<F32, 4, EF, ET, FUSED, SCH, SHORT>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
         }
         missing = __builtin_amdgcn_readfirstlane(missing);      // it is the same for all, which the compiler does not see
         __syncthreads();            // the shared arrays are used again
@@ -380,6 +380,7 @@ __global__ __launch_bounds__(kPersistThreads, 2) void k_single_pass(SinglePassAr
             if (k == 0) {               // which items the call had, for cf_given_up_items
                 *gmut<uint32_t>(v.error_flag + kLastItemsWord) = r.item_lo;
                 *gmut<uint32_t>(v.error_flag + kLastItemsWord + 1) = r.item_hi;
+                *gmut<uint32_t>(v.error_flag + kLastItemsWord + 2) = SHORT ? 1u : 0u;
             }
         }
         at = -1;
@@ -388,26 +389,31 @@ __global__ __launch_bounds__(kPersistThreads, 2) void k_single_pass(SinglePassAr
     }
 }
 
-template <int EF, int ET, bool FUSED, int SCH> const void *persistent_fn() { return reinterpret_cast<const void *>(&k_single_pass<EF, ET, FUSED, SCH>); }
-
-template <int EF, int SCH> const void *pick_width(int err_dtype, bool fused)
+template <int EF, int ET, bool FUSED, int SCH> const void *persistent_fn(bool short_items)
 {
-    if (err_dtype == BF16) return fused ? persistent_fn<EF, BF16, true, SCH>() : persistent_fn<EF, BF16, false, SCH>();
-    return fused ? persistent_fn<EF, F32, true, SCH>() : persistent_fn<EF, F32, false, SCH>();
+    // one stripe width, and no other feedback mode: a quarter of their rows would be one or two a lane
+    if (EF == EF_RECON && short_items) return reinterpret_cast<const void *>(&k_single_pass<EF_RECON, ET, FUSED, kShortStripeChannels, true>);
+    return reinterpret_cast<const void *>(&k_single_pass<EF, ET, FUSED, SCH, false>);
 }
 
-template <int EF> const void *pick_ef(int err_dtype, bool fused, bool wide, bool slim)
+template <int EF, int SCH> const void *pick_width(int err_dtype, bool fused, bool short_items)
 {
-    if (slim) return pick_width<EF, kStripeChannelsSlim>(err_dtype, fused);
-    return wide ? pick_width<EF, kStripeChannelsWide>(err_dtype, fused) : pick_width<EF, kStripeChannels>(err_dtype, fused);
+    if (err_dtype == BF16) return fused ? persistent_fn<EF, BF16, true, SCH>(short_items) : persistent_fn<EF, BF16, false, SCH>(short_items);
+    return fused ? persistent_fn<EF, F32, true, SCH>(short_items) : persistent_fn<EF, F32, false, SCH>(short_items);
 }
 
-const void *pick(int ef, int err_dtype, bool fused, bool wide, bool slim)
+template <int EF> const void *pick_ef(int err_dtype, bool fused, bool wide, bool slim, bool short_items)
 {
-    if (ef == EF_LITERAL) return pick_ef<EF_LITERAL>(err_dtype, fused, wide, slim);
-    if (ef == EF_OFF) return pick_ef<EF_OFF>(err_dtype, fused, wide, slim);
-    if (ef == EF_NAIVE) return pick_ef<EF_NAIVE>(err_dtype, fused, wide, slim);
-    return pick_ef<EF_RECON>(err_dtype, fused, wide, slim);
+    if (slim) return pick_width<EF, kStripeChannelsSlim>(err_dtype, fused, short_items);
+    return wide ? pick_width<EF, kStripeChannelsWide>(err_dtype, fused, short_items) : pick_width<EF, kStripeChannels>(err_dtype, fused, short_items);
+}
+
+const void *pick(int ef, int err_dtype, bool fused, bool wide, bool slim, bool short_items)
+{
+    if (ef == EF_LITERAL) return pick_ef<EF_LITERAL>(err_dtype, fused, wide, slim, false);
+    if (ef == EF_OFF) return pick_ef<EF_OFF>(err_dtype, fused, wide, slim, false);
+    if (ef == EF_NAIVE) return pick_ef<EF_NAIVE>(err_dtype, fused, wide, slim, false);
+    return pick_ef<EF_RECON>(err_dtype, fused, wide, slim, short_items);
 }
 
 }  // namespace
@@ -415,7 +421,7 @@ const void *pick(int ef, int err_dtype, bool fused, bool wide, bool slim)
 int persistent_max_blocks_per_cu(int ef, int err_dtype, bool fused, bool wide, bool slim)
 {
     int n = 0;
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, pick(ef, err_dtype, fused, wide, slim), kPersistThreads, 0);
+    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, pick(ef, err_dtype, fused, wide, slim, false), kPersistThreads, 0);
     if (e != hipSuccess) { (void)hipGetLastError(); return 0; }
     return n;
 }
@@ -447,7 +453,7 @@ hipError_t launch_single_pass(const BatchView &v, const LaunchRange &r, int ef, 
         }
     }
     void *args[] = {&a};
-    return hipLaunchKernel(pick(ef, err_dtype, fused, wide, r.sp_slim != 0), dim3(n_wg), dim3(kPersistThreads), args, 0, s);
+    return hipLaunchKernel(pick(ef, err_dtype, fused, wide, r.sp_slim != 0, r.sp_short != 0), dim3(n_wg), dim3(kPersistThreads), args, 0, s);
 }
 
 }  // namespace cf

@@ -11,6 +11,7 @@
 #include "compactfusion.h"
 
 extern std::vector<std::string> g_launch_log;
+extern bool g_single_pass_short;
 extern bool g_capturing;
 extern bool g_single_pass_slim, g_occupancy_slim;
 extern bool g_project_many;
@@ -257,16 +258,20 @@ int main()
         std::free(ws);
     }
 
-    // ---- which path a call takes by default: the single pass for tensors of 256 tokens and more in calls of 64
-    // items and more, two kernels for tiny ones
+    // ---- which path a call takes by default: the single pass in calls of a round of workgroups (512 items here) and for tensors that
+    // fill a third of their items, two kernels for larger calls over shorter ones
     {
         struct Case { int64_t n, c; const char *must, *must_not; uint32_t flags; };
         const Case cases[] = {
-            {4096, 512, "k_single_pass", "k_colreduce", 0},       // 16 items per group, 64 in all
-            {16384, 64, "k_colreduce k_finalize k_encode", "k_single_pass", 0},                        // 32 items of 512 rows in all: a tiny call
+            {4096, 512, "k_single_pass", "k_colreduce", 0},             // 16 items per group, 64 in all
+            {16384, 64, "k_single_pass", "k_colreduce", 0},             // 32 items of 512 rows in all
             {16384, 64, "k_single_pass", "k_colreduce", CF_FLAG_SINGLE_PASS},
-            {4096, 256, "k_colreduce k_finalize k_encode", "k_single_pass", 0},                        // 32 items in all: a tiny call
-            {128, 8192, "k_colreduce k_finalize k_encode", "k_single_pass", 0},                        // a short tensor
+            {4096, 256, "k_single_pass", "k_colreduce", 0},             // 32 items in all
+            {128, 8192, "k_single_pass", "k_colreduce", 0},             // a short tensor
+            {42, 131072, "k_single_pass", "k_colreduce", 0},            // 512 items a third full
+            {42, 131080, "k_colreduce k_finalize k_encode", "k_single_pass", 0},       // 513
+            {43, 131080, "k_single_pass", "k_colreduce", 0},
+            {42, 131080, "k_single_pass", "k_colreduce", CF_FLAG_SINGLE_PASS},
             {4096, 512, "k_colreduce k_finalize k_encode", "k_single_pass", CF_FLAG_TWO_KERNEL},
         };
         for (const Case &cs : cases) {
@@ -347,6 +352,55 @@ int main()
                 const auto &s = c.shapes.back();
                 std::printf("ef %d dtype %d ... %d x [%d, %d]: path %d instead of %d\n", c.ef, c.dtype, (int)s[0], (int)s[1], (int)s[2], (int)took, (int)c.path);
                 ++g_failed;
+            }
+            cf_destroy(ctx);
+            std::free(ws);
+        }
+    }
+
+    // ---- short items: calls of at most 8 channel-scale tensors, 1024 items and 64 items of 128 rows (64 of fp32) x 64 channels a group
+    {
+        struct Call { int32_t ef, dtype; uint32_t flags; std::vector<std::vector<int64_t>> shapes; bool is_short; };
+        const int R = CF_EF_RECON, B = CF_BF16, F = CF_F32;
+        const std::vector<Call> calls = {
+            {R, F, 0, {{1, 256, 64}}, true}, {R, B, 0, {{1, 1, 8}}, true}, {R, B, 0, {{2, 1024, 3072}}, true},
+            {R, B, 0, {{1, 8192, 1024}}, true}, {R, B, 0, {{1, 8193, 64}}, false}, {R, F, 0, {{1, 4096, 1024}}, true}, {R, F, 0, {{1, 4097, 64}}, false},
+            {R, B, 0, {{1, 8192, 1032}}, false}, {R, B, 0, {{1, 128, 65536}}, true}, {R, B, 0, {{1, 129, 65536}}, false},
+            {R, B, 0, {{8, 128, 8192}}, true}, {R, B, 0, {{8, 129, 8192}}, false}, {R, B, 0, {{9, 64, 256}}, false},
+            {R, B, CF_FLAG_FIXED_GRID, {{1, 256, 64}}, false}, {R, B, CF_FLAG_TEST_NO_WAIT, {{1, 256, 64}}, true},
+            {CF_EF_OFF, B, 0, {{1, 256, 64}}, false}, {CF_EF_NAIVE, B, 0, {{1, 256, 64}}, false},
+            {R, B, 0, {{1, 256, 64}, {1, 9000, 64}, {1, 300, 64}}, false},
+        };
+        for (const Call &c : calls) {
+            std::vector<cf_tensor_desc> d;
+            for (auto &s : c.shapes) d.insert(d.end(), (size_t)s[0], desc(s[1], s[2], c.dtype, 2, CF_SCALE_CHANNEL));
+            const int n = (int)d.size();
+            std::memset(&o, 0, sizeof o);
+            o.ef = c.ef;
+            o.flags = c.flags;
+            std::vector<void *> bufs[5];
+            uintptr_t at = (uintptr_t)1 << 40;
+            for (auto &b : bufs)
+                for (int t = 0; t < n; ++t, at += (uintptr_t)1 << 32) b.push_back((void *)at);
+            const size_t wsb = cf_workspace_bytes(d.data(), n, &o);
+            void *ws = nullptr;
+            if (posix_memalign(&ws, 256, wsb) != 0) std::abort();
+            cf_ctx *ctx = nullptr;
+            EXPECT(cf_init(&ctx, d.data(), n, &o, ws, wsb, nullptr) == CF_OK);
+            EXPECT(cf_set_warm(ctx, 0, n, 1) == CF_OK);
+            joined();
+            for (int first = 0; first < n; first += n > 1 ? n - 1 : 1) {        // the whole context, and its last tensor alone
+                g_single_pass_short = false;
+                EXPECT(cf_step_fused(ctx, first, n - first, (const void *const *)bufs[0].data() + first, bufs[1].data() + first, bufs[2].data() + first,
+                                     bufs[3].data() + first, bufs[4].data() + first, nullptr) == CF_OK);
+                const std::string seq = joined();
+                EXPECT(seq.find("wrong items") == std::string::npos);
+                if (first > 0 && !c.is_short) continue;
+                if (g_single_pass_short != c.is_short) {
+                    const auto &s = c.shapes.back();
+                    std::printf("ef %d dtype %d ... %d x [%d, %d]: short items %d\n", c.ef, c.dtype, (int)s[0], (int)s[1], (int)s[2], (int)g_single_pass_short);
+                    ++g_failed;
+                }
             }
             cf_destroy(ctx);
             std::free(ws);

@@ -14,6 +14,7 @@ using cf::TensorPtrs;
 std::vector<std::string> g_launch_log;
 bool g_capturing = false;
 bool g_single_pass_slim = false;        // the stripe width of the last single pass
+bool g_single_pass_short = false;       // and its items' height
 bool g_occupancy_slim = false;          // and the one whose co-resident workgroups were asked for last
 bool g_project_many = false;            // whether the last projection's waves take several blocks of tokens
 int g_split = 0;                        // and the workgroups that share a stripe of the last back-projection
@@ -92,6 +93,12 @@ hipError_t launch_single_pass(const BatchView &, const LaunchRange &r, int, int,
 {
     take_direct(r);
     g_single_pass_slim = r.sp_slim != 0;
+    g_single_pass_short = r.sp_short != 0;
+    if (r.sp_short)     // the call's tensors one after another, and nothing else
+        for (int k = 0; k < r.count; ++k) {
+            const uint32_t items = (uint32_t)(r.direct_descs[k].p_n_rb * r.direct_descs[k].p_n_stripes);
+            if (r.direct_descs[k].p_item_begin + items != (k + 1 < r.count ? r.direct_descs[k + 1].p_item_begin : r.item_hi)) note("wrong items");
+        }
     note("k_single_pass");
     return hipSuccess;
 }

@@ -4,7 +4,7 @@ import pytest
 import torch
 
 import paper_2507_17511_amd as cf
-from helpers import drift_stream
+from helpers import drift_stream, run_parity
 from paper_2507_17511_amd.session import CodecSession
 
 pytestmark = pytest.mark.gpu
@@ -42,6 +42,22 @@ def test_calls_over_changing_ranges(ef, flags):
     finally:
         one.close()
         two.close()
+
+
+@pytest.mark.parametrize("dtype", [cf.CF_BF16, cf.CF_F32])
+@pytest.mark.parametrize("err_dtype", [cf.CF_F32, cf.CF_BF16])
+@pytest.mark.parametrize("flags", [0, cf.CF_FLAG_TEST_NO_WAIT])
+def test_short_items(dtype, err_dtype, flags):
+    """Small calls, whose items are 128 rows of bf16 (64 of fp32) x 64 channels: token counts and widths around one item and
+    around the longest group, 64 items, every code width, fused and split; bits against the oracle."""
+    rows = 64 if dtype == cf.CF_F32 else 128
+    shapes = [(1, 8, 1), (rows - 1, 56, 2), (rows, 64, 4), (rows + 1, 72, 1), (8 * rows + 1, 136, 2), (9 * rows - 1, 120, 4), (64 * rows, 64, 2), (63 * rows + 1, 32, 1)]
+    descs = [cf.desc(n, c, dtype, bits, cf.CF_SCALE_CHANNEL) for n, c, bits in shapes]
+    streams = [drift_stream((d.n_tokens, d.n_channels), d.dtype, steps=3, seed=980 + t, device=DEV) for t, d in enumerate(descs)]
+    xs = [[streams[t][s] for t in range(len(descs))] for s in range(3)]
+    say(f"short items dtype={dtype} err_dtype={err_dtype} flags={flags}: {shapes}")
+    for mode in ("fused", "split"):
+        run_parity(descs, cf.options(err_dtype=err_dtype, flags=flags), xs, mode=mode)
 
 
 def test_small_call_replays_from_a_graph():
