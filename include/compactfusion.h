@@ -178,8 +178,8 @@ typedef struct {
  * tensors that leave most of an item empty, and on those where more
  * workgroups have to agree on a scale.  Contexts of mostly tall tensors (more than
  * 40 of the items above: 10240 tokens of bf16), and those with one of more than
- * 48, have items of twice the rows and half the channels and take up to 38 of them
- * (19456 tokens; 24 in CF_EF_NAIVE, 12288 tokens); others up to 48 (12288 tokens).
+ * 48, have items of twice the rows and half the channels and take up to 64 of them
+ * (32768 tokens); others up to 48 (12288 tokens).
  * Where most of a context are tall tensors of fewer than 32 channels, or of 72 to
  * 88, the limit is 40.
  * CF_FLAG_SINGLE_PASS takes it whenever it applies, CF_FLAG_TWO_KERNEL never.

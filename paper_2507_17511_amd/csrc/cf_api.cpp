@@ -234,13 +234,13 @@ cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &
     // [17000, 96] 310 -> 298).
     L.sp_slim = L.single_pass && !slivers && narrow_max_group > kTallGroupItems &&
                 (narrow_max_group > kNarrowGroupLimit || tall_elements >= elements - tall_elements);
-    // Largest group of a call of any size, single pass against two kernels in us.  64-channel stripes: 20 x [12288, 3072], 24
-    // items, 854 / 907; [16384, 3072], 32, 902 / 965; 30 x [17776, 1920] with bf16 error, 35, 1986 / 2096; 16 x [9500, 3072]
-    // fp32, 38, 1985 / 2120, literal 1652 / 1798; [20000, 3072], 40, 915 / 895; [32768, 3072], 64, 1080 / 992.  Naive
-    // compression reads x only, so a second read costs little: 16 x [14000, 3072], 28, 1236 / 1219; [19000, 3072], 38, 1884 /
-    // 1654.  128-channel stripes: 4 x [10000, 3072], 40, 290 / 307; one [12288, 3072] among 40 x [4096, 3072], 48, 1027 / 1311;
+    // Largest group of a call of any size, single pass against two kernels in us.  64-channel stripes: 7 x [12288, 3072] bf16, 24
+    // items, 525 / 633; 5 x [16384, 3072], 32, 488 / 596; 30 x [17776, 1920], 35, 1873 / 2374; 4 x [20000, 3072], 40, 502 / 583; 3 x [32768, 3072], 64,
+    // 629 / 707; 2 x [49152, 3072], 96, 730 / 702 (two [24576, 3072] of fp32, 96, 578 / 653).  Naive compression, which reads x only, so
+    // that a second read costs little: 28 items 434 / 454, 40 412 / 429, 48 386 / 395, 64 508 / 512, 96 606 / 518.
+    // 128-channel stripes: 4 x [10000, 3072], 40, 290 / 307; one [12288, 3072] among 40 x [4096, 3072], 48, 1027 / 1311;
     // slivers, whose second kernel runs across the row ends: 114 x [11653, 80], 46, 351 / 312, x [10500, 72], 42, 344 / 265.
-    L.sp_group_limit = L.sp_slim ? (o.ef == CF_EF_NAIVE ? kSlimGroupLimitNaive : kSlimGroupLimit)
+    L.sp_group_limit = L.sp_slim ? kSlimGroupLimit
                                  : slivers ? kTallGroupItems : kNarrowGroupLimit;
     const int stripe_channels = L.sp_wide ? kStripeChannelsWide : L.sp_slim ? kStripeChannelsSlim : kStripeChannels;
     for (int32_t t = 0; t < n; ++t) {

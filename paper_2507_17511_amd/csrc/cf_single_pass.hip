@@ -122,6 +122,7 @@ __device__ __forceinline__ float tree_over_published(int n, const uint32_t *mine
 // by 2048 / SCH row-lanes down.
 template <int SCH> struct alignas(16) Shared {
     float red[kPersistThreads / (SCH / kChunk)][SCH];       // 8 KB: level 2 of the tree; afterwards the waves' patches for whole-line stores
+    float part[kPersistThreads];    // level 3: the tree over a share of the group's partials
     float scale[SCH];
     int missing;                // the first item whose partial did not come in time, or kNoneMissing
     uint32_t sign;              // of the call's partials: kept here for the end, where a load would wait for the stores before it
@@ -235,19 +236,45 @@ __device__ __forceinline__ int persist_item(const BatchView &v, const TensorDev 
     // The partials are agent-scope atomic stores (written through to where the other XCDs read them)
     // and every partial is its own ready flag: nothing to drain, no arrival to count.
 
-    // ---- level 3: the same tree continued over the group's item partials as they appear, then the scale.  An item that is
-    // alone in its group has nothing to exchange.
+    // ---- level 3: the same tree continued over the group's item partials as they appear, then the scale.  All 256 lanes fetch: of a
+    // 64-channel stripe's lanes each takes a quarter of the tree, of a 128-channel one's half, so that there are as few round
+    // trips one after the other as can be.  An item that is alone in its group has nothing to exchange.
+    constexpr int kShares = kPersistThreads / SCH;
+    if (d.p_n_rb > 1) {
+        const int column = stripe * kStripeChannels + (tid & (SCH - 1)), share = tid / SCH;
+        int per = kPollBatch;                       // leaves of a share, a power of two: no fewer than one round trip brings
+        while (per * kShares < d.p_n_rb) per <<= 1;
+        const int lo = share * per, count = d.p_n_rb - lo < per ? d.p_n_rb - lo : per;
+        float sum = 0.0f;
+        if (column < C && count > 0) {
+            int missing = kNoneMissing;
+            sum = tree_over_published<IS_MAX, 10>(count, partial + (int64_t)lo * C + column, C, sign, max_polls, missing);
+            if (missing != kNoneMissing) atomicMin(&sh.missing, lo + missing);          // a partial did not come in time
+        }
+        if (kShares > 1 && d.p_n_rb > per) {
+            sh.part[tid] = sum;
+            __syncthreads();
+            if (owner) {
+                float shares[kShares];
+#pragma unroll
+                for (int q = 0; q < kShares; ++q) shares[q] = sh.part[q * SCH + tid];
+#pragma unroll
+                for (int w = 1; w < kShares; w <<= 1)
+#pragma unroll
+                    for (int q = 0; q < kShares; q += 2 * w) shares[q] = comb<IS_MAX>(shares[q], shares[q + w]);
+                sum = shares[0];
+            }
+        }
+        res = sum;
+    }
     if (col < C) {
-        int missing = kNoneMissing;
-        if (d.p_n_rb > 1) res = tree_over_published<IS_MAX, 10>(d.p_n_rb, partial + col, C, sign, max_polls, missing);
         const float s = IS_MAX ? res / 7.0f : res / (float)d.n_tokens;
         sh.scale[tid] = s;
-        if (missing != kNoneMissing) atomicMin(&sh.missing, missing);       // a partial did not come in time
-        else if (rb == 0) gmut<float>(p.scales)[col] = s;
     }
     __syncthreads();
     const int missing_item = __builtin_amdgcn_readfirstlane(sh.missing);
     if (missing_item != kNoneMissing) return missing_item;
+    if (rb == 0 && col < C) gmut<float>(p.scales)[col] = sh.scale[tid];
 
     // ---- a4-a8 from the registers.  z is formed again from the raw operands: keeping the first
     // phase's fp32 residuals alive across the wait would double the register footprint.

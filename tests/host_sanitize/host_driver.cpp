@@ -316,14 +316,14 @@ int main()
             {R, F, {{1, 4865, 2048}}, NARROW}, {R, F, {{1, 5120, 2048}}, NARROW}, {R, F, {{1, 5121, 2048}}, SLIM},
             {L, B, {{1, 4865, 2048}}, NARROW}, {L, B, {{1, 5120, 2048}}, NARROW}, {L, B, {{1, 5121, 2048}}, SLIM},
             {O, F, {{1, 2433, 2048}}, NARROW}, {O, F, {{1, 2560, 2048}}, NARROW}, {O, F, {{1, 2561, 2048}}, SLIM},
-            {R, B, {{1, 19456, 2048}}, SLIM}, {R, B, {{1, 19457, 2048}}, TWO}, {R, F, {{1, 9728, 2048}}, SLIM}, {R, F, {{1, 9729, 2048}}, TWO},
-            {N, B, {{1, 10240, 2048}}, NARROW}, {N, B, {{1, 12288, 2048}}, SLIM}, {N, B, {{1, 12289, 2048}}, TWO},
+            {R, B, {{1, 32768, 2048}}, SLIM}, {R, B, {{1, 32769, 2048}}, TWO}, {R, F, {{1, 16384, 2048}}, SLIM}, {R, F, {{1, 16385, 2048}}, TWO},      // 64 items of 512 rows, 65
+            {N, B, {{1, 10240, 2048}}, NARROW}, {N, B, {{1, 32768, 2048}}, SLIM}, {N, B, {{1, 32769, 2048}}, TWO},
             {R, B, {{1, 65536, 256}}, SLIM}, {R, B, {{1, 65536, 264}}, TWO},                                              // 512 items in all, 640
             {N, B, {{1, 65536, 256}}, SLIM}, {N, B, {{1, 65536, 264}}, TWO},
             {R, B, {{20, 10240, 80}}, NARROW}, {R, B, {{20, 10500, 80}}, TWO}, {R, B, {{20, 10500, 96}}, SLIM},            // slivers: 72 to 88 channels
             {R, B, {{16, 4096, 3072}, {1, 10500, 80}}, NARROW}, {R, B, {{4, 12288, 3072}, {1, 10500, 80}}, SLIM},          // one of them among others
             {R, B, {{16, 4096, 3072}, {1, 12288, 3072}}, NARROW}, {R, B, {{16, 4096, 3072}, {1, 12289, 3072}}, SLIM},      // few tall ones: 48, 49 items
-            {R, B, {{2, 4096, 3072}, {1, 12288, 3072}}, SLIM}, {R, B, {{16, 1024, 3072}, {1, 20000, 3072}}, TWO},
+            {R, B, {{2, 4096, 3072}, {1, 12288, 3072}}, SLIM}, {R, B, {{16, 1024, 3072}, {1, 32769, 3072}}, TWO},
         };
         for (const Call &c : calls) {
             std::vector<cf_tensor_desc> d;
