@@ -70,9 +70,9 @@
  * being captured into a HIP graph, uploads the whole table again, and after a
  * captured call the next call does too: a captured call is self-contained and may
  * be replayed at any time, as long as no other use of the context is in flight.
- * Warm-ups, receivers, senders without channel, rank-1 or low-rank tensors, and senders
- * of channel tensors alone that take the single pass, over
- * at most 8 tensors take their pointers along in the kernels' arguments and
+ * Warm-ups, receivers and senders without channel, rank-1 or low-rank tensors over
+ * at most 8 tensors, and senders of at most 64 channel tensors and no others that take the
+ * single pass, take their pointers along in the kernels' arguments and
  * neither read nor change the table.
  */
 #ifndef COMPACTFUSION_H

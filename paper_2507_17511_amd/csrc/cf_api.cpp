@@ -742,11 +742,12 @@ cf_status sync_ptrs(cf_ctx *ctx, int32_t first, int32_t count, const void *const
 // Calls over few tensors whose kernels read no table: the pointers go into the kernels' arguments.  Table and mirror stay as
 // they are, so this holds on any stream and under capture.  False, and nothing done, for calls over more tensors.
 struct DirectPtrs {
-    TensorPtrs sets[kDirectTensors];
-    bool take(LaunchRange &r, const void *const *x, const void *const *recon, const void *const *err, const void *const *codes, const void *const *scales)
+    TensorPtrs sets[kSinglePassSets];
+    bool take(LaunchRange &r, const void *const *x, const void *const *recon, const void *const *err, const void *const *codes, const void *const *scales,
+              int32_t most = kDirectTensors)
     {
-        if (r.count > kDirectTensors) return false;
-        std::memset(sets, 0, sizeof sets);
+        if (r.count > most) return false;
+        std::memset(sets, 0, sizeof(TensorPtrs) * (size_t)r.count);
         for (int32_t k = 0; k < r.count; ++k) {
             if (x) sets[k].x = x[k];
             if (recon) sets[k].recon = const_cast<void *>(recon[k]);
@@ -860,13 +861,13 @@ cf_status run_sender(cf_ctx *ctx, int32_t first, int32_t count, const void *cons
     DirectPtrs direct;
     // kernels that take their pointers as arguments: the row-local ones, and the single pass
     const bool one_pass = single_pass && ctx->range_all_channel(first, count);
-    const bool is_direct = count <= kDirectTensors && (one_pass || !ctx->range_has_channel(first, count)) && ctx->range_lowrank_iters(first, count) < 0 &&
-                           direct.take(r, x, recon, err, codes, reinterpret_cast<const void *const *>(scales));
+    const bool is_direct = (one_pass || !ctx->range_has_channel(first, count)) && ctx->range_lowrank_iters(first, count) < 0 &&
+                           direct.take(r, x, recon, err, codes, reinterpret_cast<const void *const *>(scales), one_pass ? kSinglePassSets : kDirectTensors);
     if (is_direct && !one_pass) {
         e = run_row_local(ctx, first, count, v, r, fused, true, s);
         return e == hipSuccess ? CF_OK : device_fail(ctx, e);
     }
-    if (is_direct && !(ctx->opts.flags & CF_FLAG_FIXED_GRID)) ctx->take_short(first, count, r, v);
+    if (is_direct && count <= kDirectTensors && !(ctx->opts.flags & CF_FLAG_FIXED_GRID)) ctx->take_short(first, count, r, v);
     if (!is_direct && (st = sync_ptrs(ctx, first, count, x, recon, err, codes, scales, s)) != CF_OK) return st;
     if (single_pass) {
         // channel-scale tensors: one pass, the operands stay in registers across the scale reduction

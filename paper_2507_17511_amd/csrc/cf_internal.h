@@ -22,6 +22,8 @@ constexpr int kMaxUploadTensors = 64;                       // pointer sets per 
 // table / arguments, us: n = 1 8.6 / 4.8, 4 13.5 / 11.3, 6 17.4 / 15.4, 8 22.1 / 19.4; with room for 16 tensors 12 29.5 / 27.3, 16 37.5 / 35.2, the
 // small calls the same.  (With room for 16 the arguments are 340 bytes longer; the lead is open.)  n x [64, 256]: 8.6 / 4.4 for any n.
 constexpr int kDirectTensors = 8;
+// k_single_pass takes the pointers of up to so many tensors along, and finds the descriptors of more than kDirectTensors in the table.
+constexpr int kSinglePassSets = 64;
 // Single-pass path: one workgroup of 256 lanes keeps an item of p_rows x 128
 // channels (x and recon, raw) in registers between the scale reduction and the
 // encode; lanes are 16 chunks x 16 row-lanes, so a row segment is 256 bytes of
@@ -161,7 +163,7 @@ struct LaunchRange {
     int32_t lr_split;           // low-rank back-projection: at most so many workgroups share a channel stripe's runs of tokens (1, 2 or 4)
     uint32_t lr_first_slot;     // lr_slot of the range's first low-rank tensor
     uint64_t lr_slices_off;     // workspace offset of the shares after the first, [low-rank tensors][lr_split - 1][lr_max_channels][32] fp32
-    const TensorPtrs *direct;   // host memory: the call's pointers, kDirectTensors sets at most, for kernels to take as arguments; null: they are in the table
+    const TensorPtrs *direct;   // host memory: the call's pointers, kDirectTensors sets at most (k_single_pass kSinglePassSets), for kernels to take as arguments; null: they are in the table
     const TensorDev *direct_descs;      // host memory: the descriptors of the call's tensors
 };
 
@@ -177,17 +179,19 @@ struct DirectRange : LaunchRange {
     }
 };
 
-// The arguments of k_single_pass: direct calls bring their tensors' descriptors and pointers along.
+// The arguments of k_single_pass: direct calls bring their tensors' pointers along, and descriptors.
 struct SinglePassArgs {
     BatchView v;
     LaunchRange r;
     struct {
-        TensorPtrs sets[kDirectTensors];
+        TensorPtrs sets[kSinglePassSets];
         TensorDev descs[kDirectTensors];
     } direct;
 };
 
 static_assert(sizeof(BatchView) + sizeof(DirectRange) == 256 + sizeof(TensorPtrs) * kDirectTensors, "where the sets begin");
+
+static_assert(sizeof(SinglePassArgs) <= 4096, "a kernel's arguments");
 
 // f(range) with the kind of range the call's kernels take
 template <class F> auto with_range(const LaunchRange &r, F &&f) { return r.direct ? f(DirectRange(r)) : f(r); }

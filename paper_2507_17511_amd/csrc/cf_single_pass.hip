@@ -360,19 +360,21 @@ __global__ __launch_bounds__(kPersistThreads, SHORT ? 4 : 2) void k_single_pass(
     for (uint32_t k = vb; k < n_items;) {
         uint32_t item = __builtin_amdgcn_readfirstlane(r.item_lo + k);
         asm volatile("" : "+s"(item));      // a second turn, which hardly ever comes, finds everything anew: kept for it, it would cost registers
-        uint64_t descs = (uint64_t)v.descs, sets = (uint64_t)v.ptrs;
-        uint32_t t;
-        if (r.direct) {             // both are among the arguments
-            t = 0;
+        uint64_t desc, set;
+        if (r.direct && r.count <= kDirectTensors) {        // both are among the arguments
+            uint32_t t = 0;
 #pragma unroll
             for (int q = 1; q < kDirectTensors; ++q) t += item >= args.direct.descs[q].p_item_begin ? 1u : 0u;
-            descs = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(SinglePassArgs, direct.descs);
-            sets = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(SinglePassArgs, direct.sets);
+            desc = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(SinglePassArgs, direct.descs) + t * sizeof(TensorDev);
+            set = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(SinglePassArgs, direct.sets) + t * sizeof(TensorPtrs);
         } else {
-            t = scalar_load<uint32_t>((uint64_t)(v.item_tensor + item));
+            const uint32_t t = scalar_load<uint32_t>((uint64_t)(v.item_tensor + item));
+            desc = (uint64_t)(v.descs + t);
+            set = r.direct ? (uint64_t)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(SinglePassArgs, direct.sets) + (t - (uint32_t)r.first) * sizeof(TensorPtrs)
+                           : (uint64_t)(v.ptrs + t);
         }
-        TensorDev d = scalar_load<TensorDev>(descs + t * sizeof(TensorDev));      // by value: scalar registers, never re-read
-        TensorPtrs p = scalar_load<TensorPtrs>(sets + t * sizeof(TensorPtrs));
+        TensorDev d = scalar_load<TensorDev>(desc);         // by value: scalar registers, never re-read
+        TensorPtrs p = scalar_load<TensorPtrs>(set);
         uint32_t state = scalar_load<uint32_t>((uint64_t)v.item_state + (item & ~3u));       // four items' bytes
         asm volatile("" : "+s"(d.n_tokens), "+s"(d.n_channels), "+s"(d.n_chunks), "+s"(d.dtype), "+s"(d.bits), "+s"(d.p_partial_off), "+s"(d.p_rows),
                           "+s"(d.p_n_rb), "+s"(d.p_item_begin), "+s"(p.x), "+s"(p.recon), "+s"(p.err), "+s"(p.codes), "+s"(p.scales), "+s"(state));  // one wait for all of them
@@ -471,13 +473,10 @@ hipError_t launch_single_pass(const BatchView &v, const LaunchRange &r, int ef, 
     a.v = v;
     a.r = r;
     std::memset(static_cast<void *>(&a.direct), 0, sizeof a.direct);
-    for (int k = 0; r.direct && k < kDirectTensors; ++k) {
-        if (k < r.count) {
-            a.direct.sets[k] = r.direct[k];
-            a.direct.descs[k] = r.direct_descs[k];
-        } else {
-            a.direct.descs[k].p_item_begin = ~0u;       // behind every item
-        }
+    if (r.direct) std::memcpy(a.direct.sets, r.direct, sizeof(TensorPtrs) * (size_t)(r.count < kSinglePassSets ? r.count : kSinglePassSets));
+    for (int k = 0; r.direct && r.count <= kDirectTensors && k < kDirectTensors; ++k) {
+        if (k < r.count) a.direct.descs[k] = r.direct_descs[k];
+        else a.direct.descs[k].p_item_begin = ~0u;      // behind every item
     }
     void *args[] = {&a};
     return hipLaunchKernel(pick(ef, err_dtype, fused, wide, r.sp_slim != 0, r.sp_short != 0), dim3(n_wg), dim3(kPersistThreads), args, 0, s);
