@@ -370,6 +370,7 @@ int main()
             {R, B, CF_FLAG_FIXED_GRID, {{1, 256, 64}}, false}, {R, B, CF_FLAG_TEST_NO_WAIT, {{1, 256, 64}}, true},
             {CF_EF_OFF, B, 0, {{1, 256, 64}}, false}, {CF_EF_NAIVE, B, 0, {{1, 256, 64}}, false},
             {R, B, 0, {{1, 256, 64}, {1, 9000, 64}, {1, 300, 64}}, false},
+            {R, B, 0, {{64, 64, 256}}, false}, {R, B, 0, {{65, 64, 256}}, false},      // 64 take their pointers along
         };
         for (const Call &c : calls) {
             std::vector<cf_tensor_desc> d;
@@ -395,6 +396,7 @@ int main()
                                      bufs[3].data() + first, bufs[4].data() + first, nullptr) == CF_OK);
                 const std::string seq = joined();
                 EXPECT(seq.find("wrong items") == std::string::npos);
+                EXPECT(seq.find("k_single_pass") != std::string::npos && uploaded(seq) == (n - first > 64));
                 if (first > 0 && !c.is_short) continue;
                 if (g_single_pass_short != c.is_short) {
                     const auto &s = c.shapes.back();
