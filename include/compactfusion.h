@@ -23,9 +23,8 @@
  * All calls enqueue work on it and return without synchronising; buffers must
  * stay valid until the stream has passed that work.  A context is not
  * thread-safe: use it from one host thread at a time, on one stream at a time.
- * (The single pass carries a bit per partial sum from one call to the next: calls of
- * one context that overlapped in time all the same may have mixed them up, and the
- * context has to be set up anew with cf_init.)
+ * Calls of one context that overlap in time all the same spoil one another's results, but
+ * nothing beyond them.
  *
  * Layouts (all dense, row-major, C contiguous; base pointers 16-byte aligned):
  *   x, recon : [N, C] of `dtype`
@@ -74,6 +73,9 @@
  * at most 8 tensors, and senders of at most 64 channel tensors and no others that take the
  * single pass, take their pointers along in the kernels' arguments and
  * neither read nor change the table.
+ * The single pass carries a bit per partial sum from one call to the next.  Once a context's
+ * single passes come on more than one stream, on hipStreamPerThread or under capture, each of
+ * them starts with a small kernel that sets those bits afresh.
  */
 #ifndef COMPACTFUSION_H
 #define COMPACTFUSION_H

@@ -290,5 +290,7 @@ int persistent_max_blocks_per_cu(int ef, int err_dtype, bool fused, bool wide, b
 // item, else `grid` workgroups that loop over the items
 hipError_t launch_single_pass(const BatchView &v, const LaunchRange &r, int ef, int err_dtype, bool fused, bool wide, int grid,
                              bool one_shot, hipStream_t s);
+// a range's partials (offset and size multiples of 256 bytes) and item states as cf_init leaves them
+hipError_t launch_fresh_partials(uint8_t *partials, size_t bytes, uint8_t *states, uint32_t n_states, hipStream_t s);
 
 }  // namespace cf

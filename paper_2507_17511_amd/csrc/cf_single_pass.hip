@@ -423,6 +423,15 @@ __global__ __launch_bounds__(kPersistThreads, SHORT ? 4 : 2) void k_single_pass(
     }
 }
 
+// States and partials as before a first call, byte by byte the states: other tensors' lie next to them.
+__global__ void k_fresh_partials(u32x4 *partials, uint64_t n_vec, uint8_t *states, uint32_t n_states)
+{
+    const uint64_t at = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (uint64_t)gridDim.x * blockDim.x;
+    const u32x4 fill = (u32x4)(kFreshPartials);
+    for (uint64_t i = at; i < n_vec; i += step) *gmut<u32x4>(partials + i) = fill;
+    for (uint64_t i = at; i < n_states; i += step) *gmut<uint8_t>(states + i) = (uint8_t)kFreshPartials;
+}
+
 template <int EF, int ET, bool FUSED, int SCH> const void *persistent_fn(bool short_items)
 {
     // one stripe width, and no other feedback mode: a quarter of their rows would be one or two a lane
@@ -458,6 +467,14 @@ int persistent_max_blocks_per_cu(int ef, int err_dtype, bool fused, bool wide, b
     hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, pick(ef, err_dtype, fused, wide, slim, false), kPersistThreads, 0);
     if (e != hipSuccess) { (void)hipGetLastError(); return 0; }
     return n;
+}
+
+hipError_t launch_fresh_partials(uint8_t *partials, size_t bytes, uint8_t *states, uint32_t n_states, hipStream_t s)
+{
+    const uint64_t n_vec = bytes / 16, want = ((n_vec > n_states ? n_vec : n_states) + 255) / 256;
+    if (want == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_fresh_partials, dim3((unsigned)(want < 2048 ? want : 2048)), dim3(256), 0, s, reinterpret_cast<u32x4 *>(partials), n_vec, states, n_states);
+    return hipGetLastError();
 }
 
 // one_shot: one workgroup per item instead of a smaller grid whose workgroups loop over the items.

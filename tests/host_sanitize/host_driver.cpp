@@ -13,6 +13,7 @@
 extern std::vector<std::string> g_launch_log;
 extern bool g_single_pass_short;
 extern bool g_capturing;
+extern std::vector<uint8_t> g_states;
 extern bool g_single_pass_slim, g_occupancy_slim;
 extern bool g_project_many;
 extern int g_split;
@@ -407,6 +408,66 @@ int main()
             cf_destroy(ctx);
             std::free(ws);
         }
+    }
+
+    // ---- single passes on one stream carry their item states on; from the first one on another stream, on hipStreamPerThread or
+    // under capture each of them starts afresh, whatever calls that overlapped have left, and leaves its neighbours' states alone
+    for (int64_t tokens : {1000, 60000}) {      // short items, and tall ones
+        const std::vector<cf_tensor_desc> d = {desc(tokens, 72, CF_BF16, 1, CF_SCALE_CHANNEL), desc(tokens, 200, CF_BF16, 1, CF_SCALE_CHANNEL),
+                                               desc(tokens, 72, CF_BF16, 1, CF_SCALE_CHANNEL)};
+        std::memset(&o, 0, sizeof o);
+        o.flags = CF_FLAG_SINGLE_PASS;
+        std::vector<void *> bufs[5];
+        uintptr_t at = (uintptr_t)1 << 40;
+        for (auto &b : bufs)
+            for (int t = 0; t < 3; ++t, at += (uintptr_t)1 << 32) b.push_back((void *)at);
+        const size_t wsb = cf_workspace_bytes(d.data(), 3, &o);
+        void *ws = nullptr;
+        if (posix_memalign(&ws, 256, wsb) != 0) std::abort();
+        cf_ctx *ctx = nullptr;
+        void *const a = (void *)0x1000, *const b = (void *)0x2000;
+        const auto fresh = [&](int first, int count, void *stream) {        // whether the call made its states anew; they have to agree then
+            EXPECT(cf_step_fused(ctx, first, count, (const void *const *)bufs[0].data() + first, bufs[1].data() + first, bufs[2].data() + first,
+                                 bufs[3].data() + first, bufs[4].data() + first, stream) == CF_OK);
+            const std::string seq = joined();
+            EXPECT(seq.find("misplaced") == std::string::npos && g_single_pass_short == (tokens == 1000));
+            const bool anew = seq.find("k_fresh_partials k_single_pass") != std::string::npos;
+            for (uint8_t state : g_states) EXPECT(!anew || state == 0x80u);
+            return anew;
+        };
+        const auto set_up = [&] {
+            cf_destroy(ctx);
+            EXPECT(cf_init(&ctx, d.data(), 3, &o, ws, wsb, b) == CF_OK && cf_set_warm(ctx, 0, 3, 1) == CF_OK);
+            joined();
+        };
+        set_up();
+        for (int k = 0; k < 3; ++k) {
+            EXPECT(!fresh(0, 3, a));                // cf_init's own stream may be another one
+            for (uint8_t state : g_states) EXPECT(state == (k % 2 ? 0u : 0x80u));
+        }
+        EXPECT(!fresh(1, 1, a));
+        EXPECT(fresh(1, 1, b) && fresh(1, 1, b) && fresh(0, 1, a));
+        EXPECT(fresh(2, 1, a) && fresh(0, 3, a));
+        set_up();
+        EXPECT(!fresh(0, 3, a) && !fresh(2, 1, a) && fresh(1, 1, b));
+        const std::vector<uint8_t> middle = g_states;
+        EXPECT(fresh(0, 3, b) && g_states.size() > middle.size());
+        set_up();
+        EXPECT(!fresh(0, 3, nullptr));
+        g_capturing = true;
+        EXPECT(fresh(0, 3, nullptr));
+        g_capturing = false;
+        EXPECT(fresh(0, 3, nullptr));
+        set_up();
+        EXPECT(fresh(0, 3, (void *)hipStreamPerThread));
+        // a call over one tensor leaves what lies next to it as it was
+        set_up();
+        EXPECT(!fresh(0, 3, a) && fresh(1, 1, b));
+        const std::vector<uint8_t> before((const uint8_t *)ws, (const uint8_t *)ws + wsb);
+        EXPECT(fresh(1, 1, b));
+        EXPECT(std::memcmp(before.data(), ws, wsb) == 0);
+        cf_destroy(ctx);
+        std::free(ws);
     }
 
     // ---- the low-rank kernels' rules count the low-rank tensors of a call as they are, and nothing else

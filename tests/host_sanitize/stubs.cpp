@@ -19,6 +19,7 @@ bool g_occupancy_slim = false;          // and the one whose co-resident workgro
 bool g_project_many = false;            // whether the last projection's waves take several blocks of tokens
 int g_split = 0;                        // and the workgroups that share a stripe of the last back-projection
 std::vector<TensorPtrs> g_direct;       // the pointers that the last kernel of a direct call took as arguments; none: it read the table
+std::vector<uint8_t> g_states;          // the item states that the last single pass found
 static void take_direct(const LaunchRange &r)
 {
     g_direct.clear();
@@ -89,17 +90,27 @@ hipError_t launch_lr_quant_u(const BatchView &, const LaunchRange &, hipStream_t
 hipError_t launch_lr_encode(const BatchView &, const LaunchRange &, int, bool, hipStream_t) { note("k_lr_apply"); return hipSuccess; }
 hipError_t launch_lr_decode(const BatchView &, const LaunchRange &r, hipStream_t) { take_direct(r); note("k_lr_apply"); return hipSuccess; }
 int persistent_max_blocks_per_cu(int, int, bool, bool, bool slim) { g_occupancy_slim = slim; return 2; }
-hipError_t launch_single_pass(const BatchView &, const LaunchRange &r, int, int, bool, bool, int, bool, hipStream_t)
+hipError_t launch_single_pass(const BatchView &v, const LaunchRange &r, int, int, bool, bool, int, bool, hipStream_t)
 {
     take_direct(r);
     g_single_pass_slim = r.sp_slim != 0;
     g_single_pass_short = r.sp_short != 0;
+    g_states.assign(v.item_state + r.item_lo, v.item_state + r.item_hi);
+    for (uint32_t i = r.item_lo; i < r.item_hi; ++i) v.item_state[i] ^= 0x80u;      // as the kernel's items do
     if (r.sp_short)     // the call's tensors one after another, and nothing else
         for (int k = 0; k < r.count; ++k) {
             const uint32_t items = (uint32_t)(r.direct_descs[k].p_n_rb * r.direct_descs[k].p_n_stripes);
             if (r.direct_descs[k].p_item_begin + items != (k + 1 < r.count ? r.direct_descs[k + 1].p_item_begin : r.item_hi)) note("wrong items");
         }
     note("k_single_pass");
+    return hipSuccess;
+}
+hipError_t launch_fresh_partials(uint8_t *partials, size_t bytes, uint8_t *states, uint32_t n_states, hipStream_t)
+{
+    note("k_fresh_partials");
+    if (reinterpret_cast<uintptr_t>(partials) % 256 != 0 || bytes % 256 != 0) note("misplaced");
+    std::memset(partials, (int)(kFreshPartials & 255u), bytes);
+    std::memset(states, (int)(kFreshPartials & 255u), n_states);
     return hipSuccess;
 }
 hipError_t static_scratch(void **ptr)

@@ -88,3 +88,35 @@ def test_small_call_replays_from_a_graph():
     finally:
         graphed.close()
         eager.close()
+
+
+@pytest.mark.parametrize("ef", [cf.CF_EF_RECON, cf.CF_EF_NAIVE])
+def test_streams_in_turn(ef):
+    """Calls of one context on two streams in turn, each after the other has been waited for: short items (default feedback mode, up
+    to eight tensors) and tall ones, single tensors between whole batches, whose neighbours' bits must stay; against two kernels."""
+    shapes = [(700, 520), (1, 8), (1030, 512), (64, 72), (2600, 264), (129, 72), (511, 1032), (257, 256), (300, 64)]
+    descs = [cf.desc(n, c, cf.CF_F32 if t % 4 == 1 else cf.CF_BF16, (1, 2, 4)[t % 3], cf.CF_SCALE_CHANNEL) for t, (n, c) in enumerate(shapes)]
+    streams = [drift_stream((d.n_tokens, d.n_channels), d.dtype, steps=4, seed=870 + t, device=DEV) for t, d in enumerate(descs)]
+    one = CodecSession(descs, cf.options(ef=ef, flags=cf.CF_FLAG_SINGLE_PASS), device=DEV)
+    two = CodecSession(descs, cf.options(ef=ef, flags=cf.CF_FLAG_TWO_KERNEL), device=DEV)
+    other = torch.cuda.Stream(device=DEV)
+    try:
+        for sess in (one, two):
+            sess.warmup([s[0] for s in streams])
+        calls = [(0, 9, 0), (0, 3, 0), (3, 1, 1), (0, 9, 1), (2, 1, 0), (1, 8, 1), (4, 1, 1), (0, 9, 0), (8, 1, 1), (0, 9, 0), (0, 8, 0)]
+        for k, (first, count, where) in enumerate(calls):
+            x = [s[1 + k % 3] for s in streams]
+            two.step_fused(x[first:first + count], first, count)
+            torch.cuda.synchronize()
+            with torch.cuda.stream(other if where else torch.cuda.current_stream()):
+                one.step_fused(x[first:first + count], first, count)
+                cf.cf_check_device(one.ctx, one.stream_handle)
+                assert cf.cf_given_up_items(one.ctx, one.stream_handle) == 0
+            say(f"ef={ef} call {k}: tensors {first}..{first + count - 1} on stream {where}")
+            for t in range(len(descs)):
+                for name in ("codes", "scales", "recon", "err"):
+                    a, b = getattr(one, name)[t], getattr(two, name)[t]
+                    assert torch.equal(a.view(torch.uint8).reshape(-1), b.view(torch.uint8).reshape(-1)), f"call {k}: {name}[{t}]"
+    finally:
+        one.close()
+        two.close()
