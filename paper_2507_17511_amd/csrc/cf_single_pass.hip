@@ -42,7 +42,9 @@
 // written after the wait).  The missing item may start meanwhile, and writes over its operands (error and reconstruction are
 // updated in place) once all partials of its group are there, its own among them: so the helper stores with a
 // compare-and-swap against the partial of the call before.  If that finds one, the item had written nothing yet and the helper
-// read what it should; if not, the item's own partial stands.  Both compute the same bits.  A workgroup helps each item of its
+// read what it should; if not, the item's own partial stands.  Both compute the same bits.  This needs every partial of an item to be
+// where other XCDs look before the item writes over an operand: the waves that publish wait for their stores (publish_landed) ahead of
+// the barrier that all of the item's other stores lie behind.  A helper's loads of operands have returned before its swap, which needs their sum.  A workgroup helps each item of its
 // group once at most, so it always ends, on a device shared with other kernels and with a dispatcher that does not go by
 // index too, and the outputs are the same bits either way.
 #include <cstddef>
@@ -57,6 +59,8 @@ namespace {
 using namespace dev;
 
 __device__ __forceinline__ void publish(uint32_t *p, uint32_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// The wave's stores, publish() among them, are where every XCD sees them: agent-scope stores go through to memory, and loads and stores count down one counter.
+__device__ __forceinline__ void publish_landed() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 __device__ __forceinline__ uint32_t fetch(const uint32_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
 // What is the same for the whole workgroup and nobody writes while it is looked at, by way of the scalar cache.
@@ -237,7 +241,7 @@ __device__ __forceinline__ int persist_item(const BatchView &v, const TensorDev 
     }
     if (help) return kNoneMissing;
     // The partials are agent-scope atomic stores (written through to where the other XCDs read them)
-    // and every partial is its own ready flag: nothing to drain, no arrival to count.
+    // and every partial is its own ready flag: nothing to drain here, no arrival to count.
 
     // ---- level 3: the same tree continued over the group's item partials as they appear, then the scale.  All 256 lanes fetch: of a
     // 64-channel stripe's lanes each takes a quarter of the tree, of a 128-channel one's half, so that there are as few round
@@ -274,6 +278,7 @@ __device__ __forceinline__ int persist_item(const BatchView &v, const TensorDev 
         const float s = IS_MAX ? res / 7.0f : res / (float)d.n_tokens;
         sh.scale[tid] = s;
     }
+    publish_landed();       // costs nothing: the loads of the partials came after
     __syncthreads();
     const int missing_item = __builtin_amdgcn_readfirstlane(sh.missing);
     if (missing_item != kNoneMissing) return missing_item;

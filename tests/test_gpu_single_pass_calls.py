@@ -120,3 +120,40 @@ def test_streams_in_turn(ef):
     finally:
         one.close()
         two.close()
+
+
+@pytest.mark.parametrize("ef, err_dtype, shapes", [
+    (cf.CF_EF_RECON, cf.CF_F32, [(8192, 64), (4096, 512), (1000, 136)]),       # short items, 64 a group
+    (cf.CF_EF_RECON, cf.CF_BF16, [(8192, 64), (4096, 512), (1000, 136)]),
+    (cf.CF_EF_RECON, cf.CF_F32, [(9000, 136), (4096, 512)]),                   # too many for them: 128-channel stripes
+    (cf.CF_EF_RECON, cf.CF_F32, [(12500, 200), (20000, 72)]),                  # 64-channel stripes
+    (cf.CF_EF_RECON, cf.CF_F32, [(2000, 1032)] * 9),                           # more than eight tensors: 256-channel stripes
+    (cf.CF_EF_OFF, cf.CF_F32, [(4096, 512), (1000, 136)]),
+    (cf.CF_EF_NAIVE, cf.CF_BF16, [(4096, 512), (1000, 136)]),
+])
+def test_missing_partial_sums_are_computed(ef, err_dtype, shapes):
+    """CF_FLAG_TEST_NO_WAIT in every geometry of items: some are given up, their workgroups store other items' partial sums while those
+    start, publish and write over their operands, and the bits are those of an ordinary run, in which nobody gives up."""
+    descs = [cf.desc(n, c, cf.CF_BF16, (2, 1, 4)[t % 3], cf.CF_SCALE_CHANNEL) for t, (n, c) in enumerate(shapes)]
+    streams = [drift_stream((d.n_tokens, d.n_channels), d.dtype, steps=4, seed=830 + t, device=DEV) for t, d in enumerate(descs)]
+    options = dict(ef=ef, err_dtype=err_dtype)
+    hasty = CodecSession(descs, cf.options(flags=cf.CF_FLAG_SINGLE_PASS | cf.CF_FLAG_TEST_NO_WAIT, **options), device=DEV)
+    quiet = CodecSession(descs, cf.options(flags=cf.CF_FLAG_SINGLE_PASS, **options), device=DEV)
+    try:
+        gave_up = 0
+        for k in range(4):
+            for sess in (hasty, quiet):
+                (sess.step_fused if k else sess.warmup)([s[k] for s in streams])
+                cf.cf_check_device(sess.ctx, sess.stream_handle)
+            if k == 0:
+                continue
+            gave_up += cf.cf_given_up_items(hasty.ctx, hasty.stream_handle)
+            assert cf.cf_given_up_items(quiet.ctx, quiet.stream_handle) == 0
+            for t in range(len(descs)):
+                for name in ("codes", "scales", "recon", "err"):
+                    assert torch.equal(getattr(hasty, name)[t], getattr(quiet, name)[t]), f"call {k}: {name}[{t}]"
+        say(f"ef={ef} {shapes}: {gave_up} items given up in three calls")
+        assert gave_up > 0, "nobody helped"
+    finally:
+        hasty.close()
+        quiet.close()
