@@ -181,7 +181,10 @@ typedef struct {
  * workgroups have to agree on a scale.  Contexts of mostly tall tensors (more than
  * 40 of the items above: 10240 tokens of bf16), and those with one of more than
  * 48, have items of twice the rows and half the channels and take up to 64 of them
- * (32768 tokens); others up to 48 (12288 tokens).
+ * (32768 tokens); others up to 48 (12288 tokens).  Where a tall tensor's rows are no whole lines
+ * of 128 bytes, or of bf16 and a multiple of 1024 channels long, 38 of them (19456 tokens), in
+ * CF_EF_NAIVE 24 (12288); but of whole lines 64 in CF_EF_LITERAL and CF_EF_OFF, and in CF_EF_NAIVE of fp32
+ * and multiples of 1024 channels 48.
  * Where most of a context are tall tensors of fewer than 32 channels, or of 72 to
  * 88, the limit is 40.
  * CF_FLAG_SINGLE_PASS takes it whenever it applies, CF_FLAG_TWO_KERNEL never.

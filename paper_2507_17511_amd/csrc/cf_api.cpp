@@ -27,7 +27,7 @@ struct Layout {
     int32_t max_group_items = 0;   // largest reduction group of the single-pass path
     bool sp_wide = false;          // single-pass items are kStripeChannelsWide channels wide (short tensors)
     bool sp_slim = false;          // ... kStripeChannelsSlim channels wide (tall tensors)
-    int32_t sp_group_limit = 0;    // larger groups take two kernels by default, but for small calls
+    bool sp_too_tall = false;      // some group is larger than its tensor's limit: two kernels by default, but for small calls
     bool single_pass = false;      // every channel-scale tensor has single-pass geometry
     // Short items: calls whose items leave the device half empty take ones a quarter as tall, kernels of their own with a
     // quarter of the code, which the first workgroup of a CU has to wait for.  Those tensors have a second geometry, with partials and item
@@ -180,6 +180,27 @@ size_t lowrank_slice_bytes(const cf_tensor_desc *descs, int32_t n)
     return align_up(most);
 }
 
+// Largest group of 64-channel stripes in a call of any size.  The taller the tensors the longer workgroups wait for the slowest of their group, and a
+// stripe of a row is one line of 128 bytes of bf16: where rows are no whole lines it is pieces of two, and where they are multiples of 1024 channels the
+// stripe's rows share their memory channels.  Single pass against two kernels in us, 2.6e8 elements of bf16 (1.5e8 of fp32 and with the error as operand):
+//   whole lines        [22358, 1920] 44 items 542 / 616, [32598, 3328] 64 497 / 578; naive [19286, 1536] 38 404 / 417, [32598, 3328] 64 365 / 409;
+//                      fp32 [16299, 1920] 64 491 / 593, naive 376 / 420; no feedback [16299, 3072] 64 887 / 993, of fp32 [8150, 3072] 724 / 801
+//   multiples of 1024  [20310, 3072] 40 items 606 / 610, [26454, 2048] 52 543 / 520, [32598, 4096] 64 404 / 334; naive [12118, 3072] 24 388 / 402, [15190,
+//                      3072] 30 434 / 418, [32598, 2048] 64 458 / 353; fp32 [16314, 2048] 64 570 / 610, naive [12203, 3072] 48 706 / 737, 64 871 / 818
+//   others             [19286, 1096] 38 1200 / 662, [32598, 1096] 64 1126 / 651; naive [11094, 1096] 22 1004 / 487, [15190, 2056] 30 1440 / 460; fp32 [12218, 3080]
+//                      48 596 / 563, [16314, 200] 64 741 / 671; no feedback [12218, 1096] 48 749 / 655, of fp32 50 x [7000,
+//                      200] 55 489 / 436, 4 x [7000, 2056] 413 / 371, but 3 x [7000, 3080] 370 / 433
+// The lines for the last two kinds are those of a fetch by one lane a channel, which all kinds had once; for rows of no whole lines two kernels are the
+// faster choice below them too.
+int32_t slim_group_limit(const cf_tensor_desc &d, const cf_options &o)
+{
+    const bool wide = d.dtype == CF_F32, naive = o.ef == CF_EF_NAIVE, three_operands = o.ef == CF_EF_LITERAL || o.ef == CF_EF_OFF;
+    const bool whole_lines = d.n_channels * (wide ? 4 : 2) % 128 == 0;
+    if (!whole_lines) return naive ? kSlimGroupLimitNaive : kSlimGroupLimitUneven;
+    if (three_operands || (wide && !naive) || d.n_channels % 1024 != 0) return kSlimGroupLimit;
+    return !naive ? kSlimGroupLimitUneven : wide ? kNarrowGroupLimit : kSlimGroupLimitNaive;
+}
+
 cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &o, Layout &L)
 {
     if (!descs || n < 1) return CF_ERR_INVALID_ARG;
@@ -234,14 +255,9 @@ cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &
     // [17000, 96] 310 -> 298).
     L.sp_slim = L.single_pass && !slivers && narrow_max_group > kTallGroupItems &&
                 (narrow_max_group > kNarrowGroupLimit || tall_elements >= elements - tall_elements);
-    // Largest group of a call of any size, single pass against two kernels in us.  64-channel stripes: 7 x [12288, 3072] bf16, 24
-    // items, 525 / 633; 5 x [16384, 3072], 32, 488 / 596; 30 x [17776, 1920], 35, 1873 / 2374; 4 x [20000, 3072], 40, 502 / 583; 3 x [32768, 3072], 64,
-    // 629 / 707; 2 x [49152, 3072], 96, 730 / 702 (two [24576, 3072] of fp32, 96, 578 / 653).  Naive compression, which reads x only, so
-    // that a second read costs little: 28 items 434 / 454, 40 412 / 429, 48 386 / 395, 64 508 / 512, 96 606 / 518.
-    // 128-channel stripes: 4 x [10000, 3072], 40, 290 / 307; one [12288, 3072] among 40 x [4096, 3072], 48, 1027 / 1311;
-    // slivers, whose second kernel runs across the row ends: 114 x [11653, 80], 46, 351 / 312, x [10500, 72], 42, 344 / 265.
-    L.sp_group_limit = L.sp_slim ? kSlimGroupLimit
-                                 : slivers ? kTallGroupItems : kNarrowGroupLimit;
+    // Largest group of a call of any size in 128-channel stripes, single pass against two kernels in us: 4 x [10000, 3072], 40, 290 / 307; one [12288,
+    // 3072] among 40 x [4096, 3072], 48, 1027 / 1311; slivers, whose second kernel runs across the row ends: 114 x [11653, 80], 46, 351 / 312, x [10500,
+    // 72], 42, 344 / 265.  In 64-channel stripes: slim_group_limit.
     const int stripe_channels = L.sp_wide ? kStripeChannelsWide : L.sp_slim ? kStripeChannelsSlim : kStripeChannels;
     for (int32_t t = 0; t < n; ++t) {
         const cf_tensor_desc &d = descs[t];
@@ -324,6 +340,7 @@ cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &
             p_partial_bytes += align_up((size_t)v.p_n_rb * (size_t)d.n_channels * sizeof(float));
             items += (uint64_t)v.p_n_rb * (uint64_t)v.p_n_stripes;
             if (v.p_n_rb > L.max_group_items) L.max_group_items = v.p_n_rb;
+            if (v.p_n_rb > (L.sp_slim ? slim_group_limit(d, o) : slivers ? kTallGroupItems : kNarrowGroupLimit)) L.sp_too_tall = true;
             if (items > 0x7fffffffull) return CF_ERR_SHAPE;
         }
     }
@@ -873,7 +890,7 @@ cf_status run_sender(cf_ctx *ctx, int32_t first, int32_t count, const void *cons
     hipError_t e;
     const int grid = ctx->persist_grid[et == CF_BF16 ? 1 : 0][fused ? 1 : 0];
     const bool forced = (ctx->opts.flags & CF_FLAG_SINGLE_PASS) != 0;
-    // unless asked for, not for very tall tensors (see sp_group_limit) in calls of more than a round of workgroups, 512 on the whole MI355X (us, single pass / two kernels:
+    // unless asked for, not for very tall tensors (see sp_too_tall) in calls of more than a round of workgroups, 512 on the whole MI355X (us, single pass / two kernels:
     // one tensor of [32768, 3072], 3072 items, 303 / 259, of [65536, 1024], 2048 items, 249 / 177; 4 x [20000, 128], 320
     // items, 34 / 48; one [65536, 128], 256 items in groups of 128, 35 / 52, [131072, 64], 256 in one group, 46 / 60, [40000,
     // 384], 474 in groups of 79, 48 / 81, [30000, 256] fp32 39 / 59)
@@ -890,7 +907,7 @@ cf_status run_sender(cf_ctx *ctx, int32_t first, int32_t count, const void *cons
             filled += ctx->L.dev[t].n_tokens;
             room += (int64_t)ctx->L.dev[t].p_n_rb * ctx->L.dev[t].p_rows;
         }
-    const bool worth_it = forced || small_call || (ctx->L.max_group_items <= ctx->L.sp_group_limit && 3 * filled >= room);
+    const bool worth_it = forced || small_call || (!ctx->L.sp_too_tall && 3 * filled >= room);
     // (a group larger than what the device holds at once would have its first workgroups wait for ones that cannot
     // start before they leave: correct, they give up and compute the missing sums, but slow: such tensors take two kernels)
     const bool single_pass = ctx->L.single_pass && grid >= ctx->L.max_group_items && grid >= 1 && r.item_hi > r.item_lo && worth_it;

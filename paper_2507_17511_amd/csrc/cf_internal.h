@@ -57,7 +57,9 @@ constexpr uint32_t kWaitPolls = 4096;
 // the whole call at once: nothing has to wait for a second round of workgroups then.
 constexpr int kTallGroupItems = 40;
 constexpr int kNarrowGroupLimit = 48;
-constexpr int kSlimGroupLimit = 64;
+constexpr int kSlimGroupLimit = 64;                         // see slim_group_limit
+constexpr int kSlimGroupLimitUneven = 38;
+constexpr int kSlimGroupLimitNaive = 24;
 constexpr int kLastItemsWord = 32;                          // 128 bytes behind the error word: the first item of the last single pass, and the one past its last
 
 // The single pass's partials carry the sign of their call in this bit; item states and partials are filled with the other word before a first call.

@@ -317,8 +317,16 @@ int main()
             {R, F, {{1, 4865, 2048}}, NARROW}, {R, F, {{1, 5120, 2048}}, NARROW}, {R, F, {{1, 5121, 2048}}, SLIM},
             {L, B, {{1, 4865, 2048}}, NARROW}, {L, B, {{1, 5120, 2048}}, NARROW}, {L, B, {{1, 5121, 2048}}, SLIM},
             {O, F, {{1, 2433, 2048}}, NARROW}, {O, F, {{1, 2560, 2048}}, NARROW}, {O, F, {{1, 2561, 2048}}, SLIM},
-            {R, B, {{1, 32768, 2048}}, SLIM}, {R, B, {{1, 32769, 2048}}, TWO}, {R, F, {{1, 16384, 2048}}, SLIM}, {R, F, {{1, 16385, 2048}}, TWO},      // 64 items of 512 rows, 65
-            {N, B, {{1, 10240, 2048}}, NARROW}, {N, B, {{1, 32768, 2048}}, SLIM}, {N, B, {{1, 32769, 2048}}, TWO},
+            {R, B, {{1, 32768, 1920}}, SLIM}, {R, B, {{1, 32769, 1920}}, TWO}, {R, F, {{1, 16384, 2048}}, SLIM}, {R, F, {{1, 16385, 2048}}, TWO},      // 64 items of 512 rows, 65
+            {N, B, {{1, 10240, 2048}}, NARROW}, {N, B, {{1, 32768, 1920}}, SLIM}, {N, B, {{1, 32769, 1920}}, TWO},
+            // rows of no whole lines of 128 bytes, and of multiples of 1024 channels: 38 items, 24
+            {R, B, {{1, 19456, 2056}}, SLIM}, {R, B, {{1, 19457, 2056}}, TWO}, {R, B, {{1, 19457, 2112}}, SLIM}, {R, B, {{1, 19457, 2096}}, TWO},
+            {R, B, {{1, 19456, 2048}}, SLIM}, {R, B, {{1, 19457, 2048}}, TWO}, {R, F, {{1, 9728, 2056}}, SLIM}, {R, F, {{1, 9729, 2056}}, TWO}, {R, F, {{1, 9729, 2080}}, SLIM},
+            {N, B, {{1, 12288, 2056}}, SLIM}, {N, B, {{1, 12289, 2056}}, TWO}, {N, B, {{1, 12288, 2048}}, SLIM}, {N, B, {{1, 12289, 2048}}, TWO}, {N, B, {{1, 12289, 1984}}, SLIM},
+            {N, F, {{1, 6144, 2056}}, SLIM}, {N, F, {{1, 6145, 2056}}, TWO}, {N, F, {{1, 12288, 2048}}, SLIM}, {N, F, {{1, 12289, 2048}}, TWO}, {N, F, {{1, 16384, 2080}}, SLIM},
+            {L, B, {{1, 9728, 2056}}, SLIM}, {L, B, {{1, 9729, 2056}}, TWO}, {L, B, {{1, 16384, 2048}}, SLIM}, {L, B, {{1, 16385, 2048}}, TWO},
+            {O, F, {{1, 4864, 2056}}, SLIM}, {O, F, {{1, 4865, 2056}}, TWO}, {O, F, {{1, 8192, 2048}}, SLIM}, {O, F, {{1, 8193, 2048}}, TWO},
+            {R, B, {{8, 20000, 1920}, {1, 20000, 2056}}, TWO}, {R, B, {{8, 20000, 1920}, {1, 12300, 2056}}, SLIM},           // each by its own
             {R, B, {{1, 65536, 256}}, SLIM}, {R, B, {{1, 65536, 264}}, TWO},                                              // 512 items in all, 640
             {N, B, {{1, 65536, 256}}, SLIM}, {N, B, {{1, 65536, 264}}, TWO},
             {R, B, {{20, 10240, 80}}, NARROW}, {R, B, {{20, 10500, 80}}, TWO}, {R, B, {{20, 10500, 96}}, SLIM},            // slivers: 72 to 88 channels
