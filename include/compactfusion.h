@@ -174,17 +174,19 @@ typedef struct {
  * reads the operands again, writes the codes.  Results are bit-identical either
  * way.  By default a call takes the single pass where it applies and the device holds the
  * items of the call at once (512 on MI355X); larger calls where no stripe has too many
- * items and the tensors fill a third of theirs: it is about 30 % faster on MI355X at the
+ * items and the tensors have 256 tokens or fill enough of their items (bf16 two fifths of
+ * one, 70 % of two; somewhat less will do in calls of up to three times that many items,
+ * and any there with a tensor of 2048 tokens): it is about 30 % faster on MI355X at the
  * sizes of the paper's models, and twice as fast on tiny calls of at most 8 tensors, which are
  * one launch of smaller items; it is slower than two kernels on large calls over
  * tensors that leave most of an item empty, and on those where more
  * workgroups have to agree on a scale.  Contexts of mostly tall tensors (more than
  * 40 of the items above: 10240 tokens of bf16), and those with one of more than
  * 48, have items of twice the rows and half the channels and take up to 64 of them
- * (32768 tokens); others up to 48 (12288 tokens).  Where a tall tensor's rows are no whole lines
- * of 128 bytes, or of bf16 and a multiple of 1024 channels long, 38 of them (19456 tokens), in
- * CF_EF_NAIVE 24 (12288); but of whole lines 64 in CF_EF_LITERAL and CF_EF_OFF, and in CF_EF_NAIVE of fp32
- * and multiples of 1024 channels 48.
+ * (32768 tokens); others up to 48 (12288 tokens).  Where a tall tensor's rows are no
+ * whole lines of 128 bytes, or are of bf16 and a multiple of 1024 channels long, it is 38
+ * of them (19456 tokens), in CF_EF_NAIVE 24 (12288); but of whole lines 64 in CF_EF_LITERAL
+ * and CF_EF_OFF, and 48 in CF_EF_NAIVE of fp32 and multiples of 1024 channels.
  * Where most of a context are tall tensors of fewer than 32 channels, or of 72 to
  * 88, the limit is 40.
  * CF_FLAG_SINGLE_PASS takes it whenever it applies, CF_FLAG_TWO_KERNEL never.

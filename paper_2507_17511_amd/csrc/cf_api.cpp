@@ -896,18 +896,37 @@ cf_status run_sender(cf_ctx *ctx, int32_t first, int32_t count, const void *cons
     // 384], 474 in groups of 79, 48 / 81, [30000, 256] fp32 39 / 59)
     const uint32_t items = r.item_hi - r.item_lo;
     const bool small_call = grid > 0 && items <= (uint32_t)grid;
-    // nor, in calls of more than a round, for tensors so short that their items are mostly empty.  Single pass / two kernels, us, wide items of
-    // 128 rows of bf16: 114 x [16, 3072] 48.9 / 33.6, 57 x [40, 3072] 32.3 / 31.6, x [77, 3072] 37.2 / 46.6, 114 x [100, 3072] 85 / 101; 64 rows of
-    // fp32: 114 x [16, 3072] 34.7 / 41.3, 57 x [77, 3072] 69.5 / 68.4.  Calls of a round, whatever their shape: 114 x [8, 1024] bf16 (456 items) 20.8 / 25.2, 30 x
-    // [128, 512] (60) 20.2 / 20.2, 9 x [64, 256] (9) 18.3 / 19.5; with their pointers along 8 x [64, 256] 9.6 / 19.3, [1, 8] 9.9 / 19.2, [4096, 256] 14.1 / 17.0,
-    // [16384, 64] 20.0 / 23.1 (what Python adds to a call, some 9 us, hides what the kernel takes below that).
-    int64_t filled = 0, room = 0;
-    for (int32_t t = first; t < first + count; ++t)
-        if (ctx->L.dev[t].p_rows > 0) {
-            filled += ctx->L.dev[t].n_tokens;
-            room += (int64_t)ctx->L.dev[t].p_n_rb * ctx->L.dev[t].p_rows;
-        }
-    const bool worth_it = forced || small_call || (!ctx->L.sp_too_tall && 3 * filled >= room);
+    // nor, in calls of more than a round, for tensors of fewer than 256 tokens that leave too much of their items empty.  Single pass / two kernels, us, 114 and 57
+    // tensors of 3072 channels:
+    //   groups of one item of 128 rows (bf16)   30 % full 53.6 / 50.9 and 30.5 / 30.7, 34 % 57.3 / 54.5 and 31.2 / 33.5, 40 % 60.0 / 60.3 and 32.2 / 36.0, 100 % 104 / 124 and 54 / 66;
+    //                                           of [50, 1096], whose last stripe is 28 % of one, 39 % 35.3 / 35.3
+    //                      64 rows              fp32 20 % 34.7 / 37.8 and 19.9 / 24.7, bf16 without feedback 20 % 34.7 / 34.6 and 20.4 / 23.0, literal 20 % 37.5 / 34.4, 25 % 38.2 / 37.6
+    //                      32 rows              fp32 without feedback 9 % 21.9 / 23.9 and 12.3 / 19.7
+    //     (an empty row costs the less the fewer of them a lane has)
+    //   groups of two, which wait for another   bf16 51 % 141 / 126 and 73.6 / 68.0, 60 % 147 / 145 and 76.7 / 77.5, 70 % 155 / 161 and 81.5 / 87.4; fp32 51 % 128 / 111 and
+    //                                           63.6 / 59.4, 60 % 135 / 132 and 67.6 / 68.0, 70 % 142 / 154; without feedback 59 % 91.2 / 82.1 and 46.7 / 48.5, 70 % 94.4 / 93.4
+    //   of three and more                       two thirds full at least: 187 / 218 (68 %) and better
+    // Several shapes count by their items: 57 x [256, 3072] with 57 x [20, 3072] 123 / 137, 20 with 80 79 / 66; 30 x [1024, 64] with 90 x [16, 3072] 52 / 44.  Two kernels
+    // take a tall tensor through one latency after another, whatever else the call has: 40 x [16, 3072] with 10 x [3072, 64] (720 items) 34 / 51, 110 with one
+    // (1344) 50 / 55, 100 with 10 (1440) 54 / 63, 114 with 20 (1848) 71 / 63, 60 x [20, 3072] with 3 x [2048, 512] 33 / 46, 80 x [16, 3072] with 10 x [1536, 64] 46 / 42.
+    // Calls of a round, whatever their shape: 114 x [8, 1024] bf16 (456 items) 20.8 / 25.2, 30 x [128, 512] (60) 20.2 / 20.2, 9 x [64, 256] (9) 18.3 / 19.5; with their
+    // pointers along 8 x [64, 256] 9.6 / 19.3, [1, 8] 9.9 / 19.2, [4096, 256] 14.1 / 17.0, [16384, 64] 20.0 / 23.1 (what Python adds to a call, some 9 us, hides what
+    // the kernel takes below that).
+    const double rounds = grid > 0 ? (double)items / grid : 0.0;
+    const int stripe = ctx->L.sp_wide ? kStripeChannelsWide : ctx->L.sp_slim ? kStripeChannelsSlim : kStripeChannels;
+    double gain = 0.0;              // over the items, how far each is filled less how far it has to be
+    bool tall = false;
+    for (int32_t t = first; t < first + count; ++t) {
+        const TensorDev &d = ctx->L.dev[t];
+        if (d.p_rows == 0) continue;
+        const int rows_per_lane = single_pass_rows_per_lane(d.dtype, ef);
+        const double rows = (double)d.n_tokens / d.p_rows, width = (double)d.n_channels / stripe;         // in items
+        tall |= d.n_tokens >= 2048;
+        if (d.n_tokens >= 256 || d.p_n_rb > 2) gain += d.p_n_stripes * d.p_n_rb * (rounds <= 3.0 ? 0.4 : 0.3);      // as full as can be
+        else if (d.p_n_rb == 2) gain += d.p_n_stripes * (rows - (rounds <= 3.0 ? 1.2 : 1.4));
+        else gain += rows * width - d.p_n_stripes * (rows_per_lane < 8 ? 0.1 : rows_per_lane < 16 ? 0.25 : rounds <= 2.0 ? 1.0 / 3.0 : 0.4);
+    }
+    const bool worth_it = forced || small_call || (!ctx->L.sp_too_tall && (gain >= 0.0 || (tall && rounds <= 3.0)));
     // (a group larger than what the device holds at once would have its first workgroups wait for ones that cannot
     // start before they leave: correct, they give up and compute the missing sums, but slow: such tensors take two kernels)
     const bool single_pass = ctx->L.single_pass && grid >= ctx->L.max_group_items && grid >= 1 && r.item_hi > r.item_lo && worth_it;

@@ -260,7 +260,7 @@ int main()
     }
 
     // ---- which path a call takes by default: the single pass in calls of a round of workgroups (512 items here) and for tensors that
-    // fill a third of their items, two kernels for larger calls over shorter ones
+    // fill enough of their items, two kernels for larger calls over shorter ones
     {
         struct Case { int64_t n, c; const char *must, *must_not; uint32_t flags; };
         const Case cases[] = {
@@ -271,7 +271,7 @@ int main()
             {128, 8192, "k_single_pass", "k_colreduce", 0},             // a short tensor
             {42, 131072, "k_single_pass", "k_colreduce", 0},            // 512 items a third full
             {42, 131080, "k_colreduce k_finalize k_encode", "k_single_pass", 0},       // 513
-            {43, 131080, "k_single_pass", "k_colreduce", 0},
+            {43, 131080, "k_single_pass", "k_colreduce", 0},            // a third of an item's 128 rows
             {42, 131080, "k_single_pass", "k_colreduce", CF_FLAG_SINGLE_PASS},
             {4096, 512, "k_colreduce k_finalize k_encode", "k_single_pass", CF_FLAG_TWO_KERNEL},
         };
@@ -333,6 +333,24 @@ int main()
             {R, B, {{16, 4096, 3072}, {1, 10500, 80}}, NARROW}, {R, B, {{4, 12288, 3072}, {1, 10500, 80}}, SLIM},          // one of them among others
             {R, B, {{16, 4096, 3072}, {1, 12288, 3072}}, NARROW}, {R, B, {{16, 4096, 3072}, {1, 12289, 3072}}, SLIM},      // few tall ones: 48, 49 items
             {R, B, {{2, 4096, 3072}, {1, 12288, 3072}}, SLIM}, {R, B, {{16, 1024, 3072}, {1, 32769, 3072}}, TWO},
+            // short tensors: how much of its items a group of one fills, 128 rows of bf16, 64 of fp32 or with a third operand, 32 of both, in up to two
+            // rounds and more; a group of two, in up to three and more
+            {R, B, {{57, 42, 3072}}, TWO}, {R, B, {{57, 43, 3072}}, NARROW}, {R, B, {{114, 51, 3072}}, TWO}, {R, B, {{114, 52, 3072}}, NARROW},
+            {R, B, {{114, 49, 1096}}, TWO}, {R, B, {{114, 50, 1096}}, NARROW},             // its last stripe is 72 channels of 256
+            {N, B, {{114, 51, 3072}}, TWO}, {N, B, {{114, 52, 3072}}, NARROW}, {O, B, {{57, 15, 3072}}, TWO}, {O, B, {{57, 16, 3072}}, NARROW},
+            {R, F, {{57, 15, 3072}}, TWO}, {R, F, {{57, 16, 3072}}, NARROW}, {O, F, {{57, 3, 3072}}, TWO}, {L, F, {{57, 4, 3072}}, NARROW},
+            {R, B, {{42, 13, 3072}}, NARROW},                                              // 504 items
+            {R, B, {{57, 128, 3072}}, NARROW}, {R, B, {{57, 129, 3072}}, TWO}, {R, B, {{57, 153, 3072}}, TWO}, {R, B, {{57, 154, 3072}}, NARROW},
+            {R, B, {{114, 179, 3072}}, TWO}, {R, B, {{114, 180, 3072}}, NARROW}, {R, F, {{57, 76, 3072}}, TWO}, {R, F, {{57, 77, 3072}}, NARROW},
+            {R, F, {{114, 89, 3072}}, TWO}, {R, F, {{114, 90, 3072}}, NARROW}, {R, F, {{114, 129, 3072}}, NARROW},
+            {O, F, {{57, 38, 3072}}, TWO}, {O, F, {{57, 39, 3072}}, NARROW}, {O, F, {{57, 65, 3072}}, NARROW},
+            {R, B, {{57, 256, 3072}, {1, 4000, 3072}}, NARROW}, {R, B, {{57, 257, 3072}, {1, 4000, 3072}}, NARROW},           // items of 256 rows
+            // several widths, by their items; up to three rounds with a tall tensor
+            {R, B, {{114, 16, 3072}, {20, 3072, 64}}, TWO}, {R, B, {{114, 30, 3072}, {30, 3072, 64}}, TWO}, {R, B, {{30, 1024, 64}, {90, 16, 3072}}, TWO},
+            {R, B, {{20, 1024, 3072}, {200, 16, 256}}, NARROW}, {R, B, {{60, 128, 3072}, {100, 16, 256}}, NARROW}, {R, B, {{57, 77, 3072}, {57, 1024, 3072}}, NARROW},
+            {R, B, {{20, 256, 3072}, {80, 20, 3072}}, TWO}, {R, B, {{57, 256, 3072}, {57, 20, 3072}}, NARROW},
+            {R, B, {{60, 16, 3072}, {1, 2047, 64}}, TWO}, {R, B, {{60, 16, 3072}, {1, 2048, 64}}, NARROW},
+            {R, B, {{126, 16, 3072}, {1, 3072, 64}}, NARROW}, {R, B, {{127, 16, 3072}, {1, 3072, 64}}, TWO},
         };
         for (const Call &c : calls) {
             std::vector<cf_tensor_desc> d;
