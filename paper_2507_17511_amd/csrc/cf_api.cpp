@@ -554,15 +554,15 @@ struct cf_ctx {
         return r;
     }
 
-    // Whether short items serve the call: `r` and `v` are theirs then.
-    bool take_short(int32_t first, int32_t count, LaunchRange &r, BatchView &v) const
+    // Whether short items serve the call: `r` and `v` are theirs then.  resident: how many the device holds at once.
+    bool take_short(int32_t first, int32_t count, uint32_t resident, LaunchRange &r, BatchView &v) const
     {
         uint32_t items = 0;
         for (int32_t t = first; t < first + count; ++t) {
             if (L.n_short_items == 0 || L.short_dev[t].p_rows == 0) return false;
             items += (uint32_t)(L.short_dev[t].p_n_rb * L.short_dev[t].p_n_stripes);
         }
-        if (items > (uint32_t)kShortItems) return false;
+        if (items > (uint32_t)kShortItems || items > resident) return false;
         r.sp_short = 1;
         r.item_lo = L.short_dev[first].p_item_begin;
         r.item_hi = r.item_lo + items;
@@ -939,7 +939,7 @@ cf_status run_sender(cf_ctx *ctx, int32_t first, int32_t count, const void *cons
         e = run_row_local(ctx, first, count, v, r, fused, true, s);
         return e == hipSuccess ? CF_OK : device_fail(ctx, e);
     }
-    if (is_direct && count <= kDirectTensors && !(ctx->opts.flags & CF_FLAG_FIXED_GRID)) ctx->take_short(first, count, r, v);
+    if (is_direct && count <= kDirectTensors && !(ctx->opts.flags & CF_FLAG_FIXED_GRID)) ctx->take_short(first, count, 2u * (uint32_t)grid, r, v);       // they need half the registers
     if (!is_direct && (st = sync_ptrs(ctx, first, count, x, recon, err, codes, scales, s)) != CF_OK) return st;
     if (single_pass) {
         // channel-scale tensors: one pass, the operands stay in registers across the scale reduction

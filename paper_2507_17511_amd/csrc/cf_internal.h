@@ -47,7 +47,7 @@ constexpr int kStripeChannelsSlim = kStripeChannels / 2;    // 64
 // 64 of bf16 and groups of twice the items: [4096, 512] 14.9 us against 12.3, 2 x [1024, 3072] 15.3 / 14.7, 8 x [512, 1024] 11.8 / 12.3); see Layout::short_dev.
 constexpr int kShortFraction = 4;
 constexpr int kShortStripeChannels = 64;
-constexpr int kShortItems = 1024;                           // the most of a call: four workgroups a CU of the MI355X
+constexpr int kShortItems = 1024;                           // the most of a call: four workgroups a CU of the whole MI355X; a part of one takes as many as it holds
 constexpr int kShortGroupLimit = 64;                        // the most of a group
 constexpr int single_pass_rows_per_lane(int dtype, int ef) { return 16 / (dtype == 0 ? 2 : 1) / ((ef == 1 || ef == 2) ? 2 : 1); }
 // A workgroup polls a missing partial this many times (a microsecond or two each) before it gives its item up.

@@ -13,6 +13,7 @@
 extern std::vector<std::string> g_launch_log;
 extern bool g_single_pass_short;
 extern bool g_capturing;
+extern int g_compute_units;
 extern std::vector<uint8_t> g_states;
 extern bool g_single_pass_slim, g_occupancy_slim;
 extern bool g_project_many;
@@ -387,7 +388,7 @@ int main()
 
     // ---- short items: calls of at most 8 channel-scale tensors, 1024 items and 64 items of 128 rows (64 of fp32) x 64 channels a group
     {
-        struct Call { int32_t ef, dtype; uint32_t flags; std::vector<std::vector<int64_t>> shapes; bool is_short; };
+        struct Call { int32_t ef, dtype; uint32_t flags; std::vector<std::vector<int64_t>> shapes; bool is_short; int compute_units = 256; };
         const int R = CF_EF_RECON, B = CF_BF16, F = CF_F32;
         const std::vector<Call> calls = {
             {R, F, 0, {{1, 256, 64}}, true}, {R, B, 0, {{1, 1, 8}}, true}, {R, B, 0, {{2, 1024, 3072}}, true},
@@ -398,6 +399,7 @@ int main()
             {CF_EF_OFF, B, 0, {{1, 256, 64}}, false}, {CF_EF_NAIVE, B, 0, {{1, 256, 64}}, false},
             {R, B, 0, {{1, 256, 64}, {1, 9000, 64}, {1, 300, 64}}, false},
             {R, B, 0, {{64, 64, 256}}, false}, {R, B, 0, {{65, 64, 256}}, false},      // 64 take their pointers along
+            {R, B, 0, {{1, 8192, 128}}, true, 32}, {R, B, 0, {{1, 8192, 136}}, false, 32}, {R, B, 0, {{1, 8192, 136}}, true, 64},     // a smaller device: 128 items
         };
         for (const Call &c : calls) {
             std::vector<cf_tensor_desc> d;
@@ -406,6 +408,7 @@ int main()
             std::memset(&o, 0, sizeof o);
             o.ef = c.ef;
             o.flags = c.flags;
+            g_compute_units = c.compute_units;
             std::vector<void *> bufs[5];
             uintptr_t at = (uintptr_t)1 << 40;
             for (auto &b : bufs)
@@ -434,6 +437,7 @@ int main()
             cf_destroy(ctx);
             std::free(ws);
         }
+        g_compute_units = 256;
     }
 
     // ---- single passes on one stream carry their item states on; from the first one on another stream, on hipStreamPerThread or

@@ -13,6 +13,7 @@ using cf::TensorPtrs;
 
 std::vector<std::string> g_launch_log;
 bool g_capturing = false;
+int g_compute_units = 256;
 bool g_single_pass_slim = false;        // the stripe width of the last single pass
 bool g_single_pass_short = false;       // and its items' height
 bool g_occupancy_slim = false;          // and the one whose co-resident workgroups were asked for last
@@ -30,7 +31,7 @@ static void note(const char *what) { g_launch_log.push_back(what); }
 extern "C" {
 hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
 hipError_t hipGetLastError(void) { return hipSuccess; }
-hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int) { *v = g_compute_units; return hipSuccess; }
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *s)
 {
     *s = g_capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
