@@ -1,5 +1,6 @@
-"""Calls over at most eight tensors carry their device pointers in the kernel's arguments, larger ones in a table in the
-workspace: both have to give the same bits, whatever was called before and wherever in the context the call starts."""
+"""Calls over at most eight tensors (single passes over channel scales alone: sixty-four) carry their device pointers in the
+kernel's arguments, larger ones in a table in the workspace: both have to give the same bits, whatever was called before and
+wherever in the context the call starts."""
 import pytest
 import torch
 
@@ -13,11 +14,14 @@ DTYPES = {"mixed": lambda k: cf.CF_BF16 if k % 3 else cf.CF_F32, "bf16": lambda 
 
 
 class _Side:
-    """One context of ten tensors with their buffers, all made from the same seed."""
+    """One context of ten tensors with their buffers, all made from the same seed.  Among channel scales the last one is a group
+    scale, with which a call reads the table."""
 
     def __init__(self, kind, dtypes="mixed", **options):
         scale, group, bits = KINDS[kind]
         self.descs = [cf.desc(40 + 7 * k, 384, DTYPES[dtypes](k), bits, scale, group) for k in range(10)]
+        if kind == "channel":
+            self.descs[9] = cf.desc(103, 384, DTYPES[dtypes](9), 4, cf.CF_SCALE_GROUP)
         opts = cf.options(**options)
         nbytes = cf.cf_workspace_bytes(self.descs, opts)
         self.ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")

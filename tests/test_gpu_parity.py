@@ -50,30 +50,32 @@ def test_parity_shapes(bits, scale, dtype, mode, flags):
 @pytest.mark.parametrize("ef", [cf.CF_EF_RECON, cf.CF_EF_LITERAL, cf.CF_EF_OFF])
 @pytest.mark.parametrize("err_dtype", [cf.CF_F32, cf.CF_BF16])
 def test_parity_ef_modes_and_err_dtypes(ef, err_dtype):
+    """By default, where calls this small take the single pass for channel scales, and on two kernels."""
     n, c = 203, 1152
     for bits, scale in COMBOS:
         for dtype in (cf.CF_BF16, cf.CF_F32):
-            say(f"ef={ef} err_dtype={err_dtype} bits={bits} scale={scale} dtype={dtype}")
             d = cf.desc(n, c, dtype, bits, scale)
             xs = drift_stream((n, c), dtype, steps=5, seed=7 * bits + ef, device=DEV)
-            run_parity([d], cf.options(ef=ef, err_dtype=err_dtype), [[x] for x in xs], mode="fused")
+            for flags in (0, cf.CF_FLAG_TWO_KERNEL) if scale == CH else (0,):
+                say(f"ef={ef} err_dtype={err_dtype} bits={bits} scale={scale} dtype={dtype} flags={flags}")
+                run_parity([d], cf.options(ef=ef, err_dtype=err_dtype, flags=flags), [[x] for x in xs], mode="fused")
 
 
 @pytest.mark.parametrize("tile_rows", [8, 16, 32, 64])
 def test_parity_every_tile_height(tile_rows):
-    """The tree over rows is split differently for every tile height; scales must not move."""
+    """The two-kernel path splits the tree over rows differently for every tile height; scales must not move."""
     n, c = 333, 1096
     for bits in (1, 2, 4):
         say(f"tile_rows={tile_rows} bits={bits}")
         d = cf.desc(n, c, cf.CF_BF16, bits, CH)
         xs = drift_stream((n, c), cf.CF_BF16, steps=3, seed=bits, device=DEV)
-        run_parity([d], cf.options(tile_rows=tile_rows), [[x] for x in xs])
+        run_parity([d], cf.options(tile_rows=tile_rows, flags=cf.CF_FLAG_TWO_KERNEL), [[x] for x in xs])
 
 
 @pytest.mark.parametrize("encode_rows", [1, 2, 3, 8, 64])
 def test_parity_every_encode_height(encode_rows):
-    """Rows per workgroup of the element-wise kernels, on channel counts with (1152, 3072) and
-    without (1096, 8) whole quads of lanes (the gathered code stores need them)."""
+    """Rows per workgroup of the element-wise kernels (for channel scales the second of two kernels), on channel counts with
+    (1152, 3072) and without (1096, 8) whole quads of lanes (the gathered code stores need them)."""
     for k, (n, c) in enumerate([(67, 1152), (130, 1096), (9, 8), (33, 3072)]):
         for bits, scale in COMBOS:
             if scale == GR and c % 128:
@@ -82,7 +84,7 @@ def test_parity_every_encode_height(encode_rows):
             d = cf.desc(n, c, cf.CF_BF16, bits, scale)
             xs = drift_stream((n, c), cf.CF_BF16, steps=3, seed=11 * k + bits, device=DEV)
             for mode in ("fused", "split"):
-                run_parity([d], cf.options(encode_rows=encode_rows), [[x] for x in xs], mode=mode)
+                run_parity([d], cf.options(encode_rows=encode_rows, flags=cf.CF_FLAG_TWO_KERNEL), [[x] for x in xs], mode=mode)
 
 
 def _mixed_batch():
@@ -220,7 +222,7 @@ def test_single_pass_every_feedback_mode(ef, err_dtype):
 @pytest.mark.parametrize("ef", [cf.CF_EF_RECON, cf.CF_EF_OFF])
 def test_single_pass_gives_up_and_redoes(ef):
     """CF_FLAG_TEST_NO_WAIT: a workgroup that does not find every partial sum of its stripe at its first look gives
-    its item up, and the second launch of the call does it.  Same bits as ever, and the give-up path did run."""
+    its item up, computes what is missing and starts again.  Same bits as ever, and the give-up path did run."""
     descs = [cf.desc(1500, 1096, cf.CF_BF16, (1, 2, 4)[t % 3], CH) for t in range(4)]
     descs += [cf.desc(700, 520, cf.CF_F32, (2, 4, 1)[t % 3], CH) for t in range(2)]
     streams = [drift_stream((d.n_tokens, d.n_channels), d.dtype, steps=3, seed=470 + 10 * ef + k, device=DEV)
@@ -237,7 +239,7 @@ def test_single_pass_gives_up_and_redoes(ef):
             c.warmup(xs[0])
             c.step_fused(xs[1])
         n_gave_up = cf.cf_given_up_items(sess.ctx, sess.stream_handle)
-        say(f"   {n_gave_up} items were given up and redone; {cf.cf_given_up_items(quiet.ctx, quiet.stream_handle)} in the ordinary run")
+        say(f"   {n_gave_up} items were given up at first; {cf.cf_given_up_items(quiet.ctx, quiet.stream_handle)} in the ordinary run")
         assert n_gave_up > 0, "the give-up path was not exercised"
         assert cf.cf_given_up_items(quiet.ctx, quiet.stream_handle) == 0
         for t in range(len(descs)):
@@ -274,7 +276,7 @@ def test_single_pass_next_to_other_work_on_the_device():
                     a = torch.tanh(b * 1e-3)
             cf.cf_check_device(busy.ctx, busy.stream_handle)
             torch.cuda.synchronize()
-            say(f"step {s} next to a busy stream: {cf.cf_given_up_items(busy.ctx, busy.stream_handle)} items given up and redone")
+            say(f"step {s} next to a busy stream: {cf.cf_given_up_items(busy.ctx, busy.stream_handle)} items given up at first")
             for t in range(len(descs)):
                 assert torch.equal(busy.recon[t], quiet.recon[t]), f"recon[{t}] differs from the quiet run at step {s}"
                 assert torch.equal(busy.err[t], quiet.err[t]) and torch.equal(busy.codes[t], quiet.codes[t])
@@ -370,11 +372,11 @@ def test_receiver_tracks_sender_through_the_wire():
 def test_zero_residual_and_exact_round_trip_on_gpu():
     say("zero residual / representable")
     rng = np.random.default_rng(3)
-    for bits, scale in COMBOS:
+    for (bits, scale), flags in [(combo, 0) for combo in COMBOS] + [(combo, cf.CF_FLAG_TWO_KERNEL) for combo in COMBOS if combo[1] == CH]:
         n, c = 384, 256
         d = cf.desc(n, c, cf.CF_F32, bits, scale)
         x0 = torch.from_numpy(np.round(rng.standard_normal((n, c)) * 4).astype(np.float32)).to(DEV)
-        s = CodecSession([d], device=DEV)
+        s = CodecSession([d], cf.options(flags=flags), device=DEV)
         s.warmup([x0])
         s.step_fused([x0])                        # x_t == recon_{t-1}
         torch.cuda.synchronize()
@@ -413,7 +415,8 @@ def test_extreme_values_stay_in_parity():
         for dtype in (cf.CF_F32, cf.CF_BF16):
             d = cf.desc(n, c, dtype, bits, scale)
             conv = (lambda a: torch.from_numpy(a).to(DEV).to(torch.bfloat16)) if dtype == cf.CF_BF16 else (lambda a: torch.from_numpy(a).to(DEV))
-            run_parity([d], cf.options(), [[conv(x0)], [conv(x1)], [conv(x1 * 0.5)]], tag=f"extreme b{bits}s{scale}d{dtype}")
+            for flags in (0, cf.CF_FLAG_TWO_KERNEL) if scale == CH else (0,):
+                run_parity([d], cf.options(flags=flags), [[conv(x0)], [conv(x1)], [conv(x1 * 0.5)]], tag=f"extreme b{bits}s{scale}d{dtype} flags={flags}")
 
 
 # ------------------------------------------------------------------ argument and state errors (need a context)
@@ -616,7 +619,8 @@ def test_parity_naive_compression(bits, scale, dtype, mode):
             say(f"naive bits={bits} scale={scale} dtype={dtype} mode={mode} err_dtype={err_dtype} N={n} C={c}")
             d = cf.desc(n, c, dtype, bits, scale)
             xs = drift_stream((n, c), dtype, steps=3, seed=500 + k, sigma=0.3, device=DEV)
-            run_parity([d], cf.options(ef=cf.CF_EF_NAIVE, err_dtype=err_dtype), [[x] for x in xs], mode=mode, tag="naive")
+            for flags in (0, cf.CF_FLAG_TWO_KERNEL) if scale == CH else (0,):
+                run_parity([d], cf.options(ef=cf.CF_EF_NAIVE, err_dtype=err_dtype, flags=flags), [[x] for x in xs], mode=mode, tag=f"naive flags={flags}")
 
 
 @pytest.mark.parametrize("bits", [1, 2])

@@ -18,27 +18,37 @@ def say(msg):
 @pytest.mark.parametrize("flags", [0, cf.CF_FLAG_FIXED_GRID, cf.CF_FLAG_TEST_NO_WAIT])
 @pytest.mark.parametrize("ef", [cf.CF_EF_RECON, cf.CF_EF_OFF])
 def test_calls_over_changing_ranges(ef, flags):
-    """Ten tensors, groups of one item to six: whole batches by the table of pointers, parts with their pointers as
-    arguments (at most eight tensors), one tensor alone, odd and even numbers of calls for each tensor; every output
-    bit for bit what the two-kernel path gives in the same sequence."""
+    """Ten channel-scale tensors, groups of one item to six, and one of group scales: calls with that one by the table of pointers,
+    the others with their pointers as arguments, up to eight tensors with their descriptors too; one tensor alone, odd and even
+    numbers of calls for each tensor; every output bit for bit what the two-kernel path gives in the same sequence."""
     shapes = [(1500, 1096), (700, 520), (1, 8), (257, 256), (256, 264), (129, 72), (1030, 512), (300, 3072), (64, 64), (511, 1032)]
     descs = [cf.desc(n, c, cf.CF_F32 if t % 4 == 1 else cf.CF_BF16, (1, 2, 4)[t % 3], cf.CF_SCALE_CHANNEL) for t, (n, c) in enumerate(shapes)]
+    descs.append(cf.desc(70, 256, cf.CF_BF16, 4, cf.CF_SCALE_GROUP))
     streams = [drift_stream((d.n_tokens, d.n_channels), d.dtype, steps=4, seed=910 + t, device=DEV) for t, d in enumerate(descs)]
     one = CodecSession(descs, cf.options(ef=ef, flags=cf.CF_FLAG_SINGLE_PASS | flags), device=DEV)
     two = CodecSession(descs, cf.options(ef=ef, flags=cf.CF_FLAG_TWO_KERNEL), device=DEV)
+    events = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+    for event in events:
+        event.record()              # before it has a handle
+    uploads = 0
     try:
         for sess in (one, two):
             sess.warmup([s[0] for s in streams])
-        for k, (first, count) in enumerate([(0, 10), (0, 3), (1, 9), (7, 1), (7, 1), (0, 8), (2, 8), (0, 10), (9, 1), (0, 10)]):
+        for k, (first, count) in enumerate([(0, 11), (0, 3), (1, 9), (7, 1), (7, 1), (3, 8), (0, 8), (2, 8), (0, 10), (0, 11), (9, 1), (0, 10), (0, 11), (0, 10)]):
             x = [s[1 + k % 3] for s in streams]
+            cf.cf_profile_next_call(one.ctx, [e.cuda_event for e in events], 1)
             for sess in (one, two):
                 sess.step_fused(x[first:first + count], first, count)
             cf.cf_check_device(one.ctx, one.stream_handle)
+            kernels = [cf.cf_profile_kernel_name(one.ctx, j) for j in range(cf.cf_profile_launch_count(one.ctx))]
+            assert "k_single_pass" in kernels and (first + count == 11 or kernels == ["k_single_pass"])
+            uploads += "k_upload_ptrs" in kernels
             say(f"ef={ef} flags={flags} call {k}: tensors {first}..{first + count - 1}, {cf.cf_given_up_items(one.ctx, one.stream_handle)} items given up")
             for t in range(len(descs)):
                 for name in ("codes", "scales", "recon", "err"):
                     a, b = getattr(one, name)[t], getattr(two, name)[t]
                     assert torch.equal(a.view(torch.uint8).reshape(-1), b.view(torch.uint8).reshape(-1)), f"call {k}: {name}[{t}]"
+        assert uploads == 3         # the last of four calls by the table finds there what the one before left
     finally:
         one.close()
         two.close()
