@@ -23,8 +23,8 @@
  * All calls enqueue work on it and return without synchronising; buffers must
  * stay valid until the stream has passed that work.  A context is not
  * thread-safe: use it from one host thread at a time, on one stream at a time.
- * Calls of one context that overlap in time all the same spoil one another's results, but
- * nothing beyond them.
+ * Calls of one context that overlap in time all the same spoil the tensors that they have in
+ * common, which hold undefined values until they are warmed up again (cf_warmup).
  *
  * Layouts (all dense, row-major, C contiguous; base pointers 16-byte aligned):
  *   x, recon : [N, C] of `dtype`
@@ -74,8 +74,8 @@
  * single pass, take their pointers along in the kernels' arguments and
  * neither read nor change the table.
  * The single pass carries a bit per partial sum from one call to the next.  Once a context's
- * single passes come on more than one stream, on hipStreamPerThread or under capture, each of
- * them starts with a small kernel that sets those bits afresh.
+ * single passes have come on more than one stream, on hipStreamPerThread or under capture, and
+ * so may have overlapped, a warm-up sets those bits afresh too.
  */
 #ifndef COMPACTFUSION_H
 #define COMPACTFUSION_H

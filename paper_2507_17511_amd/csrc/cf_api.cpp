@@ -429,6 +429,7 @@ struct cf_ctx {
     hipStream_t sp_stream = nullptr;   // stream of the single passes so far
     bool sp_called = false;
     bool sp_unordered = false;         // single passes were enqueued on several streams or captured: no stream keeps them apart for certain
+    bool sp_always_fresh = false;      // every single pass sets its signs anew
     std::vector<uint8_t> warm;
     int32_t last_hip = 0;
     int device = 0;
@@ -465,37 +466,39 @@ struct cf_ctx {
         return launch_fill_words(ws + L.off_item_state, kFreshPartials, (L.off_lr_slices - L.off_item_state) / sizeof(uint32_t), s);
     }
 
-    // Whether a single pass on `s` has to start with states and partials as before a first call.  Its kernel takes over the signs that the
-    // call before left, which calls that overlapped (against the rules) leave in disorder.  On one stream no two can; from the first
-    // that comes on another stream, or is recorded into a graph, which may be replayed on any, every single pass makes its own anew (k_fresh_partials, 3-4 us), so that
-    // overlapping calls spoil nothing but themselves.  hipStreamPerThread is a stream of its own in every thread.
-    bool needs_fresh_partials(hipStream_t s)
+    // A single pass takes over the signs that the call before left, which calls that overlapped (against the rules) may leave in disorder.  On one stream
+    // no two can; once single passes came on another stream than the ones before, or were recorded into a graph, which may be replayed on any, warm-ups, which
+    // the tensors need then, set their signs anew.  hipStreamPerThread is a stream of its own in every thread.
+    void note_single_pass(hipStream_t s)
     {
-        if (!sp_unordered) {
-            hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-            if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
-                (void)hipGetLastError();
-                cap = hipStreamCaptureStatusNone;
-            }
-            sp_unordered = cap != hipStreamCaptureStatusNone || s == hipStreamPerThread || (sp_called && sp_stream != s);
-            sp_called = true;
-            sp_stream = s;
+        if (sp_unordered) return;
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
+            (void)hipGetLastError();
+            cap = hipStreamCaptureStatusNone;
         }
-        return sp_unordered;
+        sp_unordered = cap != hipStreamCaptureStatusNone || s == hipStreamPerThread || (sp_called && sp_stream != s);
+        sp_called = true;
+        sp_stream = s;
     }
 
-    // What a single pass over the range, with its items, uses of them.
-    hipError_t fresh_partials_of(int32_t first, int32_t count, const LaunchRange &r, const BatchView &v, hipStream_t s) const
+    // Item states and partials of the range as before a first call, of the items of `devs`: L.dev or L.short_dev.
+    hipError_t fresh_partials_of(int32_t first, int32_t count, const std::vector<TensorDev> &devs, size_t off_state, hipStream_t s) const
     {
-        const std::vector<TensorDev> &devs = r.sp_short ? L.short_dev : L.dev;
         uint64_t lo = ~(uint64_t)0, hi = 0;
+        uint32_t item_lo = 0, item_hi = 0;
         for (int32_t t = first; t < first + count; ++t) {
-            if (devs[t].p_rows == 0) continue;
-            lo = std::min<uint64_t>(lo, devs[t].p_partial_off);
-            hi = std::max<uint64_t>(hi, devs[t].p_partial_off + align_up((size_t)devs[t].p_n_rb * (size_t)devs[t].n_channels * sizeof(float)));
+            const TensorDev &d = devs[t];
+            if (d.p_rows == 0) continue;
+            if (hi == 0) {
+                lo = d.p_partial_off;
+                item_lo = d.p_item_begin;
+            }
+            hi = d.p_partial_off + align_up((size_t)d.p_n_rb * (size_t)d.n_channels * sizeof(float));
+            item_hi = d.p_item_begin + (uint32_t)(d.p_n_rb * d.p_n_stripes);
         }
-        if (hi <= lo) return hipSuccess;
-        return launch_fresh_partials(ws + lo, hi - lo, v.item_state + r.item_lo, r.item_hi - r.item_lo, s);
+        if (hi == 0) return hipSuccess;
+        return launch_fresh_partials(ws + lo, hi - lo, ws + off_state + item_lo, item_hi - item_lo, s);
     }
 
     LaunchRange range(int32_t first, int32_t count) const
@@ -948,10 +951,14 @@ cf_status run_sender(cf_ctx *ctx, int32_t first, int32_t count, const void *cons
         r.sp_xcd_major = !r.sp_short && ctx->L.max_group_items <= 4;
         r.sp_wait_polls = (ctx->opts.flags & CF_FLAG_TEST_NO_WAIT) ? 0u : kWaitPolls;
         const bool one_shot = (ctx->opts.flags & CF_FLAG_FIXED_GRID) == 0;
-        if (ctx->needs_fresh_partials(s)) {
-            e = launch(ctx, s, "k_fresh_partials", [&] { return ctx->fresh_partials_of(first, count, r, v, s); });
+        if (ctx->sp_always_fresh) {
+            e = launch(ctx, s, "k_fresh_partials", [&] {
+                return r.sp_short ? ctx->fresh_partials_of(first, count, ctx->L.short_dev, ctx->L.off_short_state, s)
+                                  : ctx->fresh_partials_of(first, count, ctx->L.dev, ctx->L.off_item_state, s);
+            });
             if (e != hipSuccess) return device_fail(ctx, e);
         }
+        ctx->note_single_pass(s);
         e = launch(ctx, s, "k_single_pass", [&] { return launch_single_pass(v, r, ef, et, fused, ctx->L.sp_wide, grid, one_shot, s); });
         if (e != hipSuccess) return device_fail(ctx, e);
         r.only_group_scale = 1;
@@ -1115,6 +1122,10 @@ cf_status cf_warmup(cf_ctx *ctx, int32_t first, int32_t count, const void *const
         (st = sync_ptrs(ctx, first, count, x0, recon, err, nullptr, nullptr, s)) != CF_OK)
         return st;
     hipError_t e = launch_warmup(ctx->view(), r, ctx->opts.err_dtype, s);
+    if (e == hipSuccess && ctx->sp_unordered) {
+        e = ctx->fresh_partials_of(first, count, ctx->L.dev, ctx->L.off_item_state, s);
+        if (e == hipSuccess) e = ctx->fresh_partials_of(first, count, ctx->L.short_dev, ctx->L.off_short_state, s);
+    }
     if (e != hipSuccess) return device_fail(ctx, e);
     for (int32_t t = first; t < first + count; ++t) ctx->warm[t] = 1;
     return CF_OK;
@@ -1202,7 +1213,7 @@ cf_status cf_step_fused_static(const cf_tensor_desc *descs, int32_t n_tensors, c
         st = make_ctx(&ctx, descs, n_tensors, o, ws, kStaticScratchBytes, s);
         if (st != CF_OK) return st;
         for (auto &w : ctx->warm) w = 1;        // the caller vouches for recon and err
-        ctx->sp_unordered = true;               // every caller on the GPU shares the scratch
+        ctx->sp_unordered = ctx->sp_always_fresh = true;        // every caller on the GPU shares the scratch, and nobody warms up
     }
     return run_sender(ctx, 0, n_tensors, x, recon, err, codes, scales, stream, true);
 }

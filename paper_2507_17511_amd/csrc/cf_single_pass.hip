@@ -428,7 +428,7 @@ __global__ __launch_bounds__(kPersistThreads, SHORT ? 4 : 2) void k_single_pass(
     }
 }
 
-// States and partials as before a first call, byte by byte the states: other tensors' lie next to them.
+// States and partials as before a first call; the states byte by byte: other tensors' lie next to them.
 __global__ void k_fresh_partials(u32x4 *partials, uint64_t n_vec, uint8_t *states, uint32_t n_states)
 {
     const uint64_t at = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (uint64_t)gridDim.x * blockDim.x;
@@ -439,7 +439,8 @@ __global__ void k_fresh_partials(u32x4 *partials, uint64_t n_vec, uint8_t *state
 
 template <int EF, int ET, bool FUSED, int SCH> const void *persistent_fn(bool short_items)
 {
-    // one stripe width, and no other feedback mode: a quarter of their rows would be one or two a lane
+    // one stripe width, and the default feedback mode alone: with a third operand a quarter of the rows would be one or two a lane (naive compression
+    // would have as many as the default; no kernels for it here)
     if (EF == EF_RECON && short_items) return reinterpret_cast<const void *>(&k_single_pass<EF_RECON, ET, FUSED, kShortStripeChannels, true>);
     return reinterpret_cast<const void *>(&k_single_pass<EF, ET, FUSED, SCH, false>);
 }

@@ -14,6 +14,7 @@ extern std::vector<std::string> g_launch_log;
 extern bool g_single_pass_short;
 extern bool g_capturing;
 extern int g_compute_units;
+extern bool g_overlapping;
 extern std::vector<uint8_t> g_states;
 extern bool g_single_pass_slim, g_occupancy_slim;
 extern bool g_project_many;
@@ -440,61 +441,94 @@ int main()
         g_compute_units = 256;
     }
 
-    // ---- single passes on one stream carry their item states on; from the first one on another stream, on hipStreamPerThread or
-    // under capture each of them starts afresh, whatever calls that overlapped have left, and leaves its neighbours' states alone
+    // ---- single passes carry their item states on from call to call; once they came on several streams, on hipStreamPerThread or under
+    // capture, a warm-up makes them agree again, whatever calls that overlapped have left, and leaves its neighbours' alone
     for (int64_t tokens : {1000, 60000}) {      // short items, and tall ones
         const std::vector<cf_tensor_desc> d = {desc(tokens, 72, CF_BF16, 1, CF_SCALE_CHANNEL), desc(tokens, 200, CF_BF16, 1, CF_SCALE_CHANNEL),
-                                               desc(tokens, 72, CF_BF16, 1, CF_SCALE_CHANNEL)};
+                                               desc(64, 128, CF_BF16, 4, CF_SCALE_GROUP), desc(tokens, 72, CF_BF16, 1, CF_SCALE_CHANNEL)};
+        const int n = (int)d.size();
         std::memset(&o, 0, sizeof o);
         o.flags = CF_FLAG_SINGLE_PASS;
         std::vector<void *> bufs[5];
         uintptr_t at = (uintptr_t)1 << 40;
         for (auto &b : bufs)
-            for (int t = 0; t < 3; ++t, at += (uintptr_t)1 << 32) b.push_back((void *)at);
-        const size_t wsb = cf_workspace_bytes(d.data(), 3, &o);
+            for (int t = 0; t < n; ++t, at += (uintptr_t)1 << 32) b.push_back((void *)at);
+        const size_t wsb = cf_workspace_bytes(d.data(), n, &o);
         void *ws = nullptr;
         if (posix_memalign(&ws, 256, wsb) != 0) std::abort();
+        std::memset(ws, 0, wsb);
         cf_ctx *ctx = nullptr;
         void *const a = (void *)0x1000, *const b = (void *)0x2000;
-        const auto fresh = [&](int first, int count, void *stream) {        // whether the call made its states anew; they have to agree then
+        const auto step = [&](int first, int count, void *stream) {
             EXPECT(cf_step_fused(ctx, first, count, (const void *const *)bufs[0].data() + first, bufs[1].data() + first, bufs[2].data() + first,
                                  bufs[3].data() + first, bufs[4].data() + first, stream) == CF_OK);
             const std::string seq = joined();
-            EXPECT(seq.find("misplaced") == std::string::npos && g_single_pass_short == (tokens == 1000));
-            const bool anew = seq.find("k_fresh_partials k_single_pass") != std::string::npos;
-            for (uint8_t state : g_states) EXPECT(!anew || state == 0x80u);
-            return anew;
+            EXPECT(seq.find("k_single_pass") != std::string::npos && seq.find("k_fresh_partials") == std::string::npos);
         };
+        const auto warm_up = [&](int first, int count, void *stream) {     // how many launches set states anew
+            EXPECT(cf_warmup(ctx, first, count, (const void *const *)bufs[0].data() + first, bufs[1].data() + first, bufs[2].data() + first, stream) == CF_OK);
+            const std::string seq = joined();
+            EXPECT(seq.find("k_warmup") != std::string::npos && seq.find("misplaced") == std::string::npos);
+            int times = 0;
+            for (size_t p = seq.find("k_fresh_partials"); p != std::string::npos; p = seq.find("k_fresh_partials", p + 1)) ++times;
+            return times;
+        };
+        const int geometries = tokens == 1000 ? 2 : 1;
         const auto set_up = [&] {
             cf_destroy(ctx);
-            EXPECT(cf_init(&ctx, d.data(), 3, &o, ws, wsb, b) == CF_OK && cf_set_warm(ctx, 0, 3, 1) == CF_OK);
+            EXPECT(cf_init(&ctx, d.data(), n, &o, ws, wsb, b) == CF_OK);
             joined();
+            EXPECT(warm_up(0, n, b) == 0);
         };
-        set_up();
-        for (int k = 0; k < 3; ++k) {
-            EXPECT(!fresh(0, 3, a));                // cf_init's own stream may be another one
-            for (uint8_t state : g_states) EXPECT(state == (k % 2 ? 0u : 0x80u));
+        const auto agree = [&](uint8_t state) {
+            for (uint8_t found : g_states)
+                if (found != state) return false;
+            return !g_states.empty();
+        };
+        for (int how = 0; how < 4; ++how) {
+            set_up();
+            for (int k = 0; k < 3; ++k) {       // cf_init's own stream, or the warm-up's, may be another one
+                step(0, 2, a);
+                EXPECT(agree(k % 2 ? 0u : 0x80u) && g_single_pass_short == (tokens == 1000));
+                EXPECT(warm_up(1, 1, a) == 0);
+            }
+            step(0, n, a);                      // by the table: items as elsewhere
+            EXPECT(!g_single_pass_short);
+            if (how == 0) step(0, 1, b);
+            if (how == 1) step(0, 1, (void *)hipStreamPerThread);
+            g_capturing = how == 2;
+            step(0, 1, a);
+            g_capturing = false;
+            if (how == 3) {                     // one stream, no capture
+                EXPECT(warm_up(0, n, a) == 0);
+                continue;
+            }
+            g_overlapping = true;
+            step(0, 2, a);
+            if (geometries == 2) step(0, n, a);
+            g_overlapping = false;
+            step(0, 2, a);
+            EXPECT(!agree(0u) && !agree(0x80u));
+            EXPECT(warm_up(2, 1, b) == 0);      // no channel scales
+            EXPECT(warm_up(1, 1, a) == geometries);
+            step(1, 1, a);
+            EXPECT(agree(0x80u));
+            EXPECT(warm_up(0, n, a) == geometries);
+            step(0, 2, a);
+            EXPECT(agree(0x80u));
+            EXPECT(warm_up(0, n, a) == geometries);
+            step(0, n, a);
+            EXPECT(agree(0x80u) && !g_single_pass_short);
         }
-        EXPECT(!fresh(1, 1, a));
-        EXPECT(fresh(1, 1, b) && fresh(1, 1, b) && fresh(0, 1, a));
-        EXPECT(fresh(2, 1, a) && fresh(0, 3, a));
+        // a warm-up leaves what lies next to it as it was
         set_up();
-        EXPECT(!fresh(0, 3, a) && !fresh(2, 1, a) && fresh(1, 1, b));
-        const std::vector<uint8_t> middle = g_states;
-        EXPECT(fresh(0, 3, b) && g_states.size() > middle.size());
-        set_up();
-        EXPECT(!fresh(0, 3, nullptr));
-        g_capturing = true;
-        EXPECT(fresh(0, 3, nullptr));
-        g_capturing = false;
-        EXPECT(fresh(0, 3, nullptr));
-        set_up();
-        EXPECT(fresh(0, 3, (void *)hipStreamPerThread));
-        // a call over one tensor leaves what lies next to it as it was
-        set_up();
-        EXPECT(!fresh(0, 3, a) && fresh(1, 1, b));
+        step(0, 2, a);
+        step(0, 4, b);
+        EXPECT(warm_up(1, 1, a) == geometries);
         const std::vector<uint8_t> before((const uint8_t *)ws, (const uint8_t *)ws + wsb);
-        EXPECT(fresh(1, 1, b));
+        step(1, 1, a);
+        EXPECT(std::memcmp(before.data(), ws, wsb) != 0);
+        EXPECT(warm_up(1, 1, a) == geometries);
         EXPECT(std::memcmp(before.data(), ws, wsb) == 0);
         cf_destroy(ctx);
         std::free(ws);

@@ -20,6 +20,7 @@ bool g_occupancy_slim = false;          // and the one whose co-resident workgro
 bool g_project_many = false;            // whether the last projection's waves take several blocks of tokens
 int g_split = 0;                        // and the workgroups that share a stripe of the last back-projection
 std::vector<TensorPtrs> g_direct;       // the pointers that the last kernel of a direct call took as arguments; none: it read the table
+bool g_overlapping = false;             // single passes leave item states as calls that overlapped may
 std::vector<uint8_t> g_states;          // the item states that the last single pass found
 static void take_direct(const LaunchRange &r)
 {
@@ -97,7 +98,7 @@ hipError_t launch_single_pass(const BatchView &v, const LaunchRange &r, int, int
     g_single_pass_slim = r.sp_slim != 0;
     g_single_pass_short = r.sp_short != 0;
     g_states.assign(v.item_state + r.item_lo, v.item_state + r.item_hi);
-    for (uint32_t i = r.item_lo; i < r.item_hi; ++i) v.item_state[i] ^= 0x80u;      // as the kernel's items do
+    for (uint32_t i = r.item_lo; i < r.item_hi; i += g_overlapping ? 2 : 1) v.item_state[i] ^= 0x80u;      // as the kernel's items do, all of them or not
     if (r.sp_short)     // the call's tensors one after another, and nothing else
         for (int k = 0; k < r.count; ++k) {
             const uint32_t items = (uint32_t)(r.direct_descs[k].p_n_rb * r.direct_descs[k].p_n_stripes);

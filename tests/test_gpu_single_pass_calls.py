@@ -71,7 +71,7 @@ def test_short_items(dtype, err_dtype, flags):
 
 
 def test_small_call_replays_from_a_graph():
-    """A captured call that carries its pointers: replays and eager calls in turn, against an eager context."""
+    """A captured call that carries its pointers: replays, eager calls and a warm-up in turn, against an eager context."""
     descs = [cf.desc(1024, 512, cf.CF_BF16, 2, cf.CF_SCALE_CHANNEL), cf.desc(900, 384, cf.CF_BF16, 1, cf.CF_SCALE_CHANNEL)]
     streams = [drift_stream((d.n_tokens, d.n_channels), d.dtype, steps=8, seed=950 + t, device=DEV) for t, d in enumerate(descs)]
     graphed, eager = (CodecSession(descs, cf.options(flags=cf.CF_FLAG_SINGLE_PASS), device=DEV) for _ in range(2))
@@ -86,6 +86,9 @@ def test_small_call_replays_from_a_graph():
         for k in range(1, 8):
             for t in range(len(descs)):
                 x[t].copy_(streams[t][k])
+            if k == 6:
+                for sess in (graphed, eager):
+                    sess.warmup([s[0] for s in streams])
             if k in (3, 4):
                 graphed.step_fused(x)
             else:
@@ -103,7 +106,8 @@ def test_small_call_replays_from_a_graph():
 @pytest.mark.parametrize("ef", [cf.CF_EF_RECON, cf.CF_EF_NAIVE])
 def test_streams_in_turn(ef):
     """Calls of one context on two streams in turn, each after the other has been waited for: short items (default feedback mode, up
-    to eight tensors) and tall ones, single tensors between whole batches, whose neighbours' bits must stay; against two kernels."""
+    to eight tensors) and tall ones, and warm-ups of some tensors in between, which set the bits of their partial sums anew then and
+    must leave their neighbours' as they are; against two kernels."""
     shapes = [(700, 520), (1, 8), (1030, 512), (64, 72), (2600, 264), (129, 72), (511, 1032), (257, 256), (300, 64)]
     descs = [cf.desc(n, c, cf.CF_F32 if t % 4 == 1 else cf.CF_BF16, (1, 2, 4)[t % 3], cf.CF_SCALE_CHANNEL) for t, (n, c) in enumerate(shapes)]
     streams = [drift_stream((d.n_tokens, d.n_channels), d.dtype, steps=4, seed=870 + t, device=DEV) for t, d in enumerate(descs)]
@@ -114,11 +118,16 @@ def test_streams_in_turn(ef):
         for sess in (one, two):
             sess.warmup([s[0] for s in streams])
         calls = [(0, 9, 0), (0, 3, 0), (3, 1, 1), (0, 9, 1), (2, 1, 0), (1, 8, 1), (4, 1, 1), (0, 9, 0), (8, 1, 1), (0, 9, 0), (0, 8, 0)]
+        warm = {3: (2, 3), 4: (4, 1), 6: (0, 9), 7: (0, 1), 9: (5, 4)}         # before these calls
         for k, (first, count, where) in enumerate(calls):
             x = [s[1 + k % 3] for s in streams]
+            if k in warm:
+                two.warmup(x[warm[k][0]:sum(warm[k])], *warm[k])
             two.step_fused(x[first:first + count], first, count)
             torch.cuda.synchronize()
             with torch.cuda.stream(other if where else torch.cuda.current_stream()):
+                if k in warm:
+                    one.warmup(x[warm[k][0]:sum(warm[k])], *warm[k])
                 one.step_fused(x[first:first + count], first, count)
                 cf.cf_check_device(one.ctx, one.stream_handle)
                 assert cf.cf_given_up_items(one.ctx, one.stream_handle) == 0
