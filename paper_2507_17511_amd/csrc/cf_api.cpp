@@ -914,7 +914,8 @@ cf_status run_sender(cf_ctx *ctx, int32_t first, int32_t count, const void *cons
     // (1344) 50 / 55, 100 with 10 (1440) 54 / 63, 114 with 20 (1848) 71 / 63, 60 x [20, 3072] with 3 x [2048, 512] 33 / 46, 80 x [16, 3072] with 10 x [1536, 64] 46 / 42.
     // Calls of a round, whatever their shape: 114 x [8, 1024] bf16 (456 items) 20.8 / 25.2, 30 x [128, 512] (60) 20.2 / 20.2, 9 x [64, 256] (9) 18.3 / 19.5; with their
     // pointers along 8 x [64, 256] 9.6 / 19.3, [1, 8] 9.9 / 19.2, [4096, 256] 14.1 / 17.0, [16384, 64] 20.0 / 23.1 (what Python adds to a call, some 9 us, hides what
-    // the kernel takes below that).
+    // the kernel takes below that).  Replayed from a graph, where launches cost less, tiny bf16 calls of more than eight tensors are the slower ones: 9 x [64, 256]
+    // 15.5 / 13.1, 60 x [16, 256] 15.5 / 14.0, but 20 x [250, 1024] 19.0 / 27.6.
     const double rounds = grid > 0 ? (double)items / grid : 0.0;
     const int stripe = ctx->L.sp_wide ? kStripeChannelsWide : ctx->L.sp_slim ? kStripeChannelsSlim : kStripeChannels;
     double gain = 0.0;              // over the items, how far each is filled less how far it has to be
