@@ -23,8 +23,8 @@
  * All calls enqueue work on it and return without synchronising; buffers must
  * stay valid until the stream has passed that work.  A context is not
  * thread-safe: use it from one host thread at a time, on one stream at a time.
- * Calls of one context that overlap in time all the same spoil the tensors that they have in
- * common, which hold undefined values until they are warmed up again (cf_warmup).
+ * Calls of one context that overlap in time all the same may spoil one another's tensors, which
+ * then hold undefined values until they are warmed up again (cf_warmup).
  *
  * Layouts (all dense, row-major, C contiguous; base pointers 16-byte aligned):
  *   x, recon : [N, C] of `dtype`
