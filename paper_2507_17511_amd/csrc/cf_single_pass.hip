@@ -354,8 +354,7 @@ __global__ __launch_bounds__(kPersistThreads, SHORT ? 4 : 2) void k_single_pass(
     const LaunchRange &r = args.r;
     __shared__ Shared<SCH> sh;
     // Workgroups are handed to the 8 XCDs in turn (blockIdx.x % 8).  Taking item b in workgroup b runs the
-    // consecutive items of a reduction group on different XCDs at the same time, and a tensor whose row
-    // blocks number a multiple of 8 keeps each of them on one XCD, whose L2 then sees all stripes of a code row.  Short tensors
+    // consecutive items of a reduction group on different XCDs at the same time.  Short tensors
     // (few items per group) do better XCD-major, a run of consecutive items per XCD; the host chooses.
     const uint32_t n_items = r.item_hi - r.item_lo;
     uint32_t vb = blockIdx.x;
@@ -388,7 +387,13 @@ __global__ __launch_bounds__(kPersistThreads, SHORT ? 4 : 2) void k_single_pass(
                           "+s"(d.p_n_rb), "+s"(d.p_item_begin), "+s"(p.x), "+s"(p.recon), "+s"(p.err), "+s"(p.codes), "+s"(p.scales), "+s"(state));  // one wait for all of them
         const uint32_t local = item - d.p_item_begin;               // group-major: stripe, then row block
         const int stripe = (int)(local / (uint32_t)d.p_n_rb);
-        const int rb = at >= 0 ? at : (int)(local % (uint32_t)d.p_n_rb);
+        // The groups of a tensor begin on different XCDs unless its row blocks number a multiple of 8: each is turned, so that a row block, all but for a group's
+        // last few, is on the XCD of its number in every stripe, whose L2 then sees the stripes' pieces of a line and of a code row.  In order / turned, us, [3300, 3080]
+        // (13 row blocks) 487 / 449, [5000, 3080] (20) 506 / 460, 30 x [17776, 1920] (35) 1716 / 1662, [3268, 1504] in short items (26) 15.4 / 14.4.
+        int rb = (int)(local % (uint32_t)d.p_n_rb);
+        const int turned = rb + (int)((k - (uint32_t)rb) & 7u);
+        if ((SHORT || !r.sp_xcd_major) && d.p_n_rb >= 8) rb = turned >= d.p_n_rb ? turned - d.p_n_rb : turned;
+        if (at >= 0) rb = at;
         const uint32_t sign = ~(state << (24u - 8u * (item & 3u))) & kPartialSign;     // nobody else writes the byte, and this workgroup at the very end
         const uint32_t polls = gave_up ? 0u : r.sp_wait_polls;
         int missing;
