@@ -27,6 +27,9 @@ struct Layout {
     int32_t max_group_items = 0;   // largest reduction group of the single-pass path
     bool sp_wide = false;          // single-pass items are kStripeChannelsWide channels wide (short tensors)
     bool sp_slim = false;          // ... kStripeChannelsSlim channels wide (tall tensors)
+    bool sp_uneven = false;        // most of the context is bf16 rows that are no whole blocks of 64 bytes, see make_layout
+    bool sp_blocks = false;        // ... and the parts of blocks go out without the streaming hint
+    bool sp_uneven_tall = false;   // ... and fused steps of more than kUnevenRounds rounds of workgroups take two kernels by default
     bool sp_too_tall = false;      // some group is larger than its tensor's limit: two kernels by default, but for small calls
     bool single_pass = false;      // every channel-scale tensor has single-pass geometry
     // Short items: calls whose items leave the device half empty take ones a quarter as tall, kernels of their own with a
@@ -232,19 +235,35 @@ cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &
     // N = 2048 1.49 / 1.51 / 1.60 -> 1.52 / 1.48 / 1.55, N = 3072 1.47 / 1.52 / 1.61 -> 1.46 / 1.50 / 1.58,
     // N = 4096 1.50 / 1.55 / 1.62 -> 1.53 / 1.56 / 1.65, N = 6144 1.56 / 1.59 / 1.68 -> 1.62 / 1.66 / 1.77.
     auto narrow_item_rows = [&](int32_t dtype) { return (kPersistThreads / (kStripeChannels / kChunk)) * single_pass_rows_per_lane(dtype, o.ef); };
-    int64_t narrow_max_group = 0, elements = 0, tall_elements = 0, sliver_elements = 0;
+    int64_t narrow_max_group = 0, elements = 0, tall_elements = 0, sliver_elements = 0, uneven_elements = 0, odd_elements = 0;
     for (int32_t t = 0; t < n; ++t)
         if (descs[t].scale == CF_SCALE_CHANNEL) {
             const int64_t rows = narrow_item_rows(descs[t].dtype), c = descs[t].n_channels, last = c % kStripeChannelsSlim;
             const int64_t g = (descs[t].n_tokens + rows - 1) / rows;
             if (g > narrow_max_group) narrow_max_group = g;
             elements += descs[t].n_tokens * c;
+            if (o.ef == CF_EF_RECON && descs[t].dtype == CF_BF16 && c % 32 != 0) uneven_elements += descs[t].n_tokens * c;
+            if (o.ef == CF_EF_RECON && descs[t].dtype == CF_BF16 && c % 16 != 0) odd_elements += descs[t].n_tokens * c;
             if (g > kTallGroupItems) tall_elements += descs[t].n_tokens * c;
             // the last 64-channel stripe of a row is a few short pieces of memory and much of what there is
             if (g > kTallGroupItems && c < kStripeChannels && last > 0 && last < kStripeChannelsSlim / 2) sliver_elements += descs[t].n_tokens * c;
         }
     const bool slivers = sliver_elements > 0 && sliver_elements >= elements - sliver_elements;
-    L.sp_wide = L.single_pass && narrow_max_group > 0 && narrow_max_group <= 12;
+    // Uneven rows, bf16 ones that are no whole blocks of 64 bytes: a stripe's piece of a row shares its first and last block with the stripes beside
+    // it, and a block that reaches memory in parts costs as much as five whole ones.  Wide stripes have half as many; the parts go out without the
+    // streaming hint, so that an L2 that has both makes them whole (`blocks`); past both, two kernels, whose rows are written in one run.  In calls of few rounds
+    // the caches make more of them whole: 2 x [8000, 1512] (768 items) 76.5 / 60.1 in 128-channel stripes without and with blocks, 76.4 with two kernels.  Steps of 1.6e8
+    // elements, us, 128 / 128 blocks / 256 / 256 blocks / two kernels (channels that are an odd multiple of 8: error rows are uneven too):
+    //   odd   [1024, 1096] 205 / 161 / 165 / 145 / 181, [4096, 1096] 429 / 409 / 385 / 386 / 409, [4096, 3080] 430 / 405 / 378 / 377 / 389, [4096, 200] 296 / 255 / 247 / 220 / 224,
+    //         [5000, 1096] 451 / 447 / 425 / 423 / 417, [8000, 3080] 447 / 417 / 413 / 408 / 385, bf16 error [6100, 1096] 469 / 445 / 460 / 470 / 460, [8000, 1096] 636 / 613 / 617 /
+    //         653 / 603; not fused [6100, 1096] 395 / 373 / 411 / 415 / 450, [8000, 1096] 528 / 501 / 558 / 562 / 590
+    //   even  [1024, 1104] 333 / 298 / 276 / 265 / 345, [4096, 1104] 371 / 367 / 355 / 369 / 407, [8000, 1104] 391 / 391 / 409 / 425 / 410, [11000, 1104] 407 / 408 / 484 / 488 / 406 (64
+    //         channels 479), [17000, 3088] 451 / 449 / 631 / 643 / 411; not fused [8000, 1104] 318 / 327 / 359 / 371 / 390
+    const bool odd = odd_elements >= uneven_elements - odd_elements;
+    L.sp_uneven = L.single_pass && uneven_elements > elements - uneven_elements;
+    L.sp_blocks = L.sp_uneven && (odd || narrow_max_group <= 4);
+    L.sp_uneven_tall = L.sp_uneven && narrow_max_group > (odd ? (o.err_dtype == CF_BF16 ? kUnevenGroupLimitBf16Error : kUnevenWideGroup) : kUnevenGroupLimitEven);
+    L.sp_wide = L.single_pass && narrow_max_group > 0 && narrow_max_group <= (L.sp_uneven ? kUnevenWideGroup : 12);
     // Tall tensors the other way round: all workgroups of a group wait for its slowest, and the more they are the longer.
     // 128 -> 64 channels on batches of equal size, us: [6144, 3072] bf16 793 -> 790, [8192, 3072] 840 -> 812 (4-bit 858 ->
     // 856), [12288, 3072] 895 -> 854, [16384, 3072] 1030 -> 902, [17776, 1920] with bf16 error 2227 -> 1976.  Tensors that
@@ -253,7 +272,7 @@ cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &
     // 20 x [4096, 3072] with seven 1080 -> 1068; beyond that two kernels are the other choice: 40 x [2048, 3072] with four
     // [16384, 3072] 970 against 1078.  Not for slivers: 114 x [11653, 80] 360 -> 434 (x [11653, 64] 272 -> 199, 60 x
     // [17000, 96] 310 -> 298).
-    L.sp_slim = L.single_pass && !slivers && narrow_max_group > kTallGroupItems &&
+    L.sp_slim = L.single_pass && !slivers && !(L.sp_uneven && narrow_max_group <= kUnevenNarrowGroup) && narrow_max_group > kTallGroupItems &&
                 (narrow_max_group > kNarrowGroupLimit || tall_elements >= elements - tall_elements);
     // Largest group of a call of any size in 128-channel stripes, single pass against two kernels in us: 4 x [10000, 3072], 40, 290 / 307; one [12288,
     // 3072] among 40 x [4096, 3072], 48, 1027 / 1311; slivers, whose second kernel runs across the row ends: 114 x [11653, 80], 46, 351 / 312, x [10500,
@@ -522,6 +541,7 @@ struct cf_ctx {
         r.sp_short = 0;
         r.item_lo = L.item_prefix[first];
         r.item_hi = L.item_prefix[first + count];
+        r.sp_blocks = L.sp_blocks && r.item_hi - r.item_lo > (uint32_t)kBlocksItems;
         r.only_group_scale = 0;
         r.naive = opts.ef == CF_EF_NAIVE;
         r.dts = descs[first].dtype;
@@ -567,6 +587,7 @@ struct cf_ctx {
         }
         if (items > (uint32_t)kShortItems || items > resident) return false;
         r.sp_short = 1;
+        r.sp_blocks = L.sp_uneven && items > (uint32_t)kShortBlocksItems;
         r.item_lo = L.short_dev[first].p_item_begin;
         r.item_hi = r.item_lo + items;
         r.direct_descs = L.short_dev.data() + first;
@@ -930,7 +951,7 @@ cf_status run_sender(cf_ctx *ctx, int32_t first, int32_t count, const void *cons
         else if (d.p_n_rb == 2) gain += d.p_n_stripes * (rows - (rounds <= 3.0 ? 1.2 : 1.4));
         else gain += rows * width - d.p_n_stripes * (rows_per_lane < 8 ? 0.1 : rows_per_lane < 16 ? 0.25 : rounds <= 2.0 ? 1.0 / 3.0 : 0.4);
     }
-    const bool worth_it = forced || small_call || (!ctx->L.sp_too_tall && (gain >= 0.0 || (tall && rounds <= 3.0)));
+    const bool worth_it = forced || small_call || (!ctx->L.sp_too_tall && !(fused && ctx->L.sp_uneven_tall && rounds > kUnevenRounds) && (gain >= 0.0 || (tall && rounds <= 3.0)));
     // (a group larger than what the device holds at once would have its first workgroups wait for ones that cannot
     // start before they leave: correct, they give up and compute the missing sums, but slow: such tensors take two kernels)
     const bool single_pass = ctx->L.single_pass && grid >= ctx->L.max_group_items && grid >= 1 && r.item_hi > r.item_lo && worth_it;

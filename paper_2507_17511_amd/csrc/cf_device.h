@@ -178,6 +178,37 @@ __device__ __forceinline__ void lines_store_stream(void *run, int j, int64_t n_v
     if (((RUN + j) >> 1) < n_valid) __builtin_nontemporal_store(pieces[1], dst + RUN + j);
 }
 
+// Of a run of n 16-byte pieces from `run` on: those that fill 64-byte blocks, [first, last).  The others share a block with a neighbour's.
+struct WholeBlocks {
+    int first, last;
+    __device__ __forceinline__ WholeBlocks(const void *run, int n)
+    {
+        const int before = (int)(reinterpret_cast<uintptr_t>(run) >> 4) & 3;
+        first = -before & 3;
+        last = n - ((n + before) & 3);
+    }
+    __device__ __forceinline__ bool has(int piece) const { return piece >= first && piece < last; }
+};
+
+// The same where runs begin or end within a block: those pieces without the streaming hint, for the L2 to merge.
+template <int RUN>
+__device__ __forceinline__ void lines_store_blocks(void *run, int j, int64_t n_valid, const f32x4 (&pieces)[2])
+{
+    CF_GLOBAL f32x4 *dst = gmut<f32x4>(run);
+    const int n = 2 * (n_valid < RUN ? (int)n_valid : RUN);
+    const WholeBlocks whole(run, n);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int piece = h * RUN + j;
+        if (whole.has(piece)) {
+            __builtin_nontemporal_store(pieces[h], dst + piece);
+            asm volatile("");           // else the two become one store, without the hint
+        } else if (piece < n) {
+            dst[piece] = pieces[h];
+        }
+    }
+}
+
 // ---------------------------------------------------------------- a1 + a2
 
 // z from the raw operands; the order of the two fp32 operations is fixed.

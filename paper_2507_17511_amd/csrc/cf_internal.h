@@ -60,6 +60,19 @@ constexpr int kNarrowGroupLimit = 48;
 constexpr int kSlimGroupLimit = 64;                         // see slim_group_limit
 constexpr int kSlimGroupLimitUneven = 38;
 constexpr int kSlimGroupLimitNaive = 24;
+// Contexts of mostly uneven rows, in 128-channel items a group: 256-channel stripes up to the first, no 64-channel ones up to kUnevenNarrowGroup; fused steps of more
+// than kUnevenRounds rounds by two kernels past the first, or past these where the error is bf16 or the channels a multiple of 16.  make_layout has the figures.
+constexpr int kUnevenWideGroup = 18;
+constexpr int kUnevenNarrowGroup = 64;
+constexpr int kUnevenGroupLimitBf16Error = 28;
+constexpr int kUnevenGroupLimitEven = 32;
+constexpr double kUnevenRounds = 2.5;
+// Calls of short items over uneven rows leave parts of blocks to the L2 from so many items on: what it holds at a kernel's end has to be written then, which small
+// calls wait for.  Steps, all streamed / parts left, us: 2 x [512, 1512] (192 items) 11.4 / 12.5, 6 x [512, 1096] (432) 16.4 / 16.9, 2 x [2048, 1096] (576) 17.4 / 15.6,
+// [4096, 1096] (576) 18.4 / 16.3, [3268, 1512] (624) 20.5 / 17.2, 60 x [1024, 3080] two a call (784) 25.4 / 20.6, x [1024, 1096] six a call (864) 26.5 / 19.2
+// As for others: [8000, 328] (96 items) 16.1 / 16.9, two of them (192) 28.1 / 22.9, [8000, 1096] (288) 32.5 / 29.0.
+constexpr int kShortBlocksItems = 448;
+constexpr int kBlocksItems = 128;
 constexpr int kLastItemsWord = 32;                          // 128 bytes behind the error word: the first item of the last single pass, and the one past its last
 
 // The single pass's partials carry the sign of their call in this bit; item states and partials are filled with the other word before a first call.
@@ -152,6 +165,7 @@ struct LaunchRange {
     uint32_t sp_xcd_major;      // single-pass kernel: deal the items XCD-major (a run of consecutive items per XCD)
     uint32_t sp_wait_polls;     // single-pass kernel: polls of a missing partial before the workgroup computes it itself
     uint32_t sp_slim;           // single-pass kernel: items of kStripeChannelsSlim channels (tall tensors)
+    uint32_t sp_blocks;         // single-pass kernel: parts of 64-byte blocks go out without the streaming hint
     uint32_t sp_short;          // single-pass kernel: short items; item_lo, item_hi, direct_descs and the view's item_state are theirs
     int32_t dts;                // storage dtype of every tensor in the range (cf_dtype), or 2 if mixed
     int32_t only_group_scale;   // tiled encode: skip tensors the single-pass kernel covers

@@ -125,6 +125,7 @@ __device__ __forceinline__ float tree_over_published(int n, const uint32_t *mine
     return tree_top<LV, IS_MAX>(stack);
 }
 
+// BLOCKS: rows that are no whole blocks of 64 bytes, whose parts at a stripe's ends are left to the L2 to merge (make_layout says when).
 // SCH: channels per stripe (kStripeChannels, kStripeChannelsWide or kStripeChannelsSlim); the 256 lanes are SCH / 8 chunks across
 // by 2048 / SCH row-lanes down.
 template <int SCH> struct alignas(16) Shared {
@@ -139,7 +140,7 @@ constexpr uint32_t kMaxHelps = 4096u;
 
 // help: do no more than store the partial of item rb, which is another workgroup's.  max_polls: of a missing partial.
 // Returns kNoneMissing when the item is done, else the item whose partial was missing; nothing but a partial has been written then.
-template <int DT, int BITS, int EF, int ET, bool FUSED, int SCH, bool SHORT>
+template <int DT, int BITS, int EF, int ET, bool FUSED, int SCH, bool SHORT, bool BLOCKS>
 __device__ __forceinline__ int persist_item(const BatchView &v, const TensorDev &d, const TensorPtrs &p, int stripe,
                                             int rb, uint32_t sign, uint32_t max_polls, bool help, Shared<SCH> &sh)
 {
@@ -304,7 +305,7 @@ __device__ __forceinline__ int persist_item(const BatchView &v, const TensorDev 
     // fp32 error rows go out as whole lines (see lines_exchange): a run is the kStripeChunks lanes of one row
     // segment; the wave's patch is its 2 KB of `red`, which nobody reads any more
     float *patch = &sh.red[0][0] + (tid >> 6) * 512;
-    const int run_valid = d.n_chunks - stripe * kStripeChunks;
+    const int run_valid = d.n_chunks - stripe * kStripeChunks, run_chunks = run_valid < kStripeChunks ? run_valid : kStripeChunks;
 #pragma unroll
     for (int k = 0; k < RPT; ++k) {
         const int64_t row = row0 + k;
@@ -327,13 +328,20 @@ __device__ __forceinline__ int persist_item(const BatchView &v, const TensorDev 
         if (ET == F32) {
             f32x4 pieces[2];
             lines_exchange<kStripeChunks>(patch, tid & 63, enew, pieces);
-            if (rvalid)
-                lines_store_stream<kStripeChunks>(static_cast<float *>(p.err) + row * C + (int64_t)stripe * kStripeChannels, cl,
-                                                  run_valid, pieces);
+            if (rvalid) {
+                float *const run = static_cast<float *>(p.err) + row * C + (int64_t)stripe * kStripeChannels;
+                if (BLOCKS) lines_store_blocks<kStripeChunks>(run, cl, run_valid, pieces);
+                else lines_store_stream<kStripeChunks>(run, cl, run_valid, pieces);
+            }
         } else if (rvalid && cvalid) {
             Raw8<ET> eo;
             eo.narrow(enew);
-            eo.store_stream(p.err, e);
+            if (!BLOCKS || WholeBlocks(static_cast<uint16_t *>(p.err) + (e - cl * kChunk), run_chunks).has(cl)) {
+                eo.store_stream(p.err, e);
+                asm volatile("");
+            } else {
+                eo.store(p.err, e);
+            }
         }
         if (FUSED && rvalid && cvalid) {
             F8 nb;
@@ -341,13 +349,18 @@ __device__ __forceinline__ int persist_item(const BatchView &v, const TensorDev 
             for (int j = 0; j < 8; ++j) nb.v[j] = (EF == EF_NAIVE) ? dq.v[j] : b.v[j] + dq.v[j];
             Raw8<DT> out;
             out.narrow(nb);
-            if (DT == BF16) out.store_stream(p.recon, e); else out.store(p.recon, e);
+            if (DT == BF16 && (!BLOCKS || WholeBlocks(static_cast<uint16_t *>(p.recon) + (e - cl * kChunk), run_chunks).has(cl))) {
+                out.store_stream(p.recon, e);
+                asm volatile("");
+            } else {
+                out.store(p.recon, e);
+            }
         }
     }
     return kNoneMissing;
 }
 
-template <int EF, int ET, bool FUSED, int SCH, bool SHORT>
+template <int EF, int ET, bool FUSED, int SCH, bool SHORT, bool BLOCKS>
 __global__ __launch_bounds__(kPersistThreads, SHORT ? 4 : 2) void k_single_pass(SinglePassArgs args)
 {
     const BatchView &v = args.v;
@@ -398,13 +411,13 @@ __global__ __launch_bounds__(kPersistThreads, SHORT ? 4 : 2) void k_single_pass(
         const uint32_t polls = gave_up ? 0u : r.sp_wait_polls;
         int missing;
         if (d.dtype == BF16) {
-            if (d.bits == 1) missing = persist_item<BF16, 1, EF, ET, FUSED, SCH, SHORT>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
-            else if (d.bits == 2) missing = persist_item<BF16, 2, EF, ET, FUSED, SCH, SHORT>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
-            else missing = persist_item<BF16, 4, EF, ET, FUSED, SCH, SHORT>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
+            if (d.bits == 1) missing = persist_item<BF16, 1, EF, ET, FUSED, SCH, SHORT, BLOCKS>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
+            else if (d.bits == 2) missing = persist_item<BF16, 2, EF, ET, FUSED, SCH, SHORT, BLOCKS>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
+            else missing = persist_item<BF16, 4, EF, ET, FUSED, SCH, SHORT, BLOCKS>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
         } else {
-            if (d.bits == 1) missing = persist_item<F32, 1, EF, ET, FUSED, SCH, SHORT>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
-            else if (d.bits == 2) missing = persist_item<F32, 2, EF, ET, FUSED, SCH, SHORT>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
-            else missing = persist_item<F32, 4, EF, ET, FUSED, SCH, SHORT>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
+            if (d.bits == 1) missing = persist_item<F32, 1, EF, ET, FUSED, SCH, SHORT, BLOCKS>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
+            else if (d.bits == 2) missing = persist_item<F32, 2, EF, ET, FUSED, SCH, SHORT, BLOCKS>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
+            else missing = persist_item<F32, 4, EF, ET, FUSED, SCH, SHORT, BLOCKS>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
         }
         // The same for all, which the compiler does not see: the loop it then makes, of lanes that leave one by one, took up to 9 % longer in one
         // pass of twenty (114 x [4096, 3072], 2640 us and now and then 2700 to 2900).
@@ -442,32 +455,36 @@ __global__ void k_fresh_partials(u32x4 *partials, uint64_t n_vec, uint8_t *state
     for (uint64_t i = at; i < n_states; i += step) *gmut<uint8_t>(states + i) = (uint8_t)kFreshPartials;
 }
 
-template <int EF, int ET, bool FUSED, int SCH> const void *persistent_fn(bool short_items)
+template <int EF, int ET, bool FUSED, int SCH> const void *persistent_fn(bool blocks, bool short_items)
 {
     // one stripe width, and the default feedback mode alone: with a third operand a quarter of the rows would be one or two a lane (naive compression
     // would have as many as the default; no kernels for it here)
-    if (EF == EF_RECON && short_items) return reinterpret_cast<const void *>(&k_single_pass<EF_RECON, ET, FUSED, kShortStripeChannels, true>);
-    return reinterpret_cast<const void *>(&k_single_pass<EF, ET, FUSED, SCH, false>);
+    if constexpr (EF == EF_RECON) {
+        if (short_items && blocks) return reinterpret_cast<const void *>(&k_single_pass<EF_RECON, ET, FUSED, kShortStripeChannels, true, true>);
+        if (short_items) return reinterpret_cast<const void *>(&k_single_pass<EF_RECON, ET, FUSED, kShortStripeChannels, true, false>);
+        if (blocks) return reinterpret_cast<const void *>(&k_single_pass<EF_RECON, ET, FUSED, SCH, false, true>);
+    }
+    return reinterpret_cast<const void *>(&k_single_pass<EF, ET, FUSED, SCH, false, false>);
 }
 
-template <int EF, int SCH> const void *pick_width(int err_dtype, bool fused, bool short_items)
+template <int EF, int SCH> const void *pick_width(int err_dtype, bool fused, bool blocks, bool short_items)
 {
-    if (err_dtype == BF16) return fused ? persistent_fn<EF, BF16, true, SCH>(short_items) : persistent_fn<EF, BF16, false, SCH>(short_items);
-    return fused ? persistent_fn<EF, F32, true, SCH>(short_items) : persistent_fn<EF, F32, false, SCH>(short_items);
+    if (err_dtype == BF16) return fused ? persistent_fn<EF, BF16, true, SCH>(blocks, short_items) : persistent_fn<EF, BF16, false, SCH>(blocks, short_items);
+    return fused ? persistent_fn<EF, F32, true, SCH>(blocks, short_items) : persistent_fn<EF, F32, false, SCH>(blocks, short_items);
 }
 
-template <int EF> const void *pick_ef(int err_dtype, bool fused, bool wide, bool slim, bool short_items)
+template <int EF> const void *pick_ef(int err_dtype, bool fused, bool wide, bool slim, bool blocks, bool short_items)
 {
-    if (slim) return pick_width<EF, kStripeChannelsSlim>(err_dtype, fused, short_items);
-    return wide ? pick_width<EF, kStripeChannelsWide>(err_dtype, fused, short_items) : pick_width<EF, kStripeChannels>(err_dtype, fused, short_items);
+    if (slim) return pick_width<EF, kStripeChannelsSlim>(err_dtype, fused, blocks, short_items);
+    return wide ? pick_width<EF, kStripeChannelsWide>(err_dtype, fused, blocks, short_items) : pick_width<EF, kStripeChannels>(err_dtype, fused, blocks, short_items);
 }
 
-const void *pick(int ef, int err_dtype, bool fused, bool wide, bool slim, bool short_items)
+const void *pick(int ef, int err_dtype, bool fused, bool wide, bool slim, bool blocks, bool short_items)
 {
-    if (ef == EF_LITERAL) return pick_ef<EF_LITERAL>(err_dtype, fused, wide, slim, false);
-    if (ef == EF_OFF) return pick_ef<EF_OFF>(err_dtype, fused, wide, slim, false);
-    if (ef == EF_NAIVE) return pick_ef<EF_NAIVE>(err_dtype, fused, wide, slim, false);
-    return pick_ef<EF_RECON>(err_dtype, fused, wide, slim, short_items);
+    if (ef == EF_LITERAL) return pick_ef<EF_LITERAL>(err_dtype, fused, wide, slim, false, false);
+    if (ef == EF_OFF) return pick_ef<EF_OFF>(err_dtype, fused, wide, slim, false, false);
+    if (ef == EF_NAIVE) return pick_ef<EF_NAIVE>(err_dtype, fused, wide, slim, false, false);
+    return pick_ef<EF_RECON>(err_dtype, fused, wide, slim, blocks, short_items);
 }
 
 }  // namespace
@@ -475,7 +492,7 @@ const void *pick(int ef, int err_dtype, bool fused, bool wide, bool slim, bool s
 int persistent_max_blocks_per_cu(int ef, int err_dtype, bool fused, bool wide, bool slim)
 {
     int n = 0;
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, pick(ef, err_dtype, fused, wide, slim, false), kPersistThreads, 0);
+    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, pick(ef, err_dtype, fused, wide, slim, false, false), kPersistThreads, 0);
     if (e != hipSuccess) { (void)hipGetLastError(); return 0; }
     return n;
 }
@@ -512,7 +529,7 @@ hipError_t launch_single_pass(const BatchView &v, const LaunchRange &r, int ef, 
         else a.direct.descs[k].p_item_begin = ~0u;      // behind every item
     }
     void *args[] = {&a};
-    return hipLaunchKernel(pick(ef, err_dtype, fused, wide, r.sp_slim != 0, r.sp_short != 0), dim3(n_wg), dim3(kPersistThreads), args, 0, s);
+    return hipLaunchKernel(pick(ef, err_dtype, fused, wide, r.sp_slim != 0, r.sp_blocks != 0, r.sp_short != 0), dim3(n_wg), dim3(kPersistThreads), args, 0, s);
 }
 
 }  // namespace cf

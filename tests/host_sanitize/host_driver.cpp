@@ -353,6 +353,10 @@ int main()
             {R, B, {{20, 256, 3072}, {80, 20, 3072}}, TWO}, {R, B, {{57, 256, 3072}, {57, 20, 3072}}, NARROW},
             {R, B, {{60, 16, 3072}, {1, 2047, 64}}, TWO}, {R, B, {{60, 16, 3072}, {1, 2048, 64}}, NARROW},
             {R, B, {{126, 16, 3072}, {1, 3072, 64}}, NARROW}, {R, B, {{127, 16, 3072}, {1, 3072, 64}}, TWO},
+            // rows of no whole blocks of 64 bytes: 18 items of 128 channels, 32 where the channels are a multiple of 16, more than 1280 items in all, none of 64 channels up to 64 items
+            {R, B, {{30, 4608, 1096}}, NARROW}, {R, B, {{30, 4609, 1096}}, TWO}, {R, B, {{30, 4609, 1120}}, NARROW}, {R, B, {{30, 4609, 1104}}, NARROW}, {N, B, {{30, 4609, 1096}}, NARROW},
+            {R, F, {{30, 4609, 1096}}, NARROW}, {R, B, {{30, 8192, 1104}}, NARROW}, {R, B, {{30, 8193, 1104}}, TWO}, {R, B, {{1, 7936, 5064}}, NARROW}, {R, B, {{1, 7936, 5256}}, TWO},
+            {R, B, {{1, 12288, 1096}}, NARROW}, {R, B, {{1, 12288, 1120}}, SLIM}, {R, B, {{30, 4609, 1096}, {30, 4609, 1120}}, NARROW}, {R, B, {{31, 4609, 1096}, {30, 4609, 1088}}, TWO},
         };
         for (const Call &c : calls) {
             std::vector<cf_tensor_desc> d;

@@ -70,6 +70,24 @@ def test_short_items(dtype, err_dtype, flags):
         run_parity(descs, cf.options(err_dtype=err_dtype, flags=flags), xs, mode=mode)
 
 
+@pytest.mark.parametrize("err_dtype", [cf.CF_F32, cf.CF_BF16])
+@pytest.mark.parametrize("flags", [0, cf.CF_FLAG_TEST_NO_WAIT])
+@pytest.mark.parametrize("tokens, widths", [(1153, (328, 264, 1096)),       # 256 channels, 10 items a group: none begins where the one before did
+                                            (1030, (1104, 336, 16)),        # channels a multiple of 16; 9 items
+                                            (4700, (104, 136, 72)),         # 128 channels, 19 items
+                                            (4097, (488, 520))])            # short items, 33 a group
+def test_rows_of_no_whole_blocks(tokens, widths, err_dtype, flags):
+    """bf16 rows that are no whole blocks of 64 bytes, whose parts are stored another way: nine tensors, or two in short items, every
+    code width, fused and split; bits against the oracle."""
+    n = 2 if tokens == 4097 else 9
+    descs = [cf.desc(tokens - t % 3, widths[t % len(widths)], cf.CF_BF16, (1, 2, 4)[(t + t // 3) % 3], cf.CF_SCALE_CHANNEL) for t in range(n)]
+    streams = [drift_stream((d.n_tokens, d.n_channels), d.dtype, steps=3, seed=870 + t, device=DEV) for t, d in enumerate(descs)]
+    xs = [[streams[t][s] for t in range(n)] for s in range(3)]
+    say(f"uneven rows [{tokens}, {widths}] err_dtype={err_dtype} flags={flags}")
+    for mode in ("fused", "split"):
+        run_parity(descs, cf.options(err_dtype=err_dtype, flags=cf.CF_FLAG_SINGLE_PASS | flags), xs, mode=mode)
+
+
 def test_small_call_replays_from_a_graph():
     """A captured call that carries its pointers: replays, eager calls and a warm-up in turn, against an eager context."""
     descs = [cf.desc(1024, 512, cf.CF_BF16, 2, cf.CF_SCALE_CHANNEL), cf.desc(900, 384, cf.CF_BF16, 1, cf.CF_SCALE_CHANNEL)]
