@@ -209,6 +209,14 @@ static_assert(sizeof(BatchView) + sizeof(DirectRange) == 256 + sizeof(TensorPtrs
 
 static_assert(sizeof(SinglePassArgs) <= 4096, "a kernel's arguments");
 
+// The arguments of k_short_items: nothing of a call is elsewhere.
+struct ShortArgs {
+    BatchView v;
+    LaunchRange r;
+    TensorPtrs sets[kDirectTensors];
+    TensorDev descs[kDirectTensors];
+};
+
 // f(range) with the kind of range the call's kernels take
 template <class F> auto with_range(const LaunchRange &r, F &&f) { return r.direct ? f(DirectRange(r)) : f(r); }
 

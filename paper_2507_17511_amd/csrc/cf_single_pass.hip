@@ -360,8 +360,8 @@ __device__ __forceinline__ int persist_item(const BatchView &v, const TensorDev 
     return kNoneMissing;
 }
 
-template <int EF, int ET, bool FUSED, int SCH, bool SHORT, bool BLOCKS>
-__global__ __launch_bounds__(kPersistThreads, SHORT ? 4 : 2) void k_single_pass(SinglePassArgs args)
+template <int EF, int ET, bool FUSED, int SCH, bool BLOCKS>
+__global__ __launch_bounds__(kPersistThreads, 2) void k_single_pass(SinglePassArgs args)
 {
     const BatchView &v = args.v;
     const LaunchRange &r = args.r;
@@ -405,19 +405,19 @@ __global__ __launch_bounds__(kPersistThreads, SHORT ? 4 : 2) void k_single_pass(
         // (13 row blocks) 487 / 449, [5000, 3080] (20) 506 / 460, 30 x [17776, 1920] (35) 1716 / 1662, [3268, 1504] in short items (26) 15.4 / 14.4.
         int rb = (int)(local % (uint32_t)d.p_n_rb);
         const int turned = rb + (int)((k - (uint32_t)rb) & 7u);
-        if ((SHORT || !r.sp_xcd_major) && d.p_n_rb >= 8) rb = turned >= d.p_n_rb ? turned - d.p_n_rb : turned;
+        if (!r.sp_xcd_major && d.p_n_rb >= 8) rb = turned >= d.p_n_rb ? turned - d.p_n_rb : turned;
         if (at >= 0) rb = at;
         const uint32_t sign = ~(state << (24u - 8u * (item & 3u))) & kPartialSign;     // nobody else writes the byte, and this workgroup at the very end
         const uint32_t polls = gave_up ? 0u : r.sp_wait_polls;
         int missing;
         if (d.dtype == BF16) {
-            if (d.bits == 1) missing = persist_item<BF16, 1, EF, ET, FUSED, SCH, SHORT, BLOCKS>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
-            else if (d.bits == 2) missing = persist_item<BF16, 2, EF, ET, FUSED, SCH, SHORT, BLOCKS>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
-            else missing = persist_item<BF16, 4, EF, ET, FUSED, SCH, SHORT, BLOCKS>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
+            if (d.bits == 1) missing = persist_item<BF16, 1, EF, ET, FUSED, SCH, false, BLOCKS>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
+            else if (d.bits == 2) missing = persist_item<BF16, 2, EF, ET, FUSED, SCH, false, BLOCKS>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
+            else missing = persist_item<BF16, 4, EF, ET, FUSED, SCH, false, BLOCKS>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
         } else {
-            if (d.bits == 1) missing = persist_item<F32, 1, EF, ET, FUSED, SCH, SHORT, BLOCKS>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
-            else if (d.bits == 2) missing = persist_item<F32, 2, EF, ET, FUSED, SCH, SHORT, BLOCKS>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
-            else missing = persist_item<F32, 4, EF, ET, FUSED, SCH, SHORT, BLOCKS>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
+            if (d.bits == 1) missing = persist_item<F32, 1, EF, ET, FUSED, SCH, false, BLOCKS>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
+            else if (d.bits == 2) missing = persist_item<F32, 2, EF, ET, FUSED, SCH, false, BLOCKS>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
+            else missing = persist_item<F32, 4, EF, ET, FUSED, SCH, false, BLOCKS>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
         }
         // The same for all, which the compiler does not see: the loop it then makes, of lanes that leave one by one, took up to 9 % longer in one
         // pass of twenty (114 x [4096, 3072], 2640 us and now and then 2700 to 2900).
@@ -437,12 +437,74 @@ __global__ __launch_bounds__(kPersistThreads, SHORT ? 4 : 2) void k_single_pass(
             if (k == 0) {               // which items the call had, for cf_given_up_items
                 *gmut<uint32_t>(v.error_flag + kLastItemsWord) = r.item_lo;
                 *gmut<uint32_t>(v.error_flag + kLastItemsWord + 1) = r.item_hi;
-                *gmut<uint32_t>(v.error_flag + kLastItemsWord + 2) = SHORT ? 1u : 0u;
+                *gmut<uint32_t>(v.error_flag + kLastItemsWord + 2) = 0u;
             }
         }
         at = -1;
         gave_up = 0u;
         k += gridDim.x;
+    }
+}
+
+// Short items.  A call of them is over before a large one's first operands arrive, so what it waits for is the chain of an item, and of that its descriptor was the
+// longest link: range, then which tensor, then descriptor and state, each a load from memory that waits for the one before (3 of the 8 us that one tensor of
+// [256, 64] took).  Here the grid says which item a workgroup has: x the row block, y the stripe, z the tensor, as many as the largest tensor of the call has, and
+// the descriptor and pointers come with the range, in one round; the state comes while the operands do.
+template <int ET, bool FUSED, bool BLOCKS>
+__global__ __launch_bounds__(kPersistThreads, 4) void k_short_items(ShortArgs args)
+{
+    constexpr int EF = EF_RECON, SCH = kShortStripeChannels;
+    const BatchView &v = args.v;
+    const LaunchRange &r = args.r;
+    __shared__ Shared<SCH> sh;
+    const uint64_t given = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
+    TensorDev d = scalar_load<TensorDev>(given + offsetof(ShortArgs, descs) + blockIdx.z * sizeof(TensorDev));
+    TensorPtrs p = scalar_load<TensorPtrs>(given + offsetof(ShortArgs, sets) + blockIdx.z * sizeof(TensorPtrs));
+    uint8_t *states = v.item_state;
+    asm volatile("" : "+s"(d.n_tokens), "+s"(d.n_channels), "+s"(d.n_chunks), "+s"(d.dtype), "+s"(d.bits), "+s"(d.p_partial_off), "+s"(d.p_rows),
+                      "+s"(d.p_n_rb), "+s"(d.p_item_begin), "+s"(p.x), "+s"(p.recon), "+s"(p.err), "+s"(p.codes), "+s"(p.scales), "+s"(states));      // one wait for all of them
+    if ((int)blockIdx.x >= d.p_n_rb || (int)blockIdx.y >= d.p_n_stripes) return;        // uniform over the workgroup: a larger tensor's
+    const int stripe = (int)blockIdx.y;
+    const uint32_t item = d.p_item_begin + blockIdx.y * (uint32_t)d.p_n_rb + blockIdx.x;
+    const uint32_t state = scalar_load<uint32_t>((uint64_t)states + (item & ~3u));      // four items' bytes
+    // turned as in k_single_pass
+    const int turned = (int)(blockIdx.x + (((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x) & 7u));
+    const int mine = d.p_n_rb < 8 ? (int)blockIdx.x : turned >= d.p_n_rb ? turned - d.p_n_rb : turned;
+    const uint32_t sign = ~(state << (24u - 8u * (item & 3u))) & kPartialSign;     // nobody else writes the byte, and this workgroup at the very end
+    uint32_t gave_up = 0u;          // how often
+    int at = -1;                    // the item of the group that this workgroup helps; -1: it does its own
+    for (;;) {
+        const int rb = at >= 0 ? at : mine;
+        const uint32_t polls = gave_up ? 0u : r.sp_wait_polls;
+        int missing;
+        if (d.dtype == BF16) {
+            if (d.bits == 1) missing = persist_item<BF16, 1, EF, ET, FUSED, SCH, true, BLOCKS>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
+            else if (d.bits == 2) missing = persist_item<BF16, 2, EF, ET, FUSED, SCH, true, BLOCKS>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
+            else missing = persist_item<BF16, 4, EF, ET, FUSED, SCH, true, BLOCKS>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
+        } else {
+            if (d.bits == 1) missing = persist_item<F32, 1, EF, ET, FUSED, SCH, true, BLOCKS>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
+            else if (d.bits == 2) missing = persist_item<F32, 2, EF, ET, FUSED, SCH, true, BLOCKS>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
+            else missing = persist_item<F32, 4, EF, ET, FUSED, SCH, true, BLOCKS>(v, d, p, stripe, rb, sign, polls, at >= 0, sh);
+        }
+        missing = __builtin_amdgcn_readfirstlane(missing);      // see k_single_pass
+        if (at < 0 && missing == kNoneMissing) break;
+        __syncthreads();            // the shared arrays are used again
+        if (at >= 0) {              // helped; now its own item again
+            at = -1;
+            continue;
+        }
+        at = missing;
+        if (++gave_up <= kMaxHelps) continue;       // always: each turn brings a partial that was missing, and no group has that many
+        if (threadIdx.x == 0) __hip_atomic_store(v.error_flag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        break;
+    }
+    if (threadIdx.x == 0) {
+        *gmut<uint8_t>(v.item_state + item) = (uint8_t)(sh.sign >> 24 | (gave_up ? 1u : 0u));
+        if (item == r.item_lo) {        // which items the call had, for cf_given_up_items
+            *gmut<uint32_t>(v.error_flag + kLastItemsWord) = r.item_lo;
+            *gmut<uint32_t>(v.error_flag + kLastItemsWord + 1) = r.item_hi;
+            *gmut<uint32_t>(v.error_flag + kLastItemsWord + 2) = 1u;
+        }
     }
 }
 
@@ -455,36 +517,62 @@ __global__ void k_fresh_partials(u32x4 *partials, uint64_t n_vec, uint8_t *state
     for (uint64_t i = at; i < n_states; i += step) *gmut<uint8_t>(states + i) = (uint8_t)kFreshPartials;
 }
 
-template <int EF, int ET, bool FUSED, int SCH> const void *persistent_fn(bool blocks, bool short_items)
+template <int EF, int ET, bool FUSED, int SCH> const void *persistent_fn(bool blocks)
 {
-    // one stripe width, and the default feedback mode alone: with a third operand a quarter of the rows would be one or two a lane (naive compression
-    // would have as many as the default; no kernels for it here)
-    if constexpr (EF == EF_RECON) {
-        if (short_items && blocks) return reinterpret_cast<const void *>(&k_single_pass<EF_RECON, ET, FUSED, kShortStripeChannels, true, true>);
-        if (short_items) return reinterpret_cast<const void *>(&k_single_pass<EF_RECON, ET, FUSED, kShortStripeChannels, true, false>);
-        if (blocks) return reinterpret_cast<const void *>(&k_single_pass<EF_RECON, ET, FUSED, SCH, false, true>);
+    if constexpr (EF == EF_RECON)
+        if (blocks) return reinterpret_cast<const void *>(&k_single_pass<EF_RECON, ET, FUSED, SCH, true>);
+    return reinterpret_cast<const void *>(&k_single_pass<EF, ET, FUSED, SCH, false>);
+}
+
+template <int EF, int SCH> const void *pick_width(int err_dtype, bool fused, bool blocks)
+{
+    if (err_dtype == BF16) return fused ? persistent_fn<EF, BF16, true, SCH>(blocks) : persistent_fn<EF, BF16, false, SCH>(blocks);
+    return fused ? persistent_fn<EF, F32, true, SCH>(blocks) : persistent_fn<EF, F32, false, SCH>(blocks);
+}
+
+template <int EF> const void *pick_ef(int err_dtype, bool fused, bool wide, bool slim, bool blocks)
+{
+    if (slim) return pick_width<EF, kStripeChannelsSlim>(err_dtype, fused, blocks);
+    return wide ? pick_width<EF, kStripeChannelsWide>(err_dtype, fused, blocks) : pick_width<EF, kStripeChannels>(err_dtype, fused, blocks);
+}
+
+const void *pick(int ef, int err_dtype, bool fused, bool wide, bool slim, bool blocks)
+{
+    if (ef == EF_LITERAL) return pick_ef<EF_LITERAL>(err_dtype, fused, wide, slim, false);
+    if (ef == EF_OFF) return pick_ef<EF_OFF>(err_dtype, fused, wide, slim, false);
+    if (ef == EF_NAIVE) return pick_ef<EF_NAIVE>(err_dtype, fused, wide, slim, false);
+    return pick_ef<EF_RECON>(err_dtype, fused, wide, slim, blocks);
+}
+
+// One stripe width, and the default feedback mode alone: with a third operand a quarter of the rows would be one or two a lane (naive compression
+// would have as many as the default; no kernels for it here).
+template <int ET, bool FUSED> const void *short_fn(bool blocks)
+{
+    return blocks ? reinterpret_cast<const void *>(&k_short_items<ET, FUSED, true>) : reinterpret_cast<const void *>(&k_short_items<ET, FUSED, false>);
+}
+
+const void *pick_short(int err_dtype, bool fused, bool blocks)
+{
+    if (err_dtype == BF16) return fused ? short_fn<BF16, true>(blocks) : short_fn<BF16, false>(blocks);
+    return fused ? short_fn<F32, true>(blocks) : short_fn<F32, false>(blocks);
+}
+
+hipError_t launch_short_items(const BatchView &v, const LaunchRange &r, int err_dtype, bool fused, hipStream_t s)
+{
+    ShortArgs a;
+    a.v = v;
+    a.r = r;
+    std::memset(static_cast<void *>(a.sets), 0, sizeof a.sets);
+    std::memset(static_cast<void *>(a.descs), 0, sizeof a.descs);
+    dim3 grid(0, 0, (unsigned)r.count);
+    for (int k = 0; k < r.count; ++k) {
+        a.sets[k] = r.direct[k];
+        a.descs[k] = r.direct_descs[k];
+        grid.x = a.descs[k].p_n_rb > (int)grid.x ? (unsigned)a.descs[k].p_n_rb : grid.x;
+        grid.y = a.descs[k].p_n_stripes > (int)grid.y ? (unsigned)a.descs[k].p_n_stripes : grid.y;
     }
-    return reinterpret_cast<const void *>(&k_single_pass<EF, ET, FUSED, SCH, false, false>);
-}
-
-template <int EF, int SCH> const void *pick_width(int err_dtype, bool fused, bool blocks, bool short_items)
-{
-    if (err_dtype == BF16) return fused ? persistent_fn<EF, BF16, true, SCH>(blocks, short_items) : persistent_fn<EF, BF16, false, SCH>(blocks, short_items);
-    return fused ? persistent_fn<EF, F32, true, SCH>(blocks, short_items) : persistent_fn<EF, F32, false, SCH>(blocks, short_items);
-}
-
-template <int EF> const void *pick_ef(int err_dtype, bool fused, bool wide, bool slim, bool blocks, bool short_items)
-{
-    if (slim) return pick_width<EF, kStripeChannelsSlim>(err_dtype, fused, blocks, short_items);
-    return wide ? pick_width<EF, kStripeChannelsWide>(err_dtype, fused, blocks, short_items) : pick_width<EF, kStripeChannels>(err_dtype, fused, blocks, short_items);
-}
-
-const void *pick(int ef, int err_dtype, bool fused, bool wide, bool slim, bool blocks, bool short_items)
-{
-    if (ef == EF_LITERAL) return pick_ef<EF_LITERAL>(err_dtype, fused, wide, slim, false, false);
-    if (ef == EF_OFF) return pick_ef<EF_OFF>(err_dtype, fused, wide, slim, false, false);
-    if (ef == EF_NAIVE) return pick_ef<EF_NAIVE>(err_dtype, fused, wide, slim, false, false);
-    return pick_ef<EF_RECON>(err_dtype, fused, wide, slim, blocks, short_items);
+    void *args[] = {&a};
+    return hipLaunchKernel(pick_short(err_dtype, fused, r.sp_blocks != 0), grid, dim3(kPersistThreads), args, 0, s);
 }
 
 }  // namespace
@@ -492,7 +580,7 @@ const void *pick(int ef, int err_dtype, bool fused, bool wide, bool slim, bool b
 int persistent_max_blocks_per_cu(int ef, int err_dtype, bool fused, bool wide, bool slim)
 {
     int n = 0;
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, pick(ef, err_dtype, fused, wide, slim, false, false), kPersistThreads, 0);
+    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, pick(ef, err_dtype, fused, wide, slim, false), kPersistThreads, 0);
     if (e != hipSuccess) { (void)hipGetLastError(); return 0; }
     return n;
 }
@@ -515,6 +603,7 @@ hipError_t launch_single_pass(const BatchView &v, const LaunchRange &r, int ef, 
                              bool one_shot, hipStream_t s)
 {
     if (r.item_hi == r.item_lo) return hipSuccess;
+    if (r.sp_short) return launch_short_items(v, r, err_dtype, fused, s);
     uint32_t items = r.item_hi - r.item_lo;
     if ((uint32_t)grid > items) grid = (int)items;
     if (grid < 1) grid = 1;
@@ -529,7 +618,7 @@ hipError_t launch_single_pass(const BatchView &v, const LaunchRange &r, int ef, 
         else a.direct.descs[k].p_item_begin = ~0u;      // behind every item
     }
     void *args[] = {&a};
-    return hipLaunchKernel(pick(ef, err_dtype, fused, wide, r.sp_slim != 0, r.sp_blocks != 0, r.sp_short != 0), dim3(n_wg), dim3(kPersistThreads), args, 0, s);
+    return hipLaunchKernel(pick(ef, err_dtype, fused, wide, r.sp_slim != 0, r.sp_blocks != 0), dim3(n_wg), dim3(kPersistThreads), args, 0, s);
 }
 
 }  // namespace cf
