@@ -370,6 +370,12 @@ __global__ __launch_bounds__(kPersistThreads, 2) void k_single_pass(SinglePassAr
     // consecutive items of a reduction group on different XCDs at the same time.  Short tensors
     // (few items per group) do better XCD-major, a run of consecutive items per XCD; the host chooses.
     const uint32_t n_items = r.item_hi - r.item_lo;
+    // of direct calls; asked for along with the range, which says whether it is one
+    uint32_t begins[kDirectTensors];
+#pragma unroll
+    for (int q = 1; q < kDirectTensors; ++q) begins[q] = args.direct.descs[q].p_item_begin;
+    asm volatile("" : "+s"(begins[1]), "+s"(begins[2]), "+s"(begins[3]), "+s"(begins[4]), "+s"(begins[5]), "+s"(begins[6]), "+s"(begins[7]));
+    static_assert(kDirectTensors == 8, "all of them");
     uint32_t vb = blockIdx.x;
     if (r.sp_xcd_major) {
         const uint32_t q = gridDim.x >> 3, rem = gridDim.x & 7u, xcd = blockIdx.x & 7u;
@@ -384,7 +390,7 @@ __global__ __launch_bounds__(kPersistThreads, 2) void k_single_pass(SinglePassAr
         if (r.direct && r.count <= kDirectTensors) {        // both are among the arguments
             uint32_t t = 0;
 #pragma unroll
-            for (int q = 1; q < kDirectTensors; ++q) t += item >= args.direct.descs[q].p_item_begin ? 1u : 0u;
+            for (int q = 1; q < kDirectTensors; ++q) t += item >= begins[q] ? 1u : 0u;
             desc = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(SinglePassArgs, direct.descs) + t * sizeof(TensorDev);
             set = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(SinglePassArgs, direct.sets) + t * sizeof(TensorPtrs);
         } else {
