@@ -990,12 +990,10 @@ cf_status run_sender(cf_ctx *ctx, int32_t first, int32_t count, const void *cons
     if (ctx->range_has_channel(first, count)) {
         e = launch(ctx, s, "k_colreduce", [&] { return launch_colreduce(v, r, ef, et, s); });
         if (e != hipSuccess) return device_fail(ctx, e);
-        e = launch(ctx, s, "k_finalize", [&] { return launch_finalize(v, r, s); });
+        // the rank-1 form does k_finalize's work too
+        if (ctx->range_has_rank1(first, count)) e = launch(ctx, s, "k_finalize_rank1", [&] { return launch_finalize_rank1(v, r, s); });
+        else e = launch(ctx, s, "k_finalize", [&] { return launch_finalize(v, r, s); });
         if (e != hipSuccess) return device_fail(ctx, e);
-        if (ctx->range_has_rank1(first, count)) {
-            e = launch(ctx, s, "k_finalize_rank1", [&] { return launch_finalize_rank1(v, r, s); });
-            if (e != hipSuccess) return device_fail(ctx, e);
-        }
     }
     if ((e = run_row_local(ctx, first, count, v, r, fused, true, s)) != hipSuccess) return device_fail(ctx, e);
     return run_lowrank_sender(ctx, first, count, v, r, fused, s);

@@ -309,13 +309,56 @@ __global__ __launch_bounds__(kFinalizeThreads) void k_finalize(BatchView v, Laun
 // Rank-1 scales (App. D "Quantization"): u_i = (rowsum_i / C) / (sum_i rowsum_i / (N C)), written
 // behind v in the scales buffer.  One block per tensor: lane t owns an aligned block of B rows
 // (B a power of two); a row's sum is the tree over its 1024-channel tile sums, the total is the
-// tree over the rows (in the lane, then across lanes in LDS).
+// tree over the rows (in the lane, across the wave, then over the waves in LDS).
+// The workgroups past the tensors' do k_finalize's work, a block of it in every 256 lanes (columns do not wait for rows, nor rows for columns): a launch less.
+// Latency is all it costs, so a lane's rows are asked for together and stay in registers.  Steps in two launches with the rows by way of u / now, us: 2 x [4225, 312]
+// 31.8 / 23.0, 2 x [1108, 96] 22 / 18, [17000, 1024] 109 / 96, 30 x [1000, 1000] 92.6 / 86.9, 57 x [4096, 3072] 1723 / 1713, but 57 x [1000, 1000] 157 / 159.
+constexpr int kRank1Rows = 16, kRank1Parts = 4;
 __global__ __launch_bounds__(kRank1Threads) void k_finalize_rank1(BatchView v, LaunchRange r)
 {
+    if ((int)blockIdx.x >= r.count) {
+        __shared__ float part[kRank1Threads];
+        constexpr int kMostParts = kFinalizeThreads / kFinalizeColumns;
+        const int group = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kFinalizeThreads), lane = (int)threadIdx.x % kFinalizeThreads;
+        const uint32_t blk = r.fin_lo + (blockIdx.x - (uint32_t)r.count) * (kRank1Threads / kFinalizeThreads) + (uint32_t)group;
+        float w = 0.0f, n_tokens = 1.0f, *out = nullptr;
+        int columns = kFinalizeThreads, parts = 1, mine = 0;
+        bool is_max = false;
+        if (blk < r.fin_hi) {               // uniform over the group; a column's lanes do what k_finalize's do
+            const int t = find_slot(v.fin_prefix, r.first, r.first + r.count, blk);
+            const TensorDev d = v.descs[t];
+            columns = d.fin_columns;
+            parts = kFinalizeThreads / columns;
+            mine = lane / columns;
+            is_max = d.bits == 4;
+            const int col = (int)(blk - d.fin_begin) * columns + (lane & (columns - 1));
+            if (col < d.n_channels && (d.scale == SCALE_CHANNEL || d.scale == SCALE_RANK1)) {
+                int per = 1;
+                while (per * parts < d.n_rowblocks) per <<= 1;
+                const int first = mine * per, n = first >= d.n_rowblocks ? 0 : d.n_rowblocks - first < per ? d.n_rowblocks - first : per;
+                const CF_GLOBAL float *partial = gconst<float>(v.workspace + d.partial_off) + (int64_t)first * d.n_channels + col;
+                w = is_max ? tree_over<true, 18>(n, [&](int i) { return partial[(int64_t)i * d.n_channels]; })
+                           : tree_over<false, 18>(n, [&](int i) { return partial[(int64_t)i * d.n_channels]; });
+                if (mine == 0) out = v.ptrs[t].scales + col;
+            }
+            n_tokens = (float)d.n_tokens;
+        }
+        for (int k = 1; k < kMostParts; k <<= 1) {          // the same for all groups, whatever their parts
+            part[threadIdx.x] = w;
+            __syncthreads();
+            if (k < parts && (mine & (2 * k - 1)) == 0) {
+                const float other = part[threadIdx.x + k * columns];
+                w = is_max ? fmaxf(w, other) : w + other;
+            }
+            __syncthreads();
+        }
+        if (out) *gmut<float>(out) = is_max ? w / 7.0f : w / n_tokens;
+        return;
+    }
     const int t = r.first + (int)blockIdx.x;
     const TensorDev d = v.descs[t];
     if (d.scale != SCALE_RANK1) return;
-    __shared__ float lane_total[kRank1Threads];
+    __shared__ float wave_total[kRank1Threads / 64];
     const CF_GLOBAL float *rowpart = gconst<float>(v.workspace + d.rowpart_off);
     CF_GLOBAL float *u = gmut<float>(v.ptrs[t].scales) + d.n_channels;
     const int64_t N = d.n_tokens;
@@ -323,21 +366,39 @@ __global__ __launch_bounds__(kRank1Threads) void k_finalize_rank1(BatchView v, L
     int64_t B = 1;
     while (B * kRank1Threads < N) B <<= 1;
     const int64_t first = (int64_t)threadIdx.x * B;
-    auto rowsum = [&](int64_t i) { return tree_over<false, 4>(ncb, [&](int cb) { return rowpart[i * ncb + cb]; }); };
-    // pass 1: row sums (kept in u for pass 2) and this lane's block total
+    // pass 1: row sums and this lane's block total.  Up to 16 rows of up to 4096 channels a lane, whose partial sums are asked for together, stay in
+    // registers for pass 2; others in u
     const int nmine = first >= N ? 0 : (int)(N - first < B ? N - first : B);
-    lane_total[threadIdx.x] = tree_over<false, 12>(nmine, [&](int q) {
-        const float rs = rowsum(first + q);
-        u[first + q] = rs;
-        return rs;
-    });
-    __syncthreads();
-    for (int w = 1; w < kRank1Threads; w <<= 1) {
-        if ((threadIdx.x & (2 * w - 1)) == 0) lane_total[threadIdx.x] = lane_total[threadIdx.x] + lane_total[threadIdx.x + w];
-        __syncthreads();
+    const bool few = B <= kRank1Rows && ncb <= kRank1Parts;         // uniform
+    float rows[kRank1Rows], mine;
+    if (few) {
+#pragma unroll
+        for (int q = 0; q < kRank1Rows; ++q) {
+            float w[kRank1Parts];
+#pragma unroll
+            for (int cb = 0; cb < kRank1Parts; ++cb) w[cb] = q < nmine && cb < ncb ? rowpart[(first + q) * ncb + cb] : 0.0f;
+            rows[q] = (w[0] + w[1]) + (w[2] + w[3]);
+        }
+        mine = tree_over<false, 1>(kRank1Rows, [&](int q) { return rows[q]; });
+    } else {
+        auto rowsum = [&](int64_t i) { return tree_over<false, 4>(ncb, [&](int cb) { return rowpart[i * ncb + cb]; }); };
+        mine = tree_over<false, 12>(nmine, [&](int q) {
+            const float rs = rowsum(first + q);
+            u[first + q] = rs;
+            return rs;
+        });
     }
-    const float total = lane_total[0];
+    const float wave = wave_tree_sum(mine);
+    if ((threadIdx.x & 63) == 0) wave_total[threadIdx.x >> 6] = wave;
+    __syncthreads();
+    const float total = tree_over<false, 1>(kRank1Threads / 64, [&](int w) { return wave_total[w]; });
     const float gmean = total / (float)(N * (int64_t)d.n_channels);
+    if (few) {
+#pragma unroll
+        for (int q = 0; q < kRank1Rows; ++q)
+            if (q < nmine) u[first + q] = gmean == 0.0f ? 0.0f : rows[q] / (float)d.n_channels / gmean;
+        return;
+    }
     for (int q = 0; q < nmine; ++q) {
         const float rmean = u[first + q] / (float)d.n_channels;
         u[first + q] = gmean == 0.0f ? 0.0f : rmean / gmean;
@@ -967,7 +1028,9 @@ hipError_t launch_finalize(const BatchView &v, const LaunchRange &r, hipStream_t
 hipError_t launch_finalize_rank1(const BatchView &v, const LaunchRange &r, hipStream_t s)
 {
     if (r.count == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_finalize_rank1, dim3(r.count), dim3(kRank1Threads), 0, s, v, r);
+    constexpr unsigned kGroups = kRank1Threads / kFinalizeThreads;
+    const dim3 grid((unsigned)r.count + (r.fin_hi - r.fin_lo + kGroups - 1) / kGroups);
+    hipLaunchKernelGGL(k_finalize_rank1, grid, dim3(kRank1Threads), 0, s, v, r);
     return hipGetLastError();
 }
 
