@@ -8,6 +8,7 @@
 #include <cstdint>
 #include <cstring>
 #include <new>
+#include <utility>
 #include <vector>
 
 #include "cf_internal.h"
@@ -27,7 +28,7 @@ struct Layout {
     int32_t max_group_items = 0;   // largest reduction group of the single-pass path
     bool sp_wide = false;          // single-pass items are kStripeChannelsWide channels wide (short tensors)
     bool sp_slim = false;          // ... kStripeChannelsSlim channels wide (tall tensors)
-    bool sp_uneven = false;        // most of the context is bf16 rows that are no whole blocks of 64 bytes, see make_layout
+    bool sp_uneven = false;        // most of the context is bf16 rows that are no whole blocks of 64 bytes, see lay_out
     bool sp_blocks = false;        // ... and the parts of blocks go out without the streaming hint
     bool sp_uneven_tall = false;   // ... and fused steps of more than kUnevenRounds rounds of workgroups take two kernels by default
     bool sp_too_tall = false;      // some group is larger than its tensor's limit: two kernels by default, but for small calls
@@ -204,7 +205,8 @@ int32_t slim_group_limit(const cf_tensor_desc &d, const cf_options &o)
     return !naive ? kSlimGroupLimitUneven : wide ? kNarrowGroupLimit : kSlimGroupLimitNaive;
 }
 
-cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &o, Layout &L)
+// uneven_stripes: contexts of mostly uneven rows take stripes of their own
+cf_status lay_out(const cf_tensor_desc *descs, int32_t n, const cf_options &o, bool uneven_stripes, Layout &L)
 {
     if (!descs || n < 1) return CF_ERR_INVALID_ARG;
     for (int32_t t = 0; t < n; ++t) {
@@ -263,7 +265,7 @@ cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &
     L.sp_uneven = L.single_pass && uneven_elements > elements - uneven_elements;
     L.sp_blocks = L.sp_uneven && (odd || narrow_max_group <= 4);
     L.sp_uneven_tall = L.sp_uneven && narrow_max_group > (odd ? (o.err_dtype == CF_BF16 ? kUnevenGroupLimitBf16Error : kUnevenWideGroup) : kUnevenGroupLimitEven);
-    L.sp_wide = L.single_pass && narrow_max_group > 0 && narrow_max_group <= (L.sp_uneven ? kUnevenWideGroup : 12);
+    L.sp_wide = L.single_pass && narrow_max_group > 0 && narrow_max_group <= (L.sp_uneven && uneven_stripes ? kUnevenWideGroup : 12);
     // Tall tensors the other way round: all workgroups of a group wait for its slowest, and the more they are the longer.
     // 128 -> 64 channels on batches of equal size, us: [6144, 3072] bf16 793 -> 790, [8192, 3072] 840 -> 812 (4-bit 858 ->
     // 856), [12288, 3072] 895 -> 854, [16384, 3072] 1030 -> 902, [17776, 1920] with bf16 error 2227 -> 1976.  Tensors that
@@ -272,7 +274,7 @@ cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &
     // 20 x [4096, 3072] with seven 1080 -> 1068; beyond that two kernels are the other choice: 40 x [2048, 3072] with four
     // [16384, 3072] 970 against 1078.  Not for slivers: 114 x [11653, 80] 360 -> 434 (x [11653, 64] 272 -> 199, 60 x
     // [17000, 96] 310 -> 298).
-    L.sp_slim = L.single_pass && !slivers && !(L.sp_uneven && narrow_max_group <= kUnevenNarrowGroup) && narrow_max_group > kTallGroupItems &&
+    L.sp_slim = L.single_pass && !slivers && !(L.sp_uneven && uneven_stripes && narrow_max_group <= kUnevenNarrowGroup) && narrow_max_group > kTallGroupItems &&
                 (narrow_max_group > kNarrowGroupLimit || tall_elements >= elements - tall_elements);
     // Largest group of a call of any size in 128-channel stripes, single pass against two kernels in us: 4 x [10000, 3072], 40, 290 / 307; one [12288,
     // 3072] among 40 x [4096, 3072], 48, 1027 / 1311; slivers, whose second kernel runs across the row ends: 114 x [11653, 80], 46, 351 / 312, x [10500,
@@ -429,6 +431,16 @@ cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &
             L.dev[t].lr_g_off += L.off_partials;
         }
     }
+    return CF_OK;
+}
+
+cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &o, Layout &L)
+{
+    const cf_status st = lay_out(descs, n, o, true, L);
+    if (st != CF_OK || !L.sp_uneven || L.total <= kStaticScratchBytes) return st;
+    // The stripes of uneven rows have up to twice the partials: no tensors outgrow the static scratch because of them.
+    Layout others;
+    if (lay_out(descs, n, o, false, others) == CF_OK && others.total <= kStaticScratchBytes) L = std::move(others);
     return CF_OK;
 }
 
