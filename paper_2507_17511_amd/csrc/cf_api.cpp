@@ -261,6 +261,9 @@ cf_status lay_out(const cf_tensor_desc *descs, int32_t n, const cf_options &o, b
     //         653 / 603; not fused [6100, 1096] 395 / 373 / 411 / 415 / 450, [8000, 1096] 528 / 501 / 558 / 562 / 590
     //   even  [1024, 1104] 333 / 298 / 276 / 265 / 345, [4096, 1104] 371 / 367 / 355 / 369 / 407, [8000, 1104] 391 / 391 / 409 / 425 / 410, [11000, 1104] 407 / 408 / 484 / 488 / 406 (64
     //         channels 479), [17000, 3088] 451 / 449 / 631 / 643 / 411; not fused [8000, 1104] 318 / 327 / 359 / 371 / 390
+    // Of 49 to 64 items, as it runs in 128 channels / in 64 / two kernels: 10 x [14000, 1096] 449 / 556 / 404, not fused 309 / 352 / 346, two of them 75 / 88 / 99 and 66 / 74 / 89,
+    // 3 x [16000, 3080] not fused 326 / 352 / 319; 10 x [14000, 1104] 405 / 477 / 400, not fused 290 / 322 / 345, two of them 87 / 99 / 99 and 61 / 66 / 88.  Beyond, 64 channels
+    // without and with blocks / two kernels: 8 x [17000, 1096] 632 / 550 / 390, not fused 412 / 349 / 337, two of them 161 / 109 / 113 and 109 / 93 / 100.
     const bool odd = odd_elements >= uneven_elements - odd_elements;
     L.sp_uneven = L.single_pass && uneven_elements > elements - uneven_elements;
     L.sp_blocks = L.sp_uneven && (odd || narrow_max_group <= 4);
@@ -361,7 +364,7 @@ cf_status lay_out(const cf_tensor_desc *descs, int32_t n, const cf_options &o, b
             p_partial_bytes += align_up((size_t)v.p_n_rb * (size_t)d.n_channels * sizeof(float));
             items += (uint64_t)v.p_n_rb * (uint64_t)v.p_n_stripes;
             if (v.p_n_rb > L.max_group_items) L.max_group_items = v.p_n_rb;
-            if (v.p_n_rb > (L.sp_slim ? slim_group_limit(d, o) : slivers ? kTallGroupItems : kNarrowGroupLimit)) L.sp_too_tall = true;
+            if (v.p_n_rb > (L.sp_slim ? slim_group_limit(d, o) : slivers ? kTallGroupItems : L.sp_uneven && uneven_stripes ? kUnevenNarrowGroup : kNarrowGroupLimit)) L.sp_too_tall = true;
             if (items > 0x7fffffffull) return CF_ERR_SHAPE;
         }
     }

@@ -11,7 +11,7 @@
 #include "compactfusion.h"
 
 extern std::vector<std::string> g_launch_log;
-extern bool g_single_pass_short;
+extern bool g_single_pass_short, g_single_pass_wide, g_single_pass_blocks;
 extern bool g_capturing;
 extern int g_compute_units;
 extern bool g_overlapping;
@@ -385,6 +385,51 @@ int main()
                 const auto &s = c.shapes.back();
                 std::printf("ef %d dtype %d ... %d x [%d, %d]: path %d instead of %d\n", c.ef, c.dtype, (int)s[0], (int)s[1], (int)s[2], (int)took, (int)c.path);
                 ++g_failed;
+            }
+            cf_destroy(ctx);
+            std::free(ws);
+        }
+    }
+
+    // ---- bf16 rows that are no whole blocks of 64 bytes: stripes by the context, kernels and stores by the call
+    {
+        enum Path { TWO, WIDE, NARROW, SLIM, SHORT };
+        enum Stores { WHOLE, BLOCKS };                  // whether parts of blocks are left to the L2
+        struct Call { std::vector<std::vector<int64_t>> shapes; Path step, send; Stores stores; int first = 0, count = 0; };       // count 0: the whole context
+        const std::vector<Call> calls = {
+            // 48 and 49 items of 256 rows, 64 and 65: 128-channel stripes up to there; two kernels for steps of more than 1280 items alone
+            {{{2, 12288, 1096}}, NARROW, NARROW, BLOCKS}, {{{2, 12289, 1096}}, NARROW, NARROW, BLOCKS}, {{{10, 12289, 1096}}, TWO, NARROW, BLOCKS},
+            {{{2, 16384, 1096}}, NARROW, NARROW, BLOCKS}, {{{10, 16384, 1096}}, TWO, NARROW, BLOCKS}, {{{2, 16385, 1096}}, SLIM, SLIM, BLOCKS}, {{{10, 16385, 1096}}, TWO, SLIM, BLOCKS},
+            {{{2, 12289, 1104}}, NARROW, NARROW, WHOLE}, {{{10, 12289, 1104}}, TWO, NARROW, WHOLE}, {{{10, 16384, 1104}}, TWO, NARROW, WHOLE}, {{{10, 16385, 1104}}, TWO, SLIM, WHOLE},
+        };
+        for (size_t k = 0; k < calls.size(); ++k) {
+            const Call &c = calls[k];
+            std::vector<cf_tensor_desc> d;
+            for (auto &s : c.shapes) d.insert(d.end(), (size_t)s[0], desc(s[1], s[2], s.size() > 3 ? (int)s[3] : CF_BF16, 2, CF_SCALE_CHANNEL));
+            const int n = (int)d.size(), first = c.first, count = c.count ? c.count : n - first;
+            std::memset(&o, 0, sizeof o);
+            std::vector<void *> bufs[5];
+            uintptr_t at = (uintptr_t)1 << 40;
+            for (auto &b : bufs)
+                for (int t = 0; t < n; ++t, at += (uintptr_t)1 << 32) b.push_back((void *)at);
+            const size_t wsb = cf_workspace_bytes(d.data(), n, &o);
+            void *ws = nullptr;
+            if (posix_memalign(&ws, 256, wsb) != 0) std::abort();
+            cf_ctx *ctx = nullptr;
+            EXPECT(cf_init(&ctx, d.data(), n, &o, ws, wsb, nullptr) == CF_OK);
+            EXPECT(cf_set_warm(ctx, 0, n, 1) == CF_OK);
+            for (bool send : {false, true}) {
+                joined();
+                g_single_pass_slim = g_single_pass_wide = g_single_pass_short = g_single_pass_blocks = false;
+                EXPECT((send ? cf_compress(ctx, first, count, (const void *const *)bufs[0].data() + first, (const void *const *)bufs[1].data() + first, bufs[2].data() + first,
+                                           bufs[3].data() + first, bufs[4].data() + first, nullptr)
+                             : cf_step_fused(ctx, first, count, (const void *const *)bufs[0].data() + first, bufs[1].data() + first, bufs[2].data() + first,
+                                             bufs[3].data() + first, bufs[4].data() + first, nullptr)) == CF_OK);
+                const Path took = joined().find("k_single_pass ") == std::string::npos ? TWO : g_single_pass_short ? SHORT : g_single_pass_slim ? SLIM : g_single_pass_wide ? WIDE : NARROW;
+                if (took != (send ? c.send : c.step) || (took != TWO && g_single_pass_blocks != (c.stores == BLOCKS))) {
+                    std::printf("uneven call %zu %s: path %d, parts of blocks %d\n", k, send ? "sent" : "step", (int)took, (int)g_single_pass_blocks);
+                    ++g_failed;
+                }
             }
             cf_destroy(ctx);
             std::free(ws);

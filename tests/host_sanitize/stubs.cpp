@@ -16,6 +16,8 @@ bool g_capturing = false;
 int g_compute_units = 256;
 bool g_single_pass_slim = false;        // the stripe width of the last single pass
 bool g_single_pass_short = false;       // and its items' height
+bool g_single_pass_wide = false;
+bool g_single_pass_blocks = false;      // whether it left parts of 64-byte blocks to the L2
 bool g_occupancy_slim = false;          // and the one whose co-resident workgroups were asked for last
 bool g_project_many = false;            // whether the last projection's waves take several blocks of tokens
 int g_split = 0;                        // and the workgroups that share a stripe of the last back-projection
@@ -92,9 +94,11 @@ hipError_t launch_lr_quant_u(const BatchView &, const LaunchRange &, hipStream_t
 hipError_t launch_lr_encode(const BatchView &, const LaunchRange &, int, bool, hipStream_t) { note("k_lr_apply"); return hipSuccess; }
 hipError_t launch_lr_decode(const BatchView &, const LaunchRange &r, hipStream_t) { take_direct(r); note("k_lr_apply"); return hipSuccess; }
 int persistent_max_blocks_per_cu(int, int, bool, bool, bool slim) { g_occupancy_slim = slim; return 2; }
-hipError_t launch_single_pass(const BatchView &v, const LaunchRange &r, int, int, bool, bool, int, bool, hipStream_t)
+hipError_t launch_single_pass(const BatchView &v, const LaunchRange &r, int, int, bool, bool wide, int, bool, hipStream_t)
 {
     take_direct(r);
+    g_single_pass_wide = wide;
+    g_single_pass_blocks = r.sp_blocks != 0;
     g_single_pass_slim = r.sp_slim != 0;
     g_single_pass_short = r.sp_short != 0;
     g_states.assign(v.item_state + r.item_lo, v.item_state + r.item_hi);
