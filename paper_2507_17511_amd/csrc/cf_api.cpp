@@ -20,6 +20,10 @@ namespace {
 constexpr size_t kAlign = 256;
 inline size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
+// A tensor of such rows, in contexts of mostly such: the parts of its blocks go out without the streaming hint; fused steps of more than kUnevenRounds rounds of
+// workgroups over it take two kernels by default.
+enum : uint8_t { kUnevenRow = 1, kUnevenBlocks = 2, kUnevenTall = 4 };
+
 struct Layout {
     size_t off_descs = 0, off_ptrs = 0, off_tile_prefix = 0, off_fin_prefix = 0, off_partials = 0;
     size_t off_item_prefix = 0, off_item_tensor = 0, off_item_state = 0, off_error = 0, off_p_partials = 0;
@@ -29,8 +33,7 @@ struct Layout {
     bool sp_wide = false;          // single-pass items are kStripeChannelsWide channels wide (short tensors)
     bool sp_slim = false;          // ... kStripeChannelsSlim channels wide (tall tensors)
     bool sp_uneven = false;        // most of the context is bf16 rows that are no whole blocks of 64 bytes, see lay_out
-    bool sp_blocks = false;        // ... and the parts of blocks go out without the streaming hint
-    bool sp_uneven_tall = false;   // ... and fused steps of more than kUnevenRounds rounds of workgroups take two kernels by default
+    std::vector<uint8_t> uneven;   // per tensor, kUnevenRow and what else holds of it
     bool sp_too_tall = false;      // some group is larger than its tensor's limit: two kernels by default, but for small calls
     bool single_pass = false;      // every channel-scale tensor has single-pass geometry
     // Short items: calls whose items leave the device half empty take ones a quarter as tall, kernels of their own with a
@@ -237,15 +240,22 @@ cf_status lay_out(const cf_tensor_desc *descs, int32_t n, const cf_options &o, b
     // N = 2048 1.49 / 1.51 / 1.60 -> 1.52 / 1.48 / 1.55, N = 3072 1.47 / 1.52 / 1.61 -> 1.46 / 1.50 / 1.58,
     // N = 4096 1.50 / 1.55 / 1.62 -> 1.53 / 1.56 / 1.65, N = 6144 1.56 / 1.59 / 1.68 -> 1.62 / 1.66 / 1.77.
     auto narrow_item_rows = [&](int32_t dtype) { return (kPersistThreads / (kStripeChannels / kChunk)) * single_pass_rows_per_lane(dtype, o.ef); };
-    int64_t narrow_max_group = 0, elements = 0, tall_elements = 0, sliver_elements = 0, uneven_elements = 0, odd_elements = 0;
+    int64_t narrow_max_group = 0, elements = 0, tall_elements = 0, sliver_elements = 0, uneven_elements = 0, uneven_wide = 0, uneven_short = 0;
+    L.uneven.assign(n, 0);
     for (int32_t t = 0; t < n; ++t)
         if (descs[t].scale == CF_SCALE_CHANNEL) {
             const int64_t rows = narrow_item_rows(descs[t].dtype), c = descs[t].n_channels, last = c % kStripeChannelsSlim;
             const int64_t g = (descs[t].n_tokens + rows - 1) / rows;
             if (g > narrow_max_group) narrow_max_group = g;
             elements += descs[t].n_tokens * c;
-            if (o.ef == CF_EF_RECON && descs[t].dtype == CF_BF16 && c % 32 != 0) uneven_elements += descs[t].n_tokens * c;
-            if (o.ef == CF_EF_RECON && descs[t].dtype == CF_BF16 && c % 16 != 0) odd_elements += descs[t].n_tokens * c;
+            if (o.ef == CF_EF_RECON && descs[t].dtype == CF_BF16 && c % 32 != 0) {
+                const bool odd = c % 16 != 0;
+                const int limit = !odd ? kUnevenGroupLimitEven : o.err_dtype == CF_BF16 ? kUnevenGroupLimitBf16Error : kUnevenWideGroup;
+                L.uneven[t] = (uint8_t)(kUnevenRow | (odd || g <= 4 ? kUnevenBlocks : 0) | (g > limit ? kUnevenTall : 0));
+                uneven_elements += descs[t].n_tokens * c;
+                if (g <= kUnevenWideGroup) uneven_wide += descs[t].n_tokens * c;
+                if (g <= kWideGroup) uneven_short += descs[t].n_tokens * c;
+            }
             if (g > kTallGroupItems) tall_elements += descs[t].n_tokens * c;
             // the last 64-channel stripe of a row is a few short pieces of memory and much of what there is
             if (g > kTallGroupItems && c < kStripeChannels && last > 0 && last < kStripeChannelsSlim / 2) sliver_elements += descs[t].n_tokens * c;
@@ -264,11 +274,17 @@ cf_status lay_out(const cf_tensor_desc *descs, int32_t n, const cf_options &o, b
     // Of 49 to 64 items, as it runs in 128 channels / in 64 / two kernels: 10 x [14000, 1096] 449 / 556 / 404, not fused 309 / 352 / 346, two of them 75 / 88 / 99 and 66 / 74 / 89,
     // 3 x [16000, 3080] not fused 326 / 352 / 319; 10 x [14000, 1104] 405 / 477 / 400, not fused 290 / 322 / 345, two of them 87 / 99 / 99 and 61 / 66 / 88.  Beyond, 64 channels
     // without and with blocks / two kernels: 8 x [17000, 1096] 632 / 550 / 390, not fused 412 / 349 / 337, two of them 161 / 109 / 113 and 109 / 93 / 100.
-    const bool odd = odd_elements >= uneven_elements - odd_elements;
+    // Stripes are the context's.  Wide ones cost whole rows of 13 items and more what uneven ones of so many gain, and what those gain in steps they lose when sent: so three quarters
+    // of the context have to be such.  128 / 256 channels: 36 x [4096, 1096] 417 / 395, sent 292 / 303, x [4096, 1104] 380 / 364, sent 275 / 287; 27 x [4096, 1096] with 9 x [4096,
+    // 1088] 396 / 382, sent 281 / 297, 20 with 16 379 / 374, sent 272 / 291.  Uneven rows of up to 12 items gain more: 110 x [1024, 1096] with one [5000, 3072] 425 / 317, the 110
+    // alone 370 / 276, the one alone 31 / 35; with 14 x [6000, 1088] 597 / 501, sent 391 / 384.
+    // Stores and the second kernel are the call's, by most of its elements: 30 x [4800, 1088] of a context with 40 x [4800, 1096] take 305 in the single pass, 324 with blocks, 397 with
+    // two kernels.  Calls over both, single pass / two kernels: [4609, 1096] with [4609, 1088] 51 % 751 / 782, 67 % 774 / 775, 80 % 805 / 781, [8000, 3080] with [8000, 3072]
+    // 57 % 879 / 860, [14000, 1096] with [14000, 1088] 55 % 890 / 861.
     L.sp_uneven = L.single_pass && uneven_elements > elements - uneven_elements;
-    L.sp_blocks = L.sp_uneven && (odd || narrow_max_group <= 4);
-    L.sp_uneven_tall = L.sp_uneven && narrow_max_group > (odd ? (o.err_dtype == CF_BF16 ? kUnevenGroupLimitBf16Error : kUnevenWideGroup) : kUnevenGroupLimitEven);
-    L.sp_wide = L.single_pass && narrow_max_group > 0 && narrow_max_group <= (L.sp_uneven && uneven_stripes ? kUnevenWideGroup : 12);
+    const bool wide_uneven = uneven_stripes && ((narrow_max_group <= kUnevenWideGroup && uneven_wide >= 3 * (elements - uneven_wide)) ||
+                                                (narrow_max_group <= kNarrowGroupLimit / 2 && uneven_short > elements - uneven_short));
+    L.sp_wide = L.single_pass && narrow_max_group > 0 && (narrow_max_group <= kWideGroup || wide_uneven);
     // Tall tensors the other way round: all workgroups of a group wait for its slowest, and the more they are the longer.
     // 128 -> 64 channels on batches of equal size, us: [6144, 3072] bf16 793 -> 790, [8192, 3072] 840 -> 812 (4-bit 858 ->
     // 856), [12288, 3072] 895 -> 854, [16384, 3072] 1030 -> 902, [17776, 1920] with bf16 error 2227 -> 1976.  Tensors that
@@ -441,7 +457,7 @@ cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &
 {
     const cf_status st = lay_out(descs, n, o, true, L);
     if (st != CF_OK || !L.sp_uneven || L.total <= kStaticScratchBytes) return st;
-    // The stripes of uneven rows have up to twice the partials: no tensors outgrow the static scratch because of them.
+    // The stripes of uneven rows have up to twice the partials: no tensors outgrow the static scratch because of them (40 x [4096, 1096] 395 / 417 us).
     Layout others;
     if (lay_out(descs, n, o, false, others) == CF_OK && others.total <= kStaticScratchBytes) L = std::move(others);
     return CF_OK;
@@ -556,7 +572,7 @@ struct cf_ctx {
         r.sp_short = 0;
         r.item_lo = L.item_prefix[first];
         r.item_hi = L.item_prefix[first + count];
-        r.sp_blocks = L.sp_blocks && r.item_hi - r.item_lo > (uint32_t)kBlocksItems;
+        r.sp_blocks = 0;
         r.only_group_scale = 0;
         r.naive = opts.ef == CF_EF_NAIVE;
         r.dts = descs[first].dtype;
@@ -592,6 +608,16 @@ struct cf_ctx {
         return r;
     }
 
+    // Whether most of the call's elements with channel scales are tensors of that kind, in a context of mostly uneven rows.
+    bool mostly(int32_t first, int32_t count, uint8_t kind) const
+    {
+        if (!L.sp_uneven) return false;
+        int64_t of_kind = 0, others = 0;
+        for (int32_t t = first; t < first + count; ++t)
+            if (descs[t].scale == CF_SCALE_CHANNEL) (L.uneven[t] & kind ? of_kind : others) += descs[t].n_tokens * descs[t].n_channels;
+        return of_kind > others;
+    }
+
     // Whether short items serve the call: `r` and `v` are theirs then.  resident: how many the device holds at once.
     bool take_short(int32_t first, int32_t count, uint32_t resident, LaunchRange &r, BatchView &v) const
     {
@@ -602,7 +628,7 @@ struct cf_ctx {
         }
         if (items > (uint32_t)kShortItems || items > resident) return false;
         r.sp_short = 1;
-        r.sp_blocks = L.sp_uneven && items > (uint32_t)kShortBlocksItems;
+        r.sp_blocks = mostly(first, count, kUnevenRow) && items > (uint32_t)kShortBlocksItems;
         r.item_lo = L.short_dev[first].p_item_begin;
         r.item_hi = r.item_lo + items;
         r.direct_descs = L.short_dev.data() + first;
@@ -966,10 +992,11 @@ cf_status run_sender(cf_ctx *ctx, int32_t first, int32_t count, const void *cons
         else if (d.p_n_rb == 2) gain += d.p_n_stripes * (rows - (rounds <= 3.0 ? 1.2 : 1.4));
         else gain += rows * width - d.p_n_stripes * (rows_per_lane < 8 ? 0.1 : rows_per_lane < 16 ? 0.25 : rounds <= 2.0 ? 1.0 / 3.0 : 0.4);
     }
-    const bool worth_it = forced || small_call || (!ctx->L.sp_too_tall && !(fused && ctx->L.sp_uneven_tall && rounds > kUnevenRounds) && (gain >= 0.0 || (tall && rounds <= 3.0)));
+    const bool worth_it = forced || small_call || (!ctx->L.sp_too_tall && !(fused && rounds > kUnevenRounds && ctx->mostly(first, count, kUnevenTall)) && (gain >= 0.0 || (tall && rounds <= 3.0)));
     // (a group larger than what the device holds at once would have its first workgroups wait for ones that cannot
     // start before they leave: correct, they give up and compute the missing sums, but slow: such tensors take two kernels)
     const bool single_pass = ctx->L.single_pass && grid >= ctx->L.max_group_items && grid >= 1 && r.item_hi > r.item_lo && worth_it;
+    r.sp_blocks = items > (uint32_t)kBlocksItems && ctx->mostly(first, count, kUnevenBlocks);
     DirectPtrs direct;
     // kernels that take their pointers as arguments: the row-local ones, and the single pass
     const bool one_pass = single_pass && ctx->range_all_channel(first, count);

@@ -55,13 +55,15 @@ constexpr uint32_t kWaitPolls = 4096;
 // A tensor of more 128-channel items per group than kTallGroupItems is tall: contexts of mostly such take 64-channel
 // stripes.  Groups of more items than the limit of the stripe in use take two kernels by default, unless the device holds
 // the whole call at once: nothing has to wait for a second round of workgroups then.
+constexpr int kWideGroup = 12;
 constexpr int kTallGroupItems = 40;
 constexpr int kNarrowGroupLimit = 48;
 constexpr int kSlimGroupLimit = 64;                         // see slim_group_limit
 constexpr int kSlimGroupLimitUneven = 38;
 constexpr int kSlimGroupLimitNaive = 24;
-// Contexts of mostly uneven rows, in 128-channel items a group: 256-channel stripes up to the first, no 64-channel ones up to kUnevenNarrowGroup, nor two kernels because of
-// kNarrowGroupLimit; fused steps of more than kUnevenRounds rounds by two kernels past the first, or past these where the error is bf16 or the channels a multiple of 16.  lay_out has the figures.
+// Contexts of mostly uneven rows, in 128-channel items a group: 256-channel stripes up to the first, no 64-channel ones up to kUnevenNarrowGroup, nor two kernels
+// because of kNarrowGroupLimit; fused calls of more than kUnevenRounds rounds by two kernels where most are past the first, or past these where the error is bf16 or the channels a
+// multiple of 16.  lay_out has the figures.
 constexpr int kUnevenWideGroup = 18;
 constexpr int kUnevenNarrowGroup = 64;
 constexpr int kUnevenGroupLimitBf16Error = 28;

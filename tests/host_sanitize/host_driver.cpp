@@ -391,7 +391,7 @@ int main()
         }
     }
 
-    // ---- bf16 rows that are no whole blocks of 64 bytes: stripes by the context, kernels and stores by the call
+    // ---- bf16 rows that are no whole blocks of 64 bytes (contexts that are not near the static scratch's size): stripes by the context, kernels and stores by the call
     {
         enum Path { TWO, WIDE, NARROW, SLIM, SHORT };
         enum Stores { WHOLE, BLOCKS };                  // whether parts of blocks are left to the L2
@@ -401,6 +401,22 @@ int main()
             {{{2, 12288, 1096}}, NARROW, NARROW, BLOCKS}, {{{2, 12289, 1096}}, NARROW, NARROW, BLOCKS}, {{{10, 12289, 1096}}, TWO, NARROW, BLOCKS},
             {{{2, 16384, 1096}}, NARROW, NARROW, BLOCKS}, {{{10, 16384, 1096}}, TWO, NARROW, BLOCKS}, {{{2, 16385, 1096}}, SLIM, SLIM, BLOCKS}, {{{10, 16385, 1096}}, TWO, SLIM, BLOCKS},
             {{{2, 12289, 1104}}, NARROW, NARROW, WHOLE}, {{{10, 12289, 1104}}, TWO, NARROW, WHOLE}, {{{10, 16384, 1104}}, TWO, NARROW, WHOLE}, {{{10, 16385, 1104}}, TWO, SLIM, WHOLE},
+            // 256 channels where three quarters of a context are uneven rows and nothing is of more than 18 items, or most are of up to 12 and nothing is of more than 24
+            {{{30, 4608, 1096}}, WIDE, WIDE, BLOCKS}, {{{30, 4609, 1096}}, TWO, NARROW, BLOCKS}, {{{30, 4608, 1104}}, WIDE, WIDE, WHOLE}, {{{30, 1024, 1104}}, WIDE, WIDE, BLOCKS},
+            {{{30, 1025, 1104}}, WIDE, WIDE, WHOLE}, {{{110, 1024, 1096}, {1, 5000, 3072}}, WIDE, WIDE, BLOCKS}, {{{110, 1024, 1096}, {1, 5000, 1096}}, WIDE, WIDE, BLOCKS},
+            {{{110, 1024, 1096}, {1, 6144, 3072}}, WIDE, WIDE, BLOCKS}, {{{110, 1024, 1096}, {1, 6145, 3072}}, NARROW, NARROW, BLOCKS}, {{{110, 1024, 1096}, {40, 5000, 3072}}, NARROW, NARROW, WHOLE},
+            {{{15, 4096, 1096}, {16, 4609, 1096}}, TWO, NARROW, BLOCKS}, {{{34, 4609, 1096}, {40, 4608, 1096}}, NARROW, NARROW, BLOCKS},
+            {{{60, 4096, 1096}, {20, 4096, 1088}}, WIDE, WIDE, BLOCKS}, {{{60, 4096, 1096}, {21, 4096, 1088}}, NARROW, NARROW, BLOCKS},
+            // calls over a part of a context: two kernels, and parts of blocks left, by what most of the call is
+            {{{110, 1024, 1096}, {1, 5000, 3072}}, WIDE, WIDE, BLOCKS, 0, 110}, {{{110, 1024, 1096}, {1, 5000, 3072}}, WIDE, WIDE, WHOLE, 110, 1},
+            {{{30, 4800, 1096}, {25, 4800, 1088}}, TWO, NARROW, BLOCKS}, {{{30, 4800, 1096}, {25, 4800, 1088}}, TWO, NARROW, BLOCKS, 0, 30},
+            {{{30, 4800, 1096}, {25, 4800, 1088}}, NARROW, NARROW, WHOLE, 30, 25}, {{{30, 4800, 1096}, {25, 4800, 1088}}, NARROW, NARROW, WHOLE, 25, 12},
+            {{{30, 4800, 1096}, {25, 4800, 1088}}, TWO, NARROW, BLOCKS, 20, 19}, {{{20, 9000, 1104}, {10, 4096, 1104}}, TWO, NARROW, WHOLE},
+            {{{20, 9000, 1104}, {10, 4096, 1104}}, NARROW, NARROW, WHOLE, 20, 10}, {{{20, 9000, 1104}, {15, 9000, 1088}}, NARROW, NARROW, WHOLE, 20, 15},
+            {{{60, 4096, 1096}, {20, 4096, 1088}}, WIDE, WIDE, WHOLE, 60, 20}, {{{60, 4096, 1096}, {30, 4096, 1088}}, NARROW, NARROW, WHOLE, 60, 30}, {{{10, 13000, 1096}, {8, 13000, 1088}}, NARROW, NARROW, WHOLE, 10, 8},
+            // short items: parts of blocks from 448 items on
+            {{{30, 1024, 1096}, {9, 1024, 1088}}, SHORT, SHORT, BLOCKS, 0, 6}, {{{30, 1024, 1096}, {9, 1024, 1088}}, SHORT, SHORT, WHOLE, 0, 3},
+            {{{30, 1024, 1096}, {9, 1024, 1088}}, SHORT, SHORT, WHOLE, 30, 6}, {{{30, 1024, 1104}}, SHORT, SHORT, BLOCKS, 0, 6},
         };
         for (size_t k = 0; k < calls.size(); ++k) {
             const Call &c = calls[k];
