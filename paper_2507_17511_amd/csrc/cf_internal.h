@@ -49,6 +49,9 @@ constexpr int kShortFraction = 4;
 constexpr int kShortStripeChannels = 64;
 constexpr int kShortItems = 1024;                           // the most of a call: four workgroups a CU of the whole MI355X; a part of one takes as many as it holds
 constexpr int kShortGroupLimit = 64;                        // the most of a group
+// Workgroups without an item that a call of short items may have.  Steps, us, with / by looking up: 2 x [1024, 3072] (none) 12.9 / 13.3, [2048, 512] + [1024, 512] (64) 8.4 / 8.6,
+// [1024, 3072] + [768, 3072] (96) 12.2 / 12.1, + [512, 3072] (192) 12.1 / 11.6, [1024, 2048] + 2 x [512, 2048] (256) 11.6 / 10.1, [8192, 64] + [8, 61440] (121,856) 151 / 8.8.
+constexpr uint64_t kShortEmpty = 64;
 constexpr int single_pass_rows_per_lane(int dtype, int ef) { return 16 / (dtype == 0 ? 2 : 1) / ((ef == 1 || ef == 2) ? 2 : 1); }
 // A workgroup polls a missing partial this many times (a microsecond or two each) before it gives its item up.
 constexpr uint32_t kWaitPolls = 4096;
@@ -168,7 +171,7 @@ struct LaunchRange {
     uint32_t sp_wait_polls;     // single-pass kernel: polls of a missing partial before the workgroup computes it itself
     uint32_t sp_slim;           // single-pass kernel: items of kStripeChannelsSlim channels (tall tensors)
     uint32_t sp_blocks;         // single-pass kernel: parts of 64-byte blocks go out without the streaming hint
-    uint32_t sp_short;          // single-pass kernel: short items; item_lo, item_hi, direct_descs and the view's item_state are theirs
+    uint32_t sp_short;          // single-pass kernel: short items (2: workgroups look their tensors up, see short_grid); item_lo, item_hi, direct_descs and the view's item_state are theirs
     int32_t dts;                // storage dtype of every tensor in the range (cf_dtype), or 2 if mixed
     int32_t only_group_scale;   // tiled encode: skip tensors the single-pass kernel covers
     int32_t naive;              // decode: recon_t = D instead of recon_{t-1} + D (CF_EF_NAIVE)
@@ -210,6 +213,24 @@ struct SinglePassArgs {
 static_assert(sizeof(BatchView) + sizeof(DirectRange) == 256 + sizeof(TensorPtrs) * kDirectTensors, "where the sets begin");
 
 static_assert(sizeof(SinglePassArgs) <= 4096, "a kernel's arguments");
+
+// The grid of k_short_items: row blocks x stripes x tensors, as many as the largest of the call's tensors have, where no more than kShortEmpty workgroups of it are
+// without an item; else one workgroup per item, which looks its tensor up first.
+struct ShortGrid {
+    uint32_t x, y, z;
+    bool flat;
+};
+inline ShortGrid short_grid(const TensorDev *descs, int count)
+{
+    uint64_t rb = 0, stripes = 0, items = 0;
+    for (int k = 0; k < count; ++k) {
+        rb = (uint64_t)descs[k].p_n_rb > rb ? (uint64_t)descs[k].p_n_rb : rb;
+        stripes = (uint64_t)descs[k].p_n_stripes > stripes ? (uint64_t)descs[k].p_n_stripes : stripes;
+        items += (uint64_t)descs[k].p_n_rb * (uint64_t)descs[k].p_n_stripes;
+    }
+    if (rb * stripes * (uint64_t)count > items + kShortEmpty) return {(uint32_t)items, 1u, 1u, true};
+    return {(uint32_t)rb, (uint32_t)stripes, (uint32_t)count, false};
+}
 
 // The arguments of k_short_items: nothing of a call is elsewhere.
 struct ShortArgs {

@@ -455,7 +455,9 @@ __global__ __launch_bounds__(kPersistThreads, 2) void k_single_pass(SinglePassAr
 // Short items.  A call of them is over before a large one's first operands arrive, so what it waits for is the chain of an item, and of that its descriptor was the
 // longest link: range, then which tensor, then descriptor and state, each a load from memory that waits for the one before (3 of the 8 us that one tensor of
 // [256, 64] took).  Here the grid says which item a workgroup has: x the row block, y the stripe, z the tensor, as many as the largest tensor of the call has, and
-// the descriptor and pointers come with the range, in one round; the state comes while the operands do.
+// the descriptor and pointers come with the range, in one round; the state comes while the operands do.  Tensors of unlike shapes would leave most of such a grid
+// empty (32,768 workgroups for the 512 items of 7 x [8192, 64] with [64, 4096], 25.3 us): those calls have a workgroup per item, which finds its tensor among the
+// arguments and asks again (11.1).
 template <int ET, bool FUSED, bool BLOCKS>
 __global__ __launch_bounds__(kPersistThreads, 4) void k_short_items(ShortArgs args)
 {
@@ -464,18 +466,37 @@ __global__ __launch_bounds__(kPersistThreads, 4) void k_short_items(ShortArgs ar
     const LaunchRange &r = args.r;
     __shared__ Shared<SCH> sh;
     const uint64_t given = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
-    TensorDev d = scalar_load<TensorDev>(given + offsetof(ShortArgs, descs) + blockIdx.z * sizeof(TensorDev));
-    TensorPtrs p = scalar_load<TensorPtrs>(given + offsetof(ShortArgs, sets) + blockIdx.z * sizeof(TensorPtrs));
+    TensorDev d;
+    TensorPtrs p;
+    const auto load = [&](uint32_t t) {
+        d = scalar_load<TensorDev>(given + offsetof(ShortArgs, descs) + t * sizeof(TensorDev));
+        p = scalar_load<TensorPtrs>(given + offsetof(ShortArgs, sets) + t * sizeof(TensorPtrs));
+    };
+    load(blockIdx.z);
     uint8_t *states = v.item_state;
-    asm volatile("" : "+s"(d.n_tokens), "+s"(d.n_channels), "+s"(d.n_chunks), "+s"(d.dtype), "+s"(d.bits), "+s"(d.p_partial_off), "+s"(d.p_rows),
-                      "+s"(d.p_n_rb), "+s"(d.p_item_begin), "+s"(p.x), "+s"(p.recon), "+s"(p.err), "+s"(p.codes), "+s"(p.scales), "+s"(states));      // one wait for all of them
-    if ((int)blockIdx.x >= d.p_n_rb || (int)blockIdx.y >= d.p_n_stripes) return;        // uniform over the workgroup: a larger tensor's
-    const int stripe = (int)blockIdx.y;
-    const uint32_t item = d.p_item_begin + blockIdx.y * (uint32_t)d.p_n_rb + blockIdx.x;
+    uint32_t kind = r.sp_short;
+    asm volatile("" : "+s"(d.n_tokens), "+s"(d.n_channels), "+s"(d.n_chunks), "+s"(d.dtype), "+s"(d.bits), "+s"(d.p_partial_off), "+s"(d.p_rows), "+s"(d.p_n_rb),
+                      "+s"(d.p_n_stripes), "+s"(d.p_item_begin), "+s"(p.x), "+s"(p.recon), "+s"(p.err), "+s"(p.codes), "+s"(p.scales), "+s"(states), "+s"(kind));      // one wait for all of them
+    int stripe = (int)blockIdx.y, in_order = (int)blockIdx.x;
+    uint32_t group_begin = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x;           // the group's first workgroup
+    if (__builtin_expect(kind == 2u, 0)) {          // out of the way: the code of the others comes from memory too
+        const uint32_t first_item = args.descs[0].p_item_begin, item = first_item + blockIdx.x;
+        uint32_t t = 0;
+#pragma unroll
+        for (int q = 1; q < kDirectTensors; ++q) t += item >= args.descs[q].p_item_begin ? 1u : 0u;
+        load(t);
+        const uint32_t local = item - d.p_item_begin;               // group-major: stripe, then row block
+        stripe = (int)(local / (uint32_t)d.p_n_rb);
+        in_order = (int)(local % (uint32_t)d.p_n_rb);
+        group_begin = blockIdx.x - (uint32_t)in_order;
+    } else if (in_order >= d.p_n_rb || stripe >= d.p_n_stripes) {
+        return;                     // uniform over the workgroup: a larger tensor's
+    }
+    const uint32_t item = d.p_item_begin + (uint32_t)stripe * (uint32_t)d.p_n_rb + (uint32_t)in_order;
     const uint32_t state = scalar_load<uint32_t>((uint64_t)states + (item & ~3u));      // four items' bytes
     // turned as in k_single_pass
-    const int turned = (int)(blockIdx.x + (((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x) & 7u));
-    const int mine = d.p_n_rb < 8 ? (int)blockIdx.x : turned >= d.p_n_rb ? turned - d.p_n_rb : turned;
+    const int turned = in_order + (int)(group_begin & 7u);
+    const int mine = d.p_n_rb < 8 ? in_order : turned >= d.p_n_rb ? turned - d.p_n_rb : turned;
     const uint32_t sign = ~(state << (24u - 8u * (item & 3u))) & kPartialSign;     // nobody else writes the byte, and this workgroup at the very end
     uint32_t gave_up = 0u;          // how often
     int at = -1;                    // the item of the group that this workgroup helps; -1: it does its own
@@ -570,15 +591,18 @@ hipError_t launch_short_items(const BatchView &v, const LaunchRange &r, int err_
     a.r = r;
     std::memset(static_cast<void *>(a.sets), 0, sizeof a.sets);
     std::memset(static_cast<void *>(a.descs), 0, sizeof a.descs);
-    dim3 grid(0, 0, (unsigned)r.count);
-    for (int k = 0; k < r.count; ++k) {
-        a.sets[k] = r.direct[k];
-        a.descs[k] = r.direct_descs[k];
-        grid.x = a.descs[k].p_n_rb > (int)grid.x ? (unsigned)a.descs[k].p_n_rb : grid.x;
-        grid.y = a.descs[k].p_n_stripes > (int)grid.y ? (unsigned)a.descs[k].p_n_stripes : grid.y;
+    for (int k = 0; k < kDirectTensors; ++k) {
+        if (k < r.count) {
+            a.sets[k] = r.direct[k];
+            a.descs[k] = r.direct_descs[k];
+        } else {
+            a.descs[k].p_item_begin = ~0u;      // behind every item
+        }
     }
+    const ShortGrid grid = short_grid(r.direct_descs, r.count);
+    a.r.sp_short = grid.flat ? 2u : 1u;
     void *args[] = {&a};
-    return hipLaunchKernel(pick_short(err_dtype, fused, r.sp_blocks != 0), grid, dim3(kPersistThreads), args, 0, s);
+    return hipLaunchKernel(pick_short(err_dtype, fused, r.sp_blocks != 0), dim3(grid.x, grid.y, grid.z), dim3(kPersistThreads), args, 0, s);
 }
 
 }  // namespace

@@ -12,6 +12,7 @@
 
 extern std::vector<std::string> g_launch_log;
 extern bool g_single_pass_short, g_single_pass_wide, g_single_pass_blocks;
+extern int g_short_workgroups;
 extern bool g_capturing;
 extern int g_compute_units;
 extern bool g_overlapping;
@@ -465,6 +466,9 @@ int main()
             {CF_EF_OFF, B, 0, {{1, 256, 64}}, false}, {CF_EF_NAIVE, B, 0, {{1, 256, 64}}, false},
             {R, B, 0, {{1, 256, 64}, {1, 9000, 64}, {1, 300, 64}}, false},
             {R, B, 0, {{64, 64, 256}}, false}, {R, B, 0, {{65, 64, 256}}, false},      // 64 take their pointers along
+            // tensors of several shapes: no more than 64 workgroups without an item, whatever the largest numbers of row blocks and stripes are
+            {R, B, 0, {{7, 8192, 64}, {1, 64, 4096}}, true}, {R, B, 0, {{1, 8192, 64}, {1, 8, 61440}}, true}, {R, B, 0, {{1, 8192, 64}, {1, 128, 3072}}, true},
+            {R, B, 0, {{1, 2048, 512}, {1, 1024, 512}}, true}, {R, B, 0, {{1, 2048, 512}, {1, 896, 512}}, true}, {R, B, 0, {{1, 1024, 3072}, {2, 256, 2048}}, true}, {R, F, 0, {{3, 1, 8}, {1, 4096, 64}, {1, 70, 2048}, {1, 65, 64}}, true},
             {R, B, 0, {{1, 8192, 128}}, true, 32}, {R, B, 0, {{1, 8192, 136}}, false, 32}, {R, B, 0, {{1, 8192, 136}}, true, 64},     // a smaller device: 128 items
         };
         for (const Call &c : calls) {
@@ -491,7 +495,18 @@ int main()
                 EXPECT(cf_step_fused(ctx, first, n - first, (const void *const *)bufs[0].data() + first, bufs[1].data() + first, bufs[2].data() + first,
                                      bufs[3].data() + first, bufs[4].data() + first, nullptr) == CF_OK);
                 const std::string seq = joined();
-                EXPECT(seq.find("wrong items") == std::string::npos);
+                EXPECT(seq.find("wrong items") == std::string::npos && seq.find("wrong grid") == std::string::npos);
+                if (g_single_pass_short) {
+                    int items = 0;
+                    for (int t = first; t < n; ++t) {
+                        const int rows = d[(size_t)t].dtype == F ? 64 : 128;
+                        items += (int)((d[(size_t)t].n_tokens + rows - 1) / rows * ((d[(size_t)t].n_channels + 63) / 64));
+                    }
+                    if (g_short_workgroups < items || g_short_workgroups > items + 64) {
+                        std::printf("%d tensors from [%d, %d] on: %d workgroups for %d short items\n", n - first, (int)d[(size_t)first].n_tokens, (int)d[(size_t)first].n_channels, g_short_workgroups, items);
+                        ++g_failed;
+                    }
+                }
                 EXPECT(seq.find("k_single_pass") != std::string::npos && uploaded(seq) == (n - first > 64));
                 if (first > 0 && !c.is_short) continue;
                 if (g_single_pass_short != c.is_short) {

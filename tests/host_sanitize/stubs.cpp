@@ -16,6 +16,7 @@ bool g_capturing = false;
 int g_compute_units = 256;
 bool g_single_pass_slim = false;        // the stripe width of the last single pass
 bool g_single_pass_short = false;       // and its items' height
+int g_short_workgroups = 0;             // that a call of them launches
 bool g_single_pass_wide = false;
 bool g_single_pass_blocks = false;      // whether it left parts of 64-byte blocks to the L2
 bool g_occupancy_slim = false;          // and the one whose co-resident workgroups were asked for last
@@ -103,6 +104,11 @@ hipError_t launch_single_pass(const BatchView &v, const LaunchRange &r, int, int
     g_single_pass_short = r.sp_short != 0;
     g_states.assign(v.item_state + r.item_lo, v.item_state + r.item_hi);
     for (uint32_t i = r.item_lo; i < r.item_hi; i += g_overlapping ? 2 : 1) v.item_state[i] ^= 0x80u;      // as the kernel's items do, all of them or not
+    if (r.sp_short) {
+        const ShortGrid grid = short_grid(r.direct_descs, r.count);
+        g_short_workgroups = (int)(grid.x * grid.y * grid.z);
+        if (grid.flat ? grid.x != r.item_hi - r.item_lo || grid.y != 1 || grid.z != 1 : grid.z != (uint32_t)r.count) note("wrong grid");
+    }
     if (r.sp_short)     // the call's tensors one after another, and nothing else
         for (int k = 0; k < r.count; ++k) {
             const uint32_t items = (uint32_t)(r.direct_descs[k].p_n_rb * r.direct_descs[k].p_n_stripes);

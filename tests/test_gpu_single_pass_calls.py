@@ -70,6 +70,38 @@ def test_short_items(dtype, err_dtype, flags):
         run_parity(descs, cf.options(err_dtype=err_dtype, flags=flags), xs, mode=mode)
 
 
+@pytest.mark.parametrize("dtype", [cf.CF_BF16, cf.CF_F32])
+@pytest.mark.parametrize("flags", [0, cf.CF_FLAG_TEST_NO_WAIT])
+@pytest.mark.parametrize("shapes", [[(64, 1), (1, 2816)],                                               # row blocks of one item, 64-channel stripes: 64 x 1 and 1 x 44
+                                    [(1, 1), (9, 320), (0.1, 2048), (64, 64), (3, 136), (12, 200)],     # a chunk of the largest alone, groups of 1 to 64
+                                    [(16, 512), (8, 512)], [(16, 512), (7, 512)]])                      # 64 and 72 workgroups that would have no item: both sides of the line
+def test_short_items_of_unlike_tensors(shapes, dtype, flags):
+    """Calls whose tensors have few row blocks or stripes in common, one workgroup per item, and ones with a workgroup for each of the most; a
+    part of the context's tensors too; every code width, bits against the oracle."""
+    rows = 64 if dtype == cf.CF_F32 else 128
+    descs = [cf.desc(max(1, int(n * rows)), max(8, c // 8 * 8), dtype, (1, 2, 4)[t % 3], cf.CF_SCALE_CHANNEL) for t, (n, c) in enumerate([(2, 64)] + shapes)]
+    streams = [drift_stream((d.n_tokens, d.n_channels), d.dtype, steps=4, seed=1020 + t, device=DEV) for t, d in enumerate(descs)]
+    xs = [[streams[t][s] for t in range(len(descs))] for s in range(4)]
+    say(f"short items of unlike tensors dtype={dtype} flags={flags}: {[(d.n_tokens, d.n_channels) for d in descs]}")
+    run_parity(descs[1:], cf.options(flags=flags), [x[1:] for x in xs], mode="fused")
+    run_parity(descs[1:], cf.options(flags=flags, err_dtype=cf.CF_BF16), [x[1:] for x in xs], mode="split")
+    part, whole = (CodecSession(descs, cf.options(flags=flags), device=DEV) for _ in range(2))
+    try:
+        for sess in (part, whole):
+            sess.warmup(xs[0])
+        for x in xs[1:]:
+            part.step_fused(x[:1], 0, 1)
+            part.step_fused(x[1:], 1, len(descs) - 1)
+            whole.step_fused(x)
+        torch.cuda.synchronize()
+        for t in range(len(descs)):
+            for name in ("codes", "scales", "recon", "err"):
+                assert torch.equal(getattr(part, name)[t], getattr(whole, name)[t]), f"{name}[{t}]"
+    finally:
+        part.close()
+        whole.close()
+
+
 @pytest.mark.parametrize("err_dtype", [cf.CF_F32, cf.CF_BF16])
 @pytest.mark.parametrize("flags", [0, cf.CF_FLAG_TEST_NO_WAIT])
 @pytest.mark.parametrize("tokens, widths", [(1153, (328, 264, 1096)),       # 256 channels, 10 items a group: none begins where the one before did
