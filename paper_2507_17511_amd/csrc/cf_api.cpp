@@ -1023,7 +1023,7 @@ cf_status run_sender(cf_ctx *ctx, int32_t first, int32_t count, const void *cons
             if (e != hipSuccess) return device_fail(ctx, e);
         }
         ctx->note_single_pass(s);
-        e = launch(ctx, s, "k_single_pass", [&] { return launch_single_pass(v, r, ef, et, fused, ctx->L.sp_wide, grid, one_shot, s); });
+        e = launch(ctx, s, r.sp_short ? "k_short_items" : "k_single_pass", [&] { return launch_single_pass(v, r, ef, et, fused, ctx->L.sp_wide, grid, one_shot, s); });
         if (e != hipSuccess) return device_fail(ctx, e);
         r.only_group_scale = 1;
         if ((e = run_row_local(ctx, first, count, v, r, fused, false, s)) != hipSuccess) return device_fail(ctx, e);

@@ -495,6 +495,15 @@ int main()
                 EXPECT(cf_step_fused(ctx, first, n - first, (const void *const *)bufs[0].data() + first, bufs[1].data() + first, bufs[2].data() + first,
                                      bufs[3].data() + first, bufs[4].data() + first, nullptr) == CF_OK);
                 const std::string seq = joined();
+                {
+                    void *events[2] = {(void *)0x10, (void *)0x20};
+                    EXPECT(cf_profile_next_call(ctx, events, 1) == CF_OK);
+                    EXPECT(cf_step_fused(ctx, first, n - first, (const void *const *)bufs[0].data() + first, bufs[1].data() + first, bufs[2].data() + first,
+                                         bufs[3].data() + first, bufs[4].data() + first, nullptr) == CF_OK);
+                    joined();
+                    const char *name = cf_profile_kernel_name(ctx, cf_profile_launch_count(ctx) - 1);
+                    EXPECT(name && std::strcmp(name, g_single_pass_short ? "k_short_items" : "k_single_pass") == 0);
+                }
                 EXPECT(seq.find("wrong items") == std::string::npos && seq.find("wrong grid") == std::string::npos);
                 if (g_single_pass_short) {
                     int items = 0;
