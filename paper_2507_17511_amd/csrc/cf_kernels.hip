@@ -267,43 +267,52 @@ __global__ __launch_bounds__(kTileThreads) void k_colreduce(BatchView v, LaunchR
 // 1920] and 130 of the 150 us of a call over [16384, 512], whose 8-row tiles leave 2048 partials
 // (42 us now).  Columns of up to 32 partials stay with one lane each (114 x [103, 368] is 35.4 us a step that way, 38.1
 // split), and so do those of contexts with columns enough to fill the device (see fin_columns).
+__device__ __forceinline__ float column_share(const BatchView &v, const TensorDev &d, int col, int mine, int parts)
+{
+    const auto tree = [&](int first, int n) {
+        const CF_GLOBAL float *partial = gconst<float>(v.workspace + d.partial_off) + (int64_t)first * d.n_channels + col;
+        return d.bits == 4 ? tree_over<true, 18>(n, [&](int i) { return partial[(int64_t)i * d.n_channels]; })
+                           : tree_over<false, 18>(n, [&](int i) { return partial[(int64_t)i * d.n_channels]; });
+    };
+    if (col >= d.n_channels) return 0.0f;
+    if (parts == 1) return tree(0, d.n_rowblocks);          // uniform, and so is the count: scalar branches in the tree (13.4 -> 11.6 us for 16 x [4096, 3072])
+    int per = 1;                                            // leaves per lane: the padded count / parts, at least one
+    while (per * parts < d.n_rowblocks) per <<= 1;
+    const int first = mine * per;
+    return tree(first, first >= d.n_rowblocks ? 0 : d.n_rowblocks - first < per ? d.n_rowblocks - first : per);
+}
+
+// The shares of a column's lanes, every columns-th one's; `rounds` is the same for the whole workgroup and no less than the parts.
+__device__ __forceinline__ float column_meet(float *part, float w, const TensorDev &d, int mine, int columns, int parts, int rounds)
+{
+    for (int k = 1; k < rounds; k <<= 1) {
+        part[threadIdx.x] = w;
+        __syncthreads();
+        if (k < parts && (mine & (2 * k - 1)) == 0) {
+            const float other = part[threadIdx.x + k * columns];
+            w = d.bits == 4 ? fmaxf(w, other) : w + other;
+        }
+        __syncthreads();
+    }
+    return w;
+}
+
+__device__ __forceinline__ void column_scale(const BatchView &v, const TensorDev &d, int t, int col, float w)
+{
+    gmut<float>(v.ptrs[t].scales)[col] = d.bits == 4 ? w / 7.0f : w / (float)d.n_tokens;
+}
+
 __global__ __launch_bounds__(kFinalizeThreads) void k_finalize(BatchView v, LaunchRange r)
 {
     __shared__ float part[kFinalizeThreads];
     uint32_t blk = r.fin_lo + blockIdx.x;
     int t = find_slot(v.fin_prefix, r.first, r.first + r.count, blk);
     const TensorDev d = v.descs[t];
-    if (d.scale != SCALE_CHANNEL && d.scale != SCALE_RANK1) return;
+    if (d.scale != SCALE_CHANNEL) return;
     const int columns = d.fin_columns, parts = kFinalizeThreads / columns;      // powers of two
-    const int lane_col = (int)threadIdx.x & (columns - 1), mine = (int)threadIdx.x / columns;
-    const int col = (int)(blk - d.fin_begin) * columns + lane_col;
-    const bool cvalid = col < d.n_channels;
-    const int64_t C = d.n_channels;
-    if (parts == 1) {                                       // uniform, and so is the count: scalar branches in the tree (13.4 -> 11.6 us
-        if (!cvalid) return;                                // for 16 x [4096, 3072])
-        const CF_GLOBAL float *partial = gconst<float>(v.workspace + d.partial_off) + col;
-        const float s = d.bits == 4 ? tree_over<true, 18>(d.n_rowblocks, [&](int i) { return partial[(int64_t)i * C]; }) / 7.0f
-                                    : tree_over<false, 18>(d.n_rowblocks, [&](int i) { return partial[(int64_t)i * C]; }) / (float)d.n_tokens;
-        gmut<float>(v.ptrs[t].scales)[col] = s;
-        return;
-    }
-    int per = 1;                                            // leaves per lane: the padded count / parts, at least one
-    while (per * parts < d.n_rowblocks) per <<= 1;
-    const int first = mine * per;
-    const int n = !cvalid || first >= d.n_rowblocks ? 0 : d.n_rowblocks - first < per ? d.n_rowblocks - first : per;
-    const CF_GLOBAL float *partial = gconst<float>(v.workspace + d.partial_off) + (int64_t)first * C + (cvalid ? col : 0);
-    float w = d.bits == 4 ? tree_over<true, 18>(n, [&](int i) { return partial[(int64_t)i * C]; })
-                          : tree_over<false, 18>(n, [&](int i) { return partial[(int64_t)i * C]; });
-    for (int k = 1; k < parts; k <<= 1) {                   // uniform over the workgroup
-        part[threadIdx.x] = w;
-        __syncthreads();
-        if ((mine & (2 * k - 1)) == 0) {
-            const float other = part[threadIdx.x + k * columns];
-            w = d.bits == 4 ? fmaxf(w, other) : w + other;
-        }
-        __syncthreads();
-    }
-    if (mine == 0 && cvalid) gmut<float>(v.ptrs[t].scales)[col] = d.bits == 4 ? w / 7.0f : w / (float)d.n_tokens;
+    const int mine = (int)threadIdx.x / columns, col = (int)(blk - d.fin_begin) * columns + ((int)threadIdx.x & (columns - 1));
+    const float w = column_meet(part, column_share(v, d, col, mine, parts), d, mine, columns, parts, parts);
+    if (mine == 0 && col < d.n_channels) column_scale(v, d, t, col, w);
 }
 
 // Rank-1 scales (App. D "Quantization"): u_i = (rowsum_i / C) / (sum_i rowsum_i / (N C)), written
@@ -312,7 +321,7 @@ __global__ __launch_bounds__(kFinalizeThreads) void k_finalize(BatchView v, Laun
 // tree over the rows (in the lane, across the wave, then over the waves in LDS).
 // The workgroups past the tensors' do k_finalize's work, a block of it in every 256 lanes (columns do not wait for rows, nor rows for columns): a launch less.
 // Latency is all it costs, so a lane's rows are asked for together and stay in registers.  Steps in two launches with the rows by way of u / now, us: 2 x [4225, 312]
-// 31.8 / 23.0, 2 x [1108, 96] 22 / 18, [17000, 1024] 109 / 96, 30 x [1000, 1000] 92.6 / 86.9, 57 x [4096, 3072] 1723 / 1713, but 57 x [1000, 1000] 157 / 159.
+// 31.8 / 23.0, 2 x [1108, 96] 22 / 18, [17000, 1024] 109 / 96, 30 x [1000, 1000] 92.6 / 86.9, 57 x [4096, 3072] 1746 / 1737, 57 x [1000, 1000] 161 / 160.
 constexpr int kRank1Rows = 16, kRank1Parts = 4;
 __global__ __launch_bounds__(kRank1Threads) void k_finalize_rank1(BatchView v, LaunchRange r)
 {
@@ -321,38 +330,14 @@ __global__ __launch_bounds__(kRank1Threads) void k_finalize_rank1(BatchView v, L
         constexpr int kMostParts = kFinalizeThreads / kFinalizeColumns;
         const int group = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kFinalizeThreads), lane = (int)threadIdx.x % kFinalizeThreads;
         const uint32_t blk = r.fin_lo + (blockIdx.x - (uint32_t)r.count) * (kRank1Threads / kFinalizeThreads) + (uint32_t)group;
-        float w = 0.0f, n_tokens = 1.0f, *out = nullptr;
-        int columns = kFinalizeThreads, parts = 1, mine = 0;
-        bool is_max = false;
-        if (blk < r.fin_hi) {               // uniform over the group; a column's lanes do what k_finalize's do
-            const int t = find_slot(v.fin_prefix, r.first, r.first + r.count, blk);
-            const TensorDev d = v.descs[t];
-            columns = d.fin_columns;
-            parts = kFinalizeThreads / columns;
-            mine = lane / columns;
-            is_max = d.bits == 4;
-            const int col = (int)(blk - d.fin_begin) * columns + (lane & (columns - 1));
-            if (col < d.n_channels && (d.scale == SCALE_CHANNEL || d.scale == SCALE_RANK1)) {
-                int per = 1;
-                while (per * parts < d.n_rowblocks) per <<= 1;
-                const int first = mine * per, n = first >= d.n_rowblocks ? 0 : d.n_rowblocks - first < per ? d.n_rowblocks - first : per;
-                const CF_GLOBAL float *partial = gconst<float>(v.workspace + d.partial_off) + (int64_t)first * d.n_channels + col;
-                w = is_max ? tree_over<true, 18>(n, [&](int i) { return partial[(int64_t)i * d.n_channels]; })
-                           : tree_over<false, 18>(n, [&](int i) { return partial[(int64_t)i * d.n_channels]; });
-                if (mine == 0) out = v.ptrs[t].scales + col;
-            }
-            n_tokens = (float)d.n_tokens;
-        }
-        for (int k = 1; k < kMostParts; k <<= 1) {          // the same for all groups, whatever their parts
-            part[threadIdx.x] = w;
-            __syncthreads();
-            if (k < parts && (mine & (2 * k - 1)) == 0) {
-                const float other = part[threadIdx.x + k * columns];
-                w = is_max ? fmaxf(w, other) : w + other;
-            }
-            __syncthreads();
-        }
-        if (out) *gmut<float>(out) = is_max ? w / 7.0f : w / n_tokens;
+        const bool any = blk < r.fin_hi;            // uniform over the group
+        const int t = any ? find_slot(v.fin_prefix, r.first, r.first + r.count, blk) : r.first;
+        const TensorDev d = v.descs[t];
+        const bool reduced = any && (d.scale == SCALE_CHANNEL || d.scale == SCALE_RANK1);
+        const int columns = d.fin_columns, parts = kFinalizeThreads / columns;
+        const int mine = lane / columns, col = reduced ? (int)(blk - d.fin_begin) * columns + (lane & (columns - 1)) : d.n_channels;
+        const float w = column_meet(part, column_share(v, d, col, mine, parts), d, mine, columns, parts, kMostParts);
+        if (mine == 0 && col < d.n_channels) column_scale(v, d, t, col, w);
         return;
     }
     const int t = r.first + (int)blockIdx.x;

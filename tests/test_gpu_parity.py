@@ -139,16 +139,31 @@ def test_single_pass_stripe_width_rule_boundaries():
             run_parity(descs, cf.options(flags=cf.CF_FLAG_SINGLE_PASS), xs, mode=mode)
 
 
+@pytest.mark.parametrize("rank1", [False, True])
 @pytest.mark.parametrize("n", [1, 8, 9, 120, 128, 129, 136, 255, 256, 257, 264, 512, 513, 520, 2048, 2049, 4104])
-def test_finalise_splits_the_tree_of_a_column(n):
+def test_finalise_splits_the_tree_of_a_column(n, rank1):
     """The second level of the two-kernel reduction over 8-row partials: a lane per column up to 32 partials (256 tokens),
     aligned sixteenths of a column for a lane from 33 on (lanes with partly filled and empty ranges), full and one more,
-    a batch of 16 per lane and one more, and widths around its 16 columns."""
-    say(f"finalise N={n}")
-    descs = [cf.desc(n, c, cf.CF_BF16, b, s) for c, b, s in ((8, 1, CH), (16, 2, CH), (24, 4, CH), (136, 2, cf.CF_SCALE_RANK1))]
+    a batch of 16 per lane and one more, and widths around its 16 columns; in a kernel of its own, and in the one that finishes
+    rank-1 scales where the call has such."""
+    say(f"finalise N={n} rank1={rank1}")
+    descs = [cf.desc(n, c, cf.CF_BF16, b, s) for c, b, s in ((8, 1, CH), (16, 2, CH), (24, 4, CH), (136, 2, cf.CF_SCALE_RANK1 if rank1 else CH))]
     streams = [drift_stream((d.n_tokens, d.n_channels), d.dtype, steps=3, seed=870 + t, device=DEV) for t, d in enumerate(descs)]
     xs = [[streams[t][s] for t in range(len(descs))] for s in range(3)]
     run_parity(descs, cf.options(flags=cf.CF_FLAG_TWO_KERNEL, tile_rows=8), xs, mode="fused")
+
+
+@pytest.mark.parametrize("shapes", [[(16384, 40), (16385, 24), (20000, 8)],             # 16 rows a lane, and more than it has registers for
+                                    [(1, 4096), (1025, 4096), (1, 4104), (1025, 4104), (3, 8200)],      # four column tiles and more
+                                    [(8193, 3080), (1024, 1024), (2049, 2056)]])                        # 16 rows of four tiles each
+def test_finalise_rank1_rows(shapes):
+    """Rank-1 scales whose rows stay in a lane's registers between the two passes over them (up to 16 a lane of 1024, up to four tiles of
+    1024 channels), at the last such shapes and at the first beyond, next to channel scales; bits against the oracle."""
+    say(f"rank-1 rows {shapes}")
+    descs = [cf.desc(n, c, cf.CF_BF16, 1 + t % 2, cf.CF_SCALE_RANK1) for t, (n, c) in enumerate(shapes)] + [cf.desc(700, 136, cf.CF_BF16, 4, CH)]
+    streams = [drift_stream((d.n_tokens, d.n_channels), d.dtype, steps=3, seed=890 + t, device=DEV) for t, d in enumerate(descs)]
+    xs = [[streams[t][s] for t in range(len(descs))] for s in range(3)]
+    run_parity(descs, cf.options(), xs, mode="fused")
 
 
 @pytest.mark.parametrize("dtype", [cf.CF_BF16, cf.CF_F32])
