@@ -396,7 +396,8 @@ int main()
     {
         enum Path { TWO, WIDE, NARROW, SLIM, SHORT };
         enum Stores { WHOLE, BLOCKS };                  // whether parts of blocks are left to the L2
-        struct Call { std::vector<std::vector<int64_t>> shapes; Path step, send; Stores stores; int first = 0, count = 0; };       // count 0: the whole context
+        struct Call { std::vector<std::vector<int64_t>> shapes; Path step, send; Stores stores; int first = 0, count = 0; uint32_t flags = 0; };       // count 0: the whole context
+        const uint32_t FORCED = CF_FLAG_SINGLE_PASS;
         const std::vector<Call> calls = {
             // 48 and 49 items of 256 rows, 64 and 65: 128-channel stripes up to there; two kernels for steps of more than 1280 items alone
             {{{2, 12288, 1096}}, NARROW, NARROW, BLOCKS}, {{{2, 12289, 1096}}, NARROW, NARROW, BLOCKS}, {{{10, 12289, 1096}}, TWO, NARROW, BLOCKS},
@@ -418,6 +419,23 @@ int main()
             // short items: parts of blocks from 448 items on
             {{{30, 1024, 1096}, {9, 1024, 1088}}, SHORT, SHORT, BLOCKS, 0, 6}, {{{30, 1024, 1096}, {9, 1024, 1088}}, SHORT, SHORT, WHOLE, 0, 3},
             {{{30, 1024, 1096}, {9, 1024, 1088}}, SHORT, SHORT, WHOLE, 30, 6}, {{{30, 1024, 1104}}, SHORT, SHORT, BLOCKS, 0, 6},
+            // the kernels that the GPU tests of the single pass are for: a rule that changes must not take a test to another one unnoticed (tokens x channels; a fourth number: fp32)
+            {{{1, 10241, 64}, {1, 10241, 160}, {1, 512, 120}, {1, 513, 136}, {1, 1, 64}, {1, 255, 56}}, SLIM, SLIM, WHOLE, 0, 0, FORCED},
+            {{{5, 3072, 288}, {5, 1000, 1120}}, WIDE, WIDE, WHOLE, 0, 0, FORCED}, {{{5, 3073, 288}, {5, 1000, 1120}}, NARROW, NARROW, WHOLE, 0, 0, FORCED},
+            {{{5, 4096, 288}, {5, 4000, 160}}, NARROW, NARROW, WHOLE, 0, 0, FORCED}, {{{5, 4608, 264}, {5, 1000, 1096}}, WIDE, WIDE, BLOCKS, 0, 0, FORCED},
+            {{{5, 4609, 264}, {5, 1000, 1096}}, NARROW, NARROW, BLOCKS, 0, 0, FORCED},
+            {{{6, 1500, 1096}, {3, 700, 520, CF_F32}}, WIDE, WIDE, BLOCKS, 0, 0, FORCED}, {{{6, 1500, 1120}, {3, 700, 544, CF_F32}}, WIDE, WIDE, WHOLE, 0, 0, FORCED},
+            {{{4, 1500, 1096}, {2, 700, 520, CF_F32}}, WIDE, WIDE, BLOCKS, 0, 0, FORCED}, {{{4, 1500, 1120}, {2, 700, 544, CF_F32}}, WIDE, WIDE, WHOLE, 0, 0, FORCED},
+            {{{3, 1500, 1096}, {3, 700, 520, CF_F32}, {1, 130, 72}, {1, 1, 8, CF_F32}}, SHORT, SHORT, BLOCKS, 0, 0, FORCED},
+            {{{3, 1500, 1120}, {3, 700, 544, CF_F32}, {1, 130, 96}, {1, 1, 8, CF_F32}, {2, 300, 96}}, WIDE, WIDE, WHOLE, 0, 0, FORCED},
+            {{{6, 40000, 72}}, NARROW, NARROW, BLOCKS, 0, 0, FORCED}, {{{6, 40000, 80}}, NARROW, NARROW, WHOLE, 0, 0, FORCED}, {{{6, 40000, 96}}, SLIM, SLIM, WHOLE, 0, 0, FORCED},
+            {{{3, 1151, 328}, {3, 1151, 264}, {3, 1151, 1096}}, WIDE, WIDE, BLOCKS, 0, 0, FORCED}, {{{3, 1022, 1104}, {3, 1022, 336}, {3, 1024, 16}}, WIDE, WIDE, BLOCKS, 0, 0, FORCED},
+            {{{3, 4700, 104}, {3, 4699, 136}, {3, 4698, 72}}, NARROW, NARROW, BLOCKS, 0, 0, FORCED}, {{{1, 12291, 136}, {1, 12290, 200}}, NARROW, NARROW, BLOCKS, 0, 0, FORCED},
+            {{{1, 16387, 136}, {1, 16386, 200}}, SLIM, SLIM, BLOCKS, 0, 0, FORCED}, {{{1, 4097, 488}, {1, 4096, 520}}, SHORT, SHORT, BLOCKS, 0, 0, FORCED},
+            {{{1, 4097, 496}, {1, 4096, 528}}, SHORT, SHORT, BLOCKS, 0, 0, FORCED}, {{{1, 8192, 64}, {1, 4096, 512}, {1, 1000, 136}}, SHORT, SHORT, WHOLE, 0, 0, FORCED},
+            {{{1, 4097, 488}, {1, 4097, 520}}, SHORT, SHORT, BLOCKS, 0, 0, FORCED}, {{{1, 9000, 136}, {1, 4096, 512}}, NARROW, NARROW, WHOLE, 0, 0, FORCED},
+            {{{1, 9000, 136}, {1, 6000, 264}}, NARROW, NARROW, BLOCKS, 0, 0, FORCED}, {{{1, 12500, 224}, {1, 20000, 96}}, SLIM, SLIM, WHOLE, 0, 0, FORCED},
+            {{{1, 12500, 200}, {1, 20000, 72}}, SLIM, SLIM, BLOCKS, 0, 0, FORCED}, {{{9, 2000, 1056}}, WIDE, WIDE, WHOLE, 0, 0, FORCED}, {{{9, 2000, 1032}}, WIDE, WIDE, BLOCKS, 0, 0, FORCED},
         };
         for (size_t k = 0; k < calls.size(); ++k) {
             const Call &c = calls[k];
@@ -425,6 +443,7 @@ int main()
             for (auto &s : c.shapes) d.insert(d.end(), (size_t)s[0], desc(s[1], s[2], s.size() > 3 ? (int)s[3] : CF_BF16, 2, CF_SCALE_CHANNEL));
             const int n = (int)d.size(), first = c.first, count = c.count ? c.count : n - first;
             std::memset(&o, 0, sizeof o);
+            o.flags = c.flags;
             std::vector<void *> bufs[5];
             uintptr_t at = (uintptr_t)1 << 40;
             for (auto &b : bufs)

@@ -107,12 +107,13 @@ def test_parity_batched_mixed_launch(mode, flags):
     run_parity(descs, cf.options(flags=flags), xs, mode=mode)
 
 
-def test_single_pass_many_row_blocks_and_stripes():
-    """Reduction groups of several items (N = 1500: 6 row blocks of 256, ragged) over 9 stripes (C = 1096),
-    several tensors deep, so that workgroups take more than one item each."""
-    say("single pass, deep")
-    descs = [cf.desc(1500, 1096, cf.CF_BF16, (1, 2, 4)[t % 3], CH) for t in range(6)]
-    descs += [cf.desc(700, 520, cf.CF_F32, (2, 4, 1)[t % 3], CH) for t in range(3)]
+@pytest.mark.parametrize("widths", [(1096, 520), (1120, 544)])
+def test_single_pass_many_row_blocks_and_stripes(widths):
+    """Reduction groups of several items (N = 1500: 12 row blocks of 128, ragged) over 5 stripes of 256 channels, the last one ragged
+    (C = 1096, whose rows are no whole blocks of 64 bytes, and 1120), several tensors deep."""
+    say(f"single pass, deep, {widths}")
+    descs = [cf.desc(1500, widths[0], cf.CF_BF16, (1, 2, 4)[t % 3], CH) for t in range(6)]
+    descs += [cf.desc(700, widths[1], cf.CF_F32, (2, 4, 1)[t % 3], CH) for t in range(3)]
     streams = [drift_stream((d.n_tokens, d.n_channels), d.dtype, steps=3, seed=70 + k, device=DEV)
                for k, d in enumerate(descs)]
     xs = [[streams[t][s] for t in range(len(descs))] for s in range(3)]
@@ -123,16 +124,17 @@ def test_single_pass_many_row_blocks_and_stripes():
 
 def test_single_pass_stripe_width_rule_boundaries():
     """The single-pass kernel takes 256-channel stripes for contexts whose tallest channel-scale tensor makes at most
-    12 items per group with 128-channel ones (bf16: N <= 3072), 128-channel stripes otherwise: contexts on both sides
-    of the boundary (N = 3072 / 3328) and at N = 4096 with and without a 1-bit tensor, ragged in both directions,
-    against the oracle."""
-    cases = [[(3072, 264, 1), (1000, 1096, 2)],                 # wide, groups of 24 and 8 items
-             [(3328, 264, 1), (1000, 1096, 2)],                 # narrow, groups of 13 and 4
-             [(4096, 264, 4), (4000, 136, 2)],                  # narrow, groups of 16
-             [(4096, 264, 4), (4000, 136, 1)]]                  # narrow, groups of 16
+    12 items per group with 128-channel ones (bf16: N <= 3072), 18 where the rows are no whole blocks of 64 bytes (N <= 4608), 128-channel
+    stripes otherwise: contexts on both sides of the boundaries, of more tensors than short items serve, ragged in both directions, against the oracle."""
+    cases = [[(3072, 288, 1), (1000, 1120, 2)],                 # wide, groups of 24 and 8 items
+             [(3073, 288, 1), (1000, 1120, 2)],                 # narrow, groups of 13 and 4
+             [(4096, 288, 4), (4000, 160, 2)],                  # narrow, groups of 16
+             [(4096, 288, 4), (4000, 160, 1)],                  # narrow, groups of 16
+             [(4608, 264, 1), (1000, 1096, 2)],                 # no whole blocks: wide, groups of 36 and 8
+             [(4609, 264, 1), (1000, 1096, 2)]]                 # narrow, groups of 19 and 4
     for k, shapes in enumerate(cases):
         say(f"stripe width boundary case {k}: {shapes}")
-        descs = [cf.desc(n, c, cf.CF_BF16, bits, CH) for n, c, bits in shapes]
+        descs = [cf.desc(n, c, cf.CF_BF16, bits, CH) for n, c, bits in shapes * 5]
         streams = [drift_stream((d.n_tokens, d.n_channels), d.dtype, steps=3, seed=270 + 10 * k + t, device=DEV) for t, d in enumerate(descs)]
         xs = [[streams[t][s] for t in range(len(descs))] for s in range(3)]
         for mode in ("fused", "split"):
@@ -190,9 +192,9 @@ def test_row_local_tiles_across_row_ends(dtype, err_dtype):
 def test_single_pass_slim_stripes(dtype, ef, err_dtype):
     """64-channel stripes of items twice as tall, which contexts whose tallest tensor makes more than 40 items per group
     with 128-channel ones take: the tallest just above that line, its neighbours short ones, widths around a stripe
-    (a chunk more or less than one or two stripes), every code width, bits against the oracle."""
+    (a chunk more or less than one or two stripes; most of it whole blocks of 64 bytes), every code width, bits against the oracle."""
     rows = (128 if dtype == cf.CF_F32 else 256) // (2 if ef == cf.CF_EF_OFF else 1)       # of a 128-channel item
-    shapes = [(40 * rows + 1, 64, 1), (40 * rows + 1, 136, 2), (2 * rows, 120, 4), (2 * rows + 1, 136, 1), (1, 64, 2), (rows - 1, 56, 4)]
+    shapes = [(40 * rows + 1, 64, 1), (40 * rows + 1, 160, 2), (2 * rows, 120, 4), (2 * rows + 1, 136, 1), (1, 64, 2), (rows - 1, 56, 4)]
     say(f"single pass, slim stripes dtype={dtype} ef={ef} err_dtype={err_dtype}: {shapes}")
     descs = [cf.desc(n, c, dtype, bits, CH) for n, c, bits in shapes]
     streams = [drift_stream((d.n_tokens, d.n_channels), d.dtype, steps=3, seed=670 + t, device=DEV) for t, d in enumerate(descs)]
@@ -202,11 +204,12 @@ def test_single_pass_slim_stripes(dtype, ef, err_dtype):
     run_parity(descs, cf.options(ef=ef, err_dtype=err_dtype, flags=cf.CF_FLAG_SINGLE_PASS), xs, mode="split")
 
 
-def test_single_pass_long_groups_and_fixed_grid():
-    """Groups of 157 items (N = 40000), as one workgroup per item and as a fixed grid of workgroups that loop
-    over the items (CF_FLAG_FIXED_GRID)."""
-    say("single pass, long groups")
-    descs = [cf.desc(40000, 72, cf.CF_BF16, (1, 2, 4)[t % 3], CH) for t in range(6)]
+@pytest.mark.parametrize("width", [72, 80, 96])
+def test_single_pass_long_groups_and_fixed_grid(width):
+    """Groups of 157 items (N = 40000; 79 of 64-channel stripes, which 96 channels take), as one workgroup per item and as a fixed grid of workgroups that loop
+    over the items (CF_FLAG_FIXED_GRID); parts of 64-byte blocks left to the L2 for 72 channels, not for 80."""
+    say(f"single pass, long groups of {width} channels")
+    descs = [cf.desc(40000, width, cf.CF_BF16, (1, 2, 4)[t % 3], CH) for t in range(6)]
     streams = [drift_stream((d.n_tokens, d.n_channels), d.dtype, steps=3, seed=170 + k, device=DEV)
                for k, d in enumerate(descs)]
     xs = [[streams[t][s] for t in range(len(descs))] for s in range(3)]
@@ -216,13 +219,14 @@ def test_single_pass_long_groups_and_fixed_grid():
 
 @pytest.mark.parametrize("ef", [cf.CF_EF_RECON, cf.CF_EF_LITERAL, cf.CF_EF_OFF, cf.CF_EF_NAIVE])
 @pytest.mark.parametrize("err_dtype", [cf.CF_F32, cf.CF_BF16])
-def test_single_pass_every_feedback_mode(ef, err_dtype):
+@pytest.mark.parametrize("widths, more", [((1096, 520, 72), 0), ((1120, 544, 96), 2)])      # eight tensors: short items in the default mode; ten
+def test_single_pass_every_feedback_mode(ef, err_dtype, widths, more):
     """The single-pass kernel in every error-feedback mode (items are 256 rows of bf16 without the error buffer as an
     operand, 128 with it, half of that for fp32), ragged in both directions, several row blocks and stripes deep,
     fused and split, also as a fixed grid."""
-    descs = [cf.desc(1500, 1096, cf.CF_BF16, (1, 2, 4)[t % 3], CH) for t in range(3)]
-    descs += [cf.desc(700, 520, cf.CF_F32, (2, 4, 1)[t % 3], CH) for t in range(3)]
-    descs += [cf.desc(130, 72, cf.CF_BF16, 2, CH), cf.desc(1, 8, cf.CF_F32, 1, CH)]
+    descs = [cf.desc(1500, widths[0], cf.CF_BF16, (1, 2, 4)[t % 3], CH) for t in range(3)]
+    descs += [cf.desc(700, widths[1], cf.CF_F32, (2, 4, 1)[t % 3], CH) for t in range(3)]
+    descs += [cf.desc(130, widths[2], cf.CF_BF16, 2, CH), cf.desc(1, 8, cf.CF_F32, 1, CH)] + [cf.desc(300, 96, cf.CF_BF16, 4, CH)] * more
     streams = [drift_stream((d.n_tokens, d.n_channels), d.dtype, steps=4, seed=370 + 10 * ef + k, device=DEV)
                for k, d in enumerate(descs)]
     xs = [[streams[t][s] for t in range(len(descs))] for s in range(4)]
@@ -235,11 +239,12 @@ def test_single_pass_every_feedback_mode(ef, err_dtype):
 
 
 @pytest.mark.parametrize("ef", [cf.CF_EF_RECON, cf.CF_EF_OFF])
-def test_single_pass_gives_up_and_redoes(ef):
+@pytest.mark.parametrize("widths", [(1096, 520), (1120, 544)])
+def test_single_pass_gives_up_and_redoes(ef, widths):
     """CF_FLAG_TEST_NO_WAIT: a workgroup that does not find every partial sum of its stripe at its first look gives
     its item up, computes what is missing and starts again.  Same bits as ever, and the give-up path did run."""
-    descs = [cf.desc(1500, 1096, cf.CF_BF16, (1, 2, 4)[t % 3], CH) for t in range(4)]
-    descs += [cf.desc(700, 520, cf.CF_F32, (2, 4, 1)[t % 3], CH) for t in range(2)]
+    descs = [cf.desc(1500, widths[0], cf.CF_BF16, (1, 2, 4)[t % 3], CH) for t in range(4)]
+    descs += [cf.desc(700, widths[1], cf.CF_F32, (2, 4, 1)[t % 3], CH) for t in range(2)]
     streams = [drift_stream((d.n_tokens, d.n_channels), d.dtype, steps=3, seed=470 + 10 * ef + k, device=DEV)
                for k, d in enumerate(descs)]
     xs = [[streams[t][s] for t in range(len(descs))] for s in range(3)]
