@@ -267,8 +267,10 @@ cf_status cf_step_fused(cf_ctx *ctx, int32_t first, int32_t count, const void *c
  * workspace argument.  Its scratch is a device array inside the library
  * (CF_STATIC_SCRATCH_BYTES per GPU, held until the process ends); the call
  * allocates nothing, on the device or through any library.  The tensors must need
- * no more workspace than that (compare cf_workspace_bytes): otherwise
- * CF_ERR_WORKSPACE, nothing enqueued.  There is no warm-up call for it: the caller
+ * no more workspace than that (compare cf_workspace_bytes; batches of mostly bf16
+ * tensors with channel scales whose rows are no multiple of 64 bytes may need
+ * less here, so that the call takes some for which cf_workspace_bytes says more):
+ * otherwise CF_ERR_WORKSPACE, nothing enqueued.  There is no warm-up call for it: the caller
  * vouches that recon and err hold valid state (recon = x_0, err = 0 after the
  * uncompressed step).  Outputs are bit-identical to cf_step_fused on the same
  * buffers.  All calls on one GPU share that GPU's array: calls that overlap in

@@ -8,7 +8,6 @@
 #include <cstdint>
 #include <cstring>
 #include <new>
-#include <utility>
 #include <vector>
 
 #include "cf_internal.h"
@@ -32,7 +31,7 @@ struct Layout {
     int32_t max_group_items = 0;   // largest reduction group of the single-pass path
     bool sp_wide = false;          // single-pass items are kStripeChannelsWide channels wide (short tensors)
     bool sp_slim = false;          // ... kStripeChannelsSlim channels wide (tall tensors)
-    bool sp_uneven = false;        // most of the context is bf16 rows that are no whole blocks of 64 bytes, see lay_out
+    bool sp_uneven = false;        // most of the context is bf16 rows that are no whole blocks of 64 bytes, see make_layout
     std::vector<uint8_t> uneven;   // per tensor, kUnevenRow and what else holds of it
     bool sp_too_tall = false;      // some group is larger than its tensor's limit: two kernels by default, but for small calls
     bool single_pass = false;      // every channel-scale tensor has single-pass geometry
@@ -208,8 +207,8 @@ int32_t slim_group_limit(const cf_tensor_desc &d, const cf_options &o)
     return !naive ? kSlimGroupLimitUneven : wide ? kNarrowGroupLimit : kSlimGroupLimitNaive;
 }
 
-// uneven_stripes: contexts of mostly uneven rows take stripes of their own
-cf_status lay_out(const cf_tensor_desc *descs, int32_t n, const cf_options &o, bool uneven_stripes, Layout &L)
+// uneven_stripes: contexts of mostly uneven rows take stripes of their own, which have up to twice the partials
+cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &o, Layout &L, bool uneven_stripes = true)
 {
     if (!descs || n < 1) return CF_ERR_INVALID_ARG;
     for (int32_t t = 0; t < n; ++t) {
@@ -450,16 +449,6 @@ cf_status lay_out(const cf_tensor_desc *descs, int32_t n, const cf_options &o, b
             L.dev[t].lr_g_off += L.off_partials;
         }
     }
-    return CF_OK;
-}
-
-cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &o, Layout &L)
-{
-    const cf_status st = lay_out(descs, n, o, true, L);
-    if (st != CF_OK || !L.sp_uneven || L.total <= kStaticScratchBytes) return st;
-    // The stripes of uneven rows have up to twice the partials: no tensors outgrow the static scratch because of them (40 x [4096, 1096] 395 / 417 us).
-    Layout others;
-    if (lay_out(descs, n, o, false, others) == CF_OK && others.total <= kStaticScratchBytes) L = std::move(others);
     return CF_OK;
 }
 
@@ -738,11 +727,11 @@ cf_status device_fail(cf_ctx *ctx, hipError_t e)
 // Builds a context over `workspace` and brings its tables there.  Everything travels inside kernel arguments
 // (no host-to-device copy, no memset), so this works wherever a kernel launch does.
 cf_status make_ctx(cf_ctx **out, const cf_tensor_desc *descs, int32_t n_tensors, const cf_options &o, void *workspace,
-                   size_t workspace_bytes, hipStream_t s)
+                   size_t workspace_bytes, hipStream_t s, bool uneven_stripes = true)
 {
     cf_ctx *ctx = new (std::nothrow) cf_ctx;
     if (!ctx) return CF_ERR_INVALID_ARG;
-    cf_status st = make_layout(descs, n_tensors, o, ctx->L);
+    cf_status st = make_layout(descs, n_tensors, o, ctx->L, uneven_stripes);
     if (st != CF_OK) { delete ctx; return st; }
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) % kAlign) != 0 || workspace_bytes < ctx->L.total) {
         delete ctx;
@@ -1273,6 +1262,8 @@ cf_status cf_step_fused_static(const cf_tensor_desc *descs, int32_t n_tensors, c
         }
         // lays the tables out in the scratch array afresh (CF_ERR_WORKSPACE if these tensors need more than it holds)
         st = make_ctx(&ctx, descs, n_tensors, o, ws, kStaticScratchBytes, s);
+        // no tensors outgrow the scratch because of the stripes of uneven rows
+        if (st == CF_ERR_WORKSPACE) st = make_ctx(&ctx, descs, n_tensors, o, ws, kStaticScratchBytes, s, false);
         if (st != CF_OK) return st;
         for (auto &w : ctx->warm) w = 1;        // the caller vouches for recon and err
         ctx->sp_unordered = ctx->sp_always_fresh = true;        // every caller on the GPU shares the scratch, and nobody warms up

@@ -66,7 +66,7 @@ constexpr int kSlimGroupLimitUneven = 38;
 constexpr int kSlimGroupLimitNaive = 24;
 // Contexts of mostly uneven rows, in 128-channel items a group: 256-channel stripes up to the first, no 64-channel ones up to kUnevenNarrowGroup, nor two kernels
 // because of kNarrowGroupLimit; fused calls of more than kUnevenRounds rounds by two kernels where most are past the first, or past these where the error is bf16 or the channels a
-// multiple of 16.  lay_out has the figures.
+// multiple of 16.  make_layout has the figures.
 constexpr int kUnevenWideGroup = 18;
 constexpr int kUnevenNarrowGroup = 64;
 constexpr int kUnevenGroupLimitBf16Error = 28;

@@ -125,7 +125,7 @@ __device__ __forceinline__ float tree_over_published(int n, const uint32_t *mine
     return tree_top<LV, IS_MAX>(stack);
 }
 
-// BLOCKS: rows that are no whole blocks of 64 bytes, whose parts at a stripe's ends are left to the L2 to merge (lay_out in cf_api.cpp says when).
+// BLOCKS: rows that are no whole blocks of 64 bytes, whose parts at a stripe's ends are left to the L2 to merge (make_layout in cf_api.cpp says when).
 // SCH: channels per stripe (kStripeChannels, kStripeChannelsWide or kStripeChannelsSlim); the 256 lanes are SCH / 8 chunks across
 // by 2048 / SCH row-lanes down.
 template <int SCH> struct alignas(16) Shared {

@@ -392,7 +392,7 @@ int main()
         }
     }
 
-    // ---- bf16 rows that are no whole blocks of 64 bytes (contexts that are not near the static scratch's size): stripes by the context, kernels and stores by the call
+    // ---- bf16 rows that are no whole blocks of 64 bytes: stripes by the context, kernels and stores by the call
     {
         enum Path { TWO, WIDE, NARROW, SLIM, SHORT };
         enum Stores { WHOLE, BLOCKS };                  // whether parts of blocks are left to the L2
@@ -706,6 +706,24 @@ int main()
         EXPECT(cf_step_fused_static(many.data(), 40, &o, nothing, (void *const *)nothing, (void *const *)nothing, (void *const *)nothing,
                                     (void *const *)nothing, nullptr) == CF_ERR_WORKSPACE);
         EXPECT(cf_workspace_bytes(many.data(), 40, &o) > CF_STATIC_SCRATCH_BYTES);
+        // what fits with the stripes of other rows is taken, though a context of the caller's would have the larger partials of rows that are no whole blocks of 64 bytes
+        struct Batch { int64_t n, c; std::vector<int> counts; };
+        for (const Batch &b : {Batch{4096, 1096, {14, 24, 26, 40, 47}}, Batch{4096, 3080, {5, 9, 16}}, Batch{3300, 3080, {6, 11, 20}}, Batch{4000, 520, {29, 30, 52, 57, 85, 101}},
+                               Batch{12500, 1096, {9, 16, 17}}, Batch{16000, 1096, {7, 13}}})
+            for (int count : b.counts) {
+                const std::vector<cf_tensor_desc> d((size_t)count, desc(b.n, b.c, CF_BF16, 2, CF_SCALE_CHANNEL));
+                std::vector<void *> bufs[5];
+                uintptr_t at = (uintptr_t)1 << 40;
+                for (auto &v : bufs)
+                    for (int t = 0; t < count; ++t, at += (uintptr_t)1 << 32) v.push_back((void *)at);
+                joined();
+                EXPECT(cf_workspace_bytes(d.data(), count, &o) > CF_STATIC_SCRATCH_BYTES);
+                for (int round = 0; round < 2; ++round) {
+                    const cf_status st = cf_step_fused_static(d.data(), count, &o, (const void *const *)bufs[0].data(), bufs[1].data(), bufs[2].data(), bufs[3].data(), bufs[4].data(), nullptr);
+                    if (st != CF_OK) { std::printf("static step over %d x [%d, %d]: status %d\n", count, (int)b.n, (int)b.c, (int)st); ++g_failed; }
+                    EXPECT(st != CF_OK || !joined().empty());
+                }
+            }
         for (int round = 0; round < 3; ++round) {
             std::vector<cf_tensor_desc> some = round == 1 ? std::vector<cf_tensor_desc>{desc(256, 64, CF_F32, 2, CF_SCALE_CHANNEL)}
                                                           : std::vector<cf_tensor_desc>{desc(2048, 1024, CF_BF16, 1, CF_SCALE_CHANNEL), desc(300, 384, CF_BF16, 4, CF_SCALE_GROUP)};

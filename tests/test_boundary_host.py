@@ -10,7 +10,6 @@ import pytest
 import paper_2507_17511_amd as cf
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-STATIC_SCRATCH_BYTES = 16 << 20         # CF_STATIC_SCRATCH_BYTES
 
 
 def declared_functions():
@@ -145,13 +144,3 @@ def test_nm_sizes_and_block_lengths():
     codes, scales, recon, err = cf.cf_sizes(cf.desc(4096, 3072, cf.CF_BF16, 2, cf.CF_SPARSE_NM, 8))
     assert scales == 0 and codes == 4096 * 384 * (1 + 4)           # 16-byte blocks travel as 5 bytes
     assert cf.cf_sizes(cf.desc(3, 8, cf.CF_F32, 1, cf.CF_SPARSE_NM, 8))[0] == 16 + 3 * 4
-
-
-@pytest.mark.parametrize("tokens, channels, counts", [(4096, 1096, (14, 24, 26, 40, 47)), (4096, 3080, (5, 9, 16)), (3300, 3080, (6, 11, 20)),
-                                                      (4000, 520, (29, 30, 52, 57, 85, 101)), (12500, 1096, (9, 16, 17)), (16000, 1096, (7, 13))])
-def test_no_tensors_outgrow_the_static_scratch_because_of_their_stripes(tokens, channels, counts):
-    """bf16 rows that are no whole blocks of 64 bytes take stripes with more partial sums than others, but not where the workspace would
-    be larger than the scratch of cf_step_fused_static because of it: these fit with the stripes of other rows."""
-    for count in counts:
-        need = cf.cf_workspace_bytes([cf.desc(tokens, channels, cf.CF_BF16, 2, cf.CF_SCALE_CHANNEL)] * count)
-        assert 0 < need <= STATIC_SCRATCH_BYTES, f"{count} x [{tokens}, {channels}]: {need}"

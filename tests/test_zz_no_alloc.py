@@ -92,6 +92,24 @@ def test_static_entry_point_matches_cf_step_fused_on_calls_in_a_row():
         ref_small.close()
 
 
+def test_static_entry_point_takes_other_stripes_where_those_of_uneven_rows_do_not_fit():
+    """bf16 rows that are no whole blocks of 64 bytes: a context's stripes would need more than the scratch, those of other rows do not."""
+    opts = cf.options()
+    descs = [cf.desc(4000, 520, cf.CF_BF16, (1, 2, 4)[t % 3], cf.CF_SCALE_CHANNEL) for t in range(30)]
+    assert cf.cf_workspace_bytes(descs, opts) > cf.CF_STATIC_SCRATCH_BYTES
+    xs = [drift_stream((4000, 520), cf.CF_BF16, 4, 700 + t) for t in range(30)]
+    ref = CodecSession(descs, opts, device=DEV)
+    try:
+        ref.warmup([x[0] for x in xs])
+        st = StaticState(descs, opts, [x[0] for x in xs])
+        for k in (1, 2, 3):
+            ref.step_fused([x[k] for x in xs])
+            st.step([x[k] for x in xs])
+            compare(f"call {k}", st, ref)
+    finally:
+        ref.close()
+
+
 def test_static_entry_point_rejects_what_its_scratch_cannot_hold():
     opts = cf.options()
     many = [cf.desc(4096, 3072, cf.CF_BF16, 2, cf.CF_SCALE_CHANNEL) for _ in range(40)]
