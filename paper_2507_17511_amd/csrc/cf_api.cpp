@@ -21,7 +21,7 @@ inline size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 // A tensor of such rows, in contexts of mostly such: the parts of its blocks go out without the streaming hint; fused steps of more than kUnevenRounds rounds of
 // workgroups over it take two kernels by default.
-enum : uint8_t { kUnevenRow = 1, kUnevenBlocks = 2, kUnevenTall = 4 };
+enum : uint8_t { kUnevenRow = 1, kUnevenBlocks = 2, kUnevenTwo = 4 };
 
 struct Layout {
     size_t off_descs = 0, off_ptrs = 0, off_tile_prefix = 0, off_fin_prefix = 0, off_partials = 0;
@@ -239,7 +239,7 @@ cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &
     // N = 2048 1.49 / 1.51 / 1.60 -> 1.52 / 1.48 / 1.55, N = 3072 1.47 / 1.52 / 1.61 -> 1.46 / 1.50 / 1.58,
     // N = 4096 1.50 / 1.55 / 1.62 -> 1.53 / 1.56 / 1.65, N = 6144 1.56 / 1.59 / 1.68 -> 1.62 / 1.66 / 1.77.
     auto narrow_item_rows = [&](int32_t dtype) { return (kPersistThreads / (kStripeChannels / kChunk)) * single_pass_rows_per_lane(dtype, o.ef); };
-    int64_t narrow_max_group = 0, elements = 0, tall_elements = 0, sliver_elements = 0, uneven_elements = 0, uneven_wide = 0, uneven_short = 0;
+    int64_t narrow_max_group = 0, elements = 0, tall_elements = 0, sliver_elements = 0, uneven_elements = 0, uneven_wide = 0, uneven_short = 0, uneven_middle = 0;
     L.uneven.assign(n, 0);
     for (int32_t t = 0; t < n; ++t)
         if (descs[t].scale == CF_SCALE_CHANNEL) {
@@ -250,10 +250,11 @@ cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &
             if (o.ef == CF_EF_RECON && descs[t].dtype == CF_BF16 && c % 32 != 0) {
                 const bool odd = c % 16 != 0;
                 const int limit = !odd ? kUnevenGroupLimitEven : o.err_dtype == CF_BF16 ? kUnevenGroupLimitBf16Error : kUnevenWideGroup;
-                L.uneven[t] = (uint8_t)(kUnevenRow | (odd || g <= 4 ? kUnevenBlocks : 0) | (g > limit ? kUnevenTall : 0));
+                L.uneven[t] = (uint8_t)(kUnevenRow | (odd ? kUnevenBlocks : 0) | (g > limit ? kUnevenTwo : 0));
                 uneven_elements += descs[t].n_tokens * c;
                 if (g <= kUnevenWideGroup) uneven_wide += descs[t].n_tokens * c;
                 if (g <= kWideGroup) uneven_short += descs[t].n_tokens * c;
+                if (g >= 4 && g <= kWideGroup) uneven_middle += descs[t].n_tokens * c;
             }
             if (g > kTallGroupItems) tall_elements += descs[t].n_tokens * c;
             // the last 64-channel stripe of a row is a few short pieces of memory and much of what there is
@@ -275,14 +276,17 @@ cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &
     // without and with blocks / two kernels: 8 x [17000, 1096] 632 / 550 / 390, not fused 412 / 349 / 337, two of them 161 / 109 / 113 and 109 / 93 / 100.
     // Stripes are the context's.  Wide ones cost whole rows of 13 items and more what uneven ones of so many gain, and what those gain in steps they lose when sent: so three quarters
     // of the context have to be such.  128 / 256 channels: 36 x [4096, 1096] 417 / 395, sent 292 / 303, x [4096, 1104] 380 / 364, sent 275 / 287; 27 x [4096, 1096] with 9 x [4096,
-    // 1088] 396 / 382, sent 281 / 297, 20 with 16 379 / 374, sent 272 / 291.  Uneven rows of up to 12 items gain more: 110 x [1024, 1096] with one [5000, 3072] 425 / 317, the 110
-    // alone 370 / 276, the one alone 31 / 35; with 14 x [6000, 1088] 597 / 501, sent 391 / 384.
+    // 1088] 396 / 382, sent 281 / 297, 20 with 16 379 / 374, sent 272 / 291.  Uneven rows of up to 12 items gain more: half of the context is enough (26 x [1027, 1976] with 15 x
+    // [1675, 1024] fp32 223 / 204), and four fifths, if of 4 items at least, next to tensors of up to 24: 110 x [1024, 1096] with one [5000, 3072] 425 / 317, the 110 alone 370 / 276, the
+    // one alone 31 / 35, but 10 x [385, 2872] with one [4629, 64] 38 / 51.
     // Stores and the second kernel are the call's, by most of its elements: 30 x [4800, 1088] of a context with 40 x [4800, 1096] take 305 in the single pass, 324 with blocks, 397 with
     // two kernels.  Calls over both, single pass / two kernels: [4609, 1096] with [4609, 1088] 51 % 751 / 782, 67 % 774 / 775, 80 % 805 / 781, [8000, 3080] with [8000, 3072]
     // 57 % 879 / 860, [14000, 1096] with [14000, 1088] 55 % 890 / 861.
     L.sp_uneven = L.single_pass && uneven_elements > elements - uneven_elements;
-    const bool wide_uneven = uneven_stripes && ((narrow_max_group <= kUnevenWideGroup && uneven_wide >= 3 * (elements - uneven_wide)) ||
-                                                (narrow_max_group <= kNarrowGroupLimit / 2 && uneven_short > elements - uneven_short));
+    if (narrow_max_group <= 4)
+        for (uint8_t &u : L.uneven) u |= u ? kUnevenBlocks : 0;
+    const bool wide_uneven = uneven_stripes && ((narrow_max_group <= kUnevenWideGroup && (uneven_wide >= 3 * (elements - uneven_wide) || uneven_short > elements - uneven_short)) ||
+                                                (narrow_max_group <= kNarrowGroupLimit / 2 && uneven_middle >= 4 * (elements - uneven_middle)));
     L.sp_wide = L.single_pass && narrow_max_group > 0 && (narrow_max_group <= kWideGroup || wide_uneven);
     // Tall tensors the other way round: all workgroups of a group wait for its slowest, and the more they are the longer.
     // 128 -> 64 channels on batches of equal size, us: [6144, 3072] bf16 793 -> 790, [8192, 3072] 840 -> 812 (4-bit 858 ->
@@ -382,6 +386,17 @@ cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &
             if (v.p_n_rb > (L.sp_slim ? slim_group_limit(d, o) : slivers ? kTallGroupItems : L.sp_uneven && uneven_stripes ? kUnevenNarrowGroup : kNarrowGroupLimit)) L.sp_too_tall = true;
             if (items > 0x7fffffffull) return CF_ERR_SHAPE;
         }
+    }
+    // What else takes two kernels where others of the context decide on the stripes: uneven rows of any length in 64-channel ones; in 128-channel ones those of few row blocks, which
+    // do not keep their XCD from stripe to stripe, and with fp32 errors odd ones of more than 12 items and 2048 channels.  Fused, single pass / two kernels: 12 x [2924, 3736] with one
+    // [19336, 352] 574 / 365, 8 x [6614, 3280] with one [18008, 112] 548 / 446; 46 x [1508, 3576] with two [12327, 1472] 817 / 649, 59 x [302, 3160] with three [10872, 544]
+    // 230 / 190, 40 x [1000, 3080] 427 / 388, 110 x [1024, 1096] with one [5000, 3072] 425 / 389, but 60 x [1000, 1096] 207 / 220 (and of eight row blocks, [2000, 1096], 367 / 403);
+    // 30 x [3077, 2696] with one [6457, 192] 776 / 652, but 31 x [4096, 1096] with 20 x [6000, 1088] 624 / 697.
+    for (int32_t t = 0; t < n; ++t) {
+        if (!L.uneven[t]) continue;
+        const int32_t g = L.dev[t].p_n_rb;
+        const bool few = g < 8 && L.max_group_items > 4, long_odd = g > kWideGroup && narrow_max_group > kUnevenWideGroup && descs[t].n_channels % 16 != 0 && descs[t].n_channels > 2048 && o.err_dtype == CF_F32;
+        if (L.sp_slim || (!L.sp_wide && (few || long_odd))) L.uneven[t] |= kUnevenTwo;
     }
     L.tile_prefix[n] = (uint32_t)tiles;
     L.ew_prefix[n] = (uint32_t)ew_tiles;
@@ -981,7 +996,7 @@ cf_status run_sender(cf_ctx *ctx, int32_t first, int32_t count, const void *cons
         else if (d.p_n_rb == 2) gain += d.p_n_stripes * (rows - (rounds <= 3.0 ? 1.2 : 1.4));
         else gain += rows * width - d.p_n_stripes * (rows_per_lane < 8 ? 0.1 : rows_per_lane < 16 ? 0.25 : rounds <= 2.0 ? 1.0 / 3.0 : 0.4);
     }
-    const bool worth_it = forced || small_call || (!ctx->L.sp_too_tall && !(fused && rounds > kUnevenRounds && ctx->mostly(first, count, kUnevenTall)) && (gain >= 0.0 || (tall && rounds <= 3.0)));
+    const bool worth_it = forced || small_call || (!ctx->L.sp_too_tall && !(fused && rounds > kUnevenRounds && ctx->mostly(first, count, kUnevenTwo)) && (gain >= 0.0 || (tall && rounds <= 3.0)));
     // (a group larger than what the device holds at once would have its first workgroups wait for ones that cannot
     // start before they leave: correct, they give up and compute the missing sums, but slow: such tensors take two kernels)
     const bool single_pass = ctx->L.single_pass && grid >= ctx->L.max_group_items && grid >= 1 && r.item_hi > r.item_lo && worth_it;

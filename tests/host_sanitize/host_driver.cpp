@@ -403,12 +403,17 @@ int main()
             {{{2, 12288, 1096}}, NARROW, NARROW, BLOCKS}, {{{2, 12289, 1096}}, NARROW, NARROW, BLOCKS}, {{{10, 12289, 1096}}, TWO, NARROW, BLOCKS},
             {{{2, 16384, 1096}}, NARROW, NARROW, BLOCKS}, {{{10, 16384, 1096}}, TWO, NARROW, BLOCKS}, {{{2, 16385, 1096}}, SLIM, SLIM, BLOCKS}, {{{10, 16385, 1096}}, TWO, SLIM, BLOCKS},
             {{{2, 12289, 1104}}, NARROW, NARROW, WHOLE}, {{{10, 12289, 1104}}, TWO, NARROW, WHOLE}, {{{10, 16384, 1104}}, TWO, NARROW, WHOLE}, {{{10, 16385, 1104}}, TWO, SLIM, WHOLE},
-            // 256 channels where three quarters of a context are uneven rows and nothing is of more than 18 items, or most are of up to 12 and nothing is of more than 24
+            // 256 channels where three quarters of a context are uneven rows, or most are such of up to 12 items, and nothing is of more than 18; or four fifths are of 4 to 12 and nothing is of more than 24
             {{{30, 4608, 1096}}, WIDE, WIDE, BLOCKS}, {{{30, 4609, 1096}}, TWO, NARROW, BLOCKS}, {{{30, 4608, 1104}}, WIDE, WIDE, WHOLE}, {{{30, 1024, 1104}}, WIDE, WIDE, BLOCKS},
             {{{30, 1025, 1104}}, WIDE, WIDE, WHOLE}, {{{110, 1024, 1096}, {1, 5000, 3072}}, WIDE, WIDE, BLOCKS}, {{{110, 1024, 1096}, {1, 5000, 1096}}, WIDE, WIDE, BLOCKS},
-            {{{110, 1024, 1096}, {1, 6144, 3072}}, WIDE, WIDE, BLOCKS}, {{{110, 1024, 1096}, {1, 6145, 3072}}, NARROW, NARROW, BLOCKS}, {{{110, 1024, 1096}, {40, 5000, 3072}}, NARROW, NARROW, WHOLE},
+            {{{110, 1024, 1096}, {1, 6144, 3072}}, WIDE, WIDE, BLOCKS}, {{{110, 1024, 1096}, {1, 6145, 3072}}, TWO, NARROW, BLOCKS}, {{{110, 1024, 1096}, {40, 5000, 3072}}, NARROW, NARROW, WHOLE},
             {{{15, 4096, 1096}, {16, 4609, 1096}}, TWO, NARROW, BLOCKS}, {{{34, 4609, 1096}, {40, 4608, 1096}}, NARROW, NARROW, BLOCKS},
             {{{60, 4096, 1096}, {20, 4096, 1088}}, WIDE, WIDE, BLOCKS}, {{{60, 4096, 1096}, {21, 4096, 1088}}, NARROW, NARROW, BLOCKS},
+            {{{30, 1027, 1976}, {15, 4608, 768}}, WIDE, WIDE, BLOCKS}, {{{30, 1027, 1976}, {18, 4608, 768}}, NARROW, NARROW, WHOLE}, {{{30, 1027, 1976}, {2, 4700, 1536}}, WIDE, WIDE, BLOCKS},
+            {{{30, 1027, 1976}, {3, 4700, 1536}}, TWO, NARROW, BLOCKS}, {{{30, 700, 1976}, {1, 4700, 64}}, TWO, NARROW, BLOCKS},
+            // next to tall tensors, ones of few row blocks or of more than 12 take two kernels, in 64 channels all do
+            {{{20, 3072, 2696}, {1, 6457, 192}}, NARROW, NARROW, BLOCKS}, {{{20, 3073, 2696}, {1, 6457, 192}}, TWO, NARROW, BLOCKS}, {{{20, 3073, 2704}, {1, 6457, 192}}, NARROW, NARROW, WHOLE},
+            {{{30, 1700, 1976}, {3, 7000, 1536}}, TWO, NARROW, BLOCKS}, {{{30, 2000, 1976}, {3, 7000, 1536}}, NARROW, NARROW, BLOCKS}, {{{30, 3000, 1976}, {3, 17000, 1536}}, TWO, SLIM, BLOCKS},
             // calls over a part of a context: two kernels, and parts of blocks left, by what most of the call is
             {{{110, 1024, 1096}, {1, 5000, 3072}}, WIDE, WIDE, BLOCKS, 0, 110}, {{{110, 1024, 1096}, {1, 5000, 3072}}, WIDE, WIDE, WHOLE, 110, 1},
             {{{30, 4800, 1096}, {25, 4800, 1088}}, TWO, NARROW, BLOCKS}, {{{30, 4800, 1096}, {25, 4800, 1088}}, TWO, NARROW, BLOCKS, 0, 30},
