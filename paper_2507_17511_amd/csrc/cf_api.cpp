@@ -622,8 +622,17 @@ struct cf_ctx {
         return of_kind > others;
     }
 
+    // Bytes of errors and, fused, reconstructions that the call writes for tensors with channel scales.
+    int64_t written_bytes(int32_t first, int32_t count, bool fused) const
+    {
+        int64_t bytes = 0;
+        for (int32_t t = first; t < first + count; ++t)
+            if (descs[t].scale == CF_SCALE_CHANNEL) bytes += descs[t].n_tokens * descs[t].n_channels * (int64_t)(dtype_size(opts.err_dtype) + (fused ? dtype_size(descs[t].dtype) : 0));
+        return bytes;
+    }
+
     // Whether short items serve the call: `r` and `v` are theirs then.  resident: how many the device holds at once.
-    bool take_short(int32_t first, int32_t count, uint32_t resident, LaunchRange &r, BatchView &v) const
+    bool take_short(int32_t first, int32_t count, uint32_t resident, bool fused, LaunchRange &r, BatchView &v) const
     {
         uint32_t items = 0;
         for (int32_t t = first; t < first + count; ++t) {
@@ -632,7 +641,7 @@ struct cf_ctx {
         }
         if (items > (uint32_t)kShortItems || items > resident) return false;
         r.sp_short = 1;
-        r.sp_blocks = mostly(first, count, kUnevenRow) && items > (uint32_t)kShortBlocksItems;
+        r.sp_blocks = items > (uint32_t)kShortBlocksItems && mostly(first, count, kUnevenRow) && written_bytes(first, count, fused) >= kShortBlocksBytes;
         r.item_lo = L.short_dev[first].p_item_begin;
         r.item_hi = r.item_lo + items;
         r.direct_descs = L.short_dev.data() + first;
@@ -1000,7 +1009,8 @@ cf_status run_sender(cf_ctx *ctx, int32_t first, int32_t count, const void *cons
     // (a group larger than what the device holds at once would have its first workgroups wait for ones that cannot
     // start before they leave: correct, they give up and compute the missing sums, but slow: such tensors take two kernels)
     const bool single_pass = ctx->L.single_pass && grid >= ctx->L.max_group_items && grid >= 1 && r.item_hi > r.item_lo && worth_it;
-    r.sp_blocks = items > (uint32_t)kBlocksItems && ctx->mostly(first, count, kUnevenBlocks);
+    r.sp_blocks = ctx->mostly(first, count, kUnevenBlocks) &&
+                  ctx->written_bytes(first, count, fused) >= (ctx->L.sp_wide ? kBlocksBytesWide : ctx->L.sp_slim ? kBlocksBytesSlim : kBlocksBytes);
     DirectPtrs direct;
     // kernels that take their pointers as arguments: the row-local ones, and the single pass
     const bool one_pass = single_pass && ctx->range_all_channel(first, count);
@@ -1010,7 +1020,7 @@ cf_status run_sender(cf_ctx *ctx, int32_t first, int32_t count, const void *cons
         e = run_row_local(ctx, first, count, v, r, fused, true, s);
         return e == hipSuccess ? CF_OK : device_fail(ctx, e);
     }
-    if (is_direct && count <= kDirectTensors && !(ctx->opts.flags & CF_FLAG_FIXED_GRID)) ctx->take_short(first, count, 2u * (uint32_t)grid, r, v);       // they need half the registers
+    if (is_direct && count <= kDirectTensors && !(ctx->opts.flags & CF_FLAG_FIXED_GRID)) ctx->take_short(first, count, 2u * (uint32_t)grid, fused, r, v);       // they need half the registers
     if (!is_direct && (st = sync_ptrs(ctx, first, count, x, recon, err, codes, scales, s)) != CF_OK) return st;
     if (single_pass) {
         // channel-scale tensors: one pass, the operands stay in registers across the scale reduction

@@ -72,12 +72,16 @@ constexpr int kUnevenNarrowGroup = 64;
 constexpr int kUnevenGroupLimitBf16Error = 28;
 constexpr int kUnevenGroupLimitEven = 32;
 constexpr double kUnevenRounds = 2.5;
-// Calls of short items over uneven rows leave parts of blocks to the L2 from so many items on: what it holds at a kernel's end has to be written then, which small
-// calls wait for.  Steps, all streamed / parts left, us: 2 x [512, 1512] (192 items) 11.4 / 12.5, 6 x [512, 1096] (432) 16.4 / 16.9, 2 x [2048, 1096] (576) 17.4 / 15.6,
-// [4096, 1096] (576) 18.4 / 16.3, [3268, 1512] (624) 20.5 / 17.2, 60 x [1024, 3080] two a call (784) 25.4 / 20.6, x [1024, 1096] six a call (864) 26.5 / 19.2
-// As for others: [8000, 328] (96 items) 16.1 / 16.9, two of them (192) 28.1 / 22.9, [8000, 1096] (288) 32.5 / 29.0.
+// Calls over uneven rows leave parts of blocks to the L2 from so many bytes of errors and reconstructions on, more than its 32 MB hold: what it holds at a kernel's end has to be
+// written then, and smaller calls wait for that.  All streamed / parts left, us: steps of 12 x [300, 1096] (24 MB) 18.2 / 20.5, 24 (47) 23.8 / 25.6, 36 (71) 41.5 / 41.8, 9 x [1000,
+// 1096] (59) 28.0 / 27.2, 12 (79) 34.6 / 29.4, [12000, 328] (24) 21.5 / 24.0, [8400, 1096] (55) 34.4 / 31.2, three (166) 91 / 70, with bf16 errors (37) 27.3 / 29.2, two (74) 53.7 / 50.1;
+// sent, 9 x [2000, 520] (37) 21.9 / 23.8, 15 (62) 39.1 / 39.3, [8400, 1096] two (74) 50.9 / 49.6, with bf16 errors (37) 41.1 / 43.3, three (55) 50.6 / 52.2.
+// Narrower stripes have more parts: 128 channels, 2 x [10078, 440] (53) 34.5 / 29.8, sent (35) 25.8 / 25.9; 64 channels, [17320, 376] (39) 28 / 25, three [18773, 152] (51) 40 / 33.
+constexpr int64_t kBlocksBytesWide = 54000000, kBlocksBytes = 45000000, kBlocksBytesSlim = 36000000;
+// Short items, steps: 6 x [512, 1096] (432 items, 20 MB) 15.1 / 15.4, 2 x [2048, 1096] (576, 27) 16.0 / 13.5, 6 x [1024, 1096] (864, 40) 22.5 / 16.7, [1024, 3080] (392, 19) 11.4 / 11.1, two
+// (784, 38) 18.5 / 20.8; sent, 4 x [1024, 1096] (576, 18) 12.4 / 11.7, 6 (864, 27) 16.8 / 14.8, with bf16 errors (13) 13.1 / 14.2.
 constexpr int kShortBlocksItems = 448;
-constexpr int kBlocksItems = 128;
+constexpr int64_t kShortBlocksBytes = 17000000;
 constexpr int kLastItemsWord = 32;                          // 128 bytes behind the error word: the first item of the last single pass, and the one past its last
 
 // The single pass's partials carry the sign of their call in this bit; item states and partials are filled with the other word before a first call.

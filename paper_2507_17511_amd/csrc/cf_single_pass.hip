@@ -575,6 +575,7 @@ const void *pick(int ef, int err_dtype, bool fused, bool wide, bool slim, bool b
 // would have as many as the default; no kernels for it here).
 template <int ET, bool FUSED> const void *short_fn(bool blocks)
 {
+    if constexpr (ET == BF16 && !FUSED) return reinterpret_cast<const void *>(&k_short_items<ET, FUSED, false>);       // 1024 items write less than kShortBlocksBytes
     return blocks ? reinterpret_cast<const void *>(&k_short_items<ET, FUSED, true>) : reinterpret_cast<const void *>(&k_short_items<ET, FUSED, false>);
 }
 

@@ -104,24 +104,35 @@ def test_short_items_of_unlike_tensors(shapes, dtype, flags):
         whole.close()
 
 
+UNEVEN_ROWS = [(21, 1153, (328, 264, 1096)),        # 256 channels, 10 items a group: none begins where the one before did
+               (30, 4700, (104, 136, 72)),          # 128 channels, 19 items
+               (2, 16387, (424, 408))]              # 64 channels, 33 items
+
+
+def uneven_rows(n, tokens, widths, options, mode, steps):
+    descs = [cf.desc(tokens - t % 3, widths[t % len(widths)], cf.CF_BF16, (1, 2, 4)[(t + t // 3) % 3], cf.CF_SCALE_CHANNEL) for t in range(n)]
+    streams = [drift_stream((d.n_tokens, d.n_channels), d.dtype, steps=steps, seed=870 + t, device=DEV) for t, d in enumerate(descs)]
+    xs = [[streams[t][s] for t in range(n)] for s in range(steps)]
+    say(f"uneven rows {n} x [{tokens}, {widths}] {mode} err_dtype={options['err_dtype']} flags={options['flags']}")
+    run_parity(descs, cf.options(**options), xs, mode=mode)
+
+
 @pytest.mark.parametrize("err_dtype", [cf.CF_F32, cf.CF_BF16])
 @pytest.mark.parametrize("flags", [0, cf.CF_FLAG_TEST_NO_WAIT])
-@pytest.mark.parametrize("tokens, widths", [(1153, (328, 264, 1096)),       # 256 channels, 10 items a group: none begins where the one before did
-                                            (1024, (1104, 336, 16)),        # channels a multiple of 16, up to four 128-channel items; 8 items
-                                            (4700, (104, 136, 72)),         # 128 channels, 19 items
-                                            (12291, (136, 200)),            # 49 items
-                                            (16387, (136, 200)),            # 64 channels, 33 items
-                                            (4097, (488, 520)), (4097, (496, 528))])        # short items, 33 a group
-def test_rows_of_no_whole_blocks(tokens, widths, err_dtype, flags):
-    """bf16 rows that are no whole blocks of 64 bytes, whose parts are stored another way: nine tensors, two of more tokens, or two in short
-    items, code widths in turn, fused and split; bits against the oracle."""
-    n = 2 if tokens == 4097 or tokens > 10000 else 9
-    descs = [cf.desc(tokens - t % 3, widths[t % len(widths)], cf.CF_BF16, (1, 2, 4)[(t + t // 3) % 3], cf.CF_SCALE_CHANNEL) for t in range(n)]
-    streams = [drift_stream((d.n_tokens, d.n_channels), d.dtype, steps=3, seed=870 + t, device=DEV) for t, d in enumerate(descs)]
-    xs = [[streams[t][s] for t in range(n)] for s in range(3)]
-    say(f"uneven rows [{tokens}, {widths}] err_dtype={err_dtype} flags={flags}")
+@pytest.mark.parametrize("n, tokens, widths", UNEVEN_ROWS + [(30, 1024, (1104, 336, 16)),           # channels a multiple of 16, up to four 128-channel items; 8 items
+                                                             (2, 12291, (552, 568)),                # 128 channels, 49 items
+                                                             (2, 4097, (760, 776)), (2, 4097, (752, 784))])        # short items, 33 a group
+def test_rows_of_no_whole_blocks(n, tokens, widths, err_dtype, flags):
+    """bf16 rows that are no whole blocks of 64 bytes, whose parts are stored another way in calls that write enough: code widths in turn,
+    fused and split; bits against the oracle."""
     for mode in ("fused", "split"):
-        run_parity(descs, cf.options(err_dtype=err_dtype, flags=cf.CF_FLAG_SINGLE_PASS | flags), xs, mode=mode)
+        uneven_rows(n, tokens, widths, dict(err_dtype=err_dtype, flags=cf.CF_FLAG_SINGLE_PASS | flags), mode, 3)
+
+
+@pytest.mark.parametrize("n, tokens, widths", UNEVEN_ROWS)
+def test_sent_rows_of_no_whole_blocks_with_bf16_errors(n, tokens, widths):
+    """The same where a call writes bf16 errors alone: twice the tensors."""
+    uneven_rows(2 * n, tokens, widths, dict(err_dtype=cf.CF_BF16, flags=cf.CF_FLAG_SINGLE_PASS), "split", 2)
 
 
 def test_small_call_replays_from_a_graph():
@@ -198,12 +209,12 @@ def test_streams_in_turn(ef):
 @pytest.mark.parametrize("ef, err_dtype, shapes", [
     (cf.CF_EF_RECON, cf.CF_F32, [(8192, 64), (4096, 512), (1000, 136)]),       # short items, 64 a group
     (cf.CF_EF_RECON, cf.CF_BF16, [(8192, 64), (4096, 512), (1000, 136)]),
-    (cf.CF_EF_RECON, cf.CF_F32, [(4097, 488), (4097, 520)]),                   # short items, rows of no whole blocks of 64 bytes
+    (cf.CF_EF_RECON, cf.CF_F32, [(4097, 760), (4097, 776)]),                   # short items, rows of no whole blocks of 64 bytes
     (cf.CF_EF_RECON, cf.CF_F32, [(9000, 136), (4096, 512)]),                   # too many for them: 128-channel stripes
-    (cf.CF_EF_RECON, cf.CF_F32, [(9000, 136), (6000, 264)]),                   # the same, rows of no whole blocks
+    (cf.CF_EF_RECON, cf.CF_F32, [(9000, 520), (9000, 536)]),                   # the same, rows of no whole blocks
     (cf.CF_EF_RECON, cf.CF_F32, [(12500, 224), (20000, 96)]),                  # 64-channel stripes
     (cf.CF_EF_RECON, cf.CF_BF16, [(12500, 224), (20000, 96)]),
-    (cf.CF_EF_RECON, cf.CF_F32, [(12500, 200), (20000, 72)]),                  # rows of no whole blocks
+    (cf.CF_EF_RECON, cf.CF_F32, [(16400, 424), (20000, 136)]),                 # rows of no whole blocks
     (cf.CF_EF_RECON, cf.CF_F32, [(2000, 1056)] * 9),                           # more than eight tensors: 256-channel stripes
     (cf.CF_EF_RECON, cf.CF_F32, [(2000, 1032)] * 9),                           # rows of no whole blocks
     (cf.CF_EF_OFF, cf.CF_F32, [(4096, 512), (1000, 136)]),
