@@ -19,8 +19,8 @@ namespace {
 constexpr size_t kAlign = 256;
 inline size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
-// A tensor of such rows, in contexts of mostly such: the parts of its blocks go out without the streaming hint; fused steps of more than kUnevenRounds rounds of
-// workgroups over it take two kernels by default.
+// A bf16 tensor whose rows are no whole blocks of 64 bytes, in the default feedback mode (see make_layout); the parts of its blocks may go out without the streaming hint; fused steps
+// of more than kUnevenRounds rounds of workgroups over it take two kernels by default.
 enum : uint8_t { kUnevenRow = 1, kUnevenBlocks = 2, kUnevenTwo = 4 };
 
 struct Layout {
@@ -263,8 +263,8 @@ cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &
     const bool slivers = sliver_elements > 0 && sliver_elements >= elements - sliver_elements;
     // Uneven rows, bf16 ones that are no whole blocks of 64 bytes: a stripe's piece of a row shares its first and last block with the stripes beside
     // it, and a block that reaches memory in parts costs as much as five whole ones.  Wide stripes have half as many; the parts go out without the
-    // streaming hint, so that an L2 that has both makes them whole (`blocks`); past both, two kernels, whose rows are written in one run.  In calls of few rounds
-    // the caches make more of them whole: 2 x [8000, 1512] (768 items) 76.5 / 60.1 in 128-channel stripes without and with blocks, 76.4 with two kernels.  Steps of 1.6e8
+    // streaming hint, so that an L2 that has both makes them whole (`blocks`, in calls that write enough: kBlocksBytes); past both, two kernels, whose rows are written in one run.  In
+    // calls of few rounds the caches make more of them whole: 2 x [8000, 1512] (768 items) 76.5 / 60.1 in 128-channel stripes without and with blocks, 76.4 with two kernels.  Steps of 1.6e8
     // elements, us, 128 / 128 blocks / 256 / 256 blocks / two kernels (channels that are an odd multiple of 8: error rows are uneven too):
     //   odd   [1024, 1096] 205 / 161 / 165 / 145 / 181, [4096, 1096] 429 / 409 / 385 / 386 / 409, [4096, 3080] 430 / 405 / 378 / 377 / 389, [4096, 200] 296 / 255 / 247 / 220 / 224,
     //         [5000, 1096] 451 / 447 / 425 / 423 / 417, [8000, 3080] 447 / 417 / 413 / 408 / 385, bf16 error [6100, 1096] 469 / 445 / 460 / 470 / 460, [8000, 1096] 636 / 613 / 617 /
@@ -278,12 +278,12 @@ cf_status make_layout(const cf_tensor_desc *descs, int32_t n, const cf_options &
     // of the context have to be such.  128 / 256 channels: 36 x [4096, 1096] 417 / 395, sent 292 / 303, x [4096, 1104] 380 / 364, sent 275 / 287; 27 x [4096, 1096] with 9 x [4096,
     // 1088] 396 / 382, sent 281 / 297, 20 with 16 379 / 374, sent 272 / 291.  Uneven rows of up to 12 items gain more: half of the context is enough (26 x [1027, 1976] with 15 x
     // [1675, 1024] fp32 223 / 204), and four fifths, if of 4 items at least, next to tensors of up to 24: 110 x [1024, 1096] with one [5000, 3072] 425 / 317, the 110 alone 370 / 276, the
-    // one alone 31 / 35, but 10 x [385, 2872] with one [4629, 64] 38 / 51.
+    // one alone 31 / 35, but 10 x [385, 2872], of two items, with one [4629, 64] 38 / 51.
     // Stores and the second kernel are the call's, by most of its elements: 30 x [4800, 1088] of a context with 40 x [4800, 1096] take 305 in the single pass, 324 with blocks, 397 with
     // two kernels.  Calls over both, single pass / two kernels: [4609, 1096] with [4609, 1088] 51 % 751 / 782, 67 % 774 / 775, 80 % 805 / 781, [8000, 3080] with [8000, 3072]
     // 57 % 879 / 860, [14000, 1096] with [14000, 1088] 55 % 890 / 861.
     L.sp_uneven = L.single_pass && uneven_elements > elements - uneven_elements;
-    if (narrow_max_group <= 4)
+    if (narrow_max_group <= 4)          // even ones too: [1024, 1104] above
         for (uint8_t &u : L.uneven) u |= u ? kUnevenBlocks : 0;
     const bool wide_uneven = uneven_stripes && ((narrow_max_group <= kUnevenWideGroup && (uneven_wide >= 3 * (elements - uneven_wide) || uneven_short > elements - uneven_short)) ||
                                                 (narrow_max_group <= kNarrowGroupLimit / 2 && uneven_middle >= 4 * (elements - uneven_middle)));

@@ -34,7 +34,9 @@ constexpr int kSinglePassSets = 64;
 // as tall, twice as many per group): 57 x [1024, 3072] 0.417 -> 0.382 ms; a
 // context whose tallest channel-scale tensor makes at most 12 items per group
 // with the narrow stripe (bf16: N <= 3072) takes the wide one, and one of mostly
-// tensors of more than 40 (N > 10240) the slim one, whose items are twice as tall.
+// tensors of more than 40 (N > 10240) the slim one, whose items are twice as tall;
+// contexts of mostly bf16 rows that are no whole blocks of 64 bytes have lines of
+// their own (kUnevenWideGroup, kUnevenNarrowGroup).
 constexpr int kPersistThreads = 256;
 constexpr int kStripeChannels = 128;
 constexpr int kStripeChannelsWide = 2 * kStripeChannels;    // 256
@@ -64,8 +66,8 @@ constexpr int kNarrowGroupLimit = 48;
 constexpr int kSlimGroupLimit = 64;                         // see slim_group_limit
 constexpr int kSlimGroupLimitUneven = 38;
 constexpr int kSlimGroupLimitNaive = 24;
-// Contexts of mostly uneven rows, in 128-channel items a group: 256-channel stripes up to the first, no 64-channel ones up to kUnevenNarrowGroup, nor two kernels
-// because of kNarrowGroupLimit; fused calls of more than kUnevenRounds rounds by two kernels where most are past the first, or past these where the error is bf16 or the channels a
+// Contexts of mostly uneven rows, in 128-channel items a group: 256-channel stripes up to the first (of those that are three quarters of the context), no 64-channel ones
+// up to kUnevenNarrowGroup, nor two kernels because of kNarrowGroupLimit; fused calls of more than kUnevenRounds rounds by two kernels where most are past the first, or past these where the error is bf16 or the channels a
 // multiple of 16.  make_layout has the figures.
 constexpr int kUnevenWideGroup = 18;
 constexpr int kUnevenNarrowGroup = 64;

@@ -12,12 +12,13 @@
 //           (the literal and the no-feedback recursions); for contexts of short
 //           tensors half as tall and 256 channels wide (32 chunks x 8 row-lanes),
 //           for contexts of tall ones twice as tall and 64 wide (8 x 32);
+//           k_short_items, small calls: 128 x 64 (half as tall for fp32);
 //   group = the items of one such stripe of one tensor; only they have
 //           to agree on that stripe's scales, so there is no grid-wide barrier,
 //           and different groups drift apart, which keeps HBM busy while some
 //           workgroups wait.
 // What bounds it is HBM in large calls (114 x [4096, 3072] bf16 1-bit 14.5 GB in 2.64 ms, 5.5 TB/s), waiting for the slowest of a group in tall
-// ones (30 x [17776, 1920], 35 items a group, 8.2 GB in 1.79 ms, 4.6 TB/s), and in small calls the chain of an item: its descriptor, its
+// ones (30 x [17776, 1920], 35 items a group, 8.2 GB in 1.66 to 1.74 ms, 4.7 to 4.9 TB/s), and in small calls the chain of an item: its
 // operands, the exchange, and its code, which a CU fetches once per launch.  Those take short items (SHORT): a quarter of the rows a lane.
 // Per item: load -> |z| tree over the lane's rows -> LDS tree over row-lanes
 // -> publish the item's partial (an aligned power-of-two block of the channel
@@ -125,7 +126,6 @@ __device__ __forceinline__ float tree_over_published(int n, const uint32_t *mine
     return tree_top<LV, IS_MAX>(stack);
 }
 
-// BLOCKS: rows that are no whole blocks of 64 bytes, whose parts at a stripe's ends are left to the L2 to merge (make_layout in cf_api.cpp says when).
 // SCH: channels per stripe (kStripeChannels, kStripeChannelsWide or kStripeChannelsSlim); the 256 lanes are SCH / 8 chunks across
 // by 2048 / SCH row-lanes down.
 template <int SCH> struct alignas(16) Shared {
@@ -138,6 +138,7 @@ template <int SCH> struct alignas(16) Shared {
 constexpr int kNoneMissing = 0x7fffffff;
 constexpr uint32_t kMaxHelps = 4096u;
 
+// BLOCKS: rows that are no whole blocks of 64 bytes, whose parts at a stripe's ends are left to the L2 to merge (make_layout says for which, kBlocksBytes from which size on).
 // help: do no more than store the partial of item rb, which is another workgroup's.  max_polls: of a missing partial.
 // Returns kNoneMissing when the item is done, else the item whose partial was missing; nothing but a partial has been written then.
 template <int DT, int BITS, int EF, int ET, bool FUSED, int SCH, bool SHORT, bool BLOCKS>
