@@ -576,8 +576,9 @@ const void *pick(int ef, int err_dtype, bool fused, bool wide, bool slim, bool b
 // would have as many as the default; no kernels for it here).
 template <int ET, bool FUSED> const void *short_fn(bool blocks)
 {
-    if constexpr (ET == BF16 && !FUSED) return reinterpret_cast<const void *>(&k_short_items<ET, FUSED, false>);       // 1024 items write less than kShortBlocksBytes
-    return blocks ? reinterpret_cast<const void *>(&k_short_items<ET, FUSED, true>) : reinterpret_cast<const void *>(&k_short_items<ET, FUSED, false>);
+    if constexpr (ET == F32 || FUSED)       // the others write less than kShortBlocksBytes
+        if (blocks) return reinterpret_cast<const void *>(&k_short_items<ET, FUSED, true>);
+    return reinterpret_cast<const void *>(&k_short_items<ET, FUSED, false>);
 }
 
 const void *pick_short(int err_dtype, bool fused, bool blocks)
